@@ -50,3 +50,92 @@ def test_a_gramian_that_is_not_positive_definite_is_reported(ctx, gpu_device, d)
         als.als_status_sync(ctx)
     assert e.value.status == als.ALS_ENOTSPD
     als.als_status_sync(ctx)  # reported once
+
+
+def _topk_definition(Q, H, k, ex):
+    """Scores in fp64 with numpy's matmul; ids by (-score, id) among the admissible items with a score."""
+    S = Q.double().numpy() @ H.double().numpy().T
+    out = []
+    for q in range(S.shape[0]):
+        bad = set() if ex is None else set(ex[1][ex[0][q]:ex[0][q + 1]].tolist())
+        ok = np.array([i for i in range(S.shape[1]) if i not in bad and not np.isnan(S[q, i])], dtype=np.int64)
+        out.append(ok[np.lexsort((ok, -S[q, ok]))][:k])
+    return S, out
+
+
+# edges of segments (32), units (128 and more), thread strides of the chunk scan (1024 chunks), query groups (64, 256, 384,
+# 512) and both kernel shapes
+@pytest.mark.parametrize("nq,n,d,dtype,k", [
+    (1, 1, 16, torch.float32, 1), (3, 31, 32, torch.bfloat16, 40), (1, 129, 128, torch.float32, 10),
+    (64, 4097, 64, torch.float32, 20), (65, 33000, 32, torch.float32, 20), (256, 8191, 128, torch.bfloat16, 64),
+    (257, 5000, 128, torch.float32, 50), (385, 2047, 128, torch.bfloat16, 10), (513, 1025, 64, torch.bfloat16, 20),
+    (300, 40001, 16, torch.float32, 10), (520, 3000, 32, torch.bfloat16, 50), (2, 300007, 16, torch.bfloat16, 50)])
+def test_topk_at_the_edges_of_its_tiles(gpu_device, nq, n, d, dtype, k):
+    """Ties broken by id, zero rows on both sides, long exclusion lists of the very best items; the returned scores are held
+    to the error of an fp32 sum of d products, (d + 1) 2^-24 |q| |h|, and the ids to the definition where no neighbouring
+    scores are closer than twice that."""
+    say(f"topk nq={nq} n={n} d={d} {dtype} k={k}")
+    gen = torch.Generator().manual_seed(n + d)
+    H = (torch.randn(n, d, generator=gen) * torch.exp(0.5 * torch.randn(n, 1, generator=gen))).to(dtype)
+    Q = torch.randn(nq, d, generator=gen).to(dtype)
+    H[n // 2: n // 2 + 70] = H[n // 2]
+    H[n // 3: n // 3 + 40] = 0
+    Q[nq // 2] = 0
+    if nq > 2:
+        Q[1] = H[n // 2]
+    best = (Q.double() @ H.double().T).topk(min(n, 100)).indices
+    lens = torch.randint(0, min(n, 100) + 1, (nq,), generator=gen)
+    ptr = torch.zeros(nq + 1, dtype=torch.int64)
+    ptr[1:] = torch.cumsum(lens, 0)
+    idx = torch.cat([best[q, :int(lens[q])] for q in range(nq)]).to(torch.int32)
+    ctx = als.Context(0)
+    for ex in (None, (ptr.numpy(), idx.numpy())):
+        csr = None if ex is None else als.Csr(nq, n, ptr.to(gpu_device), idx.to(gpu_device))
+        ids, sc = als.als_topk(ctx, Q.to(gpu_device), H.to(gpu_device), k, csr)
+        torch.cuda.synchronize()
+        ids, sc = ids.cpu().numpy(), sc.cpu().numpy()
+        S, ref = _topk_definition(Q, H, k, ex)
+        tol = (d + 1) * 2.0 ** -24 * np.outer(np.linalg.norm(Q.double().numpy(), axis=1), np.linalg.norm(H.double().numpy(), axis=1))
+        for q in range(nq):
+            m = len(ref[q])
+            assert np.all(ids[q, m:] == -1) and np.all(np.isneginf(sc[q, m:]))
+            got, r = ids[q, :m], ref[q]
+            assert len(set(got.tolist())) == m
+            assert ex is None or not np.intersect1d(got, ex[1][ex[0][q]:ex[0][q + 1]]).size
+            assert np.all(np.abs(sc[q, :m] - S[q, got]) <= tol[q, got])
+            assert np.all(np.abs(S[q, got] - S[q, r]) <= 2 * (tol[q, got] + tol[q, r]))
+            same = np.flatnonzero(np.diff(sc[q, :m]) == 0)
+            assert np.all(got[same] < got[same + 1])  # equal scores by ascending id
+    ctx.close()
+
+
+def test_topk_with_values_that_cannot_be_bounded(gpu_device):
+    """Infinite, NaN, huge and tiny entries: an item whose score is NaN is never returned, infinite ones rank as numbers do, and
+    the rest of the ranking is what it is without them."""
+    say("topk with inf, nan, 1e30, 1e-30")
+    nq, n, d, k = 70, 3000, 64, 20
+    gen = torch.Generator().manual_seed(11)
+    H, Q = torch.randn(n, d, generator=gen), torch.randn(nq, d, generator=gen)
+    H[5] = float("nan")
+    H[700, 3] = float("inf")
+    H[1500] = 1e30 * H[1500]
+    H[2000:2200] *= 1e-30
+    Q[7] *= 1e-30
+    Q[8] *= 1e25
+    Q[9, 0] = float("nan")
+    Q[10, :] = 0
+    ctx = als.Context(0)
+    ids, sc = als.als_topk(ctx, Q.to(gpu_device), H.to(gpu_device), k)
+    torch.cuda.synchronize()
+    ids, sc = ids.cpu().numpy(), sc.cpu().numpy()
+    S = (Q[:, None, :] * H[None, :, :]).sum(-1).numpy()  # fp32: overflows where the library's products do
+    for q in range(nq):
+        ok = np.flatnonzero(~np.isnan(S[q]))
+        ref = ok[np.lexsort((ok, -S[q, ok]))][:k]
+        assert np.all(ids[q, len(ref):] == -1)
+        got = ids[q, :len(ref)]
+        assert 5 not in got
+        with np.errstate(invalid="ignore"):
+            close = np.abs(S[q, got] - S[q, ref]) <= 1e-4 * np.abs(S[q, ref])
+        assert np.all(close | (S[q, got] == S[q, ref])), (q, got, ref)
+    ctx.close()
