@@ -116,8 +116,8 @@ template <int D, bool BF16> __device__ __forceinline__ float margin(float qn, fl
     return qn == 0.f || hn == 0.f ? 0.f : eps * p + 4e-36f * (1.f + qn + hn);
 }
 
-// What bounds it: the matrix cores once a few hundred queries share an item (4096 queries x 10M bf16 items, d = 128),
-// the item table's read below that.  A workgroup stages a stretch of items in LDS once (coalesced, converted, its rows
+// What bounds it: the matrix cores and the barriers between stages once a few hundred queries share an item (4096 queries x
+// 10M bf16 items, d = 128: about 8.5 ms, 1.2 PFLOP/s), the item table's read below that.  A workgroup stages a stretch of items in LDS once (coalesced, converted, its rows
 // padded by 16 bytes against bank conflicts) and its wavefronts multiply it with queries kept in registers: WI = 1
 // gives every wavefront its own QT * 32 queries and all items, WI = 4 the same QT * 32 queries and a quarter of the items.
 template <int D, int WI> constexpr int topk_stage_items() { return WI == 4 || D == 16 ? 128 : 64; }
@@ -290,6 +290,9 @@ __device__ __forceinline__ void block_sort(float *sc, int32_t *id, int N, int ti
 
 // What bounds it: the latency of its few dependent phases (maxima, rescoring, sort) when there are few queries, the read
 // of the maxima and of the rescored chunks when there are many.
+// Both kernels together against a scan that scored everything in fp32 and kept candidate buffers: 64 queries x 30k items
+// (d = 64, fp32, k = 20) 2.59 -> 0.036 ms, 4096 x 1M (the same) 7.9 -> 0.79 ms, 4096 x 10M (d = 128, bf16, k = 50,
+// exclusions) 134.8 -> 10.5 ms.
 template <int D, bool BF16>
 __global__ __launch_bounds__(256) void topk_select_kernel(const void *__restrict__ Q, int64_t ldq, int64_t nq,
                                                           const void *__restrict__ H, int64_t ldh, int64_t n,
@@ -489,9 +492,9 @@ template <int D, bool BF16, int QT, int WI>
 static void bound_launch(const als_ctx *ctx, const void *Q, int64_t ldq, int64_t nq, const als_table *H, ChunkMap map,
                          float *maxima, float *norms, hipStream_t s) {
     const int64_t gq = topk_group_queries<QT, WI>(), qgroups = (nq + gq - 1) / gq, units = map.nchunks / 4;
-    // four workgroups' worth of items per place that the chip has for them: enough to even out, few enough that the
-    // queries' operands are not loaded for a handful of items
-    const int64_t want = std::max<int64_t>(1, (int64_t)ctx->num_cu * 8 / qgroups);
+    // 32 workgroups per compute unit where the table has them: the workgroups of one item stretch stay close in time, so
+    // their reads meet in L2 (4096 queries x 10M items, d = 128, bf16: 10.9 ms with 8 per unit, 10.45 with 32, 10.5 with 64)
+    const int64_t want = std::max<int64_t>(1, (int64_t)ctx->num_cu * 32 / qgroups);
     const int64_t per = std::max<int64_t>(1, (units + want - 1) / want), splits = (units + per - 1) / per;
     const unsigned blocks = (unsigned)((splits + 7) / 8 * 8 * qgroups);
     hipLaunchKernelGGL((topk_bound_kernel<D, BF16, QT, WI>), dim3(blocks), dim3(256), 0, s, Q, ldq, nq, H->data, H->ld, H->rows,
@@ -502,18 +505,21 @@ template <int D, bool BF16>
 static als_status topk_typed(als_ctx *ctx, const als_table *Q, const als_table *H, const als_csr *ex, int k,
                              int32_t *ids, float *scores, hipStream_t s) {
     constexpr int64_t ES = BF16 ? 2 : 4;
-    // Chunk size: the maxima cost 12 bytes per query and chunk (written once, read twice), rescoring about 1.3 k chunks
-    // of C rows; the sum is smallest at C^2 = 12 n / (1.3 k row bytes).
+    // Chunk size: a chunk costs 12 bytes of maxima per query (written once, read twice) and the matrix cores' pause at its
+    // end, rescoring about 1.3 k chunks of C rows each; C^2 = 48 n / (1.3 k row bytes) balances them.  Measured at the size
+    // this gives, half and twice of it: 0.79, 0.95, 0.85 ms (4096 x 1M, d = 64, fp32, k = 20), 10.45, 12.1, 10.7 ms
+    // (4096 x 10M, d = 128, bf16, k = 50).
     ChunkMap map{5, 0};
-    const double best2 = 12.0 * (double)H->rows / (1.3 * k * D * ES);
+    const double best2 = 48.0 * (double)H->rows / (1.3 * k * D * ES);
     while (map.lc < 24 && (std::exp2(2 * map.lc + 1) < best2 || (H->rows >> map.lc) >= TOPK_MAX_CHUNKS)) ++map.lc;
     map.nchunks = (int)(4 * ((H->rows + map.unit_items() - 1) / map.unit_items()));
     // Queries go in batches whose maxima fit TOPK_BATCH_BYTES; each batch reads the item table once more.
     constexpr int64_t TOPK_BATCH_BYTES = (int64_t)3 << 29;
     const int64_t per_query = (map.nchunks + 15) / 16 * 16 * (int64_t)sizeof(float);
-    const int64_t fit = std::max<int64_t>(512, TOPK_BATCH_BYTES / std::max<int64_t>(per_query, 1) / 512 * 512);
+    constexpr int QT = D == 128 ? 3 : 4, GQ = topk_group_queries<QT, 1>();
+    const int64_t fit = std::max<int64_t>(GQ, TOPK_BATCH_BYTES / std::max<int64_t>(per_query, 1) / GQ * GQ);
     const int64_t batches = (Q->rows + fit - 1) / fit;
-    const int64_t batch = std::min<int64_t>(Q->rows, ((Q->rows + batches - 1) / batches + 511) / 512 * 512);
+    const int64_t batch = std::min<int64_t>(Q->rows, ((Q->rows + batches - 1) / batches + GQ - 1) / GQ * GQ);
     const size_t norm_bytes = ((size_t)map.nchunks * sizeof(float) + 255) / 256 * 256;
     als_status st = ensure(ctx, ctx->topk_partials, norm_bytes + (size_t)(batch * per_query));
     if (st != ALS_OK) return st;
@@ -524,7 +530,7 @@ static als_status topk_typed(als_ctx *ctx, const als_table *Q, const als_table *
         const void *Qb = (const char *)Q->data + q0 * Q->ld * ES;
         if (map.nchunks > 0) {
             if (nq <= 256) bound_launch<D, BF16, 2, 4>(ctx, Qb, Q->ld, nq, H, map, maxima, norms, s);
-            else bound_launch<D, BF16, D == 128 ? 3 : 4, 1>(ctx, Qb, Q->ld, nq, H, map, maxima, norms, s);
+            else bound_launch<D, BF16, QT, 1>(ctx, Qb, Q->ld, nq, H, map, maxima, norms, s);
         }
         hipLaunchKernelGGL((topk_select_kernel<D, BF16>), dim3((unsigned)nq), dim3(256), bitmap, s, Qb, Q->ld, nq, H->data,
                            H->ld, H->rows, ex ? ex->indptr + q0 : nullptr, ex ? ex->indices : nullptr, k, map,
