@@ -23,9 +23,9 @@ template <int D, int KT, bool ZB> constexpr bool wide_resident() { return ZB; }
 
 template <int D, int KT> struct WideCfg {
     static constexpr int K = 16 * KT;
-    static constexpr int TRI = tri_row(K);           // lower triangle, rows padded (tri_solve.h)
+    static constexpr int TRI = tri_row<K>(K);           // lower triangle, rows padded (tri_solve.h)
     static constexpr int OFF_COL = TRI;              // solver's auxiliary buffer
-    static constexpr int OFF_T = OFF_COL + TRI_AUX_FLOATS;  // tbuf[K]
+    static constexpr int OFF_T = OFF_COL + TRI_AUX_FLOATS<K>;  // tbuf[K]
     static constexpr int OFF_ID = OFF_T + K;         // ids[K]
     static constexpr int LDS_FLOATS = OFF_ID + K;
 };
@@ -116,7 +116,7 @@ __device__ __forceinline__ void dual_wide_step(const int64_t *__restrict__ indpt
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[v] += c0 + v == Rr ? 1.f : 0.f;
             }
-            *(float4 *)(tri + tri_row(Rr) + c0) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+            *(float4 *)(tri + tri_row<K>(Rr) + c0) = make_float4(acc[0], acc[1], acc[2], acc[3]);
         }
     }
     wave_sync();
@@ -133,7 +133,7 @@ __device__ __forceinline__ void dual_wide_step(const int64_t *__restrict__ indpt
     // ---- 4. r = Z_I^T t
     if constexpr (RES) {
         // the triangle is free now: the remainders of the cut of t, a block of zeros and the finished row go there
-        static_assert(tri_row(K) >= 3 * K + D, "the triangle area holds the parts of t and the row");
+        static_assert(tri_row<K>(K) >= 3 * K + D, "the triangle area holds the parts of t and the row");
         float *p1 = tri, *p2 = tri + K, *zeros = tri + 2 * K, *rbuf = tri + 3 * K;
 #pragma unroll
         for (int e0 = 0; e0 < K; e0 += 64) {
@@ -158,7 +158,7 @@ __device__ __forceinline__ void dual_wide_step(const int64_t *__restrict__ indpt
         for (int x = 0; x < 2 * NP; ++x) out[x] = floatx4{0.f, 0.f, 0.f, 0.f};
         if constexpr (ZB)
             zt_times_t<KT, NP>([&](int t, int j) { return __builtin_bit_cast(bf16x8, zop[t].v[j]); }, top, sel, out);
-        float *dump = aux + 128 + lane;  // the solver's per-lane dump slots
+        float *dump = aux + TRI_AUX_DUMP<K> + lane;  // the solver's per-lane dump slots
 #pragma unroll
         for (int x = 0; x < 2 * NP; ++x)
             *(q == 0 ? rbuf + column_of_result(x >> 1, x & 1, a) : dump) = out[x][0] + out[x][1] + out[x][2];

@@ -259,9 +259,9 @@ __device__ __forceinline__ void cholesky_solve_lds(float *a, float *aux, int32_t
 // LDS layout of the direct solver for D >= 64: lower triangle, the solver's auxiliary and result
 // buffers (tri_solve.h), the right-hand side.
 template <int D> struct Packed {
-    static constexpr int TRI = tri_row(D);
+    static constexpr int TRI = tri_row<D>(D);
     static constexpr int OFF_COL = TRI;                        // the solver's auxiliary buffer
-    static constexpr int OFF_T = OFF_COL + TRI_AUX_FLOATS;     // tbuf[D]
+    static constexpr int OFF_T = OFF_COL + TRI_AUX_FLOATS<D>;     // tbuf[D]
     static constexpr int OFF_RHS = OFF_T + D;      // rhs[D]
     static constexpr size_t LDS_BYTES = (size_t)(OFF_RHS + D) * sizeof(float);
 };
@@ -447,7 +447,7 @@ __device__ __forceinline__ bool primal_step(
                 float *tri = lds, *rhs = lds + Packed<D>::OFF_RHS;
                 deliver(
                     [&](int r, int c, float v) {
-                        if (c <= r) tri[tri_row(r) + c] = v + alpha * G[r * D + c] + (r == c ? lambda : 0.f);
+                        if (c <= r) tri[tri_row<D>(r) + c] = v + alpha * G[r * D + c] + (r == c ? lambda : 0.f);
                     },
                     [&](int c, float v) { rhs[c] = v; });
                 __syncthreads();
@@ -550,7 +550,7 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
                 const float s = p0[e];
                 if (e < D * D) {
                     const int r = e / D, c = e % D;
-                    if (c <= r) tri[tri_row(r) + c] = s + alpha * G[e] + (r == c ? lambda : 0.f);
+                    if (c <= r) tri[tri_row<D>(r) + c] = s + alpha * G[e] + (r == c ? lambda : 0.f);
                 } else {
                     rhs[e - D * D] = s;
                 }

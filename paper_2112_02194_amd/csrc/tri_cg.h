@@ -1,6 +1,6 @@
 // One wavefront solves a symmetric positive definite K x K system (K <= 128, a multiple of 16) by conjugate
 // gradients (the solver Section 4.5 settles on), on the same LDS layout as tri_solve.h: lower triangle, row r
-// starting at tri_row(r).  Lane i owns rows i and 64+i of every vector.  The product S p reads row i up to the
+// starting at tri_row<K>(r).  Lane i owns rows i and 64+i of every vector.  The product S p reads row i up to the
 // diagonal and column i below it (S is symmetric), p from an LDS copy.  Starts from zero, stops when
 // |residual| <= tol * |y| or after max_iters steps.  Rows at or beyond k are identity rows with zero
 // right-hand side (the caller guarantees it): their unknowns are zero and they are left out of the products.
@@ -26,7 +26,7 @@ __device__ __forceinline__ void tri_cg(const float *tri, float *pbuf, float *tbu
     const int lane = opaque_tid() & 63;
     const bool hasa = lane < k, hasb = TWO && 64 + lane < k;
     const int ra = hasa ? lane : 0, rb = hasb ? 64 + lane : 0;  // lanes without a row read row 0 and drop the result
-    const int rowa = tri_row(ra), rowb = tri_row(rb);
+    const int rowa = tri_row<K>(ra), rowb = tri_row<K>(rb);
     float x0 = 0.f, x1 = 0.f;
     float r0 = hasa ? y0 : 0.f, r1 = hasb ? y1 : 0.f;
     float p0 = r0, p1 = r1;
@@ -39,7 +39,7 @@ __device__ __forceinline__ void tri_cg(const float *tri, float *pbuf, float *tbu
         float a0 = 0.f, a1 = 0.f;
         for (int j = 0; j < k; ++j) {
             const float pj = pbuf[j];
-            const int rj = tri_row(j);
+            const int rj = tri_row<K>(j);
             a0 += tri[j <= ra ? rowa + j : rj + ra] * pj;
             if constexpr (TWO) a1 += tri[j <= rb ? rowb + j : rj + rb] * pj;
         }

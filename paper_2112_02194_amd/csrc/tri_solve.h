@@ -1,5 +1,5 @@
 // One wavefront solves a symmetric positive definite K x K system (K <= 128, a multiple of 16) whose
-// lower triangle sits in LDS, row r starting at tri_row(r).  Rows are padded to multiples of sixteen floats:
+// lower triangle sits in LDS, row r starting at tri_row<K>(r).  Rows are padded to multiples of sixteen floats:
 // a row at or below a panel of 16 columns then holds all 16 of them inside its own storage (beyond its
 // diagonal: padding, never used), so a panel is read and written back with 16-byte accesses and no
 // per-element test.
@@ -28,10 +28,17 @@
 
 namespace als {
 
-// first float of row r in the padded triangle; tri_row(K) is the size of the whole triangle
-__host__ __device__ constexpr int tri_row(int r) { return 16 * (r / 16 + 1) * (8 * (r / 16) + r % 16); }
+// First float of row r in the padded triangle; tri_row<K>(K) is the size of the whole triangle.  Beyond 64 rows every row
+// starts four floats further on: with row lengths of 16 to 128 floats alone, sixteen lanes that read 16 bytes each
+// from sixteen rows meet in one to four groups of four banks, with the shift in sixteen different ones (a power-law
+// epoch of 50M rows, bf16, d = 128: 259 -> 253 ms).  Up to 64 rows the shift costs more resident workgroups than it gains.
+template <int K> __host__ __device__ constexpr int tri_row(int r) {
+    return 16 * (r / 16 + 1) * (8 * (r / 16) + r % 16) + (K > 64 ? 4 * r : 0);
+}
 
-constexpr int TRI_AUX_FLOATS = 192;  // reciprocal pivots [128]; the other 64 are the callers' per-lane dump slots
+// reciprocal pivots, then the callers' 64 per-lane dump slots
+template <int K> constexpr int TRI_AUX_DUMP = K > 64 ? 128 : 64;
+template <int K> constexpr int TRI_AUX_FLOATS = TRI_AUX_DUMP<K> + 64;
 
 __device__ __forceinline__ float lane_value(float v, int src_lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src_lane));
@@ -45,7 +52,7 @@ template <int DST> __device__ __forceinline__ float lane_set(float v, float unif
 }
 
 template <int K>
-__device__ __forceinline__ void tri_solve(float *tri, float *aux /* [192] */, float *tbuf /* [K] */, float y0,
+__device__ __forceinline__ void tri_solve(float *tri, float *aux /* [TRI_AUX_FLOATS<K>] */, float *tbuf /* [K] */, float y0,
                                           float y1, int k, int32_t *err_flag) {
     static_assert(K % 16 == 0 && K >= 16 && K <= 128, "unsupported system size");
     constexpr bool TWO = K > 64;
@@ -55,7 +62,7 @@ __device__ __forceinline__ void tri_solve(float *tri, float *aux /* [192] */, fl
     const bool hasa = ra < K, hasb = TWO && rb < K;
     const int a = lane & 15, q = lane >> 4;
     float *rpbuf = aux;
-    float *rowa = tri + tri_row(hasa ? ra : 0), *rowb = tri + tri_row(hasb ? rb : 0);
+    float *rowa = tri + tri_row<K>(hasa ? ra : 0), *rowb = tri + tri_row<K>(hasb ? rb : 0);
     float rp0 = 1.f, rp1 = 1.f;
     static_for<0, NT>([&](auto pp) {
         constexpr int p = decltype(pp)::value;
@@ -142,7 +149,7 @@ __device__ __forceinline__ void tri_solve(float *tri, float *aux /* [192] */, fl
                 const float4 rpv = *(const float4 *)(rpbuf + P0 + 4 * q);
                 float4 z[T];
 #pragma unroll
-                for (int t = 0; t < T; ++t) z[t] = *(const float4 *)(tri + tri_row(16 * (p + 1 + t) + a) + P0 + 4 * q);
+                for (int t = 0; t < T; ++t) z[t] = *(const float4 *)(tri + tri_row<K>(16 * (p + 1 + t) + a) + P0 + 4 * q);
                 static_for<0, T>([&](auto tii) {
                     constexpr int ti = decltype(tii)::value;
                     const float4 za = make_float4(-z[ti].x * rpv.x, -z[ti].y * rpv.y, -z[ti].z * rpv.z, -z[ti].w * rpv.w);
@@ -154,7 +161,7 @@ __device__ __forceinline__ void tri_solve(float *tri, float *aux /* [192] */, fl
                     float4 *cell[ti + 1];
 #pragma unroll
                     for (int tj = 0; tj <= ti; ++tj) {
-                        cell[tj] = (float4 *)(tri + tri_row(16 * (p + 1 + ti) + a) + 16 * (p + 1 + tj) + 4 * q);
+                        cell[tj] = (float4 *)(tri + tri_row<K>(16 * (p + 1 + ti) + a) + 16 * (p + 1 + tj) + 4 * q);
                         const float4 c4 = *cell[tj];
                         acc[tj] = floatx4{c4.x, c4.y, c4.z, c4.w};
                     }
@@ -179,8 +186,8 @@ __device__ __forceinline__ void tri_solve(float *tri, float *aux /* [192] */, fl
 
     // ---- back-substitution, eight rows of the factor fetched ahead of the dependent chain.  Every lane reads
     // row R at its own column: lanes at or beyond R have their unknown already and go on computing on
-    // whatever lies there (the row's padding, later rows, at most the first 127 floats after the triangle,
-    // which every caller's LDS layout has).  Groups of rows at or beyond k hold t = 0.
+    // whatever lies there (the row's padding, later rows, at most the first 127 floats after the triangle - 63 for
+    // K <= 64 -, which every caller's LDS layout has).  Groups of rows at or beyond k hold t = 0.
     float t0 = 0.f, t1v = 0.f;
     static_for<0, K / 8>([&](auto gg) {
         constexpr int Rt = K - 1 - 8 * decltype(gg)::value;  // the group's last row; rows Rt-7 .. Rt
@@ -189,7 +196,7 @@ __device__ __forceinline__ void tri_solve(float *tri, float *aux /* [192] */, fl
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int Rr = Rt - i;
-                const float *row = tri + tri_row(Rr);
+                const float *row = tri + tri_row<K>(Rr);
                 fa[i] = row[lane];
                 if (Rr >= 64) fb[i] = row[64 + lane];
             }
