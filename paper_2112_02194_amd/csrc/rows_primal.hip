@@ -4,12 +4,12 @@
 //     for every stored (u, i, y):  A += v_i (x) v_i ;  b += y * v_i
 //     x_u = A^{-1} b            (Cholesky, A is symmetric positive definite because lambda > 0)
 //
-// One workgroup owns one row (or one segment of a long row).  The gathered rows of the fixed
+// One workgroup owns one row (or one segment of a long row).  d < 64: the gathered rows of the fixed
 // table go straight from global memory into MFMA operand registers (no staging): lane (m, kk)
 // loads the NC consecutive columns NC*m.. of the kk-th entry of the current step, wavefront I of
-// the workgroup accumulates tile-row I of V_I^T V_I (see Geo<>).  The finished tiles are written
-// to LDS together with alpha*G + lambda*I, factorised there, and the two triangular solves give
-// the new row, which is rounded once to the table's element type.
+// the workgroup accumulates tile-row I of V_I^T V_I (see Geo<>).  d >= 64: accumulate_staged.  The finished
+// tiles are written to LDS together with alpha*G + lambda*I, factorised there, and the two triangular solves
+// give the new row, which is rounded once to the table's element type.
 //
 // Rows longer than `split` are cut into segments (the counterpart of the paper's Section 4.3 row
 // splitting): each segment's partial statistics go to a workspace and a second kernel sums them
@@ -95,19 +95,28 @@ __device__ __forceinline__ void accumulate_entries(const void *__restrict__ V, i
     }
 }
 
-// ---------------------------------------------------------------------------------------------- accumulate, bf16 tables
-// The same statistics for bf16 tables with d = 64 or 128 on the bf16 matrix cores (16 times the fp32 rate;
-// bf16 x bf16 products are exact in fp32, so nothing changes numerically except the order of the sums).  A
-// step takes 32 entries: lane (m, kq) loads columns 16 c + 8 kq .. of entry m (16 bytes per piece); the
-// matrix core transposes each 32-column block by a product with a constant 0/1 selection operand (see
-// gramian_bf16_kernel: exact), the packed results are the K-contiguous operands (K = the step's entries) of
-// the block products V_I^T V_I.  Every wavefront gathers and transposes all entries but owns only the block
-// pairs p with p % 4 == wave of the upper block triangle (ten pairs at d = 128, three at d = 64), so that it
-// carries at most three accumulator tiles.  b = sum y v is formed by wavefront 0 from the transposed fp32
-// values.  On return acc[p / 4] holds pair p = (gi, gj): element v of lane (m, kq) is entry
-// (32 gi + 8 (v / 4) + 4 kq + v % 4, 32 gj + m); lanes with kq == 0 of wavefront 0 hold b[32 g + m] in bsum[g].
+// ---------------------------------------------------------------------------------------------- accumulate, d >= 64
+// The same statistics for d = 64 or 128 on the bf16 matrix cores.  bf16 entries are operands as they are; fp32 entries are
+// cut into three bf16 parts, x = h + m + l exactly, and a product is taken as hh' + hm' + mh' + hl' + lh' + mm' (what is
+// dropped is below the rounding of an fp32 product); the products of 16 entries are summed inside the matrix core from
+// zero, small terms first, and join the running sum by a vector addition, which rounds to nearest.
+//
+// Batches of 32 entries: the workgroup gathers each row once (16 bytes of the parts per thread, whole rows side by side, the
+// next batch requested before this one's products), cuts it and leaves the parts in LDS.  The product contracts over the
+// entries, so an operand needs eight entries of one column per lane, which is what the transposing LDS read delivers
+// (ds_read_b64_tr_b16: of four rows of 16 elements, lane i of a group of 16 gets column i).  The 64-byte blocks of a row
+// are permuted by its number, so that the four rows of a read lie in different banks.  Wavefront w owns the block pairs
+// p with p % 4 == w of the upper block triangle (ten at d = 128, three at d = 64).
+// On return acc[p / 4] holds pair p = (gi, gj): element v of lane (m, kq) is entry
+// (32 gi + 8 (v / 4) + 4 kq + v % 4, 32 gj + m), and thread c < D holds b[c] in b.
+//
+// What bounds it: with fp32 tables the matrix cores (480 products of 32 clocks per batch and d = 128, four wavefronts; the
+// fp32 instruction, which has no use for the symmetry either, takes 4.3 times as long), with bf16 tables the gather and the
+// solve that follows.  Together with the solve by four wavefronts, against a gather by every wavefront, the fp32 instruction
+// and one solving wavefront: 825 000 rows of 129 to 512 entries, bf16, 59 -> 34 ms; the segments of a 10M x 10M fp32 half
+// 7.6 -> 3.45 ms, its rows of 129 to 512 entries 2.66 -> 1.44 ms (all d = 128).
 template <int D> struct BlockPairs {
-    static constexpr int NB = D / 32, COUNT = NB * (NB + 1) / 2;
+    static constexpr int NB = D / 32, COUNT = NB * (NB + 1) / 2, PER_WAVE = (COUNT + 3) / 4;
     static constexpr int first(int p) {  // pairs in the order (0,0) (0,1) .. (0,NB-1) (1,1) ..
         int g = 0;
         while (p >= NB - g) {
@@ -126,82 +135,154 @@ template <int D> struct BlockPairs {
     }
 };
 
-template <int D>
-__device__ __forceinline__ void accumulate_entries_bf16(const uint16_t *__restrict__ V, int64_t ld,
-                                                        const int32_t *__restrict__ indices,
-                                                        const float *__restrict__ values, int64_t begin, int64_t end,
-                                                        int wave, floatx16 (&acc)[3], float (&bsum)[4]) {
+template <int D, bool BF16> struct Staging {
+    static constexpr int BATCH = 32, PARTS = BF16 ? 1 : 3, ROW = 2 * D, PLANE = BATCH * ROW;
+    static constexpr int BUFS = BF16 ? 2 : 1;  // two buffers need one barrier per batch, one needs two; three parts take the space
+    static constexpr int PPR = D / 8, EPP = 256 / PPR, NP = BATCH / EPP;  // pieces of 8 columns per row; entries per pass; passes
+    static constexpr int BYTES = BUFS * PARTS * PLANE, SUM_BYTES = EPP * D * 4;  // the sums of b reuse the space
+    static constexpr int LDS_BYTES = BYTES > SUM_BYTES ? BYTES : SUM_BYTES;
+    // rows that share 256 bytes of LDS lie in different banks anyway; the next ones get their blocks exchanged
+    static __device__ int block_shift(int entry) { return (entry / (256 / ROW)) % (ROW / 64); }
+};
+
+template <int D, bool BF16>
+__device__ __forceinline__ void accumulate_staged(const void *__restrict__ V, int64_t ld, const int32_t *__restrict__ indices,
+                                                  const float *__restrict__ values, int64_t begin, int64_t end, int wave_s,
+                                                  char *lds, floatx16 (&acc)[BlockPairs<D>::PER_WAVE], float &b) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef short shortx4 __attribute__((ext_vector_type(4)));
+    typedef short shortx8 __attribute__((ext_vector_type(8)));
+    using S = Staging<D, BF16>;
     using BP = BlockPairs<D>;
-    constexpr int NB = D / 32, NCH = D / 16;
-    const int lane = opaque_tid() & 63, m = lane & 31, kq = lane >> 5;
-    const uint32_t ld32 = (uint32_t)ld;
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-    bf16x8 sel[2];  // selection operands: sel[h] has a one at (k, 16 h + k)
+    const int tid = opaque_tid(), lane = tid & 63;
+    const uint32_t ld32 = (uint32_t)ld;  // the leading dimension fits 32 bits (checked on the host)
+    const int pc = tid % S::PPR, e0 = tid / S::PPR;  // this thread's piece, its entry of a pass
+    constexpr int RAW = BF16 ? 1 : 2;                // 16-byte loads per piece
+
+    float4 raw[S::NP][RAW];
+    float y[S::NP], bsum[8];
+    int32_t idx[S::NP];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        u32x4 w = {0u, 0u, 0u, 0u};
-        const int k = m - 16 * h - 8 * kq;
+    for (int c = 0; c < 8; ++c) bsum[c] = 0.f;
+    auto ids = [&](int64_t base) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-            if (k == e) w[e / 2] = (e & 1) ? 0x3F800000u : 0x00003F80u;
-        sel[h] = __builtin_bit_cast(bf16x8, w);
-    }
-    for (int64_t base = begin; base < end; base += 64) {
-        const int64_t p = base + lane;
-        const int myidx = p < end ? indices[p] : -1;
-        const float myy = p < end ? (values ? values[p] : 1.f) : 0.f;
-        const int cnt = (int)((end - base) < 64 ? (end - base) : 64);
-        for (int s0 = 0; s0 < cnt; s0 += 32) {
-            const int idx = __shfl(myidx, s0 + m);
-            u32x4 raw[NCH];
+        for (int i = 0; i < S::NP; ++i) {
+            const int64_t p = base + i * S::EPP + e0;
+            idx[i] = p < end ? indices[p] : -1;
+        }
+    };
+    auto fetch = [&](int64_t base) {
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) raw[c] = u32x4{0u, 0u, 0u, 0u};
-            if (idx >= 0) {
-                const uint16_t *row = V + (int64_t)((uint64_t)(uint32_t)idx * ld32) + 8 * kq;
+        for (int i = 0; i < S::NP; ++i) {
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) raw[c] = *(const u32x4 *)(row + 16 * c);
-            }
-            bf16x8 op[NB][2];
-#pragma unroll
-            for (int g = 0; g < NB; ++g) {
-                floatx16 t;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) t[v] = 0.f;
-                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, raw[2 * g]), sel[0], t, 0, 0, 0);
-                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, raw[2 * g + 1]), sel[1], t, 0, 0, 0);
-                // t[v] = V[entry s0 + 8 (v / 4) + 4 kq + v % 4][32 g + m]
-#pragma unroll
-                for (int x = 0; x < 2; ++x) {
-                    const u32x4 w = {__builtin_amdgcn_perm(__float_as_uint(t[8 * x + 1]), __float_as_uint(t[8 * x + 0]), 0x07060302u),
-                                     __builtin_amdgcn_perm(__float_as_uint(t[8 * x + 3]), __float_as_uint(t[8 * x + 2]), 0x07060302u),
-                                     __builtin_amdgcn_perm(__float_as_uint(t[8 * x + 5]), __float_as_uint(t[8 * x + 4]), 0x07060302u),
-                                     __builtin_amdgcn_perm(__float_as_uint(t[8 * x + 7]), __float_as_uint(t[8 * x + 6]), 0x07060302u)};
-                    op[g][x] = __builtin_bit_cast(bf16x8, w);
+            for (int r = 0; r < RAW; ++r) raw[i][r] = make_float4(0.f, 0.f, 0.f, 0.f);
+            y[i] = 0.f;
+            if (idx[i] >= 0) {
+                const int64_t off = (int64_t)((uint64_t)(uint32_t)idx[i] * ld32) + 8 * pc;
+                y[i] = values ? values[base + i * S::EPP + e0] : 1.f;
+                if constexpr (BF16) {
+                    raw[i][0] = *(const float4 *)((const uint16_t *)V + off);
+                } else {
+                    raw[i][0] = *(const float4 *)((const float *)V + off);
+                    raw[i][1] = *(const float4 *)((const float *)V + off + 4);
                 }
-                if (wave_s == 0) {  // scalar branch: the right-hand side rides in wavefront 0
-                    if (values) {
+            }
+        }
+    };
+    auto stash = [&](char *buf) {
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) bsum[g] += __shfl(myy, s0 + 8 * (v >> 2) + 4 * kq + (v & 3)) * t[v];
-                    } else {  // y = 1; slots without an entry hold zeros
+        for (int i = 0; i < S::NP; ++i) {
+            const int e = i * S::EPP + e0;
+            char *dst = buf + e * S::ROW + (((pc / 4) ^ S::block_shift(e)) * 64 + (pc % 4) * 16);
+            float x[8];
+            if constexpr (BF16) {
+                *(float4 *)dst = raw[i][0];
+                const u32x4 w = __builtin_bit_cast(u32x4, raw[i][0]);
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) bsum[g] += t[v];
+                for (int c = 0; c < 4; ++c) {
+                    x[2 * c] = __uint_as_float(w[c] << 16);
+                    x[2 * c + 1] = __uint_as_float(w[c] & 0xffff0000u);
+                }
+            } else {
+                x[0] = raw[i][0].x; x[1] = raw[i][0].y; x[2] = raw[i][0].z; x[3] = raw[i][0].w;
+                x[4] = raw[i][RAW - 1].x; x[5] = raw[i][RAW - 1].y; x[6] = raw[i][RAW - 1].z; x[7] = raw[i][RAW - 1].w;
+                float r[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) r[c] = x[c];
+#pragma unroll
+                for (int part = 0; part < 3; ++part) {
+                    *(u32x4 *)(dst + part * S::PLANE) = u32x4{pack_upper(r[0], r[1]), pack_upper(r[2], r[3]), pack_upper(r[4], r[5]), pack_upper(r[6], r[7])};
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) r[c] = lower_part(r[c]);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 8; ++c) bsum[c] = fmaf(y[i], x[c], bsum[c]);
+        }
+    };
+    // this lane's address inside a plane for column block 0, entries 0..: row 8 (lane / 32) + lane % 16 / 4, columns
+    // 16 (lane / 16 % 2) + 4 (lane % 4) ..; the block number enters by exclusive or
+    const int trow = 8 * (lane >> 5) + ((lane >> 2) & 3);
+    const int tbase = trow * S::ROW + S::block_shift(trow) * 64 + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    auto operand = [&](const char *plane, int ks, int g) {  // eight entries of column 32 g + lane % 32
+        typedef __attribute__((address_space(3))) shortx4 *lds_ptr;
+        const char *at = plane + (tbase ^ (g * 64)) + 16 * ks * S::ROW;
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(at));
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(at + 4 * S::ROW));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+
+    ids(begin);
+    fetch(begin);
+    ids(begin + S::BATCH);
+    int which = 0;
+    for (int64_t base = begin; base < end; base += S::BATCH) {
+        char *buf = lds + which * (S::PARTS * S::PLANE);
+        stash(buf);
+        fetch(base + S::BATCH);  // past the end: zeros, no loads
+        ids(base + 2 * S::BATCH);
+        __syncthreads();
+        static_for<0, BP::COUNT>([&](auto pp) {
+            constexpr int pr = decltype(pp)::value, gi = BP::first(pr), gj = BP::second(pr);
+            if (wave_s == pr % 4) {  // scalar branch
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    bf16x8 A[S::PARTS], B[S::PARTS];
+#pragma unroll
+                    for (int t = 0; t < S::PARTS; ++t) {
+                        A[t] = operand(buf + t * S::PLANE, ks, gi);
+                        B[t] = gi == gj ? A[t] : operand(buf + t * S::PLANE, ks, gj);
+                    }
+                    if constexpr (BF16) {
+                        acc[pr / 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[0], B[0], acc[pr / 4], 0, 0, 0);
+                    } else {
+                        constexpr int PA[6] = {1, 2, 0, 1, 0, 0}, PB[6] = {1, 0, 2, 0, 1, 0};  // mm lh hl mh hm hh
+                        floatx16 t16;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) t16[v] = 0.f;
+#pragma unroll
+                        for (int t = 0; t < 6; ++t) t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[PA[t] % S::PARTS], B[PB[t] % S::PARTS], t16, 0, 0, 0);
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[pr / 4][v] += t16[v];
                     }
                 }
             }
-            static_for<0, BP::COUNT>([&](auto pp) {
-                constexpr int pr = decltype(pp)::value, gi = BP::first(pr), gj = BP::second(pr);
-                if (wave_s == pr % 4) {
-                    acc[pr / 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[gi][0], op[gj][0], acc[pr / 4], 0, 0, 0);
-                    acc[pr / 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[gi][1], op[gj][1], acc[pr / 4], 0, 0, 0);
-                }
-            });
-        }
+        });
+        if constexpr (S::BUFS == 1) __syncthreads();
+        else which ^= 1;
     }
-    if (wave_s == 0) {
-#pragma unroll
-        for (int g = 0; g < NB; ++g) bsum[g] += __shfl_xor(bsum[g], 32);
+    // b: the threads of one piece, summed in a fixed order
+    if constexpr (S::BUFS == 2) __syncthreads();
+    float *sums = (float *)lds;
+    *(float4 *)(sums + e0 * D + 8 * pc) = make_float4(bsum[0], bsum[1], bsum[2], bsum[3]);
+    *(float4 *)(sums + e0 * D + 8 * pc + 4) = make_float4(bsum[4], bsum[5], bsum[6], bsum[7]);
+    __syncthreads();
+    b = 0.f;
+    if (tid < D) {
+#pragma unroll 8
+        for (int e = 0; e < S::EPP; ++e) b += sums[e * D + tid];
     }
+    __syncthreads();  // the caller may overwrite the LDS
 }
 
 // Sum bsum over the KS lanes that hold the same columns; afterwards lanes with kk == 0 hold b.
@@ -266,20 +347,25 @@ template <int D> struct Packed {
     static constexpr size_t LDS_BYTES = (size_t)(OFF_RHS + D) * sizeof(float);
 };
 
-// Called by one wavefront after a workgroup barrier: solves the packed system and stores the row,
-// rounded once to the table's element type.  The other wavefronts of the workgroup may have exited.
+// Called by the whole workgroup behind a barrier: solves the packed system and stores the row, rounded once to the
+// table's element type.  Returns at once in the wavefronts that have nothing left to do; wavefront 0 stores.
 template <int D, bool BF16>
-__device__ __forceinline__ void packed_solve_store(float *lds, void *X, int64_t xoff, int32_t *err_flag) {
+__device__ __forceinline__ void packed_solve_store(float *lds, void *X, int64_t xoff, int wave_s, int32_t *err_flag) {
     const int lane = opaque_tid() & 63;
-    float *tbuf = lds + Packed<D>::OFF_T;
-    const float *rhs = lds + Packed<D>::OFF_RHS;
-    const float y0 = lane < D ? rhs[lane] : 0.f;
-    const float y1 = (D > 64 && 64 + lane < D) ? rhs[64 + lane] : 0.f;
+    float *tbuf = lds + Packed<D>::OFF_T, *aux = lds + Packed<D>::OFF_COL, *rhs = lds + Packed<D>::OFF_RHS;
+    team_tri_eliminate<D>(lds, aux, rhs, wave_s, err_flag);
+    if (wave_s != 0) return;
     int k = D;
-    asm volatile("" : "+s"(k));  // opaque on purpose: with a compile-time step count the solver's steps merge
-                                 // into one block, whose scheduling runs out of registers
-    tri_solve<D>(lds, lds + Packed<D>::OFF_COL, tbuf, y0, y1, k, err_flag);
+    asm volatile("" : "+s"(k));  // opaque on purpose: with a compile-time step count the steps merge into one block,
+                                 // whose scheduling runs out of registers
+    tri_back<D>(lds, tbuf, rhs[lane], D > 64 ? rhs[64 + lane] : 0.f, aux[lane], D > 64 ? aux[64 + lane] : 1.f, k);
     for (int c = lane; c < D; c += 64) store_elem<BF16>(X, xoff + c, tbuf[c]);
+}
+
+// Four consecutive entries of G, whose base need not be 16-byte aligned (`aligned`: it is; uniform for the launch).
+__device__ __forceinline__ float4 load_g4(const float *__restrict__ G, int at, bool aligned) {
+    if (aligned) return *(const float4 *)(G + at);
+    return make_float4(G[at], G[at + 1], G[at + 2], G[at + 3]);
 }
 
 // ---------------------------------------------------------------------------------------------- conjugate gradients
@@ -340,12 +426,12 @@ __device__ __forceinline__ void cg_solve_lds(const float *a, float *aux, int max
 
 template <int D>
 __device__ __forceinline__ void solve_spd_lds(float *a, float *aux, int32_t *err_flag, int solver, int cg_iters,
-                                              float cg_tol) {
+                                              float cg_tol) {  // d < 64
     if (solver == ALS_SOLVER_CG) {  // uniform for the launch
         cg_solve_lds<D>(a, aux, cg_iters, cg_tol);
         return;
     }
-    if constexpr (D < 64) cholesky_solve_lds<D>(a, aux, err_flag);  // D >= 64: packed path of the callers
+    cholesky_solve_lds<D>(a, aux, err_flag);
 }
 
 // ---------------------------------------------------------------------------------------------- kernels
@@ -378,52 +464,82 @@ __device__ __forceinline__ bool primal_step(
         end = segs[item].end;
     }
 
-    // The statistics are accumulated in one of two register layouts (fp32 matrix cores: tile-row `wave` of the
-    // column-interleaved tiles; bf16 tables with d >= 64: block pairs of the upper block triangle, see
-    // accumulate_entries_bf16) and handed, element by element, to whatever wants them: deliver(put, put_b)
-    // calls put(r, c, value) for entries of V_I^T V_I - every (r, c) with c <= r at least once, possibly also
-    // the mirror (c, r) - and put_b(c, value) for the entries of b.
-    constexpr bool CORES16 = BF16 && D >= 64;
-    acc_t acc[CORES16 ? 1 : NC];
-    floatx16 acc16[CORES16 ? 3 : 1];
-    float bsum[NC];
+    if constexpr (D >= 64) {
+        using BP = BlockPairs<D>;
+        const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+        floatx16 acc[BP::PER_WAVE];
+        float b;
 #pragma unroll
-    for (int j = 0; j < NC; ++j) bsum[j] = 0.f;
-    if constexpr (CORES16) {
+        for (int j = 0; j < BP::PER_WAVE; ++j)
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc16[j][v] = 0.f;
-        accumulate_entries_bf16<D>((const uint16_t *)V, ldv, indices, values, begin, end, wave, acc16, bsum);
-    } else {
-#pragma unroll
-        for (int j = 0; j < NC; ++j)
-#pragma unroll
-            for (int v = 0; v < ACC; ++v) acc[j][v] = 0.f;
-        accumulate_entries<D, BF16>(V, ldv, indices, values, begin, end, wave, acc, bsum);
-        fold_b<D>(bsum);
-    }
-    auto deliver = [&](auto &&put, auto &&put_b) {
-        if constexpr (CORES16) {
-            using BP = BlockPairs<D>;
+            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+        accumulate_staged<D, BF16>(V, ldv, indices, values, begin, end, wave_s, (char *)lds, acc, b);
+        // put4(r, c, values) for columns c .. c + 3 of row r: the blocks of the lower block triangle, whole
+        auto deliver = [&](auto &&put4) {
             const int m32 = lane & 31, kq = lane >> 5;
-            const int wave_s = __builtin_amdgcn_readfirstlane(wave);
             static_for<0, BP::COUNT>([&](auto pp) {
                 constexpr int pr = decltype(pp)::value, gi = BP::first(pr), gj = BP::second(pr);
                 if (wave_s == pr % 4) {
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int r = 32 * gi + 8 * (v >> 2) + 4 * kq + (v & 3), c = 32 * gj + m32;
-                        put(r, c, acc16[pr / 4][v]);
-                        if constexpr (gi != gj) put(c, r, acc16[pr / 4][v]);
-                    }
+                    for (int x = 0; x < 4; ++x)
+                        put4(32 * gj + m32, 32 * gi + 8 * x + 4 * kq,
+                             make_float4(acc[pr / 4][4 * x], acc[pr / 4][4 * x + 1], acc[pr / 4][4 * x + 2], acc[pr / 4][4 * x + 3]));
                 }
             });
-            if (wave_s == 0 && kq == 0) {
-#pragma unroll
-                for (int g = 0; g < D / 32; ++g) put_b(32 * g + m32, bsum[g]);
-            }
+        };
+        if constexpr (MODE == MODE_SEGMENT) {  // only the lower block triangle of the partial is written and read
+            float *out = partials + item * (int64_t)(D * D + D);
+            deliver([&](int r, int c, const float4 &v) { *(float4 *)(out + r * D + c) = v; });
+            if (opaque_tid() < D) out[D * D + opaque_tid()] = b;
+            (void)last;
+            return true;
         } else {
+            const bool g_aligned = ((uintptr_t)G & 15) == 0;
+            auto finished = [&](int r, int c, const float4 &v) {  // + alpha*G + lambda*I
+                const float4 g = load_g4(G, r * D + c, g_aligned);
+                return make_float4(v.x + alpha * g.x + (r == c ? lambda : 0.f), v.y + alpha * g.y + (r == c + 1 ? lambda : 0.f),
+                                   v.z + alpha * g.z + (r == c + 2 ? lambda : 0.f), v.w + alpha * g.w + (r == c + 3 ? lambda : 0.f));
+            };
+            if (solver == ALS_SOLVER_DIRECT) {  // uniform for the launch
+                // lower triangle of A = alpha*G + lambda*I + V_I^T V_I, packed: what a row holds beyond its last tile of
+                // 16 columns is not stored
+                deliver([&](int r, int c, const float4 &v) {
+                    if (c < 16 * (r / 16 + 1)) *(float4 *)(lds + tri_row<D>(r) + c) = finished(r, c, v);
+                });
+                if (opaque_tid() < D) lds[Packed<D>::OFF_RHS + opaque_tid()] = b;
+                __syncthreads();
+                packed_solve_store<D, BF16>(lds, X, u * ldx, wave_s, err_flag);
+                if (last && wave_s != 0) return false;
+            } else {
+                // entry (r, c) at a[c*LD + r], both triangles; warm start from the row's current content
+                deliver([&](int r, int c, const float4 &v) {
+                    const float4 w = finished(r, c, v);
+                    const float e[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (c + i <= r) a[(c + i) * LD + r] = a[r * LD + c + i] = e[i];
+                });
+                if (opaque_tid() < D) bvec[opaque_tid()] = b;
+                for (int c = opaque_tid(); c < D; c += Team<D>::THREADS) aux[2 * D + c] = load_elem<BF16>(X, u * ldx + c);
+                __syncthreads();
+                cg_solve_lds<D>(a, aux, cg_iters, cg_tol);
+                for (int c = opaque_tid(); c < D; c += Team<D>::THREADS) store_elem<BF16>(X, u * ldx + c, aux[2 * D + c]);
+            }
+            if (!last) __syncthreads();  // the solver is done with the LDS before the next row arrives
+            return true;
+        }
+    } else {
+        acc_t acc[NC];
+        float bsum[NC];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            bsum[j] = 0.f;
+#pragma unroll
+            for (int v = 0; v < ACC; ++v) acc[j][v] = 0.f;
+        }
+        accumulate_entries<D, BF16>(V, ldv, indices, values, begin, end, wave, acc, bsum);
+        fold_b<D>(bsum);
+        auto deliver = [&](auto &&put, auto &&put_b) {
 #pragma unroll
             for (int j = 0; j < NC; ++j)
 #pragma unroll
@@ -432,47 +548,26 @@ __device__ __forceinline__ bool primal_step(
 #pragma unroll
                 for (int j = 0; j < NC; ++j) put_b(NC * m + j, bsum[j]);
             }
-        }
-    };
-
-    if constexpr (MODE == MODE_SEGMENT) {
-        float *out = partials + item * (int64_t)(D * D + D);
-        deliver([&](int r, int c, float v) { out[r * D + c] = v; }, [&](int c, float v) { out[D * D + c] = v; });
-        (void)last;
-        return true;
-    } else {
-        if constexpr (D >= 64) {
-            if (solver == ALS_SOLVER_DIRECT) {  // uniform for the launch
-                // lower triangle of A = alpha*G + lambda*I + V_I^T V_I, packed, then one wavefront solves
-                float *tri = lds, *rhs = lds + Packed<D>::OFF_RHS;
-                deliver(
-                    [&](int r, int c, float v) {
-                        if (c <= r) tri[tri_row<D>(r) + c] = v + alpha * G[r * D + c] + (r == c ? lambda : 0.f);
-                    },
-                    [&](int c, float v) { rhs[c] = v; });
-                __syncthreads();
-                // scalar test: the solver must not sit in (what looks like) divergent control flow
-                if (__builtin_amdgcn_readfirstlane(wave) != 0) {
-                    if (last) return false;
-                } else {
-                    packed_solve_store<D, BF16>(lds, X, u * ldx, err_flag);
-                }
-                if (!last) __syncthreads();  // the solver is done with the LDS before the next row's tiles arrive
-                return true;
+        };
+        if constexpr (MODE == MODE_SEGMENT) {
+            float *out = partials + item * (int64_t)(D * D + D);
+            deliver([&](int r, int c, float v) { out[r * D + c] = v; }, [&](int c, float v) { out[D * D + c] = v; });
+            (void)last;
+            return true;
+        } else {
+            // A = alpha*G + lambda*I + V_I^T V_I into LDS (entry (r,c) at a[c*LD + r])
+            deliver([&](int r, int c, float v) { a[c * LD + r] = v + alpha * G[r * D + c] + (r == c ? lambda : 0.f); },
+                    [&](int c, float v) { bvec[c] = v; });
+            if (solver == ALS_SOLVER_CG) {  // warm start from the row's current content
+                for (int c = opaque_tid(); c < D; c += Team<D>::THREADS) aux[2 * D + c] = load_elem<BF16>(X, u * ldx + c);
             }
+            __syncthreads();
+            solve_spd_lds<D>(a, aux, err_flag, solver, cg_iters, cg_tol);
+            const float *xout = aux + 2 * D;
+            for (int c = opaque_tid(); c < D; c += Team<D>::THREADS) store_elem<BF16>(X, u * ldx + c, xout[c]);
+            if (!last) __syncthreads();  // before the next row's tiles overwrite the LDS
+            return true;
         }
-        // A = alpha*G + lambda*I + V_I^T V_I into LDS (entry (r,c) at a[c*LD + r])
-        deliver([&](int r, int c, float v) { a[c * LD + r] = v + alpha * G[r * D + c] + (r == c ? lambda : 0.f); },
-                [&](int c, float v) { bvec[c] = v; });
-        if (solver == ALS_SOLVER_CG) {  // warm start from the row's current content
-            for (int c = opaque_tid(); c < D; c += Team<D>::THREADS) aux[2 * D + c] = load_elem<BF16>(X, u * ldx + c);
-        }
-        __syncthreads();
-        solve_spd_lds<D>(a, aux, err_flag, solver, cg_iters, cg_tol);
-        const float *xout = aux + 2 * D;
-        for (int c = opaque_tid(); c < D; c += Team<D>::THREADS) store_elem<BF16>(X, u * ldx + c, xout[c]);
-        if (!last) __syncthreads();  // before the next row's tiles overwrite the LDS
-        return true;
     }
 }
 
@@ -482,7 +577,7 @@ __device__ __forceinline__ bool primal_step(
 // The two launch forms (see StepGrid): LOOP = false, workgroup b takes item first + b if there is one;
 // LOOP = true, grid-stride walk from item `first` on.  *count_ptr is the number of items (device memory).
 template <int D, bool BF16, int MODE, bool LOOP>
-__global__ __launch_bounds__(Team<D>::THREADS, LOOP ? 1 : 2) void primal_kernel(
+__global__ __launch_bounds__(Team<D>::THREADS, D < 64 ? (LOOP ? 1 : 2) : (D == 128 && !BF16 ? (LOOP ? 2 : 3) : 4 - LOOP)) void primal_kernel(
     const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices, const float *__restrict__ values,
     const void *__restrict__ V, int64_t ldv, const float *__restrict__ G, float alpha, float lambda,
     void *__restrict__ X, int64_t ldx, int64_t row_begin, const int32_t *__restrict__ row_list,
@@ -519,6 +614,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const LongRow *__r
     const LongRow lr = long_rows[row];
     const int e = blockIdx.y * 256 + opaque_tid();
     if (e >= D * D + D || lr.nseg <= 1) continue;
+    if (D >= 64 && e < D * D && e % D / 32 > e / D / 32) continue;  // segments leave the lower block triangle only
     float *p0 = partials + (int64_t)lr.seg_first * (D * D + D) + e;
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
     int g = 0;
@@ -545,22 +641,21 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
     const float *p0 = partials + (int64_t)lr.seg_first * (D * D + D);
     if constexpr (D >= 64) {
         if (solver == ALS_SOLVER_DIRECT) {
-            float *tri = lds, *rhs = lds + Packed<D>::OFF_RHS;
-            for (int e = opaque_tid(); e < D * D + D; e += T) {
-                const float s = p0[e];
-                if (e < D * D) {
-                    const int r = e / D, c = e % D;
-                    if (c <= r) tri[tri_row<D>(r) + c] = s + alpha * G[e] + (r == c ? lambda : 0.f);
-                } else {
-                    rhs[e - D * D] = s;
+            const bool g_aligned = ((uintptr_t)G & 15) == 0;
+            for (int e = opaque_tid(); e < D * D / 4; e += T) {
+                const int r = e / (D / 4), c = 4 * (e % (D / 4));
+                if (c < 16 * (r / 16 + 1)) {
+                    const float4 v = *(const float4 *)(p0 + 4 * e), g = load_g4(G, 4 * e, g_aligned);
+                    *(float4 *)(lds + tri_row<D>(r) + c) =
+                        make_float4(v.x + alpha * g.x + (r == c ? lambda : 0.f), v.y + alpha * g.y + (r == c + 1 ? lambda : 0.f),
+                                    v.z + alpha * g.z + (r == c + 2 ? lambda : 0.f), v.w + alpha * g.w + (r == c + 3 ? lambda : 0.f));
                 }
             }
+            if (opaque_tid() < D) lds[Packed<D>::OFF_RHS + opaque_tid()] = p0[D * D + opaque_tid()];
             __syncthreads();
-            if (__builtin_amdgcn_readfirstlane(opaque_tid() >> 6) != 0) {
-                if (last) return false;
-            } else {
-                packed_solve_store<D, BF16>(lds, X, lr.row * ldx, err_flag);
-            }
+            const int wave_s = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
+            packed_solve_store<D, BF16>(lds, X, lr.row * ldx, wave_s, err_flag);
+            if (last && wave_s != 0) return false;
             if (!last) __syncthreads();
             return true;
         }
@@ -569,7 +664,10 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
         const float s = p0[e];
         if (e < D * D) {
             const int r = e / D, c = e % D;
-            a[c * LD + r] = s + alpha * G[e] + (r == c ? lambda : 0.f);
+            if (D >= 64 && c > r) continue;  // the lower triangle serves both
+            const float v = s + alpha * G[e] + (r == c ? lambda : 0.f);
+            a[c * LD + r] = v;
+            if (D >= 64) a[r * LD + c] = v;
         } else {
             bvec[e - D * D] = s;
         }
@@ -578,7 +676,8 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
         for (int c = opaque_tid(); c < D; c += T) aux[2 * D + c] = load_elem<BF16>(X, lr.row * ldx + c);
     }
     __syncthreads();
-    solve_spd_lds<D>(a, aux, err_flag, solver, cg_iters, cg_tol);
+    if constexpr (D >= 64) cg_solve_lds<D>(a, aux, cg_iters, cg_tol);
+    else solve_spd_lds<D>(a, aux, err_flag, solver, cg_iters, cg_tol);
     const float *xout = aux + 2 * D;
     for (int c = opaque_tid(); c < D; c += T) store_elem<BF16>(X, lr.row * ldx + c, xout[c]);
     if (!last) __syncthreads();
@@ -609,6 +708,11 @@ __global__ __launch_bounds__(Team<D>::THREADS) void reduce_solve_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------- launchers
+// LDS of a workgroup that accumulates (segments), solves (summed segments), or does both
+template <int D, bool BF16> static constexpr size_t staging_lds_bytes() {
+    if constexpr (D >= 64) return Staging<D, BF16>::LDS_BYTES;
+    else return 0;
+}
 template <int D> static size_t solve_lds_bytes(int solver) {
     if constexpr (D >= 64) {
         if (solver == ALS_SOLVER_DIRECT) return Packed<D>::LDS_BYTES;
@@ -632,7 +736,7 @@ static als_status primal_typed(als_ctx *ctx, const als_csr *Y, const als_table *
         (const void *)kern_loop, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Team<D>::LDS_BYTES);  // both once per process
     ALS_HIP(ctx, attr);
     ALS_HIP(ctx, attr_loop);
-    const size_t lds_bytes = solve_lds_bytes<D>(prm->solver);
+    const size_t lds_bytes = std::max(solve_lds_bytes<D>(prm->solver), staging_lds_bytes<D, BF16>());
     timer_begin(ctx, T_PRIMAL, s);
     if (g.known > 0)
         hipLaunchKernelGGL(kern, dim3(g.known), dim3(Team<D>::THREADS), lds_bytes, s, Y->indptr, Y->indices, Y->values,
@@ -669,13 +773,14 @@ static als_status long_typed(als_ctx *ctx, const als_csr *Y, const als_table *V,
     ALS_HIP(ctx, attr);
     ALS_HIP(ctx, attr_loop);
     float *partials = (float *)ctx->seg_partials.p;
+    constexpr size_t seg_lds = staging_lds_bytes<D, BF16>();  // at most 24 KB: no attribute needed
     timer_begin(ctx, T_SEGMENT, s);
     if (g_seg.known > 0)
-        hipLaunchKernelGGL((primal_kernel<D, BF16, MODE_SEGMENT, false>), dim3(g_seg.known), dim3(Team<D>::THREADS), 0, s,
+        hipLaunchKernelGGL((primal_kernel<D, BF16, MODE_SEGMENT, false>), dim3(g_seg.known), dim3(Team<D>::THREADS), seg_lds, s,
                            Y->indptr, Y->indices, Y->values, V->data, V->ld, G, prm->alpha, prm->lambda, X->data, X->ld,
                            (int64_t)0, (const int32_t *)nullptr, segs, partials, counters + 1, 0, err, 0, 0, 0.f);
     if (g_seg.rest > 0)
-        hipLaunchKernelGGL((primal_kernel<D, BF16, MODE_SEGMENT, true>), dim3(g_seg.rest), dim3(Team<D>::THREADS), 0, s,
+        hipLaunchKernelGGL((primal_kernel<D, BF16, MODE_SEGMENT, true>), dim3(g_seg.rest), dim3(Team<D>::THREADS), seg_lds, s,
                            Y->indptr, Y->indices, Y->values, V->data, V->ld, G, prm->alpha, prm->lambda, X->data, X->ld,
                            (int64_t)0, (const int32_t *)nullptr, segs, partials, counters + 1, (int)g_seg.known, err, 0,
                            0, 0.f);

@@ -51,6 +51,47 @@ template <int DST> __device__ __forceinline__ float lane_set(float v, float unif
     return v;
 }
 
+// Back-substitution of the eliminated system by one wavefront: y0 / y1 hold u = M^-1 y and rp0 / rp1 the reciprocal
+// pivots of rows lane / 64+lane.
+template <int K>
+__device__ __forceinline__ void tri_back(const float *tri, float *tbuf, float y0, float y1, float rp0, float rp1, int k) {
+    const int lane = opaque_tid() & 63;
+    // Eight rows of the factor fetched ahead of the dependent chain.  Every lane reads
+    // row R at its own column: lanes at or beyond R have their unknown already and go on computing on
+    // whatever lies there (the row's padding, later rows, at most the first 127 floats after the triangle - 63 for
+    // K <= 64 -, which every caller's LDS layout has).  Groups of rows at or beyond k hold t = 0.
+    float t0 = 0.f, t1v = 0.f;
+    static_for<0, K / 8>([&](auto gg) {
+        constexpr int Rt = K - 1 - 8 * decltype(gg)::value;  // the group's last row; rows Rt-7 .. Rt
+        if (Rt - 7 < k) {
+            float fa[8], fb[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int Rr = Rt - i;
+                const float *row = tri + tri_row<K>(Rr);
+                fa[i] = row[lane];
+                if (Rr >= 64) fb[i] = row[64 + lane];
+            }
+            static_for<0, 8>([&](auto ii) {
+                constexpr int i = decltype(ii)::value, Rr = Rt - i;
+                if constexpr (Rr >= 64) {
+                    const float tR = lane_value(y1 * rp1, Rr - 64);
+                    t1v = lane_set<Rr - 64>(t1v, tR);
+                    y1 -= fb[i] * tR;
+                    y0 -= fa[i] * tR;
+                } else {
+                    const float tR = lane_value(y0 * rp0, Rr);
+                    t0 = lane_set<Rr>(t0, tR);
+                    y0 -= fa[i] * tR;
+                }
+            });
+        }
+    });
+    if (lane < K) tbuf[lane] = t0;
+    if (K > 64 && 64 + lane < K) tbuf[64 + lane] = t1v;
+    wave_sync();
+}
+
 template <int K>
 __device__ __forceinline__ void tri_solve(float *tri, float *aux /* [TRI_AUX_FLOATS<K>] */, float *tbuf /* [K] */, float y0,
                                           float y1, int k, int32_t *err_flag) {
@@ -184,39 +225,113 @@ __device__ __forceinline__ void tri_solve(float *tri, float *aux /* [TRI_AUX_FLO
     // negative, zero and NaN come out of the Newton step as NaN.
     if (__any(!(rp0 > 0.f) || !(rp1 > 0.f)) && lane == 0) atomicOr(err_flag, 1);
 
-    // ---- back-substitution, eight rows of the factor fetched ahead of the dependent chain.  Every lane reads
-    // row R at its own column: lanes at or beyond R have their unknown already and go on computing on
-    // whatever lies there (the row's padding, later rows, at most the first 127 floats after the triangle - 63 for
-    // K <= 64 -, which every caller's LDS layout has).  Groups of rows at or beyond k hold t = 0.
-    float t0 = 0.f, t1v = 0.f;
-    static_for<0, K / 8>([&](auto gg) {
-        constexpr int Rt = K - 1 - 8 * decltype(gg)::value;  // the group's last row; rows Rt-7 .. Rt
-        if (Rt - 7 < k) {
-            float fa[8], fb[8];
+    tri_back<K>(tri, tbuf, y0, y1, rp0, rp1, k);
+}
+// The same elimination by a workgroup of four wavefronts, for systems too few per compute unit to hide one wavefront's
+// chain (K = 128: a workgroup's triangle takes a quarter of the LDS).  Every wavefront that works on a panel eliminates the
+// panel's 16 pivot rows for itself (lanes 0 .. 15) and 48 of the rows below in its other lanes - the steps cost what
+// they cost with 16 rows, nothing is exchanged between wavefronts, and the numbers are those of tri_solve -, and the tiles
+// of the trailing update are dealt out to all four.  rhs[K] in LDS: y on entry, u = M^-1 y on exit; aux[0..K): reciprocal
+// pivots.  Called by all 256 threads behind a barrier; wavefront 0 returns last and may read what it and the others have
+// left in LDS, the others must not touch the LDS again before the next barrier.
+// With one wavefront the solve took 57 000 of a row's 131 000 clocks in the 50M-row power-law epoch (d = 128, bf16).
+template <int K>
+__device__ __forceinline__ void team_tri_eliminate(float *tri, float *aux, float *rhs, int wave_s, int32_t *err_flag) {
+    constexpr int NT = K / 16;
+    const int lane = opaque_tid() & 63, a = lane & 15, q = lane >> 4;
+    bool bad = false;
+    static_for<0, NT>([&](auto pp) {
+        constexpr int p = decltype(pp)::value, P0 = 16 * p, BELOW = K - P0 - 16, W = BELOW > 0 ? (BELOW + 47) / 48 : 1;
+        float x[16], y = 0.f;
+        const int row = lane < 16 ? P0 + lane : P0 + 48 * wave_s + lane;
+        const bool has = row < K;
+        float *cells = tri + tri_row<K>(has ? row : P0) + P0;
+        if (wave_s < W) {  // scalar branch
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int Rr = Rt - i;
-                const float *row = tri + tri_row<K>(Rr);
-                fa[i] = row[lane];
-                if (Rr >= 64) fb[i] = row[64 + lane];
+            for (int c4 = 0; c4 < 4; ++c4) {
+                const float4 v = *(const float4 *)(cells + 4 * c4);
+                x[4 * c4] = v.x; x[4 * c4 + 1] = v.y; x[4 * c4 + 2] = v.z; x[4 * c4 + 3] = v.w;
             }
-            static_for<0, 8>([&](auto ii) {
-                constexpr int i = decltype(ii)::value, Rr = Rt - i;
-                if constexpr (Rr >= 64) {
-                    const float tR = lane_value(y1 * rp1, Rr - 64);
-                    t1v = lane_set<Rr - 64>(t1v, tR);
-                    y1 -= fb[i] * tR;
-                    y0 -= fa[i] * tR;
-                } else {
-                    const float tR = lane_value(y0 * rp0, Rr);
-                    t0 = lane_set<Rr>(t0, tR);
-                    y0 -= fa[i] * tR;
+            y = rhs[has ? row : P0];
+            float rp, mine = 1.f;
+            auto prepare = [&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                const float pivot = lane_value(x[c], c);
+                rp = __builtin_amdgcn_rcpf(pivot);
+                rp = rp * (2.f - pivot * rp);  // one Newton step on the hardware reciprocal
+                mine = lane == c ? rp : mine;
+            };
+            prepare(std::integral_constant<int, 0>{});
+            static_for<0, 16>([&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                float cv[16];
+#pragma unroll
+                for (int j = c + 1; j < 16; ++j) cv[j] = lane_value(x[c], j);
+                const float uc = lane_value(y, c);
+                const float f = lane > c ? x[c] * rp : 0.f;
+                y -= f * uc;
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (c < 15) {
+                    x[c + 1] -= f * cv[c + 1];
+                    prepare(std::integral_constant<int, c + 1>{});
+#pragma unroll
+                    for (int j = c + 2; j < 16; ++j) x[j] -= f * cv[j];
                 }
+                __builtin_amdgcn_sched_barrier(0);
             });
+            if (lane >= 16 && has) {
+#pragma unroll
+                for (int c4 = 0; c4 < 4; ++c4) *(float4 *)(cells + 4 * c4) = make_float4(x[4 * c4], x[4 * c4 + 1], x[4 * c4 + 2], x[4 * c4 + 3]);
+                rhs[row] = y;
+            }
+            if (wave_s == 0 && lane < 16) aux[P0 + lane] = mine;
+            bad = bad || !(mine > 0.f);
+        }
+        if constexpr (p + 1 < NT) __syncthreads();
+        // the pivot rows go back only now that no wavefront can still be reading them
+        if (wave_s == 0 && lane < 16) {
+#pragma unroll
+            for (int c4 = 0; c4 < 4; ++c4) *(float4 *)(cells + 4 * c4) = make_float4(x[4 * c4], x[4 * c4 + 1], x[4 * c4 + 2], x[4 * c4 + 3]);
+            rhs[row] = y;
+        }
+        if constexpr (p + 1 < NT) {
+            constexpr int T = NT - p - 1, TILES = T * (T + 1) / 2, PER = (TILES + 3) / 4, GRP = 4;
+            const float4 rpv = *(const float4 *)(aux + P0 + 4 * q);
+            auto block_row = [&](int b) { return tri + (128 * b * (b + 1) + (K > 64 ? 64 * b : 0)) + (16 * (b + 1) + (K > 64 ? 4 : 0)) * a; };
+            static_for<0, (PER + GRP - 1) / GRP>([&](auto gg) {
+                constexpr int g0 = decltype(gg)::value * GRP, N = PER - g0 < GRP ? PER - g0 : GRP;
+                float4 zj[N], za[N], *cell[N];
+                floatx4 acc[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const int t = wave_s + 4 * (g0 + u) < TILES ? wave_s + 4 * (g0 + u) : 0;  // tile (ti, tj <= ti) in row order
+                    const int ti = (t >= 1) + (t >= 3) + (t >= 6) + (t >= 10) + (t >= 15) + (t >= 21), tj = t - ti * (ti + 1) / 2;
+                    const float *ri = block_row(p + 1 + ti);
+                    const float4 zi = *(const float4 *)(ri + P0 + 4 * q);
+                    zj[u] = *(const float4 *)(block_row(p + 1 + tj) + P0 + 4 * q);
+                    cell[u] = (float4 *)(ri + 16 * (p + 1 + tj) + 4 * q);
+                    const float4 c4 = *cell[u];
+                    acc[u] = floatx4{c4.x, c4.y, c4.z, c4.w};
+                    za[u] = make_float4(-zi.x * rpv.x, -zi.y * rpv.y, -zi.z * rpv.z, -zi.w * rpv.w);
+                }
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(zj[u].x, za[u].x, acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(zj[u].y, za[u].y, acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(zj[u].z, za[u].z, acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(zj[u].w, za[u].w, acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+                    if (wave_s + 4 * (g0 + u) < TILES) *cell[u] = make_float4(acc[u][0], acc[u][1], acc[u][2], acc[u][3]);
+            });
+            __syncthreads();
         }
     });
-    if (hasa) tbuf[ra] = t0;
-    if (hasb) tbuf[rb] = t1v;
     wave_sync();
+    // a pivot that is not positive shows in its reciprocal (see tri_solve)
+    if (wave_s == 0 && __any(bad && lane < 16) && lane == 0) atomicOr(err_flag, 1);
 }
+
 }  // namespace als

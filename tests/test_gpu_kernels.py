@@ -139,3 +139,37 @@ def test_topk_with_values_that_cannot_be_bounded(gpu_device):
             close = np.abs(S[q, got] - S[q, ref]) <= 1e-4 * np.abs(S[q, ref])
         assert np.all(close | (S[q, got] == S[q, ref])), (q, got, ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("d,dtype", [(64, torch.float32), (64, torch.bfloat16), (128, torch.float32), (128, torch.bfloat16)])
+@pytest.mark.parametrize("solver", [als.SOLVER_DIRECT, als.SOLVER_CG])
+def test_primal_rows_at_the_edges_of_their_batches(ctx, gpu_device, d, dtype, solver):
+    """One entry, the batch of 32 and the split threshold with a neighbour on each side, segments with a short tail; labels of
+    both signs and a Gramian whose base is not 16-byte aligned.  Tolerance: rounding of d-long sums amplified by the
+    system's condition, 4 sqrt(d) 2^-24 cond (CG stops at 1e-6 |b|: plus 1e-6 cond; it starts
+    from the row's content, whose size its rounding errors would follow: here 0); bf16 results round by 2^-8."""
+    say(f"primal rows d={d} {dtype} solver={solver}")
+    gen = torch.Generator().manual_seed(d)
+    lens = [1, 2, 31, 32, 33, 63, 64, 65, 96, 127, 129, 511, 512, 513, 1025, 1100, 0]
+    n, alpha, lam, rows = 4001, 0.1, 1e-1, len(lens)
+    H = (0.3 * torch.randn((n, d), generator=gen)).to(dtype)
+    ptr = torch.tensor([0] + lens).cumsum(0)
+    idx = torch.cat([torch.randperm(n, generator=gen)[:k] for k in lens]).to(torch.int32)
+    val = torch.rand(int(ptr[-1]), generator=gen) * 2 - 0.5
+    Hd = H.double()
+    G = Hd.T @ Hd
+    Gbuf = torch.zeros(d * d + 1, device=gpu_device)
+    Gbuf[1:] = G.float().flatten().to(gpu_device)
+    for Gdev in (Gbuf[1:].view(d, d), G.float().to(gpu_device)):
+        X = torch.full((rows, d), 7.0 if solver == als.SOLVER_DIRECT else 0.0, dtype=dtype, device=gpu_device)
+        Y = als.Csr(rows, n, ptr.to(gpu_device), idx.to(gpu_device), val.to(gpu_device))
+        als.als_solve_rows(ctx, Y, H.to(gpu_device), Gdev, als.make_params(alpha, lam, path=als.PATH_PRIMAL, solver=solver), X)
+        als.als_status_sync(ctx)
+        got = f64(X)
+        for u, k in enumerate(lens):
+            x = Hd[idx[ptr[u]:ptr[u + 1]].long()].numpy()
+            A = alpha * G.numpy() + lam * np.eye(d) + x.T @ x
+            ref = np.linalg.solve(A, x.T @ val[ptr[u]:ptr[u + 1]].double().numpy())
+            cond = np.linalg.cond(A)
+            tol = 4 * np.sqrt(d) * 2.0 ** -24 * cond + (1e-6 * cond if solver == als.SOLVER_CG else 0) + (2.0 ** -8 if dtype == torch.bfloat16 else 0)
+            assert np.linalg.norm(got[u] - ref) <= tol * max(np.linalg.norm(ref), 1e-300), (k, tol)
