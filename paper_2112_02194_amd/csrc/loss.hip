@@ -4,45 +4,68 @@
 // <W^T W, H^T H>_F (sum over a,b of G_W[a][b]*G_H[a][b]) and the norms are the Gramians' traces.
 // Products are fp32, every sum across entries is fp64, summed in a fixed order.
 #include "als_internal.h"
+#include "row_piece.h"
 
 namespace als {
 
 constexpr int LOSS_THREADS = 256;
-constexpr int LOSS_MAX_BLOCKS = 2048;
+constexpr int LOSS_MAX_BLOCKS = 8192;  // 1M rows: 1.64 ms with 2048, 1.41 with 8192
 
-// A group of LPE = D/4 lanes owns one stored entry at a time (each lane 4 columns); a wavefront
-// walks the rows assigned to it.
+// A group of LPE = D/8 lanes owns one stored entry at a time (each lane 8 columns); a wavefront walks the rows assigned to
+// it, reads their column ids 64 at a time and requests the rows of 32 entries together.
+// What bounds it: the gather (1M x 1M, d = 64, fp32, 3e7 entries of 256 bytes); with four entries in flight per wavefront
+// it was the latency of one batch after the other.
 template <int D, bool BF16>
 __global__ __launch_bounds__(LOSS_THREADS) void loss_observed_kernel(
     const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices, const float *__restrict__ values,
     int64_t rows, const void *__restrict__ W, int64_t ldw, const void *__restrict__ H, int64_t ldh,
     double *__restrict__ block_sums) {
-    constexpr int LPE = D / 4, EPW = 64 / LPE;  // lanes per entry, entries per wave step
+    constexpr int LPE = D / 8, EPW = 64 / LPE, U = 32 / EPW;  // lanes per entry, entries per step, steps in flight
     __shared__ double red[LOSS_THREADS / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int sub = lane % LPE, grp = lane / LPE;
     const int64_t wave_id = (int64_t)blockIdx.x * (LOSS_THREADS / 64) + wave;
     const int64_t nwaves = (int64_t)gridDim.x * (LOSS_THREADS / 64);
     double total = 0.0;
+    int64_t next_b = 0, next_e = 0;
+    if (wave_id < rows) {
+        next_b = indptr[wave_id];
+        next_e = indptr[wave_id + 1];
+    }
     for (int64_t u = wave_id; u < rows; u += nwaves) {
-        const int64_t b = indptr[u], e = indptr[u + 1];
+        const int64_t b = next_b, e = next_e;
+        if (u + nwaves < rows) {  // the next row's bounds while this one is worked on
+            next_b = indptr[u + nwaves];
+            next_e = indptr[u + nwaves + 1];
+        }
         if (e == b) continue;
-        float w[4];
-        load_vec<4, BF16>(W, u * ldw + 4 * sub, w);
-        for (int64_t p0 = b; p0 < e; p0 += EPW) {
-            const int64_t p = p0 + grp;
-            float dot = 0.f, y = 0.f;
-            if (p < e) {
-                float h[4];
-                load_vec<4, BF16>(H, (int64_t)indices[p] * ldh + 4 * sub, h);
-                dot = w[0] * h[0] + w[1] * h[1] + w[2] * h[2] + w[3] * h[3];
-                y = values ? values[p] : 1.f;
-            }
+        float w[8];
+        piece_floats<BF16>(piece_load<BF16>(W, u * ldw + 8 * sub), w);
+        for (int64_t p0 = b; p0 < e; p0 += 64) {
+            const int64_t mine = p0 + lane;
+            const int32_t my_id = mine < e ? indices[mine] : -1;
+            const float my_y = mine < e && values ? values[mine] : 1.f;
+            const int cnt = (int)(e - p0 < 64 ? e - p0 : 64);
+            for (int s0 = 0; s0 < cnt; s0 += 32) {
+                int32_t id[U];
+                Piece<BF16> h[U];
 #pragma unroll
-            for (int off = LPE / 2; off >= 1; off >>= 1) dot += __shfl_xor(dot, off);
-            if (p < e && sub == 0) {
-                const float r = y - dot;
-                total += (double)r * (double)r;
+                for (int x = 0; x < U; ++x) id[x] = __shfl(my_id, s0 + x * EPW + grp);
+#pragma unroll
+                for (int x = 0; x < U; ++x) {
+                    h[x] = piece_zero<BF16>();
+                    if (id[x] >= 0) h[x] = piece_load<BF16>(H, (int64_t)id[x] * ldh + 8 * sub);
+                }
+#pragma unroll
+                for (int x = 0; x < U; ++x) {
+                    float v[8], dot = 0.f;
+                    piece_floats<BF16>(h[x], v);
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) dot = fmaf(w[c], v[c], dot);
+                    dot = group_reduce<LPE>(dot, [](float a, float c) { return a + c; });
+                    const float r = __shfl(my_y, s0 + x * EPW + grp) - dot;
+                    if (sub == 0 && id[x] >= 0) total += (double)r * (double)r;
+                }
             }
         }
     }
@@ -98,7 +121,7 @@ template <int D, bool BF16>
 static als_status loss_typed(als_ctx *ctx, const als_csr *Y, const als_table *W, const als_table *H,
                              const float *GW, const float *GH, const als_params *prm, double *out_dev,
                              hipStream_t s) {
-    int nblocks = (int)std::min<int64_t>(LOSS_MAX_BLOCKS, std::max<int64_t>(1, (Y->rows + 15) / 16));
+    int nblocks = (int)std::min<int64_t>(LOSS_MAX_BLOCKS, std::max<int64_t>(1, (Y->rows + 3) / 4));
     als_status st = ensure(ctx, ctx->loss_partials, (size_t)LOSS_MAX_BLOCKS * sizeof(double));
     if (st != ALS_OK) return st;
     hipLaunchKernelGGL((loss_observed_kernel<D, BF16>), dim3(nblocks), dim3(LOSS_THREADS), 0, s, Y->indptr,
