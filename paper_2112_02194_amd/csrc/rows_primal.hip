@@ -295,49 +295,8 @@ template <int D> __device__ __forceinline__ void fold_b(float (&bsum)[Geo<D>::NC
     }
 }
 
-// ---------------------------------------------------------------------------------------------- LDS solve
-// a: [D][LD] with entry (r, c), r >= c, at a[c*LD + r]; on exit column c of L sits at a[c*LD + r]
-// and its mirror copy at a[r*LD + c].  aux: dinv[D], z[D], xout[D], bvec[D].
-template <int D>
-__device__ __forceinline__ void cholesky_solve_lds(float *a, float *aux, int32_t *err_flag) {
-    constexpr int LD = Team<D>::LD, T = Team<D>::THREADS, TY = T / 32;
-    float *dinv = aux, *z = aux + D, *xout = aux + 2 * D, *bvec = aux + 3 * D;
-    const int t = opaque_tid(), tx = t & 31, ty = t >> 5;
-    for (int k = 0; k < D; ++k) {
-        const float pivot = a[k * LD + k];
-        if (t == 0 && !(pivot > 0.f)) atomicOr(err_flag, 1);
-        const float rinv = 1.0f / sqrtf(pivot);
-        for (int i = k + 1 + t; i < D; i += T) {
-            const float l = a[k * LD + i] * rinv;
-            a[k * LD + i] = l;
-            a[i * LD + k] = l;
-        }
-        if (t == 0) dinv[k] = rinv;
-        __syncthreads();
-        for (int j = k + 1 + ty; j < D; j += TY) {
-            const float cj = a[k * LD + j];
-            for (int i = j + tx; i < D; i += 32) a[j * LD + i] -= a[k * LD + i] * cj;
-        }
-        __syncthreads();
-    }
-    // L z = b
-    for (int j = 0; j < D; ++j) {
-        const float zj = bvec[j] * dinv[j];  // final: only entries i > j change in step j
-        for (int i = j + 1 + t; i < D; i += T) bvec[i] -= a[j * LD + i] * zj;
-        if (t == 0) z[j] = zj;
-        __syncthreads();
-    }
-    // L^T x = z
-    for (int i = D - 1; i >= 0; --i) {
-        const float xi = z[i] * dinv[i];
-        for (int j = t; j < i; j += T) z[j] -= a[i * LD + j] * xi;
-        if (t == 0) xout[i] = xi;
-        __syncthreads();
-    }
-}
-
-// ---------------------------------------------------------------------------------------------- one-wavefront solve
-// LDS layout of the direct solver for D >= 64: lower triangle, the solver's auxiliary and result
+// ---------------------------------------------------------------------------------------------- direct solve
+// LDS layout of the direct solver: lower triangle, the solver's auxiliary and result
 // buffers (tri_solve.h), the right-hand side.
 template <int D> struct Packed {
     static constexpr int TRI = tri_row<D>(D);
@@ -348,17 +307,24 @@ template <int D> struct Packed {
 };
 
 // Called by the whole workgroup behind a barrier: solves the packed system and stores the row, rounded once to the
-// table's element type.  Returns at once in the wavefronts that have nothing left to do; wavefront 0 stores.
+// table's element type.  Returns at once in the wavefronts that have nothing left to do; wavefront 0 stores.  One or two
+// panels (d < 64) are worked on by wavefront 0 alone; a Cholesky factorisation in LDS with two barriers per column
+// took an epoch of 50k x 30k rows (d = 32, half of them longer than 32) to 838 us instead of 444.
 template <int D, bool BF16>
 __device__ __forceinline__ void packed_solve_store(float *lds, void *X, int64_t xoff, int wave_s, int32_t *err_flag) {
     const int lane = opaque_tid() & 63;
     float *tbuf = lds + Packed<D>::OFF_T, *aux = lds + Packed<D>::OFF_COL, *rhs = lds + Packed<D>::OFF_RHS;
-    team_tri_eliminate<D>(lds, aux, rhs, wave_s, err_flag);
-    if (wave_s != 0) return;
     int k = D;
     asm volatile("" : "+s"(k));  // opaque on purpose: with a compile-time step count the steps merge into one block,
                                  // whose scheduling runs out of registers
-    tri_back<D>(lds, tbuf, rhs[lane], D > 64 ? rhs[64 + lane] : 0.f, aux[lane], D > 64 ? aux[64 + lane] : 1.f, k);
+    if constexpr (D >= 64) {
+        team_tri_eliminate<D>(lds, aux, rhs, wave_s, err_flag);
+        if (wave_s != 0) return;
+        tri_back<D>(lds, tbuf, rhs[lane], D > 64 ? rhs[64 + lane] : 0.f, aux[lane], D > 64 ? aux[64 + lane] : 1.f, k);
+    } else {
+        if (wave_s != 0) return;
+        tri_solve<D>(lds, aux, tbuf, lane < D ? rhs[lane] : 0.f, 0.f, k, err_flag);
+    }
     for (int c = lane; c < D; c += 64) store_elem<BF16>(X, xoff + c, tbuf[c]);
 }
 
@@ -422,16 +388,6 @@ __device__ __forceinline__ void cg_solve_lds(const float *a, float *aux, int max
     __syncthreads();
     if (mine) xvec[i] = x;
     __syncthreads();
-}
-
-template <int D>
-__device__ __forceinline__ void solve_spd_lds(float *a, float *aux, int32_t *err_flag, int solver, int cg_iters,
-                                              float cg_tol) {  // d < 64
-    if (solver == ALS_SOLVER_CG) {  // uniform for the launch
-        cg_solve_lds<D>(a, aux, cg_iters, cg_tol);
-        return;
-    }
-    cholesky_solve_lds<D>(a, aux, err_flag);
 }
 
 // ---------------------------------------------------------------------------------------------- kernels
@@ -555,16 +511,22 @@ __device__ __forceinline__ bool primal_step(
             (void)last;
             return true;
         } else {
-            // A = alpha*G + lambda*I + V_I^T V_I into LDS (entry (r,c) at a[c*LD + r])
-            deliver([&](int r, int c, float v) { a[c * LD + r] = v + alpha * G[r * D + c] + (r == c ? lambda : 0.f); },
-                    [&](int c, float v) { bvec[c] = v; });
-            if (solver == ALS_SOLVER_CG) {  // warm start from the row's current content
+            if (solver == ALS_SOLVER_DIRECT) {  // uniform for the launch
+                deliver([&](int r, int c, float v) { if (c <= r) lds[tri_row<D>(r) + c] = v + alpha * G[r * D + c] + (r == c ? lambda : 0.f); },
+                        [&](int c, float v) { lds[Packed<D>::OFF_RHS + c] = v; });
+                __syncthreads();
+                const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+                packed_solve_store<D, BF16>(lds, X, u * ldx, wave_s, err_flag);
+                if (last && wave_s != 0) return false;
+            } else {
+                // entry (r,c) at a[c*LD + r]; warm start from the row's current content
+                deliver([&](int r, int c, float v) { a[c * LD + r] = v + alpha * G[r * D + c] + (r == c ? lambda : 0.f); },
+                        [&](int c, float v) { bvec[c] = v; });
                 for (int c = opaque_tid(); c < D; c += Team<D>::THREADS) aux[2 * D + c] = load_elem<BF16>(X, u * ldx + c);
+                __syncthreads();
+                cg_solve_lds<D>(a, aux, cg_iters, cg_tol);
+                for (int c = opaque_tid(); c < D; c += Team<D>::THREADS) store_elem<BF16>(X, u * ldx + c, aux[2 * D + c]);
             }
-            __syncthreads();
-            solve_spd_lds<D>(a, aux, err_flag, solver, cg_iters, cg_tol);
-            const float *xout = aux + 2 * D;
-            for (int c = opaque_tid(); c < D; c += Team<D>::THREADS) store_elem<BF16>(X, u * ldx + c, xout[c]);
             if (!last) __syncthreads();  // before the next row's tiles overwrite the LDS
             return true;
         }
@@ -639,26 +601,24 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
     constexpr int LD = Team<D>::LD, T = Team<D>::THREADS;
     float *a = lds, *aux = lds + D * LD, *bvec = aux + 3 * D;
     const float *p0 = partials + (int64_t)lr.seg_first * (D * D + D);
-    if constexpr (D >= 64) {
-        if (solver == ALS_SOLVER_DIRECT) {
-            const bool g_aligned = ((uintptr_t)G & 15) == 0;
-            for (int e = opaque_tid(); e < D * D / 4; e += T) {
-                const int r = e / (D / 4), c = 4 * (e % (D / 4));
-                if (c < 16 * (r / 16 + 1)) {
-                    const float4 v = *(const float4 *)(p0 + 4 * e), g = load_g4(G, 4 * e, g_aligned);
-                    *(float4 *)(lds + tri_row<D>(r) + c) =
-                        make_float4(v.x + alpha * g.x + (r == c ? lambda : 0.f), v.y + alpha * g.y + (r == c + 1 ? lambda : 0.f),
-                                    v.z + alpha * g.z + (r == c + 2 ? lambda : 0.f), v.w + alpha * g.w + (r == c + 3 ? lambda : 0.f));
-                }
+    if (solver == ALS_SOLVER_DIRECT) {
+        const bool g_aligned = ((uintptr_t)G & 15) == 0;
+        for (int e = opaque_tid(); e < D * D / 4; e += T) {
+            const int r = e / (D / 4), c = 4 * (e % (D / 4));
+            if (c < 16 * (r / 16 + 1)) {
+                const float4 v = *(const float4 *)(p0 + 4 * e), g = load_g4(G, 4 * e, g_aligned);
+                *(float4 *)(lds + tri_row<D>(r) + c) =
+                    make_float4(v.x + alpha * g.x + (r == c ? lambda : 0.f), v.y + alpha * g.y + (r == c + 1 ? lambda : 0.f),
+                                v.z + alpha * g.z + (r == c + 2 ? lambda : 0.f), v.w + alpha * g.w + (r == c + 3 ? lambda : 0.f));
             }
-            if (opaque_tid() < D) lds[Packed<D>::OFF_RHS + opaque_tid()] = p0[D * D + opaque_tid()];
-            __syncthreads();
-            const int wave_s = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
-            packed_solve_store<D, BF16>(lds, X, lr.row * ldx, wave_s, err_flag);
-            if (last && wave_s != 0) return false;
-            if (!last) __syncthreads();
-            return true;
         }
+        if (opaque_tid() < D) lds[Packed<D>::OFF_RHS + opaque_tid()] = p0[D * D + opaque_tid()];
+        __syncthreads();
+        const int wave_s = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
+        packed_solve_store<D, BF16>(lds, X, lr.row * ldx, wave_s, err_flag);
+        if (last && wave_s != 0) return false;
+        if (!last) __syncthreads();
+        return true;
     }
     for (int e = opaque_tid(); e < D * D + D; e += T) {
         const float s = p0[e];
@@ -672,12 +632,9 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
             bvec[e - D * D] = s;
         }
     }
-    if (solver == ALS_SOLVER_CG) {
-        for (int c = opaque_tid(); c < D; c += T) aux[2 * D + c] = load_elem<BF16>(X, lr.row * ldx + c);
-    }
+    for (int c = opaque_tid(); c < D; c += T) aux[2 * D + c] = load_elem<BF16>(X, lr.row * ldx + c);
     __syncthreads();
-    if constexpr (D >= 64) cg_solve_lds<D>(a, aux, cg_iters, cg_tol);
-    else solve_spd_lds<D>(a, aux, err_flag, solver, cg_iters, cg_tol);
+    cg_solve_lds<D>(a, aux, cg_iters, cg_tol);
     const float *xout = aux + 2 * D;
     for (int c = opaque_tid(); c < D; c += T) store_elem<BF16>(X, lr.row * ldx + c, xout[c]);
     if (!last) __syncthreads();
@@ -714,10 +671,7 @@ template <int D, bool BF16> static constexpr size_t staging_lds_bytes() {
     else return 0;
 }
 template <int D> static size_t solve_lds_bytes(int solver) {
-    if constexpr (D >= 64) {
-        if (solver == ALS_SOLVER_DIRECT) return Packed<D>::LDS_BYTES;
-    }
-    return Team<D>::LDS_BYTES;
+    return solver == ALS_SOLVER_DIRECT ? Packed<D>::LDS_BYTES : Team<D>::LDS_BYTES;
 }
 
 template <int D, bool BF16>
