@@ -198,7 +198,7 @@ void timer_end(als_ctx *ctx, hipStream_t s);
 struct StepGrid {
     unsigned known, rest;
 };
-StepGrid step_grid(const als_ctx *ctx, int64_t capacity, int64_t hint, int per_cu);
+StepGrid step_grid(const als_ctx *ctx, int64_t capacity, int64_t hint, int per_cu, int64_t blind_limit);
 
 #define ALS_HIP(ctx, expr)                                                                      \
     do {                                                                                        \
