@@ -199,25 +199,40 @@ __global__ __launch_bounds__(FACTOR_THREADS) void factor_kernel(const float *__r
 // m: for the contraction block kb (TM input columns) it holds the BW = TM/KS consecutive columns
 // TM*kb + BW*kq .. of its row, loaded straight from global memory as 16-byte pieces; step i of the
 // block contracts column TM*kb + BW*kq + i (A and B operands only have to agree on that mapping).
-// The transposed matrix sits in LDS (one copy per workgroup, MT[c][j], padded rows) and supplies the
-// B operands; blocks that only meet zeros of the triangular matrix are skipped.
+// The transposed matrix Mt (Mt[c][j] = M[j][c]; the factorisation leaves both) sits in LDS (one copy per
+// workgroup, padded rows) and supplies the B operands; blocks that only meet zeros of the triangular matrix
+// are skipped.
+//
+// GATHER (Z = V L^{-T} for few entries of a large table): "row" p of the pass is entry p of the CSR arrays, its input
+// the table row ids[p], its output row p of Z; the range of p is read from *first and *last on the device, and
+// entry_ids[p] = p becomes the index by which the row kernels find their entries.
+struct Gather {
+    const int32_t *ids;
+    const int64_t *first, *last;
+    int32_t *entry_ids;
+    int64_t limit;  // rows of Z: an indptr that claims more entries is cut off
+    __device__ int64_t begin() const { return *first < 0 ? 0 : *first; }
+    __device__ int64_t end() const { return *last < limit ? *last : limit; }
+};
 template <int D> struct XfCfg {
     using GE = Geo<D>;
     static constexpr int TM = GE::TM, KS = GE::KS, NB = D / TM, BW = TM / KS, MLD = D + 4;
     static constexpr size_t LDS_BYTES = (size_t)D * MLD * sizeof(float);
 };
 
-template <int D, bool IN_BF16, bool OUT_BF16, bool UPPER>
+template <int D, bool IN_BF16, bool OUT_BF16, bool UPPER, bool GATHER>
 __global__ __launch_bounds__(256) void transform_kernel(const void *In, int64_t ldi, void *Out, int64_t ldo,
-                                                        const float *__restrict__ M, int64_t r0, int64_t r1,
-                                                        const int64_t *__restrict__ indptr, int64_t k_max) {
+                                                        const float *__restrict__ Mt, int64_t r0, int64_t r1,
+                                                        const int64_t *__restrict__ indptr, int64_t k_max, Gather ga) {
     using C = XfCfg<D>;
     constexpr int TM = C::TM, NB = C::NB, BW = C::BW, MLD = C::MLD, ACC = Geo<D>::ACC;
     typedef typename AccT<ACC>::type acc_t;
     extern __shared__ float MT[];  // MT[c * MLD + j] = M[j][c]
-    for (int e = threadIdx.x; e < D * D; e += 256) {
-        const int j = e / D, c = e % D;
-        MT[c * MLD + j] = M[e];
+#pragma unroll 4
+    for (int e = threadIdx.x; e < D * D / 4; e += 256) *(float4 *)(MT + e / (D / 4) * MLD + 4 * (e % (D / 4))) = ((const float4 *)Mt)[e];
+    if constexpr (GATHER) {
+        r0 = ga.begin();
+        r1 = ga.end();
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -226,13 +241,18 @@ __global__ __launch_bounds__(256) void transform_kernel(const void *In, int64_t 
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntiles; tile += nwaves) {
         const int64_t base = r0 + tile * TM, row = base + m;
+        int64_t src = row;
+        if constexpr (GATHER) {
+            src = row < r1 ? ga.ids[row] : 0;
+            if (kq == 0 && row < r1) ga.entry_ids[row] = (int32_t)row;
+        }
         float a[NB][BW];
 #pragma unroll
         for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
             for (int i4 = 0; i4 < BW / 4; ++i4) {
                 float x[4] = {0.f, 0.f, 0.f, 0.f};
-                if (row < r1) load_vec<4, IN_BF16>(In, row * ldi + TM * kb + BW * kq + 4 * i4, x);
+                if (row < r1) load_vec<4, IN_BF16>(In, src * ldi + TM * kb + BW * kq + 4 * i4, x);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) a[kb][4 * i4 + c] = x[c];
             }
@@ -290,23 +310,29 @@ template <int D> struct Xf16Cfg {
     static constexpr size_t LDS_BYTES = (size_t)2 * D * MLD * sizeof(uint16_t);
 };
 
-template <int D, bool IN_BF16, bool UPPER>
+template <int D, bool IN_BF16, bool UPPER, bool GATHER>
 __global__ __launch_bounds__(256, 2) void transform16_kernel(const void *__restrict__ In, int64_t ldi,
                                                           uint16_t *__restrict__ Out, int64_t ldo,
-                                                          const float *__restrict__ M, int64_t r0, int64_t r1,
-                                                          const int64_t *__restrict__ indptr, int64_t k_max) {
+                                                          const float *__restrict__ Mt, int64_t r0, int64_t r1,
+                                                          const int64_t *__restrict__ indptr, int64_t k_max, Gather ga) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef float floatx2 __attribute__((ext_vector_type(2)));
     constexpr int MLD = Xf16Cfg<D>::MLD, NKB = D / 16, NJB = D / 32;
     extern __shared__ uint16_t mt[];  // hi: mt[c * MLD + j] = bf16(M[j][c]); lo: the same at offset D * MLD
     auto rne = [](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){x, y}, bf16x2)); };
-    for (int e = threadIdx.x; e < D * D; e += 256) {
-        const int j = e / D, c = e % D;
-        const float v = M[e];
-        const uint32_t h = rne(v, 0.f) & 0xffffu;
-        mt[c * MLD + j] = (uint16_t)h;
-        mt[D * MLD + c * MLD + j] = (uint16_t)(rne(v - __uint_as_float(h << 16), 0.f) & 0xffffu);
+#pragma unroll 4
+    for (int e = threadIdx.x; e < D * D / 4; e += 256) {
+        const float4 v = ((const float4 *)Mt)[e];
+        const uint32_t h0 = rne(v.x, v.y), h1 = rne(v.z, v.w);
+        uint16_t *at = mt + e / (D / 4) * MLD + 4 * (e % (D / 4));
+        *(uint2 *)at = make_uint2(h0, h1);
+        *(uint2 *)(at + D * MLD) = make_uint2(rne(v.x - __uint_as_float(h0 << 16), v.y - __uint_as_float(h0 & 0xffff0000u)),
+                                              rne(v.z - __uint_as_float(h1 << 16), v.w - __uint_as_float(h1 & 0xffff0000u)));
+    }
+    if constexpr (GATHER) {
+        r0 = ga.begin();
+        r1 = ga.end();
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -323,18 +349,23 @@ __global__ __launch_bounds__(256, 2) void transform16_kernel(const void *__restr
             keep = k > 0 && k <= k_max;
         }
         // this lane's share of its row: columns 16 kb + 8 kq .., as bf16 operands (hi and, for fp32 input, lo)
+        int64_t src = row;
+        if constexpr (GATHER) {
+            src = row < r1 ? ga.ids[row] : 0;
+            if (kq == 0 && row < r1) ga.entry_ids[row] = (int32_t)row;
+        }
         bf16x8 xh[NKB], xl[IN_BF16 ? 1 : NKB];
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
             if constexpr (IN_BF16) {
                 u32x4 w = {0u, 0u, 0u, 0u};
-                if (row < r1) w = *(const u32x4 *)((const uint16_t *)In + row * ldi + 16 * kb + 8 * kq);
+                if (row < r1) w = *(const u32x4 *)((const uint16_t *)In + src * ldi + 16 * kb + 8 * kq);
                 xh[kb] = __builtin_bit_cast(bf16x8, w);
             } else {
                 float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                 if (row < r1) {
-                    const float4 p = *(const float4 *)((const float *)In + row * ldi + 16 * kb + 8 * kq);
-                    const float4 q4 = *(const float4 *)((const float *)In + row * ldi + 16 * kb + 8 * kq + 4);
+                    const float4 p = *(const float4 *)((const float *)In + src * ldi + 16 * kb + 8 * kq);
+                    const float4 q4 = *(const float4 *)((const float *)In + src * ldi + 16 * kb + 8 * kq + 4);
                     x[0] = p.x; x[1] = p.y; x[2] = p.z; x[3] = p.w; x[4] = q4.x; x[5] = q4.y; x[6] = q4.z; x[7] = q4.w;
                 }
                 u32x4 h, l;
@@ -396,20 +427,21 @@ template <int D> struct XfsCfg {
 
 template <int D, bool UPPER>
 __global__ __launch_bounds__(XFS_THREADS, 2) void transform_split_kernel(const float *In, int64_t ldi, float *Out,
-                                                                         int64_t ldo, const float *__restrict__ M,
+                                                                         int64_t ldo, const float *__restrict__ Mt,
                                                                          int64_t r0, int64_t r1,
                                                                          const int64_t *__restrict__ indptr, int64_t k_max) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     constexpr int MLD = XfsCfg<D>::MLD, NKB = D / 16, NJB = D / 32;
     extern __shared__ uint16_t mt[];  // part t: mt[t * D * MLD + c * MLD + j] = part t of M[j][c]
     auto rest = [](float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
-    for (int e = threadIdx.x; e < D * D; e += XFS_THREADS) {
-        const int j = e / D, c = e % D;
-        float v = M[e];
+#pragma unroll 4
+    for (int e = threadIdx.x; e < D * D / 4; e += XFS_THREADS) {
+        float4 v = ((const float4 *)Mt)[e];
+        uint16_t *at = mt + e / (D / 4) * MLD + 4 * (e % (D / 4));
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
-            mt[t * D * MLD + c * MLD + j] = (uint16_t)(__float_as_uint(v) >> 16);
-            v = rest(v);
+            *(uint2 *)(at + t * D * MLD) = make_uint2(pack_upper(v.x, v.y), pack_upper(v.z, v.w));
+            v = make_float4(rest(v.x), rest(v.y), rest(v.z), rest(v.w));
         }
     }
     __syncthreads();
@@ -491,13 +523,17 @@ int dual_supported_max_k(int d) { return d < 128 ? (d < 64 ? d : 64) : 128; }
 // 32-column matrix-core step and Z stays fp32.
 template <int D, bool BF16> constexpr bool z_is_bf16() { return BF16 && D >= 32; }
 
-// Part 1 (needs no row classification): factorise B and build Z = V L^{-T}.
+// Part 1 (needs no row classification): factorise B and build Z = V L^{-T}, of the whole table, or (`entries`) of
+// the table rows that the entries of rows [r0, r1) name, in the order of the entries.
 template <int D, bool BF16>
 static als_status dual_prepare_typed(als_ctx *ctx, const als_table *V, const float *G, const als_params *prm,
-                                     hipStream_t s) {
+                                     const als_csr *entries, int64_t r0, int64_t r1, hipStream_t s) {
     constexpr bool ZB = z_is_bf16<D, BF16>();
-    als_status st = ensure(ctx, ctx->ztable, (size_t)V->rows * D * (ZB ? 2 : 4));
+    const int64_t zrows = entries ? entries->nnz : V->rows;
+    als_status st = ensure(ctx, ctx->ztable, (size_t)zrows * D * (ZB ? 2 : 4));
     if (st != ALS_OK) return st;
+    Gather ga = {nullptr, nullptr, nullptr, nullptr, 0};
+    if (entries) ga = {entries->indices, entries->indptr + r0, entries->indptr + r1, (int32_t *)ctx->entry_ids.p, entries->nnz};
     float *Linv = (float *)((char *)ctx->small.p + SM_FACTOR), *LinvT = Linv + 128 * 128;
     int32_t *err = (int32_t *)((char *)ctx->small.p + SM_COUNTERS) + 2;
     constexpr size_t factor_lds = FactorCfg<D>::LDS_BYTES;
@@ -507,24 +543,30 @@ static als_status dual_prepare_typed(als_ctx *ctx, const als_table *V, const flo
     timer_begin(ctx, T_TRANSFORM, s);
     hipLaunchKernelGGL(factor_kernel<D>, dim3(1), dim3(FACTOR_THREADS), factor_lds, s, G, prm->alpha, prm->lambda, Linv, LinvT,
                        err);
-    const unsigned tblocks = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(1, (V->rows + 127) / 128));
-    if constexpr (ZB) {
-        static const hipError_t attr_t = hipFuncSetAttribute((const void *)transform16_kernel<D, true, true>,
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                             (int)Xf16Cfg<D>::LDS_BYTES);  // once per process
-        ALS_HIP(ctx, attr_t);
-        hipLaunchKernelGGL((transform16_kernel<D, true, true>), dim3(tblocks), dim3(256), Xf16Cfg<D>::LDS_BYTES, s, V->data,
-                           V->ld, (uint16_t *)ctx->ztable.p, (int64_t)D, (const float *)LinvT, (int64_t)0, V->rows,
-                           (const int64_t *)nullptr, (int64_t)0);
-    } else {
-        static const hipError_t attr_t = hipFuncSetAttribute((const void *)transform_kernel<D, BF16, false, true>,
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                             (int)XfCfg<D>::LDS_BYTES);  // once per process
-        ALS_HIP(ctx, attr_t);
-        hipLaunchKernelGGL((transform_kernel<D, BF16, false, true>), dim3(tblocks), dim3(256), XfCfg<D>::LDS_BYTES, s,
-                           V->data, V->ld, ctx->ztable.p, (int64_t)D, (const float *)LinvT, (int64_t)0, V->rows,
-                           (const int64_t *)nullptr, (int64_t)0);
-    }
+    const unsigned tblocks = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(1, (zrows + 127) / 128));
+    auto transform = [&](auto gather) {  // L^{-1} is the transpose of the matrix applied
+        constexpr bool GA = decltype(gather)::value;
+        if constexpr (ZB) {
+            static const hipError_t attr = hipFuncSetAttribute((const void *)transform16_kernel<D, true, true, GA>,
+                                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                               (int)Xf16Cfg<D>::LDS_BYTES);  // once per process
+            if (attr == hipSuccess)
+                hipLaunchKernelGGL((transform16_kernel<D, true, true, GA>), dim3(tblocks), dim3(256), Xf16Cfg<D>::LDS_BYTES, s,
+                                   V->data, V->ld, (uint16_t *)ctx->ztable.p, (int64_t)D, (const float *)Linv, (int64_t)0,
+                                   V->rows, (const int64_t *)nullptr, (int64_t)0, ga);
+            return attr;
+        } else {
+            static const hipError_t attr = hipFuncSetAttribute((const void *)transform_kernel<D, BF16, false, true, GA>,
+                                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                               (int)XfCfg<D>::LDS_BYTES);  // once per process
+            if (attr == hipSuccess)
+                hipLaunchKernelGGL((transform_kernel<D, BF16, false, true, GA>), dim3(tblocks), dim3(256), XfCfg<D>::LDS_BYTES, s,
+                                   V->data, V->ld, ctx->ztable.p, (int64_t)D, (const float *)Linv, (int64_t)0, V->rows,
+                                   (const int64_t *)nullptr, (int64_t)0, ga);
+            return attr;
+        }
+    };
+    ALS_HIP(ctx, entries ? transform(std::true_type{}) : transform(std::false_type{}));
     timer_end(ctx, s);
     ALS_HIP(ctx, hipGetLastError());
     return ALS_OK;
@@ -546,7 +588,7 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
         R = (float *)ctx->rtable.p - r0 * D;  // row u lives at rtable[(u - r0) * D]
         ldr = D;
     }
-    const float *Linv = (const float *)((char *)ctx->small.p + SM_FACTOR);
+    const float *LinvT = (const float *)((char *)ctx->small.p + SM_FACTOR) + 128 * 128;  // transpose of the matrix applied
     int32_t *err = (int32_t *)((char *)ctx->small.p + SM_COUNTERS) + 2;
     const void *Z = ctx->ztable.p;
     constexpr bool zb16 = z_is_bf16<D, BF16>();
@@ -592,12 +634,12 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     timer_begin(ctx, T_TRANSFORM_X, s);
     const unsigned xblocks = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(1, (r1 - r0 + 127) / 128));
     if constexpr (zb16) {
-        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform16_kernel<D, false, false>,
+        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform16_kernel<D, false, false, false>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize,
                                                              (int)Xf16Cfg<D>::LDS_BYTES);  // once per process
         ALS_HIP(ctx, attr_x);
-        hipLaunchKernelGGL((transform16_kernel<D, false, false>), dim3(xblocks), dim3(256), Xf16Cfg<D>::LDS_BYTES, s,
-                           (const void *)R, ldr, (uint16_t *)X->data, X->ld, Linv, r0, r1, Y->indptr, (int64_t)dual_max);
+        hipLaunchKernelGGL((transform16_kernel<D, false, false, false>), dim3(xblocks), dim3(256), Xf16Cfg<D>::LDS_BYTES, s,
+                           (const void *)R, ldr, (uint16_t *)X->data, X->ld, LinvT, r0, r1, Y->indptr, (int64_t)dual_max, Gather{});
     } else if constexpr (!BF16 && D >= 64) {
         static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_split_kernel<D, false>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -605,14 +647,14 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
         ALS_HIP(ctx, attr_x);
         const unsigned sblocks = (unsigned)std::min<int64_t>(512, std::max<int64_t>(1, (r1 - r0 + 255) / 256));
         hipLaunchKernelGGL((transform_split_kernel<D, false>), dim3(sblocks), dim3(XFS_THREADS), XfsCfg<D>::LDS_BYTES, s,
-                           (const float *)R, ldr, (float *)X->data, X->ld, Linv, r0, r1, Y->indptr, (int64_t)dual_max);
+                           (const float *)R, ldr, (float *)X->data, X->ld, LinvT, r0, r1, Y->indptr, (int64_t)dual_max);
     } else {
-        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_kernel<D, false, BF16, false>,
+        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_kernel<D, false, BF16, false, false>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize,
                                                              (int)XfCfg<D>::LDS_BYTES);  // once per process
         ALS_HIP(ctx, attr_x);
-        hipLaunchKernelGGL((transform_kernel<D, false, BF16, false>), dim3(xblocks), dim3(256), XfCfg<D>::LDS_BYTES, s,
-                           (const void *)R, ldr, X->data, X->ld, Linv, r0, r1, Y->indptr, (int64_t)dual_max);
+        hipLaunchKernelGGL((transform_kernel<D, false, BF16, false, false>), dim3(xblocks), dim3(256), XfCfg<D>::LDS_BYTES, s,
+                           (const void *)R, ldr, X->data, X->ld, LinvT, r0, r1, Y->indptr, (int64_t)dual_max, Gather{});
     }
     timer_end(ctx, s);
     ALS_HIP(ctx, hipGetLastError());
@@ -620,13 +662,13 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
 }
 
 als_status launch_dual_prepare(als_ctx *ctx, const als_table *V, const float *G, const als_params *prm,
-                               hipStream_t s) {
+                               const als_csr *entries, int64_t r0, int64_t r1, hipStream_t s) {
     const bool bf = V->dtype == ALS_BF16;
     switch (V->d) {
-        case 16: return bf ? dual_prepare_typed<16, true>(ctx, V, G, prm, s) : dual_prepare_typed<16, false>(ctx, V, G, prm, s);
-        case 32: return bf ? dual_prepare_typed<32, true>(ctx, V, G, prm, s) : dual_prepare_typed<32, false>(ctx, V, G, prm, s);
-        case 64: return bf ? dual_prepare_typed<64, true>(ctx, V, G, prm, s) : dual_prepare_typed<64, false>(ctx, V, G, prm, s);
-        case 128: return bf ? dual_prepare_typed<128, true>(ctx, V, G, prm, s) : dual_prepare_typed<128, false>(ctx, V, G, prm, s);
+        case 16: return bf ? dual_prepare_typed<16, true>(ctx, V, G, prm, entries, r0, r1, s) : dual_prepare_typed<16, false>(ctx, V, G, prm, entries, r0, r1, s);
+        case 32: return bf ? dual_prepare_typed<32, true>(ctx, V, G, prm, entries, r0, r1, s) : dual_prepare_typed<32, false>(ctx, V, G, prm, entries, r0, r1, s);
+        case 64: return bf ? dual_prepare_typed<64, true>(ctx, V, G, prm, entries, r0, r1, s) : dual_prepare_typed<64, false>(ctx, V, G, prm, entries, r0, r1, s);
+        case 128: return bf ? dual_prepare_typed<128, true>(ctx, V, G, prm, entries, r0, r1, s) : dual_prepare_typed<128, false>(ctx, V, G, prm, entries, r0, r1, s);
     }
     return fail(ctx, ALS_EDTYPE, "unsupported d");
 }

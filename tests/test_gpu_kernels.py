@@ -173,3 +173,41 @@ def test_primal_rows_at_the_edges_of_their_batches(ctx, gpu_device, d, dtype, so
             cond = np.linalg.cond(A)
             tol = 4 * np.sqrt(d) * 2.0 ** -24 * cond + (1e-6 * cond if solver == als.SOLVER_CG else 0) + (2.0 ** -8 if dtype == torch.bfloat16 else 0)
             assert np.linalg.norm(got[u] - ref) <= tol * max(np.linalg.norm(ref), 1e-300), (k, tol)
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rows_with_fewer_entries_than_the_table_has_rows(ctx, gpu_device, d, dtype):
+    """Z holds one row per entry: every row class, a row range that starts inside the entries, repeated items, empty rows.
+    Tolerances: the project's 1e-4 for fp32 tables and 1e-2 for bf16 ones, row by row."""
+    say(f"entries < table rows, d={d} {dtype}")
+    gen = torch.Generator().manual_seed(100 + d)
+    lens = [3, 9, 0, 1, 2, 4, 5, 8, 9, 16, 17, 31, 32, 33, 48, 49, 64, 65, 80, 96, 97, 112, 128, 129, 200, 530, 0, 7, 40, 6]
+    rows, n, lo, hi, alpha, lam = len(lens), 4099, 2, 28, 0.1, 1e-2
+    ptr = torch.tensor([0] + lens).cumsum(0)
+    nnz = int(ptr[-1])
+    assert nnz < n
+    H = (0.3 * torch.randn((n, d), generator=gen) * torch.linspace(1, 0.1, d)).to(dtype)
+    idx = torch.randint(0, n, (nnz,), generator=gen).to(torch.int32)
+    idx[20:24] = idx[20]
+    val = torch.rand(nnz, generator=gen) + 0.5
+    Hd = H.double()
+    G = Hd.T @ Hd
+    Hg, Gg = H.to(gpu_device), G.float().to(gpu_device)
+    X = torch.full((rows, d), 3.0, dtype=dtype, device=gpu_device)
+    Y = als.Csr(rows, n, ptr.to(gpu_device), idx.to(gpu_device), val.to(gpu_device))
+    als.als_solve_rows(ctx, Y, Hg, Gg, als.make_params(alpha, lam), X, lo, hi)
+    als.als_status_sync(ctx)
+    got = f64(X)
+    for u, k in enumerate(lens):
+        if not lo <= u < hi:
+            assert np.all(got[u] == 3.0)
+            continue
+        x = Hd[idx[ptr[u]:ptr[u + 1]].long()].numpy()
+        ref = np.linalg.solve(alpha * G.numpy() + lam * np.eye(d) + x.T @ x, x.T @ val[ptr[u]:ptr[u + 1]].double().numpy())
+        assert np.linalg.norm(got[u] - ref) <= (1e-4 if dtype == torch.float32 else 1e-2) * np.linalg.norm(ref), (u, k)
+    # an indptr that claims more entries than nnz is reported; nothing beyond nnz is read or written
+    short = als.Csr(rows, n, Y.indptr, Y.indices[:int(ptr[12])], Y.values[:int(ptr[12])])
+    als.als_solve_rows(ctx, short, Hg, Gg, als.make_params(alpha, lam), X)
+    with pytest.raises(als.AlsError):
+        als.als_status_sync(ctx)
