@@ -371,14 +371,16 @@ __global__ __launch_bounds__(256) void gramian_slice_kernel(const float *__restr
     slices[(int64_t)blockIdx.y * D * D + e] = s;
 }
 
-// Stage 3: the slices in order.
-template <int D>
-__global__ __launch_bounds__(256) void gramian_reduce_kernel(const double *__restrict__ slices, int nslices,
+// Stage 3: the slices in order, or the partials themselves where there are no more of them than slices (each slice
+// would be one partial: the same sums, one launch less).
+template <int D, class T>
+__global__ __launch_bounds__(256) void gramian_reduce_kernel(const T *__restrict__ slices, int nslices,
                                                              float *__restrict__ G) {
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e >= D * D) return;
     double s = 0.0;
-    for (int b = 0; b < nslices; ++b) s += slices[(int64_t)b * D * D + e];
+#pragma unroll 8
+    for (int b = 0; b < nslices; ++b) s += (double)slices[(int64_t)b * D * D + e];
     G[e] = (float)s;
 }
 
@@ -412,9 +414,14 @@ static void gramian_enqueue(const als_table *V, float *G, void *work, int nblock
     else
         hipLaunchKernelGGL((gramian_partial_kernel<D, BF16>), dim3(nblocks), dim3(GRAM_THREADS), 0, s, V->data, V->rows,
                            V->ld, partials);
+    if (nblocks <= nslices) {
+        hipLaunchKernelGGL((gramian_reduce_kernel<D, float>), dim3((D * D + 255) / 256), dim3(256), 0, s,
+                           (const float *)partials, nblocks, G);
+        return;
+    }
     hipLaunchKernelGGL((gramian_slice_kernel<D>), dim3((D * D + 255) / 256, nslices), dim3(256), 0, s,
                        (const float *)partials, nblocks, slices);
-    hipLaunchKernelGGL((gramian_reduce_kernel<D>), dim3((D * D + 255) / 256), dim3(256), 0, s,
+    hipLaunchKernelGGL((gramian_reduce_kernel<D, double>), dim3((D * D + 255) / 256), dim3(256), 0, s,
                        (const double *)slices, nslices, G);
 }
 

@@ -565,6 +565,20 @@ __global__ __launch_bounds__(Team<D>::THREADS, D < 64 ? (LOOP ? 1 : 2) : (D == 1
     }
 }
 
+// One element of a long row's partials, summed in a fixed order.
+template <int D> __device__ __forceinline__ float segment_sum(const float *p0, int nseg) {
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+    int g = 0;
+    for (; g + 4 <= nseg; g += 4) {
+        s0 += p0[(int64_t)(g + 0) * (D * D + D)];
+        s1 += p0[(int64_t)(g + 1) * (D * D + D)];
+        s2 += p0[(int64_t)(g + 2) * (D * D + D)];
+        s3 += p0[(int64_t)(g + 3) * (D * D + D)];
+    }
+    for (; g < nseg; ++g) s0 += p0[(int64_t)g * (D * D + D)];
+    return (s0 + s1) + (s2 + s3);
+}
+
 // Adds the segment partials of every long row in a fixed order: workgroup (x, y) handles elements
 // [256y, 256y+256) of long row x and overwrites the row's first partial with the sum.
 template <int D>
@@ -578,18 +592,13 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const LongRow *__r
     if (e >= D * D + D || lr.nseg <= 1) continue;
     if (D >= 64 && e < D * D && e % D / 32 > e / D / 32) continue;  // segments leave the lower block triangle only
     float *p0 = partials + (int64_t)lr.seg_first * (D * D + D) + e;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    int g = 0;
-    for (; g + 4 <= lr.nseg; g += 4) {
-        s0 += p0[(int64_t)(g + 0) * (D * D + D)];
-        s1 += p0[(int64_t)(g + 1) * (D * D + D)];
-        s2 += p0[(int64_t)(g + 2) * (D * D + D)];
-        s3 += p0[(int64_t)(g + 3) * (D * D + D)];
-    }
-    for (; g < lr.nseg; ++g) s0 += p0[(int64_t)g * (D * D + D)];
-    p0[0] = (s0 + s1) + (s2 + s3);
+    p0[0] = segment_sum<D>(p0, lr.nseg);
     }
 }
+
+// Below d = 64 a row's partials are a few kilobytes each: the solving workgroup sums them itself, and
+// reduce_partials_kernel is not launched.
+template <int D> constexpr bool sums_segments() { return D < 64; }
 
 // Loads the summed statistics of one long row, adds alpha*G + lambda*I, solves, stores.  `last` and the
 // return value as in primal_step.
@@ -601,18 +610,22 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
     constexpr int LD = Team<D>::LD, T = Team<D>::THREADS;
     float *a = lds, *aux = lds + D * LD, *bvec = aux + 3 * D;
     const float *p0 = partials + (int64_t)lr.seg_first * (D * D + D);
+    const int nsum = sums_segments<D>() ? lr.nseg : 1;
     if (solver == ALS_SOLVER_DIRECT) {
         const bool g_aligned = ((uintptr_t)G & 15) == 0;
         for (int e = opaque_tid(); e < D * D / 4; e += T) {
             const int r = e / (D / 4), c = 4 * (e % (D / 4));
             if (c < 16 * (r / 16 + 1)) {
-                const float4 v = *(const float4 *)(p0 + 4 * e), g = load_g4(G, 4 * e, g_aligned);
+                const float4 v = nsum > 1 ? make_float4(segment_sum<D>(p0 + 4 * e, nsum), segment_sum<D>(p0 + 4 * e + 1, nsum),
+                                                        segment_sum<D>(p0 + 4 * e + 2, nsum), segment_sum<D>(p0 + 4 * e + 3, nsum))
+                                          : *(const float4 *)(p0 + 4 * e);
+                const float4 g = load_g4(G, 4 * e, g_aligned);
                 *(float4 *)(lds + tri_row<D>(r) + c) =
                     make_float4(v.x + alpha * g.x + (r == c ? lambda : 0.f), v.y + alpha * g.y + (r == c + 1 ? lambda : 0.f),
                                 v.z + alpha * g.z + (r == c + 2 ? lambda : 0.f), v.w + alpha * g.w + (r == c + 3 ? lambda : 0.f));
             }
         }
-        if (opaque_tid() < D) lds[Packed<D>::OFF_RHS + opaque_tid()] = p0[D * D + opaque_tid()];
+        if (opaque_tid() < D) lds[Packed<D>::OFF_RHS + opaque_tid()] = segment_sum<D>(p0 + D * D + opaque_tid(), nsum);
         __syncthreads();
         const int wave_s = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
         packed_solve_store<D, BF16>(lds, X, lr.row * ldx, wave_s, err_flag);
@@ -621,7 +634,7 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
         return true;
     }
     for (int e = opaque_tid(); e < D * D + D; e += T) {
-        const float s = p0[e];
+        const float s = segment_sum<D>(p0 + e, nsum);
         if (e < D * D) {
             const int r = e / D, c = e % D;
             if (D >= 64 && c > r) continue;  // the lower triangle serves both
@@ -741,7 +754,7 @@ static als_status long_typed(als_ctx *ctx, const als_csr *Y, const als_table *V,
     timer_end(ctx, s);
     timer_begin(ctx, T_REDUCE, s);
     const unsigned red_blocks = std::max(1u, g_long.known + g_long.rest);  // grid-stride over the long rows
-    hipLaunchKernelGGL(reduce_partials_kernel<D>, dim3(red_blocks, (D * D + D + 255) / 256), dim3(256), 0, s, long_rows,
+    if constexpr (!sums_segments<D>()) hipLaunchKernelGGL(reduce_partials_kernel<D>, dim3(red_blocks, (D * D + D + 255) / 256), dim3(256), 0, s, long_rows,
                        partials, counters);
     const size_t lds_bytes = solve_lds_bytes<D>(prm->solver);
     if (g_long.known > 0)

@@ -99,12 +99,11 @@ __global__ __launch_bounds__(CLS_THREADS) void long_stat_kernel(const int64_t *_
 // The split threshold in use: the requested one, raised until the segments of all long rows fit the
 // workspace.  With s >= entries_beyond / (SEG_CAPACITY / 2) the rows longer than s number at most
 // SEG_CAPACITY / 2 and their segments (each row: at most k/s + 1) at most SEG_CAPACITY.
-__global__ void decide_split_kernel(const unsigned long long *__restrict__ long_stat, int64_t split,
-                                    int32_t *__restrict__ counters) {
+__device__ __forceinline__ int32_t decide_split(const unsigned long long *__restrict__ long_stat, int64_t split) {
     const unsigned long long need = (long_stat[0] + SEG_CAPACITY / 2 - 1) / (SEG_CAPACITY / 2);
     unsigned long long s = (unsigned long long)split;
     if (need > s) s = need;
-    counters[7] = (int32_t)(s > 0x7fffffffull ? 0x7fffffffull : s);
+    return (int32_t)(s > 0x7fffffffull ? 0x7fffffffull : s);
 }
 
 // One workgroup per CLS_ROWS consecutive rows of [r0, r1):
@@ -113,8 +112,8 @@ __global__ void decide_split_kernel(const unsigned long long *__restrict__ long_
 //                       (row id relative to r0)
 //   dual_max < k <= split  appended to the mid list (primal, one workgroup per row)
 //   k > split           becomes a long row cut into balanced segments of about `split` entries
-//                       (at most MAX_SEGS_PER_ROW of them); split is the threshold decide_split_kernel left
-//                       in counters[7]
+//                       (at most MAX_SEGS_PER_ROW of them); split is the threshold of decide_split, left in
+//                       counters[7] too
 // List positions are reserved with one atomic per workgroup and list (counts gathered in LDS), and
 // rows keep their order inside a workgroup's slice.  A matrix whose indptr does not fit its nnz can ask
 // for more long rows or segments than the workspace holds, or for entries at or beyond entry_limit: those rows are
@@ -124,12 +123,13 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
     const int64_t *__restrict__ indptr, int64_t r0, int64_t r1, int64_t dual_max, int d,
     void *__restrict__ X, int64_t ldx, int32_t *__restrict__ counters, LongRow *__restrict__ long_rows,
     Segment *__restrict__ segs, int32_t *__restrict__ mid_list, int64_t cap_mid, int32_t *__restrict__ dual_lists,
-    ListOffsets list_off, int64_t entry_limit) {
+    ListOffsets list_off, int64_t entry_limit, const unsigned long long *__restrict__ long_stat, int64_t split_wanted) {
     __shared__ int32_t cnt[11], base[11];
     const int t = threadIdx.x;
     if (t < 11) cnt[t] = 0;
     __syncthreads();
-    const int64_t split = counters[7];
+    const int64_t split = decide_split(long_stat, split_wanted);
+    if (blockIdx.x == 0 && t == 0) counters[7] = (int32_t)split;
     const int64_t u0 = r0 + (int64_t)blockIdx.x * CLS_ROWS;
     int cls[CLS_RPT], pos[CLS_RPT];
 #pragma unroll
@@ -299,16 +299,14 @@ als_status launch_solve_rows(als_ctx *ctx, const als_csr *Y, const als_table *V,
     hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, counters, (long long *)long_stat);
     const unsigned cblocks = (unsigned)((nrows + CLS_ROWS - 1) / CLS_ROWS);
     hipLaunchKernelGGL(long_stat_kernel, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr, r0, r1, split, long_stat);
-    hipLaunchKernelGGL(decide_split_kernel, dim3(1), dim3(1), 0, s, (const unsigned long long *)long_stat, split,
-                       counters);
     if (V->dtype == ALS_BF16)
         hipLaunchKernelGGL(classify_kernel<true>, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr, r0, r1,
                            (int64_t)dual_max, V->d, X->data, X->ld, counters, long_rows, segs, mid_list, cap_mid,
-                           dual_lists, list_off, by_entry ? Y->nnz : INT64_MAX);
+                           dual_lists, list_off, by_entry ? Y->nnz : INT64_MAX, (const unsigned long long *)long_stat, split);
     else
         hipLaunchKernelGGL(classify_kernel<false>, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr, r0, r1,
                            (int64_t)dual_max, V->d, X->data, X->ld, counters, long_rows, segs, mid_list, cap_mid,
-                           dual_lists, list_off, by_entry ? Y->nnz : INT64_MAX);
+                           dual_lists, list_off, by_entry ? Y->nnz : INT64_MAX, (const unsigned long long *)long_stat, split);
     hipLaunchKernelGGL(publish_counts_kernel, dim3(1), dim3(64), 0, s, counters, cap_mid, list_off,
                        ctx->hint_counts_dev + (size_t)slot * HINT_INTS, hs.seq);
     timer_end(ctx, s);
