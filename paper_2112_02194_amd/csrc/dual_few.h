@@ -1,0 +1,23 @@
+// The class lists of a call as one launch sees them (dual_few.hip).
+#pragma once
+
+#include "als_internal.h"
+
+namespace als {
+
+// rows per step of lists 0..9 (see dual_few.hip)
+constexpr int FEW_ROWS[10] = {4, 4, 1, 1, 1, 1, 1, 1, 16, 8};
+// Steps that all lists together can hold at most for the common launch.  Fold-ins against 1M items (d = 128, fp32), a
+// launch per class / one launch, us: 256 rows 170 / 101, 6000 rows 268 / 169, 20 000 rows 372 / 284, 60 000 rows
+// 652 / 581 (about 131 000 steps), 150 000 rows 854 / 963.
+constexpr int64_t FEW_STEPS = 1 << 17;
+
+struct FewLists {
+    const int32_t *list[10], *count[10];
+    int32_t start[11];  // first workgroup of each list; the last: the number of workgroups
+};
+
+als_status launch_dual_few(als_ctx *ctx, int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
+                           const FewLists &few, int32_t *err, hipStream_t s);
+
+}  // namespace als

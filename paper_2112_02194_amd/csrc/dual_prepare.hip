@@ -20,6 +20,7 @@
 //                          lower triangle in LDS, blocked elimination with MFMA trailing updates
 //   transform_kernel  X = R L^{-1}   (rows r -> L^{-T} r), rounding to the table's element type
 #include "dual_common.h"
+#include "dual_few.h"
 
 namespace als {
 
@@ -610,6 +611,22 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     // one-row-per-wavefront kernel, the classes up to k = 32 through its smallest instance
     const WideSolver ws = {prm->solver == ALS_SOLVER_CG, prm->cg_max_iters > 0 ? prm->cg_max_iters : 2 * D,
                            prm->cg_tol > 0.f ? prm->cg_tol : 1e-6f};
+    FewLists few;
+    int64_t steps = 0;
+    for (int c = 0; c < 10; ++c) {
+        few.list[c] = lists[c];
+        few.count[c] = counts_dev[c];
+        few.start[c] = (int32_t)std::min<int64_t>(steps, INT32_MAX);
+        steps += (caps[c] + FEW_ROWS[c] - 1) / FEW_ROWS[c];
+    }
+    few.start[10] = (int32_t)std::min<int64_t>(steps, INT32_MAX);
+    if (!ws.cg && steps <= FEW_STEPS) {
+        if (steps > 0) {
+            timer_begin(ctx, T_DUAL_CLASS0, s);
+            stb = launch_dual_few(ctx, D, Y, Z, zb16, R, ldr, r0, few, err, s);
+            timer_end(ctx, s);
+        }
+    } else {
     if (ws.cg) {
         if constexpr (D < 64) return fail(ctx, ALS_EINVAL, "conjugate gradients on the dual systems need d >= 64");
         ALS_TIMED_CLASS(T_DUAL_CLASS0 + 1, 1, 1, (stb = launch_dual_wide3(ctx, D, Y, Z, zb16, R, ldr, r0, lists[1], counts_dev[1], g, err, ws, s)))
@@ -629,6 +646,7 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     ALS_TIMED_CLASS(T_DUAL_CLASS0 + 5, 5, 1, (stb = launch_dual_wide6(ctx, D, Y, Z, zb16, R, ldr, r0, lists[5], counts_dev[5], g, err, ws, s)))
     ALS_TIMED_CLASS(T_DUAL_CLASS0 + 6, 6, 1, (stb = launch_dual_wide7(ctx, D, Y, Z, zb16, R, ldr, r0, lists[6], counts_dev[6], g, err, ws, s)))
     ALS_TIMED_CLASS(T_DUAL_CLASS0 + 7, 7, 1, (stb = launch_dual_wide8(ctx, D, Y, Z, zb16, R, ldr, r0, lists[7], counts_dev[7], g, err, ws, s)))
+    }
 #undef ALS_TIMED_CLASS
     if (stb != ALS_OK) return stb;
     timer_begin(ctx, T_TRANSFORM_X, s);
