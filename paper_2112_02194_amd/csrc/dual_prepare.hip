@@ -49,7 +49,7 @@ ALS_DECL_WIDE(3) ALS_DECL_WIDE(4) ALS_DECL_WIDE(5) ALS_DECL_WIDE(6) ALS_DECL_WID
 // A_ij -= W_i P^{-1} W_j^T on the fp64 matrix cores, spread over the workgroup's wavefronts.  The inverse of M
 // follows block by block (N_ij = -N_ii sum_k M_ik N_kj), a column of blocks per wavefront without a barrier, and
 // is kept in the upper blocks of the same LDS array.  L^{-1} = P^{-1/2} M^{-1}.
-// D = 128: 600 us as an element-wise Cholesky with a barrier per column, 58 us in this form (d = 64: 158 and 20 us).
+// D = 128: 600 us as an element-wise Cholesky with a barrier per column, 44 us in this form (d = 64: 158 and 20 us).
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int FACTOR_THREADS = 512;
 
@@ -77,6 +77,7 @@ __global__ __launch_bounds__(FACTOR_THREADS) void factor_kernel(const float *__r
     double *a = fa, *nd = fa + C::OFF_N, *rpb = fa + C::OFF_RP;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int i16 = lane & 15, q = lane >> 4;
+#pragma unroll 8
     for (int e = t; e < D * D; e += T) {
         const int r = e / D, c = e % D;
         a[r * LD + c] = (double)alpha * (double)G[e] + (r == c ? (double)lambda : 0.0);
@@ -182,6 +183,7 @@ __global__ __launch_bounds__(FACTOR_THREADS) void factor_kernel(const float *__r
         const double n = br == bc ? nd[r * 17 + (c & 15)] : a[(16 * bc + (r & 15)) * LD + 16 * br + (c & 15)];
         return (float)(n * rpb[r]);
     };
+#pragma unroll 4
     for (int e = t; e < D * D; e += T) {
         const int r = e / D, c = e % D;
         Linv[e] = entry(r, c);
