@@ -1,5 +1,4 @@
-// Dual row update for rows with very few stored entries: k <= G with G = 8 or 4, compiled once per
-// class with -DSMALL_G=8 / -DSMALL_G=4.  Several rows share one 16-entry MFMA tile (16/G rows per
+// Dual row update for rows with very few stored entries: k <= G with G = 8 or 4.  Several rows share one 16-entry MFMA tile (16/G rows per
 // tile, four tiles per wavefront, so 8 or 16 rows per wavefront): the tile's 16x16 product then holds
 // the rows' G x G systems S = I + Z_I Z_I^T as its diagonal blocks; the off-diagonal blocks are never
 // read.  Lane i of a tile's 16-lane group owns row i of the tile, i.e. row i % G of sub-system i / G;

@@ -1,5 +1,5 @@
-// Dual row update for 32 < k <= 128 (d = 128; k <= 64 also at d = 64), compiled once per class with
-// -DWIDE_KT=3..8 (k <= 16*WIDE_KT).  The algebra is in the header comment of dual_prepare.hip.
+// Dual row update for 32 < k <= 128 (d = 128; k <= 64 also at d = 64), in classes KT = 3..8
+// (k <= 16*KT).  The algebra is in the header comment of dual_prepare.hip.
 #pragma once
 
 #include "dual_common.h"
