@@ -13,8 +13,8 @@
 // select kernel  one workgroup per query.  k chunks whose best is at least some value hold k different items that
 //                are at least that good, so the k-th largest lower bound is a bar that the k-th best item clears
 //                (chunks with excluded items do not count for the bar).  The chunks whose upper bound reaches the
-//                bar, little more than k of them, are scored again with fp32 products and sums, the survivors
-//                checked against the exclusion list, sorted, and the best k written.
+//                bar, little more than k of them, are scored again in full (score_tile), the survivors checked
+//                against the exclusion list, sorted, and the best k written.
 // Order everywhere: descending score, equal scores by ascending item id, so the result is unique.  What cannot be
 // bounded (entries that are infinite, NaN or so large that a product may overflow) has an infinite margin: it never
 // sets the bar and is always scored exactly.
@@ -245,11 +245,55 @@ __device__ __forceinline__ void block_sort(float *sc, int32_t *id, int N, int ti
     }
 }
 
+// Full-accuracy scores of 16 queries and 16 items: bf16 rows of 32 elements and more as they are stored on the bf16 matrix
+// cores (exact products, fp32 sums), everything else as fp32 on v_mfma_f32_16x16x4f32, which rounds every product's sum to
+// nearest.  The order of the sums is fixed, 16 or 32 elements per round of matrix instructions: it decides which of two items
+// whose scores differ by less than their rounding comes first, so a score has the same bits wherever it is computed.  Lane
+// (a, q) = (lane % 16, lane / 16) holds, of query a and of item a, the 16-byte pieces j of the row: elements (4 j + q) EPP ..
+template <int D, bool BF16> constexpr bool score_native() { return BF16 && D >= 32; }
+template <int D, bool BF16> constexpr int score_pieces() { return D / (score_native<D, BF16>() ? 32 : 16); }
+template <int D, bool BF16>
+__device__ __forceinline__ void score_load(const void *T, int64_t elem0, bool ok, int q, float4 (&z)[score_pieces<D, BF16>()]) {
+    constexpr int NP = score_pieces<D, BF16>();
+#pragma unroll
+    for (int j = 0; j < NP; ++j) z[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (ok) {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            if constexpr (score_native<D, BF16>()) {
+                z[j] = *(const float4 *)((const uint16_t *)T + elem0 + (4 * j + q) * 8);
+            } else {
+                float x[4];
+                load_vec<4, BF16>(T, elem0 + (4 * j + q) * 4, x);
+                z[j] = make_float4(x[0], x[1], x[2], x[3]);
+            }
+        }
+    }
+}
+// element v of lane (a, q): <query 4 q + v, item a>
+template <int D, bool BF16>
+__device__ __forceinline__ floatx4 score_tile(const float4 (&zq)[score_pieces<D, BF16>()], const float4 (&zh)[score_pieces<D, BF16>()]) {
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < score_pieces<D, BF16>(); ++j) {
+        if constexpr (score_native<D, BF16>()) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, zq[j]), __builtin_bit_cast(bf16x8, zh[j]), acc, 0, 0, 0);
+        } else {
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(zq[j].x, zh[j].x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(zq[j].y, zh[j].y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(zq[j].z, zh[j].z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(zq[j].w, zh[j].w, acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
+
 // What bounds it: the latency of its few dependent phases (maxima, rescoring, sort) when there are few queries, the read
 // of the maxima and of the rescored chunks when there are many.
-// Both kernels together against a scan that scored everything in fp32 and kept candidate buffers: 64 queries x 30k items
-// (d = 64, fp32, k = 20) 2.59 -> 0.036 ms, 4096 x 1M (the same) 7.9 -> 0.79 ms, 4096 x 10M (d = 128, bf16, k = 50,
-// exclusions) 134.8 -> 10.5 ms.
+// Both kernels together against a scan that scored everything in full and kept candidate buffers: 64 queries x 30k items
+// (d = 64, fp32, k = 20) 2.36 -> 0.039 ms, 4096 x 1M (the same) 7.9 -> 0.87 ms, 4096 x 10M (d = 128, bf16, k = 50,
+// exclusions) 132.5 -> 10.5 ms.  Rescoring with eight products per lane and a sum over lanes takes 0.036, 0.80 and 10.4 ms,
+// but ranks items whose scores differ in the last bits in another order.
 template <int D, bool BF16>
 __global__ __launch_bounds__(256) void topk_select_kernel(const void *__restrict__ Q, int64_t ldq, int64_t nq,
                                                           const void *__restrict__ H, int64_t ldh, int64_t n,
@@ -257,18 +301,20 @@ __global__ __launch_bounds__(256) void topk_select_kernel(const void *__restrict
                                                           const int32_t *__restrict__ ex_indices, int k, ChunkMap map,
                                                           const float *__restrict__ maxima, const float *__restrict__ norms,
                                                           int32_t *__restrict__ ids, float *__restrict__ scores) {
-    constexpr int LPI = D / 8, IPS = 64 / LPI, STEPS = TOPK_SEG / IPS;  // lanes per item, items per step and wavefront
+    constexpr int LPI = D / 8, NP = score_pieces<D, BF16>();
     constexpr int32_t NO_ID = 0x7fffffff;
     extern __shared__ uint32_t touched[];  // one bit per chunk: it holds an excluded item
     __shared__ float tmax[256], sc[TOPK_CAND], list_u[TOPK_LIST];
     __shared__ int32_t id[TOPK_CAND], list_c[TOPK_LIST];
     __shared__ int count, nlist, bar_id;
     __shared__ float bar;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t q = blockIdx.x;
     const int64_t eb = ex_indptr ? ex_indptr[q] : 0, ee = ex_indptr ? ex_indptr[q + 1] : 0;
 
-    float qx[8];  // this lane's eight elements of the query
+    float4 zq[NP];
+    score_load<D, BF16>(Q, q * ldq, true, lane >> 4, zq);
+    float qx[8];  // eight elements of the query, for its norm
     piece_floats<BF16>(piece_load<BF16>(Q, q * ldq + (lane % LPI) * 8), qx);
     float ss = 0.f, am = 0.f;
 #pragma unroll
@@ -381,26 +427,18 @@ __global__ __launch_bounds__(256) void topk_select_kernel(const void *__restrict
                 const int64_t i0 = map.segment(list_c[g >> lr], g & ((1 << lr) - 1));
                 const float u = list_u[g >> lr];
                 if (u < b || (u == b && i0 > bi)) continue;
-                Piece<BF16> p[STEPS];
+                float4 z[2][NP];
+                floatx4 acc[2];
 #pragma unroll
-                for (int s = 0; s < STEPS; ++s) {
-                    const int64_t item = i0 + s * IPS + lane / LPI;
-                    p[s] = piece_zero<BF16>();
-                    if (item < n) p[s] = piece_load<BF16>(H, item * ldh + (lane % LPI) * 8);
-                }
+                for (int t = 0; t < 2; ++t) score_load<D, BF16>(H, (i0 + 16 * t + (lane & 15)) * ldh, i0 + 16 * t + (lane & 15) < n, lane >> 4, z[t]);
 #pragma unroll
-                for (int s = 0; s < STEPS; ++s) {
-                    const int64_t item = i0 + s * IPS + lane / LPI;
-                    float x[8], v = 0.f;
-                    piece_floats<BF16>(p[s], x);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v = fmaf(qx[e], x[e], v);
-                    v = group_reduce<LPI>(v, [](float u, float w) { return u + w; });
-                    if (lane % LPI == 0 && item < n && (v > b || (v == b && (int32_t)item < bi))) {
-                        const int pos = atomicAdd(&count, 1);  // a round adds at most 4 * TOPK_ROUND * TOPK_SEG
-                        sc[pos] = v;
-                        id[pos] = (int32_t)item;
-                    }
+                for (int t = 0; t < 2; ++t) acc[t] = score_tile<D, BF16>(zq, z[t]);
+                const float v = lane < 16 ? acc[0][0] : acc[1][0];  // every row of a tile is this query
+                const int64_t item = i0 + lane;
+                if (lane < TOPK_SEG && item < n && (v > b || (v == b && (int32_t)item < bi))) {
+                    const int pos = atomicAdd(&count, 1);  // a round adds at most 4 * TOPK_ROUND * TOPK_SEG
+                    sc[pos] = v;
+                    id[pos] = (int32_t)item;
                 }
             }
             __syncthreads();

@@ -211,3 +211,39 @@ def test_rows_with_fewer_entries_than_the_table_has_rows(ctx, gpu_device, d, dty
     als.als_solve_rows(ctx, short, Hg, Gg, als.make_params(alpha, lam), X)
     with pytest.raises(als.AlsError):
         als.als_status_sync(ctx)
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_topk_scores_are_summed_in_one_stated_order(ctx, gpu_device, d, dtype):
+    """The bits of a score decide which of two close items comes first, so they are pinned: fp32 (and d = 16) one fused
+    multiply-add per element in the order 16 j + 4 q + c (j outermost, then c, then q); bf16 with d >= 32 eight exact
+    products at a time in storage order.  Entries are chosen so that fp64 holds every product and every sum before its
+    rounding to fp32: twelve-bit mantissas for the chain, whole numbers of eight bits for the groups, the first group 2^8
+    times the others so that its sum pushes the low bits of what follows out of fp32."""
+    say(f"order of the sums of a score d={d} {dtype}")
+    rng = np.random.default_rng(d)
+    nq, n = 130, 64
+    native = dtype == torch.bfloat16 and d >= 32
+    if native:
+        def entries(rows):
+            x = rng.integers(128, 256, (rows, d)) * rng.choice([-1.0, 1.0], (rows, d))
+            x[:, :8] *= 16
+            return x
+        groups = [list(range(i, i + 8)) for i in range(0, d, 8)]
+    else:
+        def entries(rows):
+            x = torch.from_numpy(rng.integers(-2047, 2048, (rows, d)) * 2.0 ** rng.integers(-4, 5, (rows, d)))
+            return x.to(dtype).double().numpy()
+        groups = [[16 * j + 4 * q + c] for j in range(d // 16) for c in range(4) for q in range(4)]
+    Q, H = entries(nq), entries(n)
+    ref = np.zeros((nq, n))
+    for g in groups:
+        ref = (ref + Q[:, g] @ H[:, g].T).astype(np.float32).astype(np.float64)
+    ids, sc = als.als_topk(ctx, torch.from_numpy(Q).to(dtype).to(gpu_device), torch.from_numpy(H).to(dtype).to(gpu_device), n)
+    torch.cuda.synchronize()
+    ids, sc = ids.cpu().numpy(), sc.cpu().numpy()
+    for q in range(nq):
+        best = np.lexsort((np.arange(n), -ref[q]))
+        assert np.array_equal(ids[q], best)
+        assert np.array_equal(sc[q].astype(np.float64), ref[q, best])
