@@ -116,8 +116,9 @@ __device__ __forceinline__ int32_t decide_split(const unsigned long long *__rest
 //                       counters[7] too
 // List positions are reserved with one atomic per workgroup and list (counts gathered in LDS), and
 // rows keep their order inside a workgroup's slice.  A matrix whose indptr does not fit its nnz can ask
-// for more long rows or segments than the workspace holds, or for entries at or beyond entry_limit: those rows are
-// dropped and the error flag is set.
+// for more long rows or segments than the workspace holds; those rows are dropped and the error flag is set.  So are, when Z
+// holds one row per entry (entry_limit = nnz, else INT64_MAX), rows with entries outside those that Gather walks, from
+// indptr[r0] to indptr[r1] and below entry_limit: an indptr that is not monotone has such rows, and Z has nothing for them.
 template <bool BF16>
 __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
     const int64_t *__restrict__ indptr, int64_t r0, int64_t r1, int64_t dual_max, int d,
@@ -130,6 +131,9 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
     __syncthreads();
     const int64_t split = decide_split(long_stat, split_wanted);
     if (blockIdx.x == 0 && t == 0) counters[7] = (int32_t)split;
+    const bool by_entry = entry_limit != INT64_MAX;
+    const int64_t first_entry = by_entry && indptr[r0] > 0 ? indptr[r0] : 0;
+    const int64_t end_entry = by_entry && indptr[r1] < entry_limit ? indptr[r1] : entry_limit;
     const int64_t u0 = r0 + (int64_t)blockIdx.x * CLS_ROWS;
     int cls[CLS_RPT], pos[CLS_RPT];
 #pragma unroll
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
         pos[i] = 0;
         if (u < r1) {
             const int64_t b = indptr[u], e = indptr[u + 1], k = e - b;
-            if (b < 0 || e > entry_limit) {  // entries that Z has no row for
+            if (b < first_entry || e > end_entry) {
                 atomicOr(&counters[2], 2);
             } else if (k <= 0) {
                 for (int c = 0; c < d; ++c) store_elem<BF16>(X, u * ldx + c, 0.f);

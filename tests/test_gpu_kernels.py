@@ -247,3 +247,36 @@ def test_topk_scores_are_summed_in_one_stated_order(ctx, gpu_device, d, dtype):
         best = np.lexsort((np.arange(n), -ref[q]))
         assert np.array_equal(ids[q], best)
         assert np.array_equal(sc[q].astype(np.float64), ref[q, best])
+
+
+@pytest.mark.parametrize("d,dtype", [(16, torch.float32), (128, torch.float32), (128, torch.bfloat16)])
+def test_rows_outside_the_entries_of_their_range_are_reported(ctx, gpu_device, d, dtype):
+    """Z holds one row per entry between the first and the last indptr of the range.  With an indptr that is not monotone a
+    row can reach beyond them although it stays within nnz: it is dropped and reported, Z is not read for it."""
+    say(f"indptr not monotone d={d} {dtype}")
+    gen = torch.Generator().manual_seed(d)
+    n, alpha, lam = 300, 0.1, 1e-2
+    H = (0.3 * torch.randn((n, d), generator=gen)).to(dtype).to(gpu_device)
+    G = als.als_gramian(ctx, H)
+    prm = als.make_params(alpha, lam)
+    for ptr, lo, hi, dropped in (([0, 10, 4], 0, 2, [0]), ([0, 4, 12, 8, 12], 1, 3, [1]), ([0, 6, 2, 9, 12], 2, 4, [])):
+        rows, idx = len(ptr) - 1, torch.randint(0, n, (ptr[-1] if ptr[-1] > 4 else 10,), generator=gen).to(torch.int32).to(gpu_device)
+        Y = als.Csr(rows, n, torch.tensor(ptr, device=gpu_device), idx)
+        X = torch.full((rows, d), 5.0, dtype=dtype, device=gpu_device)
+        als.als_solve_rows(ctx, Y, H, G, prm, X, lo, hi)
+        if dropped:
+            with pytest.raises(als.AlsError) as e:
+                als.als_status_sync(ctx)
+            assert e.value.status == als.ALS_EINVAL
+        als.als_status_sync(ctx)
+        for u in range(rows):
+            if u in dropped:
+                continue  # what a dropped row holds is not stated
+            if not lo <= u < hi:
+                assert bool((X[u] == 5.0).all())
+            elif ptr[u + 1] <= ptr[u]:
+                assert bool((X[u] == 0.0).all())
+            else:
+                x = f64(H[idx[ptr[u]:ptr[u + 1]].long()])
+                ref = np.linalg.solve(alpha * f64(G) + lam * np.eye(d) + x.T @ x, x.T @ np.ones(len(x)))
+                assert np.linalg.norm(f64(X[u]) - ref) <= (1e-4 if dtype == torch.float32 else 1e-2) * np.linalg.norm(ref)
