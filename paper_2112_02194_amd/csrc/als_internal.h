@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "als.h"
+#include "launch_size.h"
 
 namespace als {
 
@@ -29,6 +30,9 @@ template <> struct Geo<128> { static constexpr int TM = 32, NC = 4, KS = 2, ACC 
 template <> struct Geo<64>  { static constexpr int TM = 16, NC = 4, KS = 4, ACC = 4; };
 template <> struct Geo<32>  { static constexpr int TM = 16, NC = 2, KS = 4, ACC = 4; };
 template <> struct Geo<16>  { static constexpr int TM = 16, NC = 1, KS = 4, ACC = 4; };
+
+// threads of a workgroup that forms one row's (or segment's) d x d statistics: one wavefront per tile-row
+constexpr int primal_threads(int d) { return d >= 64 ? 256 : 4 * d; }
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -191,16 +195,6 @@ als_status fail(als_ctx *ctx, als_status st, const std::string &msg);
 als_status ensure(als_ctx *ctx, DevBuf &b, size_t bytes);
 void timer_begin(als_ctx *ctx, int slot, hipStream_t s);
 void timer_end(als_ctx *ctx, hipStream_t s);
-// How a list of `capacity` steps at most is launched when its length is only known on the device.  The
-// row kernels come in two forms: one step per workgroup (launched with `known` workgroups, the length the
-// previous call on the same matrix saw; steps beyond the true length return at once), and a grid-stride walk
-// over everything from step `known` on (launched with `rest` workgroups; finds nothing to do when the hint
-// was right).  Together they cover the list whatever the hint was.
-struct StepGrid {
-    unsigned known, rest;
-};
-StepGrid step_grid(const als_ctx *ctx, int64_t capacity, int64_t hint, int per_cu, int64_t blind_limit);
-
 #define ALS_HIP(ctx, expr)                                                                      \
     do {                                                                                        \
         hipError_t e__ = (expr);                                                                \

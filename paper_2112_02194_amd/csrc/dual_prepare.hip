@@ -600,7 +600,7 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     auto grid = [&](int cls, int rpw) {
         const int64_t cap = (caps[cls] + rpw - 1) / rpw;
         const int64_t hint = hints[cls] < 0 ? -1 : ((int64_t)hints[cls] + rpw - 1) / rpw;
-        return step_grid(ctx, cap, hint, 32, rpw > 1 ? 1 << 24 : 1 << 22);
+        return step_grid(ctx->num_cu, 64, cap, hint, 32, rpw > 1 ? 1 << 24 : 1 << 22);  // one wavefront per workgroup
     };
 #define ALS_TIMED_CLASS(slot, cls, rpw, call)           \
     if (caps[cls] > 0 && stb == ALS_OK) {               \

@@ -24,6 +24,7 @@ namespace als {
 template <int D> struct Team {
     static constexpr int WAVES = Geo<D>::NC;      // one wavefront per tile-row
     static constexpr int THREADS = 64 * WAVES;
+    static_assert(THREADS == primal_threads(D), "the launch sizes count on it");
     static constexpr int LD = D + 1;              // LDS leading dimension (odd: conflict-free both ways)
     static constexpr size_t LDS_BYTES = (size_t)(D * LD + 6 * D + 8) * sizeof(float);
 };

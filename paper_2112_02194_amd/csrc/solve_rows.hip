@@ -30,20 +30,6 @@ constexpr int SEG_CAPACITY = 32768;  // segments whose partial statistics the wo
 constexpr int MAX_SEGS_PER_ROW = 128;
 constexpr int64_t BLIND_PRIMAL = 1 << 20;  // see step_grid; workgroups of up to four wavefronts
 
-StepGrid step_grid(const als_ctx *ctx, int64_t capacity, int64_t hint, int per_cu, int64_t blind_limit) {
-    StepGrid g = {0u, 0u};
-    if (capacity <= 0) return g;
-    // A workgroup that finds nothing to do costs 0.2 ns of the launch.  A list that can hold a few thousand steps only is
-    // launched whole: one launch instead of two (an epoch of 2000 x 1500: 184 -> 170 us).  Without a hint, too, the
-    // list is covered in the one-step form as far as it can reach or `blind_limit` allows: the grid-stride form takes a
-    // quarter to a third longer per step (1M x 1M, d = 64, no hint: 7.3 -> 6.5 ms).
-    constexpr int64_t WHOLE = 4096, LAUNCH_MAX = 1 << 24;  // a launch holds fewer than 2^32 threads
-    if (capacity <= WHOLE) g.known = (unsigned)capacity;
-    else g.known = (unsigned)std::min<int64_t>(hint < 0 ? blind_limit : hint, std::min<int64_t>(capacity, LAUNCH_MAX));
-    g.rest = (unsigned)std::min<int64_t>(capacity - g.known, (int64_t)ctx->num_cu * per_cu);
-    return g;
-}
-
 __global__ void clear_counters_kernel(int32_t *counters, long long *long_stat) {
     const int t = threadIdx.x;
     if (t < 16 && t != 2 && t != 4) counters[t] = 0;  // [2] is the sticky error flag, [4] the CSR check flag
@@ -325,12 +311,13 @@ als_status launch_solve_rows(als_ctx *ctx, const als_csr *Y, const als_table *V,
     }
     // segments: at most 2 nnz / split + 1 of them exist, and never more than the workspace holds
     const int64_t seg_capacity = std::min<int64_t>(SEG_CAPACITY, 2 * (Y->nnz / split) + 2);
-    const StepGrid g_long = step_grid(ctx, std::min<int64_t>(SEG_CAPACITY / 2, Y->nnz / split + 1), hint[0], 4, SEG_CAPACITY);
-    const StepGrid g_seg = step_grid(ctx, seg_capacity, hint[1], 8, SEG_CAPACITY);
+    const int pt = primal_threads(V->d);
+    const StepGrid g_long = step_grid(ctx->num_cu, pt, std::min<int64_t>(SEG_CAPACITY / 2, Y->nnz / split + 1), hint[0], 4, SEG_CAPACITY);
+    const StepGrid g_seg = step_grid(ctx->num_cu, pt, seg_capacity, hint[1], 8, SEG_CAPACITY);
     if ((st = launch_primal_long(ctx, Y, V, G, prm, X, long_rows, segs, counters, seg_capacity, g_long, g_seg, s)) != ALS_OK)
         return st;
-    if ((st = launch_primal_fused(ctx, Y, V, G, prm, X, r0, mid_list, counters + 3, step_grid(ctx, cap_mid, hint[3], 8, BLIND_PRIMAL),
-                                  s)) != ALS_OK)
+    if ((st = launch_primal_fused(ctx, Y, V, G, prm, X, r0, mid_list, counters + 3,
+                                  step_grid(ctx->num_cu, pt, cap_mid, hint[3], 8, BLIND_PRIMAL), s)) != ALS_OK)
         return st;
     if (dual_max > 0) {
         const int32_t *lists[10], *counts_dev[10];

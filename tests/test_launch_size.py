@@ -1,0 +1,54 @@
+"""The launch sizes of the row lists (host arithmetic of csrc/launch_size.h), compiled here with the host compiler."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2112_02194_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def step_grid(tmp_path_factory):
+    d = tmp_path_factory.mktemp("launch_size")
+    src, lib = d / "l.cpp", d / "l.so"
+    src.write_text('#include "launch_size.h"\n'
+                   'extern "C" void grid(int cu, int threads, int64_t cap, int64_t hint, int per_cu, int64_t blind, unsigned *out) {\n'
+                   '    const als::StepGrid g = als::step_grid(cu, threads, cap, hint, per_cu, blind); out[0] = g.known; out[1] = g.rest; }\n')
+    subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, "-o", str(lib), str(src)])
+    f = ctypes.CDLL(str(lib)).grid
+    f.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_void_p]
+
+    def call(threads, cap, hint, per_cu=32, blind=1 << 22, cu=256):
+        out = (ctypes.c_uint * 2)()
+        f(cu, threads, cap, hint, per_cu, blind, out)
+        return int(out[0]), int(out[1])
+    return call
+
+
+SIZES = [0, 1, 4095, 4096, 4097, 100_000, (1 << 24) - 1, 1 << 24, 25_000_000, 50_000_000, (1 << 26) - 1, 1 << 26, (1 << 31) - 1]
+
+
+@pytest.mark.parametrize("threads", [64, 128, 256])
+def test_the_two_forms_cover_the_list_and_fit_one_launch(step_grid, threads):
+    for cap in SIZES:
+        for hint in [-1] + SIZES:
+            known, rest = step_grid(threads, cap, hint)
+            assert known <= cap and (known + rest) * threads < 1 << 32
+            assert known + rest == cap or rest == 256 * 32  # what the first form leaves is walked by the second
+            if cap <= 4096:
+                assert (known, rest) == (cap, 0)
+            elif hint >= 0 and (hint + 256 * 32) * threads < 1 << 32:
+                assert known == min(hint, cap)  # a hint is followed as far as a launch can hold it
+            elif hint < 0:
+                assert known == min(cap, 1 << 22)
+
+
+def test_a_long_list_of_small_workgroups_is_launched_whole(step_grid):
+    """2.2e7 steps of four rows (a 100M-row epoch): more than 2^24 workgroups of 64 threads are one launch."""
+    assert step_grid(64, 25_000_000, 22_000_000) == (22_000_000, 8192)
+
+
+def test_a_long_list_of_large_workgroups_stays_below_the_launch_limit(step_grid):
+    known, rest = step_grid(256, 50_000_000, 50_000_000)
+    assert known < 1 << 24 and rest == 8192
