@@ -280,3 +280,82 @@ def test_rows_outside_the_entries_of_their_range_are_reported(ctx, gpu_device, d
                 x = f64(H[idx[ptr[u]:ptr[u + 1]].long()])
                 ref = np.linalg.solve(alpha * f64(G) + lam * np.eye(d) + x.T @ x, x.T @ np.ones(len(x)))
                 assert np.linalg.norm(f64(X[u]) - ref) <= (1e-4 if dtype == torch.float32 else 1e-2) * np.linalg.norm(ref)
+
+
+def _stale_hint_case(d, dtype, first, second, n, params, gpu_device):
+    """Solve a matrix whose rows have `first` entries, rewrite it in place to `second` (the launch sizes that the first call
+    left are those of the old content), solve again; the same with a fresh context, whose calls have no such sizes."""
+    gen = torch.Generator().manual_seed(d)
+    rows, nnz = len(first), int(first.sum())
+    assert len(second) == rows and int(second.sum()) == nnz
+
+    def ptr(lens):
+        p = torch.zeros(rows + 1, dtype=torch.int64)
+        p[1:] = torch.cumsum(lens, 0)
+        return p
+    idx = torch.randint(0, n, (nnz,), generator=gen).to(torch.int32).to(gpu_device)
+    val = (torch.rand(nnz, generator=gen) + 0.5).to(gpu_device)
+    H = (0.3 * torch.randn((n, d), generator=gen)).to(dtype).to(gpu_device)
+    Y = als.Csr(rows, n, ptr(first).to(gpu_device), idx, val)
+    out = []
+    for warm in (True, False):
+        c = als.Context(0)
+        G = als.als_gramian(c, H)
+        if warm:
+            als.als_solve_rows(c, Y, H, G, params, torch.empty((rows, d), dtype=dtype, device=gpu_device))
+            als.als_status_sync(c)
+        Y.indptr.copy_(ptr(second))
+        X = torch.full((rows, d), 7.0, dtype=dtype, device=gpu_device)
+        als.als_solve_rows(c, Y, H, G, params, X)
+        als.als_status_sync(c)
+        out.append(X)
+        c.close()
+    assert torch.isfinite(out[0].float()).all()
+    assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("what", ["rows", "segments"])
+def test_primal_rows_beyond_a_launch_hint_that_is_too_small(gpu_device, d, dtype, what):
+    """The grid-stride form of the primal kernels with several items per workgroup: 2048 (rows, segments) or 1024 (long rows)
+    workgroups walk what lies beyond the hint.  The numbers do not depend on the form, bit for bit."""
+    say(f"hint too small: primal {what} d={d} {dtype}")
+    rows = 6400
+    lens = torch.arange(rows) % 15 + 1  # 1 .. 15, 8 on average up to the cut of the last cycle
+    if what == "rows":  # 100 rows of 512 entries, then every row
+        second = lens.clone()
+        second[-1] += 512 * 100 - int(lens.sum())
+        first = torch.zeros(rows, dtype=torch.int64)
+        first[::64] = 512
+        _stale_hint_case(d, dtype, first, second, 3000, als.make_params(0.1, 1e-2, path=als.PATH_PRIMAL), gpu_device)
+    else:  # no row longer than 8 entries, then 5120 of ten or more in two segments each
+        first = torch.full((rows,), 8)
+        second = torch.zeros(rows, dtype=torch.int64)
+        second[:5120] = 9 + torch.arange(5120) % 3
+        second[0] += 8 * rows - int(second.sum())
+        _stale_hint_case(d, dtype, first, second, 3000, als.make_params(0.1, 1e-2, path=als.PATH_PRIMAL, split_nnz=8), gpu_device)
+
+
+@pytest.mark.parametrize("d,dtype", [(16, torch.float32), (32, torch.float32), (32, torch.bfloat16), (64, torch.float32),
+                                     (128, torch.float32), (128, torch.bfloat16)])
+def test_dual_rows_beyond_a_launch_hint_that_is_too_small(gpu_device, d, dtype):
+    """The same for every dual class: 8192 workgroups walk the steps (of 16, 8, 4 and 1 rows) that no hint announced."""
+    say(f"hint too small: dual classes d={d} {dtype}")
+    counts = {3: 140_000, 7: 70_000, 13: 36_000}
+    if d >= 32:
+        counts[25] = 36_000
+    if d >= 64:
+        counts.update({40: 9000, 56: 9000})
+    if d >= 128:
+        counts.update({72: 9000, 88: 9000, 104: 9000, 120: 9000})
+    lens = torch.cat([torch.full((c,), k) for k, c in counts.items()])
+    lens = lens[torch.randperm(len(lens), generator=torch.Generator().manual_seed(1))]
+    total = int(lens.sum())
+    # empty rows bring the lists' capacity beyond the 2^17 steps of the common launch: 7/16 of a step per row for k <= 16 alone
+    second = torch.cat([lens, torch.zeros(total // 500 + 120_000, dtype=torch.int64)])
+    assert len(second) * 7 // 16 > 1 << 17
+    first = torch.zeros(len(second), dtype=torch.int64)  # rows too long for the dual form, then none
+    first[:total // 500] = 500
+    first[0] += total % 500
+    _stale_hint_case(d, dtype, first, second, 5000, als.make_params(0.1, 1e-2), gpu_device)
