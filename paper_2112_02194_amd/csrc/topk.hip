@@ -15,6 +15,17 @@
 //                (chunks with excluded items do not count for the bar).  The chunks whose upper bound reaches the
 //                bar, little more than k of them, are scored again in full (score_tile), the survivors checked
 //                against the exclusion list, sorted, and the best k written.
+// Where many chunks reach the bar (nearly parallel rows, ties, a query without a bound) rescoring would walk the table once
+// per query and share nothing.  Such queries are left to
+//
+// scan kernel    a wavefront owns 16 of them (their operand registers stay loaded) and walks the item tiles of its slice
+//                of the table, 16 items at a time, with score_tile.  A score at least as large as the query's current
+//                k-th best is appended to the query's candidate buffer in LDS (after a look at the query's exclusion
+//                list); a buffer that fills up is sorted by the wavefront and cut back to its best k, which also raises
+//                the bar.  The four wavefronts of a workgroup walk the same tiles for 64 different queries, so a tile
+//                comes from HBM once per 64 queries.  Each slice leaves its best k per query in a workspace.
+// merge kernel   one wavefront per query sorts the slices' candidates and writes the best k.
+//
 // Order everywhere: descending score, equal scores by ascending item id, so the result is unique.  What cannot be
 // bounded (entries that are infinite, NaN or so large that a product may overflow) has an infinite margin: it never
 // sets the bar and is always scored exactly.
@@ -29,6 +40,10 @@ constexpr int TOPK_SEG = 32;      // items of one matrix-core tile; a chunk is m
 constexpr int TOPK_CAND = 1024;   // candidate slots of the select kernel
 constexpr int TOPK_LIST = 2048;   // chunks listed for rescoring at a time
 constexpr int TOPK_ROUND = 6;     // segments per wavefront between two looks at the candidate count
+constexpr int SCAN_CAP = 128;       // scan: candidate slots per query in LDS
+constexpr int SCAN_MERGE = 1024;    // candidates the merge sorts per query (slices * padded k)
+constexpr int SCAN_QPW = 16, SCAN_WAVES = 4;
+constexpr int SCAN_TILES = 2;       // tiles of 16 items a wavefront scores per round
 constexpr int TOPK_MAX_CHUNKS = 1 << 18;  // the select kernel's chunk bitmap takes 32 KB of LDS
 static_assert(4 * TOPK_ROUND * TOPK_SEG + ALS_TOPK_MAX_K <= TOPK_CAND, "a round must fit behind the kept candidates");
 static_assert(ALS_TOPK_MAX_K <= 256, "the bar is the k-th largest of 256 thread maxima");
@@ -84,13 +99,15 @@ template <int D, bool BF16, int QT, int WI>
 __global__ __launch_bounds__(256, 2) void topk_bound_kernel(const void *__restrict__ Q, int64_t ldq, int64_t nq,
                                                             const void *__restrict__ H, int64_t ldh, int64_t n,
                                                             ChunkMap map, unsigned qgroups, int64_t units_per_group,
-                                                            float *__restrict__ maxima, float *__restrict__ norms) {
+                                                            float *__restrict__ maxima, float *__restrict__ norms,
+                                                            int32_t *__restrict__ deferred) {
     constexpr int S = topk_stage_items<D, WI>(), PITCH = 2 * D + 16, PPR = D / 8;
     constexpr int NP = S * PPR / 256, KS = D / 16, SUB = WI == 1 ? S / TOPK_SEG : 1, NM = WI == 1 ? 4 : 1;
     static_assert(NP >= 1 && S * PPR % 256 == 0, "every thread stages the same number of pieces");
     __shared__ __align__(16) char lds[2][S * PITCH];
     __shared__ unsigned nmax[2][4];  // largest norm of a chunk (as bits: they order like the values, NaN last), by unit parity
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, a = lane & 31, h = lane >> 5;
+    if (blockIdx.x == 0 && tid == 0) deferred[0] = 0;
     // Consecutive workgroups go to different XCDs: those that read the same items for other queries sit 8 apart, so that
     // they meet in one L2.
     const unsigned slot = blockIdx.x >> 3;
@@ -300,6 +317,7 @@ __global__ __launch_bounds__(256) void topk_select_kernel(const void *__restrict
                                                           const int64_t *__restrict__ ex_indptr,
                                                           const int32_t *__restrict__ ex_indices, int k, ChunkMap map,
                                                           const float *__restrict__ maxima, const float *__restrict__ norms,
+                                                          int32_t *__restrict__ deferred, int defer_chunks,
                                                           int32_t *__restrict__ ids, float *__restrict__ scores) {
     constexpr int LPI = D / 8, NP = score_pieces<D, BF16>();
     constexpr int32_t NO_ID = 0x7fffffff;
@@ -463,6 +481,10 @@ __global__ __launch_bounds__(256) void topk_select_kernel(const void *__restrict
         for (int c0 = 4 * tid; c0 < map.nchunks; c0 += 1024) scan4(c0);
     __syncthreads();
     const int found = nlist;
+    if (found > defer_chunks) {  // the scan takes this query
+        if (tid == 0) deferred[1 + atomicAdd(&deferred[0], 1)] = (int32_t)q;
+        return;
+    }
     if (found <= TOPK_LIST) {
         rescore(found);
     } else {  // ties or values without a bound: 1024 chunks at a time, the bar rising between
@@ -483,9 +505,166 @@ __global__ __launch_bounds__(256) void topk_select_kernel(const void *__restrict
     }
 }
 
+// Bitonic sort of N (a power of two) candidates in LDS by one wavefront, best first.
+template <int N> __device__ __forceinline__ void wave_sort(float *sc, int32_t *id, int lane) {
+    for (int k2 = 2; k2 <= N; k2 <<= 1) {
+        for (int j = k2 >> 1; j > 0; j >>= 1) {
+            for (int t = lane; t < N / 2; t += 64) {
+                const int i = (t / j) * 2 * j + (t % j), l = i + j;
+                const float sa = sc[i], sb = sc[l];
+                const int32_t ia = id[i], ib = id[l];
+                const bool first_i = (i & k2) == 0;  // this block is sorted best-first / best-last
+                if (ranks_before(sb, ib, sa, ia) == first_i) {
+                    sc[i] = sb; sc[l] = sa;
+                    id[i] = ib; id[l] = ia;
+                }
+            }
+            wave_sync();
+        }
+    }
+}
+
+// What bounds it: the latency of one round after the other for few queries, the fp32 matrix instruction for many.
+// deferred[0] queries are left to it (none, usually: the workgroups return at once), deferred[1 + x] is the x-th; its
+// slice y leaves its candidates at [y * nq + x].
+template <int D, bool BF16>
+__global__ __launch_bounds__(64 * SCAN_WAVES) void topk_scan_kernel(
+    const void *__restrict__ Q, int64_t ldq, int64_t nq, const void *__restrict__ H, int64_t ldh, int64_t n,
+    const int64_t *__restrict__ ex_indptr, const int32_t *__restrict__ ex_indices, int k, int kpad,
+    int64_t slice_items, const int32_t *__restrict__ deferred, float *__restrict__ part_sc, int32_t *__restrict__ part_id) {
+    extern __shared__ float lds[];
+    constexpr int NP = score_pieces<D, BF16>();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, a = lane & 15, q = lane >> 4;
+    // per wavefront: scores [16][CAP], ids [16][CAP], count [16], bar [16]
+    float *sc = lds + wave * (2 * SCAN_QPW * SCAN_CAP + 2 * SCAN_QPW);
+    int32_t *id = (int32_t *)(sc + SCAN_QPW * SCAN_CAP);
+    int32_t *cnt = id + SCAN_QPW * SCAN_CAP;
+    float *bar = (float *)(cnt + SCAN_QPW);
+    const int64_t todo = deferred[0];
+    const int64_t q0 = ((int64_t)blockIdx.x * SCAN_WAVES + wave) * SCAN_QPW;
+    if (q0 >= todo) return;  // wavefronts are independent of each other: no workgroup barrier below
+    if (lane < SCAN_QPW) {
+        cnt[lane] = 0;
+        bar[lane] = -INFINITY;
+    }
+    float4 zq[NP];
+    score_load<D, BF16>(Q, q0 + a < todo ? deferred[1 + q0 + a] * ldq : 0, q0 + a < todo, q, zq);
+    wave_sync();
+    const int64_t i0 = (int64_t)blockIdx.y * slice_items, i1 = i0 + slice_items < n ? i0 + slice_items : n;
+
+    auto compact = [&](int qy) {  // sort query qy's buffer, keep its best k, raise its bar
+        float *s = sc + qy * SCAN_CAP;
+        int32_t *d = id + qy * SCAN_CAP;
+        const int c = cnt[qy];
+        for (int t = c + lane; t < SCAN_CAP; t += 64) {
+            s[t] = -INFINITY;
+            d[t] = 0x7fffffff;
+        }
+        wave_sync();
+        wave_sort<SCAN_CAP>(s, d, lane);
+        if (lane == 0) {
+            const int keep = c < k ? c : k;
+            cnt[qy] = keep;
+            bar[qy] = keep == k ? s[k - 1] : -INFINITY;
+        }
+        wave_sync();
+    };
+
+    // SCAN_TILES tiles of 16 items per round; the next round's rows are requested before this round's products
+    float4 zh[SCAN_TILES][NP], zn[SCAN_TILES][NP];
+#pragma unroll
+    for (int u = 0; u < SCAN_TILES; ++u) score_load<D, BF16>(H, (i0 + 16 * u + a) * ldh, i0 + 16 * u + a < i1, q, zh[u]);
+    for (int64_t t0 = i0; t0 < i1; t0 += 16 * SCAN_TILES) {
+#pragma unroll
+        for (int u = 0; u < SCAN_TILES; ++u) {
+            const int64_t nxt = t0 + 16 * (SCAN_TILES + u) + a;
+            score_load<D, BF16>(H, nxt * ldh, nxt < i1, q, zn[u]);
+        }
+        floatx4 acc[SCAN_TILES];
+#pragma unroll
+        for (int u = 0; u < SCAN_TILES; ++u) acc[u] = score_tile<D, BF16>(zq, zh[u]);
+        // acc[u][v] = <query q0 + 4q + v, item t0 + 16 u + a>
+        const float4 b4 = *(const float4 *)(bar + 4 * q);
+        const float bq[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+        for (int u = 0; u < SCAN_TILES; ++u) {
+            const int64_t item = t0 + 16 * u + a;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int qy = 4 * q + v;
+                if (item < i1 && q0 + qy < todo && acc[u][v] >= bq[v]) {
+                    bool skip = false;
+                    if (ex_indptr) {
+                        const int64_t row = deferred[1 + q0 + qy], eb = ex_indptr[row], ee = ex_indptr[row + 1];
+                        for (int64_t p = eb; p < ee; ++p) skip |= ex_indices[p] == (int32_t)item;
+                    }
+                    if (!skip) {
+                        const int pos = atomicAdd(&cnt[qy], 1);  // at most 16 per tile and query: never beyond CAP
+                        sc[qy * SCAN_CAP + pos] = acc[u][v];
+                        id[qy * SCAN_CAP + pos] = (int32_t)item;
+                    }
+                }
+            }
+        }
+        wave_sync();
+        const int mine = lane < SCAN_QPW ? cnt[lane] : 0;
+        unsigned long long full = __ballot(mine > SCAN_CAP - 16 * SCAN_TILES);
+        while (full) {
+            const int qy = __ffsll((long long)full) - 1;
+            full &= full - 1;
+            compact(qy);
+        }
+#pragma unroll
+        for (int u = 0; u < SCAN_TILES; ++u)
+#pragma unroll
+            for (int j = 0; j < NP; ++j) zh[u][j] = zn[u][j];
+    }
+    for (int qy = 0; qy < SCAN_QPW; ++qy) {
+        compact(qy);
+        if (q0 + qy < todo && lane < kpad) {
+            const int64_t o = ((int64_t)blockIdx.y * nq + q0 + qy) * kpad + lane;
+            const bool have = lane < cnt[qy];
+            part_sc[o] = have ? sc[qy * SCAN_CAP + lane] : -INFINITY;
+            part_id[o] = have ? id[qy * SCAN_CAP + lane] : 0x7fffffff;
+        }
+    }
+}
+
+// One wavefront per deferred query: the slices' candidates, sorted, best k written (ids -1 and scores -inf where the
+// table has fewer than k admissible rows).
+__global__ __launch_bounds__(64) void topk_merge_kernel(const float *__restrict__ part_sc,
+                                                        const int32_t *__restrict__ part_id, int64_t nq, int slices,
+                                                        int kpad, int k, const int32_t *__restrict__ deferred,
+                                                        int32_t *__restrict__ ids, float *__restrict__ scores) {
+    __shared__ float sc[SCAN_MERGE];
+    __shared__ int32_t id[SCAN_MERGE];
+    const int lane = threadIdx.x;
+    if ((int64_t)blockIdx.x >= deferred[0]) return;
+    const int64_t row = deferred[1 + blockIdx.x];
+    const int total = slices * kpad;
+    for (int t = lane; t < SCAN_MERGE; t += 64) {
+        float s = -INFINITY;
+        int32_t d = 0x7fffffff;
+        if (t < total) {
+            const int64_t o = ((int64_t)(t / kpad) * nq + blockIdx.x) * kpad + t % kpad;
+            s = part_sc[o];
+            d = part_id[o];
+        }
+        sc[t] = s;
+        id[t] = d;
+    }
+    wave_sync();
+    wave_sort<SCAN_MERGE>(sc, id, lane);
+    if (lane < k) {
+        const bool have = id[lane] != 0x7fffffff;
+        ids[row * k + lane] = have ? id[lane] : -1;
+        scores[row * k + lane] = have ? sc[lane] : -INFINITY;
+    }
+}
+
 template <int D, bool BF16, int QT, int WI>
 static void bound_launch(const als_ctx *ctx, const void *Q, int64_t ldq, int64_t nq, const als_table *H, ChunkMap map,
-                         float *maxima, float *norms, hipStream_t s) {
+                         float *maxima, float *norms, int32_t *deferred, hipStream_t s) {
     const int64_t gq = topk_group_queries<QT, WI>(), qgroups = (nq + gq - 1) / gq, units = map.nchunks / 4;
     // 32 workgroups per compute unit where the table has them: the workgroups of one item stretch stay close in time, so
     // their reads meet in L2 (4096 queries x 10M items, d = 128, bf16: 10.9 ms with 8 per unit, 10.45 with 32, 10.5 with 64)
@@ -493,7 +672,7 @@ static void bound_launch(const als_ctx *ctx, const void *Q, int64_t ldq, int64_t
     const int64_t per = std::max<int64_t>(1, (units + want - 1) / want), splits = (units + per - 1) / per;
     const unsigned blocks = (unsigned)((splits + 7) / 8 * 8 * qgroups);
     hipLaunchKernelGGL((topk_bound_kernel<D, BF16, QT, WI>), dim3(blocks), dim3(256), 0, s, Q, ldq, nq, H->data, H->ld, H->rows,
-                       map, (unsigned)qgroups, per, maxima, norms);
+                       map, (unsigned)qgroups, per, maxima, norms, deferred);
 }
 
 template <int D, bool BF16>
@@ -508,28 +687,66 @@ static als_status topk_typed(als_ctx *ctx, const als_table *Q, const als_table *
     const double best2 = 48.0 * (double)H->rows / (1.3 * k * D * ES);
     while (map.lc < 24 && (std::exp2(2 * map.lc + 1) < best2 || (H->rows >> map.lc) >= TOPK_MAX_CHUNKS)) ++map.lc;
     map.nchunks = (int)(4 * ((H->rows + map.unit_items() - 1) / map.unit_items()));
-    // Queries go in batches whose maxima fit TOPK_BATCH_BYTES; each batch reads the item table once more.
+    // A query is left to the scan when more than 1/16 of the chunks reach its bar (and more than eight times what k items in
+    // different chunks need, on small tables).  Alone, one workgroup walks a table at about 30 GB/s and a chip full of them at
+    // 8 TB/s, while the scan takes as long for one query as for some hundred.  Nearly parallel rows, every query by itself
+    // to the end / left to the scan / a scan from the start (d = 64, fp32, k = 20): 4096 x 1M 133 / 9.0 / 8.0 ms,
+    // 1024 x 1M 29 / 2.5 / 2.1 ms, 1 x 1M 8.8 / 1.4 / 1.3 ms, 8192 x 30k 3.4 / 1.08 / 0.91 ms, 64 x 30k 0.36 / - / 0.52 ms.
+    // Small calls and tables, where walking alone is the shorter, are spared the scan's two launches (about 5 us when no
+    // query needs them).
+    const double table_bytes = (double)H->rows * D * ES;
+    const int many_chunks = std::max(map.nchunks / 16, 8 * k);
+    const bool may_scan = many_chunks < map.nchunks &&
+                          (table_bytes >= (double)(1 << 24) || table_bytes * (double)Q->rows >= 4294967296.0);
+    const int defer_chunks = may_scan ? many_chunks : INT32_MAX;
+    int kpad = 1;
+    while (kpad < k) kpad <<= 1;
+    int slices = (int)std::min<int64_t>(SCAN_MERGE / kpad, std::max<int64_t>(1, (H->rows + 8191) / 8192));
+    const int64_t slice_items = ((H->rows + slices - 1) / slices + 15) / 16 * 16;
+    if (may_scan) slices = (int)((H->rows + slice_items - 1) / slice_items);
+    // Queries go in batches whose maxima and partial lists fit TOPK_BATCH_BYTES; each batch reads the item table once more.
     constexpr int64_t TOPK_BATCH_BYTES = (int64_t)3 << 29;
-    const int64_t per_query = (map.nchunks + 15) / 16 * 16 * (int64_t)sizeof(float);
+    const int64_t maxima_bytes = (map.nchunks + 15) / 16 * 16 * (int64_t)sizeof(float);
+    const int64_t scan_bytes = may_scan ? (int64_t)slices * kpad * (int64_t)(sizeof(float) + sizeof(int32_t)) : 0;
+    const int64_t per_query = std::max(maxima_bytes, scan_bytes);  // the scan's partial lists lie where the maxima were
     constexpr int QT = D == 128 ? 3 : 4, GQ = topk_group_queries<QT, 1>();
     const int64_t fit = std::max<int64_t>(GQ, TOPK_BATCH_BYTES / std::max<int64_t>(per_query, 1) / GQ * GQ);
     const int64_t batches = (Q->rows + fit - 1) / fit;
     const int64_t batch = std::min<int64_t>(Q->rows, ((Q->rows + batches - 1) / batches + GQ - 1) / GQ * GQ);
     const size_t norm_bytes = ((size_t)map.nchunks * sizeof(float) + 255) / 256 * 256;
-    als_status st = ensure(ctx, ctx->topk_partials, norm_bytes + (size_t)(batch * per_query));
+    const size_t defer_bytes = ((size_t)(batch + 1) * sizeof(int32_t) + 255) / 256 * 256;
+    als_status st = ensure(ctx, ctx->topk_partials, norm_bytes + defer_bytes + (size_t)(batch * per_query));
     if (st != ALS_OK) return st;
-    float *norms = (float *)ctx->topk_partials.p, *maxima = (float *)((char *)ctx->topk_partials.p + norm_bytes);
+    float *norms = (float *)ctx->topk_partials.p, *maxima = (float *)((char *)ctx->topk_partials.p + norm_bytes + defer_bytes);
+    int32_t *deferred = (int32_t *)((char *)ctx->topk_partials.p + norm_bytes);
+    float *part_sc = maxima;
+    int32_t *part_id = (int32_t *)(part_sc + (size_t)slices * batch * kpad);
     const size_t bitmap = ex ? ((size_t)map.nchunks + 31) / 32 * 4 : 0;
+    constexpr int scan_lds = SCAN_WAVES * (2 * SCAN_QPW * SCAN_CAP + 2 * SCAN_QPW) * 4;
+    static const hipError_t attr = hipFuncSetAttribute((const void *)topk_scan_kernel<D, BF16>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, scan_lds);  // once per process
+    ALS_HIP(ctx, attr);
     for (int64_t q0 = 0; q0 < Q->rows; q0 += batch) {
         const int64_t nq = std::min(batch, Q->rows - q0);
         const void *Qb = (const char *)Q->data + q0 * Q->ld * ES;
+        const int64_t *ex_ptr = ex ? ex->indptr + q0 : nullptr;
+        const int32_t *ex_idx = ex ? ex->indices : nullptr;
         if (map.nchunks > 0) {
-            if (nq <= 256) bound_launch<D, BF16, 2, 4>(ctx, Qb, Q->ld, nq, H, map, maxima, norms, s);
-            else bound_launch<D, BF16, QT, 1>(ctx, Qb, Q->ld, nq, H, map, maxima, norms, s);
+            if (nq <= 256) bound_launch<D, BF16, 2, 4>(ctx, Qb, Q->ld, nq, H, map, maxima, norms, deferred, s);
+            else bound_launch<D, BF16, QT, 1>(ctx, Qb, Q->ld, nq, H, map, maxima, norms, deferred, s);
         }
         hipLaunchKernelGGL((topk_select_kernel<D, BF16>), dim3((unsigned)nq), dim3(256), bitmap, s, Qb, Q->ld, nq, H->data,
-                           H->ld, H->rows, ex ? ex->indptr + q0 : nullptr, ex ? ex->indices : nullptr, k, map,
-                           (const float *)maxima, (const float *)norms, ids + q0 * k, scores + q0 * k);
+                           H->ld, H->rows, ex_ptr, ex_idx, k, map, (const float *)maxima, (const float *)norms, deferred,
+                           defer_chunks, ids + q0 * k, scores + q0 * k);
+        if (may_scan) {
+            const unsigned groups = (unsigned)((nq + SCAN_QPW * SCAN_WAVES - 1) / (SCAN_QPW * SCAN_WAVES));
+            hipLaunchKernelGGL((topk_scan_kernel<D, BF16>), dim3(groups, slices), dim3(64 * SCAN_WAVES), scan_lds, s, Qb, Q->ld,
+                               nq, H->data, H->ld, H->rows, ex_ptr, ex_idx, k, kpad, slice_items, (const int32_t *)deferred,
+                               part_sc, part_id);
+            hipLaunchKernelGGL(topk_merge_kernel, dim3((unsigned)nq), dim3(64), 0, s, (const float *)part_sc,
+                               (const int32_t *)part_id, nq, slices, kpad, k, (const int32_t *)deferred, ids + q0 * k,
+                               scores + q0 * k);
+        }
     }
     ALS_HIP(ctx, hipGetLastError());
     return ALS_OK;

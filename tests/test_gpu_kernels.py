@@ -359,3 +359,66 @@ def test_dual_rows_beyond_a_launch_hint_that_is_too_small(gpu_device, d, dtype):
     first[:total // 500] = 500
     first[0] += total % 500
     _stale_hint_case(d, dtype, first, second, 5000, als.make_params(0.1, 1e-2), gpu_device)
+
+
+def _nearly_parallel(rows, d, dtype, gen):
+    """Rows whose scores spread by less than the bound's margin: whole numbers, so that every score is exact."""
+    x = 64 + torch.randint(0, 3, (rows, d), generator=gen).double()
+    return x.to(dtype)
+
+
+# tables just beyond the size from which the scan is kept (2^24 bytes) and one below it with many queries; queries beyond one
+# workgroup of the scan (64)
+@pytest.mark.parametrize("nq,n,d,dtype,k", [(70, 65_600, 64, torch.float32, 20), (130, 66_001, 128, torch.bfloat16, 64), (3, 262_200, 16, torch.float32, 1),
+                                            (65, 131_100, 32, torch.float32, 33), (5, 524_300, 16, torch.bfloat16, 50), (600, 33_000, 64, torch.float32, 10)])
+def test_topk_of_queries_that_are_left_to_the_scan(ctx, gpu_device, nq, n, d, dtype, k):
+    """Queries whose scores hardly spread, queries without a bound (an infinite entry) and ordinary ones side by side, with
+    and without exclusions.  The entries are whole numbers, the scores therefore exact: ids and scores are compared as they are."""
+    say(f"topk scan nq={nq} n={n} d={d} {dtype} k={k}")
+    gen = torch.Generator().manual_seed(n)
+    H, Q = _nearly_parallel(n, d, dtype, gen), _nearly_parallel(nq, d, dtype, gen)
+    Q[1::3] = torch.randint(-60, 61, Q[1::3].shape, generator=gen).to(dtype)  # spreads
+    H[n // 2: n // 2 + 200, ::2] *= -1
+    if nq > 3:
+        Q[3, 0] = float("inf")
+        Q[4] = 0
+    S = (Q.double().to(gpu_device) @ H.double().to(gpu_device).T)
+    if nq > 3:
+        S[3] = torch.where(H[:, 0].to(gpu_device) > 0, float("inf"), -float("inf"))
+    lens = torch.randint(0, 80, (nq,), generator=gen)
+    ptr = torch.zeros(nq + 1, dtype=torch.int64)
+    ptr[1:] = torch.cumsum(lens, 0)
+    order = torch.sort(S, dim=1, descending=True, stable=True).indices[:, :k + 100]  # equal scores by ascending id
+    idx = torch.cat([order[q, torch.randperm(k + 90, generator=gen)[:int(lens[q])].to(gpu_device)] for q in range(nq)]).to(torch.int32)
+    Qd, Hd = Q.to(gpu_device), H.to(gpu_device)
+    for ex in (False, True):
+        csr = als.Csr(nq, n, ptr.to(gpu_device), idx) if ex else None
+        ids, sc = als.als_topk(ctx, Qd, Hd, k, csr)
+        torch.cuda.synchronize()
+        for q in range(nq):
+            r = order[q]
+            if ex:
+                r = r[~torch.isin(r, idx[int(ptr[q]):int(ptr[q + 1])].long())]
+            r = r[:k]
+            assert torch.equal(ids[q].long(), r), q
+            assert torch.equal(sc[q].double(), S[q, r])
+
+
+def test_topk_of_nearly_parallel_rows_takes_no_longer_than_a_scan(ctx, gpu_device):
+    """1024 queries x 1M items: with one workgroup per query walking the table alone this took 75 times as long as on rows
+    whose scores spread; the scan for all of them takes 7 times as long."""
+    say("topk time on nearly parallel rows")
+    gen = torch.Generator(device=gpu_device).manual_seed(1)
+    ms = {}
+    for name, mean, spread in (("wide", 0.0, 1.0), ("tight", 1.0, 1e-3)):
+        H = mean + spread * torch.randn((1_000_000, 64), device=gpu_device, generator=gen)
+        Q = mean + spread * torch.randn((1024, 64), device=gpu_device, generator=gen)
+        als.als_topk(ctx, Q, H, 20)
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(3):
+            als.als_topk(ctx, Q, H, 20)
+        e1.record()
+        torch.cuda.synchronize()
+        ms[name] = e0.elapsed_time(e1) / 3
+    assert ms["tight"] <= 25 * ms["wide"], ms
