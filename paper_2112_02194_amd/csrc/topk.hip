@@ -33,6 +33,7 @@
 
 #include "dual_common.h"
 #include "row_piece.h"
+#include "topk_batch.h"
 
 namespace als {
 
@@ -312,7 +313,7 @@ __device__ __forceinline__ floatx4 score_tile(const float4 (&zq)[score_pieces<D,
 // exclusions) 132.5 -> 10.5 ms.  Rescoring with eight products per lane and a sum over lanes takes 0.036, 0.80 and 10.4 ms,
 // but ranks items whose scores differ in the last bits in another order.
 template <int D, bool BF16>
-__global__ __launch_bounds__(256) void topk_select_kernel(const void *__restrict__ Q, int64_t ldq, int64_t nq,
+__global__ __launch_bounds__(TOPK_SELECT_THREADS) void topk_select_kernel(const void *__restrict__ Q, int64_t ldq, int64_t nq,
                                                           const void *__restrict__ H, int64_t ldh, int64_t n,
                                                           const int64_t *__restrict__ ex_indptr,
                                                           const int32_t *__restrict__ ex_indices, int k, ChunkMap map,
@@ -709,11 +710,9 @@ static als_status topk_typed(als_ctx *ctx, const als_table *Q, const als_table *
     const int64_t maxima_bytes = (map.nchunks + 15) / 16 * 16 * (int64_t)sizeof(float);
     const int64_t scan_bytes = may_scan ? (int64_t)slices * kpad * (int64_t)(sizeof(float) + sizeof(int32_t)) : 0;
     const int64_t per_query = std::max(maxima_bytes, scan_bytes);  // the scan's partial lists lie where the maxima were
-    constexpr int QT = D == 128 ? 3 : 4, GQ = topk_group_queries<QT, 1>();
-    const int64_t fit = std::max<int64_t>(GQ, TOPK_BATCH_BYTES / std::max<int64_t>(per_query, 1) / GQ * GQ);
-    const int64_t batches = (Q->rows + fit - 1) / fit;
-    const int64_t batch = std::min<int64_t>(Q->rows, ((Q->rows + batches - 1) / batches + GQ - 1) / GQ * GQ);
+    constexpr int QT = D == 128 ? 3 : 4;
     const size_t norm_bytes = ((size_t)map.nchunks * sizeof(float) + 255) / 256 * 256;
+    const int64_t batch = topk_batch(Q->rows, per_query, topk_group_queries<QT, 1>(), TOPK_BATCH_BYTES);
     const size_t defer_bytes = ((size_t)(batch + 1) * sizeof(int32_t) + 255) / 256 * 256;
     als_status st = ensure(ctx, ctx->topk_partials, norm_bytes + defer_bytes + (size_t)(batch * per_query));
     if (st != ALS_OK) return st;
@@ -735,7 +734,7 @@ static als_status topk_typed(als_ctx *ctx, const als_table *Q, const als_table *
             if (nq <= 256) bound_launch<D, BF16, 2, 4>(ctx, Qb, Q->ld, nq, H, map, maxima, norms, deferred, s);
             else bound_launch<D, BF16, QT, 1>(ctx, Qb, Q->ld, nq, H, map, maxima, norms, deferred, s);
         }
-        hipLaunchKernelGGL((topk_select_kernel<D, BF16>), dim3((unsigned)nq), dim3(256), bitmap, s, Qb, Q->ld, nq, H->data,
+        hipLaunchKernelGGL((topk_select_kernel<D, BF16>), dim3((unsigned)nq), dim3(TOPK_SELECT_THREADS), bitmap, s, Qb, Q->ld, nq, H->data,
                            H->ld, H->rows, ex_ptr, ex_idx, k, map, (const float *)maxima, (const float *)norms, deferred,
                            defer_chunks, ids + q0 * k, scores + q0 * k);
         if (may_scan) {

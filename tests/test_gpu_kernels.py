@@ -422,3 +422,21 @@ def test_topk_of_nearly_parallel_rows_takes_no_longer_than_a_scan(ctx, gpu_devic
         torch.cuda.synchronize()
         ms[name] = e0.elapsed_time(e1) / 3
     assert ms["tight"] <= 25 * ms["wide"], ms
+
+
+def test_topk_of_more_queries_than_one_launch_holds(ctx, gpu_device):
+    """2^24 + 70 queries of one workgroup of 256 threads each are more than 2^32 threads: they go in batches.  Whole numbers,
+    so the scores are exact."""
+    say("topk with more than 2^24 queries")
+    nq, n, d = (1 << 24) + 70, 100, 16
+    gen = torch.Generator(device=gpu_device).manual_seed(5)
+    Q = torch.randint(-3, 4, (nq, d), device=gpu_device, generator=gen, dtype=torch.int8).to(torch.bfloat16)
+    H = torch.randint(-3, 4, (n, d), device=gpu_device, generator=gen).to(torch.bfloat16)
+    ids, sc = als.als_topk(ctx, Q, H, 1)
+    torch.cuda.synchronize()
+    for q0 in range(0, nq, 1 << 21):
+        S = Q[q0:q0 + (1 << 21)].float() @ H.float().T
+        best = S.max(dim=1).values
+        assert torch.equal(sc[q0:q0 + (1 << 21), 0], best)
+        first = torch.where(S == best[:, None], torch.arange(n, device=gpu_device), n).min(dim=1).values  # ties: smallest id
+        assert torch.equal(ids[q0:q0 + (1 << 21), 0].long(), first)
