@@ -712,10 +712,19 @@ static als_status topk_typed(als_ctx *ctx, const als_table *Q, const als_table *
     const int64_t per_query = std::max(maxima_bytes, scan_bytes);  // the scan's partial lists lie where the maxima were
     constexpr int QT = D == 128 ? 3 : 4;
     const size_t norm_bytes = ((size_t)map.nchunks * sizeof(float) + 255) / 256 * 256;
-    const int64_t batch = topk_batch(Q->rows, per_query, topk_group_queries<QT, 1>(), TOPK_BATCH_BYTES);
-    const size_t defer_bytes = ((size_t)(batch + 1) * sizeof(int32_t) + 255) / 256 * 256;
-    als_status st = ensure(ctx, ctx->topk_partials, norm_bytes + defer_bytes + (size_t)(batch * per_query));
-    if (st != ALS_OK) return st;
+    size_t defer_bytes = 0;
+    int64_t batch = topk_batch(Q->rows, per_query, topk_group_queries<QT, 1>(), TOPK_BATCH_BYTES);
+    for (const std::string last = ctx->last_error;;) {
+        defer_bytes = ((size_t)(batch + 1) * sizeof(int32_t) + 255) / 256 * 256;
+        const als_status st = ensure(ctx, ctx->topk_partials, norm_bytes + defer_bytes + (size_t)(batch * per_query));
+        if (st == ALS_OK) {
+            ctx->last_error = last;
+            break;
+        }
+        const int64_t less = topk_smaller_batch(batch);  // a nearly full card: the table is read more often
+        if (st != ALS_ENOMEM || less == batch) return st;
+        batch = less;
+    }
     float *norms = (float *)ctx->topk_partials.p, *maxima = (float *)((char *)ctx->topk_partials.p + norm_bytes + defer_bytes);
     int32_t *deferred = (int32_t *)((char *)ctx->topk_partials.p + norm_bytes);
     float *part_sc = maxima;

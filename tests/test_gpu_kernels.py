@@ -440,3 +440,30 @@ def test_topk_of_more_queries_than_one_launch_holds(ctx, gpu_device):
         assert torch.equal(sc[q0:q0 + (1 << 21), 0], best)
         first = torch.where(S == best[:, None], torch.arange(n, device=gpu_device), n).min(dim=1).values  # ties: smallest id
         assert torch.equal(ids[q0:q0 + (1 << 21), 0].long(), first)
+
+
+def test_topk_on_a_nearly_full_card(gpu_device):
+    """Where the workspace for all queries (about 0.3 GB) cannot be had, fewer are worked on together; the results are the same."""
+    say("topk with 200 MB left on the card")
+    nq, n, d, k = 8192, 4_000_000, 16, 20
+    gen = torch.Generator(device=gpu_device).manual_seed(6)
+    Q = torch.randn((nq, d), device=gpu_device, generator=gen).to(torch.bfloat16)
+    H = torch.randn((n, d), device=gpu_device, generator=gen).to(torch.bfloat16)
+    roomy = als.Context(0)
+    want = als.als_topk(roomy, Q, H, k)
+    torch.cuda.synchronize()
+    roomy.close()
+    c = als.Context(0)
+    als.als_topk(c, Q[:1], H[:1000], k)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    filler = torch.empty(torch.cuda.mem_get_info()[0] - (200 << 20), dtype=torch.uint8, device=gpu_device)
+    try:
+        got = als.als_topk(c, Q, H, k)
+        torch.cuda.synchronize()
+    finally:
+        del filler
+        torch.cuda.empty_cache()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert c.lib.als_last_error(c.handle) == b""
+    c.close()

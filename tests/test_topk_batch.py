@@ -13,11 +13,14 @@ def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("topk_batch")
     src, out = d / "b.cpp", d / "b.so"
     src.write_text('#include "topk_batch.h"\n'
-                   'extern "C" int64_t batch(int64_t q, int64_t per, int64_t group, int64_t limit) { return als::topk_batch(q, per, group, limit); }\n')
+                   'extern "C" int64_t batch(int64_t q, int64_t per, int64_t group, int64_t limit) { return als::topk_batch(q, per, group, limit); }\n'
+                   'extern "C" int64_t smaller(int64_t b) { return als::topk_smaller_batch(b); }\n')
     subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, "-o", str(out), str(src)])
     lib = ctypes.CDLL(str(out))
-    lib.batch.restype = ctypes.c_int64
+    for f in (lib.batch, lib.smaller):
+        f.restype = ctypes.c_int64
     lib.batch.argtypes = [ctypes.c_int64] * 4
+    lib.smaller.argtypes = [ctypes.c_int64]
     return lib
 
 
@@ -33,3 +36,12 @@ def test_batches_fit_the_launch_and_the_workspace(lib, group):
             assert b * 256 < 1 << 32  # one workgroup of 256 threads per query
             assert b * per <= LIMIT or b <= group
 
+
+def test_smaller_batches_end(lib):
+    for b in (1, 63, 64, 65, 127, 128, 384, 4096, 4097, 16_776_960):
+        steps = 0
+        while lib.smaller(b) != b:
+            n = lib.smaller(b)
+            assert 64 <= n < b
+            b, steps = n, steps + 1
+        assert b <= 64 and steps <= 20
