@@ -116,7 +116,7 @@ als_status als_gramian(als_ctx *ctx, const als_table *V, float *G, void *stream)
 
 /* als_gramian for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  No context; calls no hipMalloc, hipFree or any other allocating
- * routine.  The per-workgroup partial sums live in a static device array of 10 MiB that every GPU the library
+ * routine.  The per-workgroup partial sums live in a static device array of 8 MiB that every GPU the library
  * runs on holds until the process ends; it fits tables of at most ALS_GRAMIAN_STATIC_MAX_ROWS rows, larger
  * ones are refused with ALS_ESHAPE.  `device` must be the calling thread's current device.  Same kernels,
  * same summation order and therefore the same bits as als_gramian.  The address of the array is looked up

@@ -5,7 +5,7 @@
 // row with a single vector load and feeds them as both MFMA operands (see Geo<> for the column
 // interleave), accumulating all (d/TM)^2 output tiles in registers.  The four wavefronts of a
 // workgroup are summed through LDS in a fixed order, every workgroup writes one fp32 partial
-// Gramian, and two further kernels add the partials in fp64 in a fixed order, so the result is
+// Gramian, and one or two further kernels add the partials in fp64 in a fixed order, so the result is
 // reproducible bit for bit.  The grid grows with the table so that no fp32 summation chain inside
 // the matrix core is longer than GRAM_CHAIN steps: on a 1e8-row table chains of 12 000 steps showed a
 // relative error of 1.3e-5 on the diagonal (sums of squares), all of one sign.
@@ -372,16 +372,37 @@ __global__ __launch_bounds__(256) void gramian_slice_kernel(const float *__restr
     slices[(int64_t)blockIdx.y * D * D + e] = s;
 }
 
-// Stage 3: the slices in order, or the partials themselves where there are no more of them than slices (each slice
-// would be one partial: the same sums, one launch less).
-template <int D, class T>
-__global__ __launch_bounds__(256) void gramian_reduce_kernel(const T *__restrict__ slices, int nslices,
+// Stage 3: the slices in order.
+template <int D>
+__global__ __launch_bounds__(256) void gramian_reduce_kernel(const double *__restrict__ slices, int nslices,
                                                              float *__restrict__ G) {
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e >= D * D) return;
     double s = 0.0;
+    for (int b = 0; b < nslices; ++b) s += slices[(int64_t)b * D * D + e];
+    G[e] = (float)s;
+}
+
+// Stages 2 and 3 in one launch, for at most 2 nslices partials: the same sums in the same order.  A launch of this size is
+// bound by the latency of its loads: a workgroup has 32 elements of all partials in flight and sums the slices from LDS.
+constexpr int FEW_ELEMS = 32;
+template <int D>
+__global__ __launch_bounds__(256) void gramian_reduce_few_kernel(const float *__restrict__ partials, int nblocks, int nslices,
+                                                                 float *__restrict__ G) {
+    constexpr int GROUPS = 256 / FEW_ELEMS;
+    __shared__ double slice[GRAM_SLICES][FEW_ELEMS];
+    const int x = threadIdx.x % FEW_ELEMS, e = blockIdx.x * FEW_ELEMS + x;
 #pragma unroll 8
-    for (int b = 0; b < nslices; ++b) s += (double)slices[(int64_t)b * D * D + e];
+    for (int y = threadIdx.x / FEW_ELEMS; y < nslices; y += GROUPS) {
+        const float first = partials[(int64_t)y * D * D + e];
+        const float second = y + nslices < nblocks ? partials[(int64_t)(y + nslices) * D * D + e] : 0.f;
+        slice[y][x] = (double)first + (double)second;
+    }
+    __syncthreads();
+    if (threadIdx.x >= FEW_ELEMS) return;
+    double s = 0.0;
+#pragma unroll 8
+    for (int y = 0; y < nslices; ++y) s += slice[y][x];
     G[e] = (float)s;
 }
 
@@ -405,11 +426,13 @@ template <int D, bool BF16 = false> static int gramian_blocks(int64_t rows) {
     return (int)std::min<int64_t>(GRAM_MAX_BLOCKS, std::max<int64_t>(1, (rows + per_block - 1) / per_block));
 }
 
-// The three launches; `work` holds nblocks fp32 partials followed by nslices fp64 slices.
+// The two or three launches; `work` holds nblocks fp32 partials followed by nslices fp64 slices.  `few`: one reducing
+// launch, without slices (with no more partials than slices it is the shorter one, too).
 template <int D, bool BF16>
-static void gramian_enqueue(const als_table *V, float *G, void *work, int nblocks, int nslices, hipStream_t s) {
+static void gramian_enqueue(const als_table *V, float *G, void *work, int nblocks, bool few, hipStream_t s) {
     float *partials = (float *)work;
     double *slices = (double *)((char *)work + (size_t)nblocks * D * D * sizeof(float));
+    const int nslices = std::min(nblocks, GRAM_SLICES);
     if constexpr (gram_bf16_cores<D, BF16>())
         hipLaunchKernelGGL((gramian_bf16_kernel<D>), dim3(nblocks), dim3(GRAM_THREADS), 0, s, (const uint16_t *)V->data,
                            V->rows, V->ld, partials);
@@ -419,14 +442,14 @@ static void gramian_enqueue(const als_table *V, float *G, void *work, int nblock
     else
         hipLaunchKernelGGL((gramian_partial_kernel<D, BF16>), dim3(nblocks), dim3(GRAM_THREADS), 0, s, V->data, V->rows,
                            V->ld, partials);
-    if (nblocks <= nslices) {
-        hipLaunchKernelGGL((gramian_reduce_kernel<D, float>), dim3((D * D + 255) / 256), dim3(256), 0, s,
-                           (const float *)partials, nblocks, G);
+    if (few) {
+        hipLaunchKernelGGL((gramian_reduce_few_kernel<D>), dim3(D * D / FEW_ELEMS), dim3(256), 0, s, (const float *)partials,
+                           nblocks, nslices, G);
         return;
     }
     hipLaunchKernelGGL((gramian_slice_kernel<D>), dim3((D * D + 255) / 256, nslices), dim3(256), 0, s,
                        (const float *)partials, nblocks, slices);
-    hipLaunchKernelGGL((gramian_reduce_kernel<D, double>), dim3((D * D + 255) / 256), dim3(256), 0, s,
+    hipLaunchKernelGGL((gramian_reduce_kernel<D>), dim3((D * D + 255) / 256), dim3(256), 0, s,
                        (const double *)slices, nslices, G);
 }
 
@@ -438,7 +461,7 @@ static als_status gramian_typed(als_ctx *ctx, const als_table *V, float *G, hipS
                                                         (size_t)nslices * D * D * sizeof(double));
     if (st != ALS_OK) return st;
     timer_begin(ctx, T_GRAMIAN, s);
-    gramian_enqueue<D, BF16>(V, G, ctx->gram_partials.p, nblocks, nslices, s);
+    gramian_enqueue<D, BF16>(V, G, ctx->gram_partials.p, nblocks, nblocks <= GRAM_SLICES, s);
     timer_end(ctx, s);
     ALS_HIP(ctx, hipGetLastError());
     return ALS_OK;
@@ -459,12 +482,10 @@ als_status launch_gramian(als_ctx *ctx, const als_table *V, float *G, hipStream_
 // als_gramian_static: the same kernels with their partial sums in a file-scope device array instead of
 // the context's workspace, for callers that cannot allocate.  Every GPU holds its own copy of the array
 // at its own address; the address is looked up once per device (with that device current) and kept.
-// Nothing in the array has to start at zero: every partial and slice that is read has been written by
-// the same call.  Calls that overlap on one GPU share the array and race.
+// Nothing in the array has to start at zero: every partial that is read has been written by the same call.  Calls that overlap on one GPU share the array and race.
 constexpr int STATIC_BLOCKS = 128;   // 262 144 rows at d = 128 (2048 rows per workgroup)
-constexpr int STATIC_SLICES = 16;
-constexpr size_t STATIC_BYTES = (size_t)STATIC_BLOCKS * 128 * 128 * sizeof(float) +
-                                (size_t)STATIC_SLICES * 128 * 128 * sizeof(double);
+static_assert(STATIC_BLOCKS <= 2 * GRAM_SLICES, "their partials are reduced by one launch");
+constexpr size_t STATIC_BYTES = (size_t)STATIC_BLOCKS * 128 * 128 * sizeof(float);
 static __device__ __align__(256) unsigned char scratch[STATIC_BYTES];
 
 constexpr int STATIC_MAX_DEVICES = 64;
@@ -488,7 +509,7 @@ static als_status gramian_static_typed(const als_table *V, float *G, void *work,
     // the caller has checked the row count: with STATIC_BLOCKS workgroups no wavefront exceeds its step limit
     // (the kernels stride over the table, so fewer workgroups only means more steps each)
     const int nblocks = std::min(gramian_blocks<D, BF16>(V->rows), STATIC_BLOCKS);
-    gramian_enqueue<D, BF16>(V, G, work, nblocks, std::min(nblocks, STATIC_SLICES), s);
+    gramian_enqueue<D, BF16>(V, G, work, nblocks, true, s);
     return hipGetLastError() == hipSuccess ? ALS_OK : ALS_EHIP;
 }
 

@@ -61,3 +61,26 @@ def test_static_gramian_refuses_what_does_not_fit(gpu_device):
     als.als_gramian_static(V[:262144], out)  # the largest table that fits
     torch.cuda.synchronize()
     assert torch.all(out == 0.0)
+
+
+@pytest.mark.parametrize("d,dtype", [(16, torch.float32), (32, torch.bfloat16), (64, torch.float32), (128, torch.bfloat16), (128, torch.float32)])
+@pytest.mark.parametrize("rows", [129, 2113, 8192, 200001, 262144])
+def test_static_gramian_has_the_bits_of_als_gramian_where_the_order_shows(gpu_device, d, dtype, rows):
+    """One to 128 partial sums.  A few rows, spread over the table, are 2^40 times the others and come in pairs that cancel in
+    the products of an even and an odd column: what is left of such an entry depends on which partials were added first, in its
+    leading digits, fp64 or not."""
+    say(f"als_gramian_static bits d={d} {dtype} rows={rows}")
+    torch.cuda.set_device(0)
+    gen = torch.Generator().manual_seed(rows + d)
+    V = torch.randint(-8, 9, (rows, d), generator=gen).float()
+    big = torch.randperm(rows, generator=gen)[:64]
+    V[big] = 2.0 ** 40
+    V[big[::2], 1::2] = -2.0 ** 40
+    V = V.to(dtype).to(gpu_device)
+    ctx = als.Context(0)
+    out = torch.empty((d, d), device=gpu_device)
+    als.als_gramian_static(V, out)
+    want = als.als_gramian(ctx, V)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    ctx.close()
