@@ -172,7 +172,9 @@ als_status als_loss(als_ctx *ctx, const als_csr *Y, const als_table *W, const al
  * column ids stored in row q of `exclude` (nq rows, n columns; its values are not read; may be NULL).
  * ids: device int32 [nq*k], scores: device fp32 [nq*k], row q at offset q*k, best first, equal scores by
  * ascending id; where fewer than k rows are admissible the tail holds id -1 and score -inf.  Products and
- * sums are fp32 (bf16 tables are widened exactly).  1 <= k <= ALS_TOPK_MAX_K.  Asynchronous on `stream`. */
+ * sums are fp32 (bf16 tables are widened exactly).  1 <= k <= ALS_TOPK_MAX_K.  Asynchronous on `stream`.
+ * The workspace holds some bytes per query and stretch of items, 1.8 GB at most (4096 queries x 10M items: 1.4 GB); where the
+ * card has less left, queries are worked on in smaller batches. */
 #define ALS_TOPK_MAX_K 64
 als_status als_topk(als_ctx *ctx, const als_table *Q, const als_table *H, const als_csr *exclude, int32_t k,
                     int32_t *ids, float *scores, void *stream);
@@ -192,9 +194,10 @@ als_status als_copy_probe(als_ctx *ctx, const void *src, void *dst, int64_t byte
 
 /* Diagnostics, not part of the method.  GPU time in milliseconds (HIP events on the call's stream) of the
  * kernels launched by the most recent als_gramian / als_solve_rows / als_epoch / als_loss, per kernel:
- *   [0] Gramian (3 kernels)   [1] row classification (5 kernels)   [2] shared factorisation + Z = V L^-T
+ *   [0] Gramian (2 or 3 kernels)   [1] row classification (4 kernels)   [2] shared factorisation + Z = V L^-T
  *   [3] X = R L^-1   [4] primal fused row kernel   [5] long-row segment accumulation   [6] long-row reduce + solve
  *   [7] dual rows k <= 4   [8] dual rows 5 <= k <= 8   [9 + c] dual rows 16c < k <= 16(c+1), c = 0..7 (c = 0: 8 < k)
+ * Small calls, whose dual classes share one launch, have the time of all of them in [9]; [7], [8] and [10] to [16] are 0 then.
  * followed by the number of timed launches of each slot in [ALS_TIMING_SLOTS + slot].  Timing is recorded only
  * while enabled with als_set_timing(ctx, 1); reading waits for the recorded events. */
 #define ALS_TIMING_SLOTS 17

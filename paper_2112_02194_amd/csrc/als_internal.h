@@ -155,7 +155,7 @@ struct als_ctx {
     als::DevBuf rtable;         // fp32 [rows][d] untransformed dual solutions when the output table is bf16
     als::DevBuf small;          // counters, flags, factor matrices, scalars
     als::DevBuf loss_partials;  // fp64 per-workgroup sums
-    als::DevBuf topk_partials;  // per slice and query: best k scores and ids
+    als::DevBuf topk_partials;  // top-k: chunk norms, queries left to the scan, chunk maxima per query (or the scan's lists)
     als::DevBuf gram_w, gram_h; // fp32 [d*d] Gramians used by als_epoch / als_loss
     int32_t *host_counters = nullptr;  // pinned, 16 ints
     double *host_scalar = nullptr;     // pinned, 2 doubles

@@ -75,9 +75,9 @@ template <bool BF16> __device__ __forceinline__ bf16x8 piece_bf16(const Piece<BF
 }
 
 // Upper bound of a row's 2-norm from its sum of squares and largest magnitude (the squares of very small entries
-// underflow; NaN and infinity stay).
+// underflow; NaN and infinity stay: fmaxf drops a NaN entry from amax, the sum keeps it).
 __device__ __forceinline__ float norm_bound(float sumsq, float amax, int d) {
-    return sumsq >= 1e-24f || !(amax < 1.f) ? sqrtf(sumsq) * 1.00001f : amax * sqrtf((float)d);
+    return !(sumsq < 1e-24f) || !(amax < 1.f) ? sqrtf(sumsq) * 1.00001f : amax * sqrtf((float)d);
 }
 // |bf16 score - computed fp32 score| <= margin: both operands rounded to bf16 (2^-8 each) for fp32 tables, exact
 // products otherwise; d 2^-21 covers the fp32 sums of both sides however they are ordered or rounded, the last term
