@@ -308,10 +308,13 @@ __device__ __forceinline__ floatx4 score_tile(const float4 (&zq)[score_pieces<D,
 
 // What bounds it: the latency of its few dependent phases (maxima, rescoring, sort) when there are few queries, the read
 // of the maxima and of the rescored chunks when there are many.
+// Rescoring takes two forms.  bf16 rows of 32 elements and more go through score_tile at once.  The fp32 matrix instruction,
+// of which fifteen sixteenths are idle here, would bound the kernel: such rows are first scored by eight products per lane and
+// a sum over lanes, and only the items that this does not rule out (its rounding allowed for) go through score_tile, 16 at a
+// time (every item through it / as it is: 4096 x 10M fp32, d = 128, k = 20: 29.6 / 20.4 ms, 64 x 30k, d = 64: 38 / 36 us).
 // Both kernels together against a scan that scored everything in full and kept candidate buffers: 64 queries x 30k items
-// (d = 64, fp32, k = 20) 2.36 -> 0.039 ms, 4096 x 1M (the same) 7.9 -> 0.87 ms, 4096 x 10M (d = 128, bf16, k = 50,
-// exclusions) 132.5 -> 10.5 ms.  Rescoring with eight products per lane and a sum over lanes takes 0.036, 0.80 and 10.4 ms,
-// but ranks items whose scores differ in the last bits in another order.
+// (d = 64, fp32, k = 20) 2.36 -> 0.036 ms, 4096 x 1M (the same) 7.9 -> 0.82 ms, 4096 x 10M (d = 128, bf16, k = 50,
+// exclusions) 131 -> 10.4 ms.
 template <int D, bool BF16>
 __global__ __launch_bounds__(TOPK_SELECT_THREADS) void topk_select_kernel(const void *__restrict__ Q, int64_t ldq, int64_t nq,
                                                           const void *__restrict__ H, int64_t ldh, int64_t n,
@@ -320,7 +323,9 @@ __global__ __launch_bounds__(TOPK_SELECT_THREADS) void topk_select_kernel(const 
                                                           const float *__restrict__ maxima, const float *__restrict__ norms,
                                                           int32_t *__restrict__ deferred, int defer_chunks,
                                                           int32_t *__restrict__ ids, float *__restrict__ scores) {
-    constexpr int LPI = D / 8, NP = score_pieces<D, BF16>();
+    constexpr int LPI = D / 8, IPS = 64 / LPI, STEPS = TOPK_SEG / IPS;  // lanes per item, items per step and wavefront
+    constexpr int NP = score_pieces<D, BF16>();
+    constexpr bool NATIVE = score_native<D, BF16>();
     constexpr int32_t NO_ID = 0x7fffffff;
     extern __shared__ uint32_t touched[];  // one bit per chunk: it holds an excluded item
     __shared__ float tmax[256], sc[TOPK_CAND], list_u[TOPK_LIST];
@@ -331,9 +336,9 @@ __global__ __launch_bounds__(TOPK_SELECT_THREADS) void topk_select_kernel(const 
     const int64_t q = blockIdx.x;
     const int64_t eb = ex_indptr ? ex_indptr[q] : 0, ee = ex_indptr ? ex_indptr[q + 1] : 0;
 
-    float4 zq[NP];
-    score_load<D, BF16>(Q, q * ldq, true, lane >> 4, zq);
-    float qx[8];  // eight elements of the query, for its norm
+    float4 zq[NATIVE ? NP : 1];
+    if constexpr (NATIVE) score_load<D, BF16>(Q, q * ldq, true, lane >> 4, zq);
+    float qx[8];  // this lane's eight elements of the query
     piece_floats<BF16>(piece_load<BF16>(Q, q * ldq + (lane % LPI) * 8), qx);
     float ss = 0.f, am = 0.f;
 #pragma unroll
@@ -446,22 +451,60 @@ __global__ __launch_bounds__(TOPK_SELECT_THREADS) void topk_select_kernel(const 
                 const int64_t i0 = map.segment(list_c[g >> lr], g & ((1 << lr) - 1));
                 const float u = list_u[g >> lr];
                 if (u < b || (u == b && i0 > bi)) continue;
-                float4 z[2][NP];
-                floatx4 acc[2];
+                if constexpr (NATIVE) {
+                    float4 z[2][NP];
+                    floatx4 acc[2];
 #pragma unroll
-                for (int t = 0; t < 2; ++t) score_load<D, BF16>(H, (i0 + 16 * t + (lane & 15)) * ldh, i0 + 16 * t + (lane & 15) < n, lane >> 4, z[t]);
+                    for (int t = 0; t < 2; ++t) score_load<D, BF16>(H, (i0 + 16 * t + (lane & 15)) * ldh, i0 + 16 * t + (lane & 15) < n, lane >> 4, z[t]);
 #pragma unroll
-                for (int t = 0; t < 2; ++t) acc[t] = score_tile<D, BF16>(zq, z[t]);
-                const float v = lane < 16 ? acc[0][0] : acc[1][0];  // every row of a tile is this query
-                const int64_t item = i0 + lane;
-                if (lane < TOPK_SEG && item < n && (v > b || (v == b && (int32_t)item < bi))) {
-                    const int pos = atomicAdd(&count, 1);  // a round adds at most 4 * TOPK_ROUND * TOPK_SEG
-                    sc[pos] = v;
-                    id[pos] = (int32_t)item;
+                    for (int t = 0; t < 2; ++t) acc[t] = score_tile<D, BF16>(zq, z[t]);
+                    const float v = lane < 16 ? acc[0][0] : acc[1][0];  // every row of a tile is this query
+                    const int64_t item = i0 + lane;
+                    if (lane < TOPK_SEG && item < n && (v > b || (v == b && (int32_t)item < bi))) {
+                        const int pos = atomicAdd(&count, 1);  // a round adds at most 4 * TOPK_ROUND * TOPK_SEG
+                        sc[pos] = v;
+                        id[pos] = (int32_t)item;
+                    }
+                } else {
+                    // the order of a score's sums does not matter yet: both are within `slack` of each other
+                    const float slack = margin<D, true>(qn, norms[list_c[g >> lr]]);
+                    Piece<BF16> p[STEPS];
+#pragma unroll
+                    for (int s = 0; s < STEPS; ++s) {
+                        const int64_t item = i0 + s * IPS + lane / LPI;
+                        p[s] = piece_zero<BF16>();
+                        if (item < n) p[s] = piece_load<BF16>(H, item * ldh + (lane % LPI) * 8);
+                    }
+#pragma unroll
+                    for (int s = 0; s < STEPS; ++s) {
+                        const int64_t item = i0 + s * IPS + lane / LPI;
+                        float x[8], v = 0.f;
+                        piece_floats<BF16>(p[s], x);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) v = fmaf(qx[e], x[e], v);
+                        v = group_reduce<LPI>(v, [](float u, float w) { return u + w; });
+                        if (lane % LPI == 0 && item < n && !(v + slack < b)) id[atomicAdd(&count, 1)] = (int32_t)item;
+                    }
                 }
             }
             __syncthreads();
             const int after = count;
+            if constexpr (!NATIVE) {
+                for (int t0 = before + 16 * wave; t0 < after; t0 += 64) {
+                    const int t = t0 + (lane & 15);
+                    const int32_t item = t < after ? id[t] : 0;
+                    float4 zq[NP], z[NP];
+                    score_load<D, BF16>(Q, q * ldq, true, lane >> 4, zq);
+                    score_load<D, BF16>(H, item * ldh, t < after, lane >> 4, z);
+                    const float v = score_tile<D, BF16>(zq, z)[0];  // every row of the tile is this query
+                    if (lane < 16 && t < after) {
+                        const bool keep = v > b || (v == b && item < bi);
+                        sc[t] = keep ? v : -INFINITY;
+                        if (!keep) id[t] = NO_ID;
+                    }
+                }
+                if (after > before) __syncthreads();
+            }
             if (after > before && ee > eb) {
                 for (int64_t p = eb + tid; p < ee; p += 256) {
                     const int32_t e = ex_indices[p];
