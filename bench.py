@@ -38,7 +38,7 @@ def measured_traffic(workload, kernel):
 
 HBM_PEAK_GBS = 8000.0
 MFMA_F32_PEAK_TFLOPS = 157.3
-MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense; top-k bounds every score on these cores
+MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense
 
 
 def log(*a):
@@ -190,9 +190,12 @@ def main():
     #   Z = V L^-T and X = R L^-1:   HBM-bound,  rows*d*(s_in + s_out) bytes
     #   Gramian:                     HBM-bound, rows*d*s bytes (d >= 64: products on the bf16 matrix cores); fp32 tables
     #                                with d < 64: fp32-MFMA-bound, 2*rows*d^2 flop
-    #   primal fused rows:           fp32 tables: fp32-MFMA-bound, 2*nnz_p*d^2 + rows_p*(d^3/3 + 2*d^2) flop;
-    #                                bf16 tables: the fp32 solves on the vector ALU, rows_p*(d^3/3 + 2*d^2) flop
-    #   long-row segments:           fp32 tables: fp32-MFMA-bound, 2*nnz_l*d^2 flop; bf16 tables: HBM-bound gather
+    #   primal fused rows:           fp32 tables, d >= 64: bf16-MFMA-bound, six part products on the upper triangle of 32 x 32
+    #                                blocks, 6*nnz_p*d*(d + 32) flop; d < 64: fp32-MFMA-bound, 2*nnz_p*d^2 +
+    #                                rows_p*(d^3/3 + 2*d^2) flop; bf16 tables: the fp32 solves on the vector ALU,
+    #                                rows_p*(d^3/3 + 2*d^2) flop
+    #   long-row segments:           fp32 tables: as the primal rows, without a solve; bf16 tables: HBM-bound gather
+    #   short class lists (c1):      all dual classes in one launch, dual_common, with the sum of their work
     # achieved = work of the launches timed / their summed duration (HIP events on the launch stream).
     nsteps = max(args.steps, 1)
     deg = {"row": p.indptr[1:] - p.indptr[:-1], "col": p.t_indptr[1:] - p.t_indptr[:-1]}
@@ -237,17 +240,26 @@ def main():
         prim_rows += int(msk.sum())
         prim_nnz += int(kdeg[msk].sum())
         long_nnz += int(kdeg[kdeg > split].sum())
-    if es == 4:  # fp32 tables: the statistics run on the fp32 matrix cores
+    if es == 4 and d >= 64:  # fp32 tables: the statistics run as six products of bf16 parts on the bf16 matrix cores
+        work["primal"] = ["mfma_bf16", 6.0 * prim_nnz * d * (d + 32)]
+        work["segment"] = ["mfma_bf16", 6.0 * long_nnz * d * (d + 32)]
+        work["gramian"] = ["hbm", float(m + n) * d * es]  # three-way split products leave the table read as the bound
+    elif es == 4:  # the statistics run on the fp32 matrix cores
         work["primal"] = ["mfma", 2.0 * prim_nnz * d * d + prim_rows * (d ** 3 / 3.0 + 2.0 * d * d)]
         work["segment"] = ["mfma", 2.0 * long_nnz * d * d]
-        # d >= 64: three-way split products on the bf16 matrix cores leave the table read as the bound
-        work["gramian"] = ["hbm", float(m + n) * d * es] if d >= 64 else ["mfma", 2.0 * (m + n) * d * d]
+        work["gramian"] = ["mfma", 2.0 * (m + n) * d * d]
     else:       # bf16 tables: statistics on the bf16 matrix cores leave the gather (HBM) and the fp32 solve (vector ALU)
         work["primal"] = ["alu", prim_rows * (d ** 3 / 3.0 + 2.0 * d * d)]
         work["segment"] = ["hbm", float(long_nnz) * (d * es + 4)]
         work["gramian"] = ["hbm", float(m + n) * d * es]
     work["transform_z"] = ["hbm", float(m + n) * d * (es + zs)]
     work["transform_x"] = ["hbm", float(m + n) * d * (4 + es)]
+    # lists that are short together share one launch, which the library times in the slot of 8 < k <= 16
+    dual_names = [name for name, _, _ in bounds]
+    if args.solver == "direct" and [name for name in dual_names if stage_launches.get(name, 0.0) > 0] == ["dual_k16"]:
+        work["dual_common"] = ["hbm", sum(work.pop(name)[1] for name in dual_names)]
+        stage_ms["dual_common"], stage_launches["dual_common"] = stage_ms.pop("dual_k16"), stage_launches.pop("dual_k16")
+        kernel_names["dual_common"] = f"dual_few_kernel<{d},{zbt}>"
     stages = {}
     for name, (bound, per_epoch) in work.items():
         ms = stage_ms.get(name, 0.0) / nsteps
@@ -255,8 +267,10 @@ def main():
             continue
         if bound == "hbm":
             ach, peak, unit = per_epoch / (ms * 1e-3) / 1e9, HBM_PEAK_GBS, "GB/s"
-        else:  # "mfma": fp32 matrix cores; "alu": fp32 vector units - the same published 157.3 TFLOP/s
-            ach, peak, unit = per_epoch / (ms * 1e-3) / 1e12, MFMA_F32_PEAK_TFLOPS, "TFLOP/s"
+        else:  # "mfma_bf16": bf16 matrix cores; "mfma": fp32 ones, "alu": fp32 vector units - the same published 157.3 TFLOP/s
+            peak = MFMA_BF16_PEAK_TFLOPS if bound == "mfma_bf16" else MFMA_F32_PEAK_TFLOPS
+            bound = "mfma" if bound == "mfma_bf16" else bound
+            ach, unit = per_epoch / (ms * 1e-3) / 1e12, "TFLOP/s"
         launches = stage_launches.get(name, 0.0) / nsteps
         stages[name] = {"kernel": kernel_names.get(name, name), "ms_per_epoch": round(ms, 4), "launches_per_epoch": launches,
                         "bound": bound, "achieved": round(ach, 2), "peak": peak, "unit": unit, "frac": round(ach / peak, 4),
@@ -302,7 +316,8 @@ def main():
         log("graph replay:", out["graph_replay"])
         als.als_status_sync(ctx)
     if args.topk_queries > 0:
-        # retrieval (Sec. 4.6 / Sec. 5's evaluation): exact top-20 by inner product; 2*nq*n*d flop on the fp32 matrix cores
+        # retrieval (Sec. 4.6 / Sec. 5's evaluation): exact top-20 by inner product; the scores' bounds take 2*nq*n*d flop on the
+        # bf16 matrix cores
         nq, kk = min(args.topk_queries, m), 20
         Q = W[:nq].contiguous()
         als.als_topk(ctx, Q, H, kk)
@@ -320,7 +335,8 @@ def main():
                        "bound": "mfma", "achieved": round(tf, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                        "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4),
                        # the table is read once per group of queries (topk.hip)
-                       "item_table_GBps": round(math.ceil(nq / (384 if d == 128 else 512)) * n * d * es / (tk_ms * 1e-3) / 1e9, 1)}
+                       "item_table_GBps": round(math.ceil(nq / (64 if nq <= 256 else 384 if d == 128 else 512)) * n * d * es
+                                                / (tk_ms * 1e-3) / 1e9, 1)}
         log("top-k:", out["topk"])
     if args.rows:
         out["config"]["note"] = "node count overridden: not the named workload"
