@@ -379,6 +379,7 @@ __global__ __launch_bounds__(256) void gramian_reduce_kernel(const double *__res
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e >= D * D) return;
     double s = 0.0;
+#pragma unroll 8
     for (int b = 0; b < nslices; ++b) s += slices[(int64_t)b * D * D + e];
     G[e] = (float)s;
 }
