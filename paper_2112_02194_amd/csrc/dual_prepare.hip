@@ -49,7 +49,7 @@ ALS_DECL_WIDE(3) ALS_DECL_WIDE(4) ALS_DECL_WIDE(5) ALS_DECL_WIDE(6) ALS_DECL_WID
 // A_ij -= W_i P^{-1} W_j^T on the fp64 matrix cores, spread over the workgroup's wavefronts.  The inverse of M
 // follows block by block (N_ij = -N_ii sum_k M_ik N_kj), a column of blocks per wavefront without a barrier, and
 // is kept in the upper blocks of the same LDS array.  L^{-1} = P^{-1/2} M^{-1}.
-// D = 128: 600 us as an element-wise Cholesky with a barrier per column, 44 us in this form (d = 64: 158 and 20 us).
+// D = 128: 600 us as an element-wise Cholesky with a barrier per column, 48 to 58 us in this form (d = 64: 158 and 21 us).
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int FACTOR_THREADS = 512;
 
