@@ -21,6 +21,7 @@ __global__ __launch_bounds__(64) void dual_multi_kernel(const int64_t *__restric
     const int count = *count_ptr;
     int blk = first_blk + blockIdx.x;
     if constexpr (!LOOP) {
+        blk = xcd_step(blk, gridDim.x, (count + 3) / 4);
         if (blk * 4 < count) dual_multi_step<D, M, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
     } else {
         for (; blk * 4 < count; blk += gridDim.x) {

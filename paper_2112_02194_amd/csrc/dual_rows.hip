@@ -17,6 +17,7 @@ __global__ __launch_bounds__(64) void dual_rows_kernel(const int64_t *__restrict
     const int count = *count_ptr;
     int blk = first_blk + blockIdx.x;
     if constexpr (!LOOP) {
+        blk = xcd_step(blk, gridDim.x, (count + 3) / 4);
         if (blk * DualCfg<D>::RPW < count) dual_rows_step<D, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
     } else {
         for (; blk * DualCfg<D>::RPW < count; blk += gridDim.x) {

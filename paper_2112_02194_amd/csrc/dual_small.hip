@@ -22,6 +22,7 @@ __global__ __launch_bounds__(64) void dual_small_kernel(const int64_t *__restric
     const int count = *count_ptr;
     int blk = first_blk + blockIdx.x;
     if constexpr (!LOOP) {
+        blk = xcd_step(blk, gridDim.x, (count + NR - 1) / NR);
         if (blk * NR < count) dual_small_step<D, G, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
     } else {
         for (; blk * NR < count; blk += gridDim.x) {

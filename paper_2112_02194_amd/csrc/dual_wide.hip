@@ -21,6 +21,7 @@ __global__ __launch_bounds__(64, (LOOP || KT >= 7) ? 1 : (KT <= 4 ? 3 : 2)) void
     const int count = *count_ptr;
     int item = first_item + blockIdx.x;
     if constexpr (!LOOP) {
+        item = xcd_step(item, gridDim.x, count);
         if (item < count)
             dual_wide_step<D, KT, ZB, CG>(indptr, indices, values, Z, R, ldr, r0, list, err_flag, item, lds, cg_iters, cg_tol);
     } else {

@@ -14,8 +14,10 @@ def step_grid(tmp_path_factory):
     src, lib = d / "l.cpp", d / "l.so"
     src.write_text('#include "launch_size.h"\n'
                    'extern "C" void grid(int cu, int threads, int64_t cap, int64_t hint, int per_cu, int64_t blind, unsigned *out) {\n'
-                   '    const als::StepGrid g = als::step_grid(cu, threads, cap, hint, per_cu, blind); out[0] = g.known; out[1] = g.rest; }\n')
+                   '    const als::StepGrid g = als::step_grid(cu, threads, cap, hint, per_cu, blind); out[0] = g.known; out[1] = g.rest; }\n'
+                   'extern "C" int xcd(int b, int grid, int steps) { return als::xcd_step(b, grid, steps); }\n')
     subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, "-o", str(lib), str(src)])
+    xcd.f = ctypes.CDLL(str(lib)).xcd
     f = ctypes.CDLL(str(lib)).grid
     f.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_void_p]
 
@@ -24,6 +26,10 @@ def step_grid(tmp_path_factory):
         f(cu, threads, cap, hint, per_cu, blind, out)
         return int(out[0]), int(out[1])
     return call
+
+
+def xcd(b, grid, steps):
+    return xcd.f(b, grid, steps)
 
 
 SIZES = [0, 1, 4095, 4096, 4097, 100_000, (1 << 24) - 1, 1 << 24, 25_000_000, 50_000_000, (1 << 26) - 1, 1 << 26, (1 << 31) - 1]
@@ -52,3 +58,13 @@ def test_a_long_list_of_small_workgroups_is_launched_whole(step_grid):
 def test_a_long_list_of_large_workgroups_stays_below_the_launch_limit(step_grid):
     known, rest = step_grid(256, 50_000_000, 50_000_000)
     assert known < 1 << 24 and rest == 8192
+
+
+@pytest.mark.parametrize("grid", [1, 7, 8, 9, 63, 64, 1000, 4097])
+def test_steps_are_dealt_out_once_each_in_eight_parts(step_grid, grid):
+    for steps in [0, 1, 7, 8, grid - 1, grid, grid + 1, 10 * grid]:
+        order = [xcd(b, grid, steps) for b in range(grid)]
+        assert sorted(order) == list(range(grid))
+        for die in range(8):  # what one die gets of the divisible part is contiguous and in order
+            part = [s for s in order[die::8] if s < min(steps, grid) // 8 * 8]
+            assert part == list(range(part[0], part[0] + len(part))) if part else True
