@@ -64,6 +64,11 @@ template <int C> __device__ __forceinline__ void fmac_bcast16(float &acc, float 
                  : "+v"(acc)
                  : "v"(src), "v"(mul), "n"(C));
 }
+template <int C> __device__ __forceinline__ void fmac_bcast16_neg(float &acc, float src, float mul) {  // acc -= ..
+    asm volatile("v_fmac_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+                 : "+v"(acc)
+                 : "v"(src), "v"(mul), "n"(C));
+}
 __device__ __forceinline__ void dpp_settle(float &a) { asm volatile("s_nop 1" : "+v"(a)); }
 __device__ __forceinline__ void dpp_settle(float &a, float &b) { asm volatile("s_nop 1" : "+v"(a), "+v"(b)); }
 
@@ -158,6 +163,32 @@ template <bool ZB, int CPL> __device__ __forceinline__ void row_cols(const void 
             c[0] = __uint_as_float((uint32_t)((const uint16_t *)row)[lane] << 16);
         }
     }
+}
+
+// The second gather of fp32 rows (r = Z_I^T t): a lane loads 16 bytes of an entry's row, LPR lanes a row, EPI rows per
+// instruction.  What bounds the gathers where Z is cached is the rate at which addresses are worked off (four lanes a clock
+// if they lie side by side, one a clock if not), so narrower loads cost as much per instruction.
+template <int D> struct GatherCols { static constexpr int LPR = D / 4, EPI = 64 / LPR; };
+
+// Lanes 0..31: x summed over the two halves of the wavefront; lanes 32..63: y likewise.
+__device__ __forceinline__ floatx4 swap_add32(floatx4 x, floatx4 y) {
+    floatx4 r;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[c]), __float_as_uint(y[c]), false, false);
+        r[c] = __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    }
+    return r;
+}
+// Even rows of 16 lanes: x summed over a row and the next one; odd rows: y likewise.
+__device__ __forceinline__ floatx4 swap_add16(floatx4 x, floatx4 y) {
+    floatx4 r;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[c]), __float_as_uint(y[c]), false, false);
+        r[c] = __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    }
+    return r;
 }
 
 // acc += A B^T over all columns of two entries' bf16 rows held as NP pieces each

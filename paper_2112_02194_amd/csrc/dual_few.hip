@@ -16,7 +16,7 @@ template <int D, bool ZB> constexpr int few_lds_floats() {
     auto take = [&](int x) { n = x > n ? x : n; };
     take(SmallCfg<D, 4>::LDS_FLOATS);
     take(SmallCfg<D, 8>::LDS_FLOATS);
-    if constexpr (D >= 32) take(multi_resident<D, 2, ZB>() ? MultiCfg<D, 2>::LDS_FLOATS_RESIDENT : MultiCfg<D, 2>::LDS_FLOATS);
+    if constexpr (D >= 32) take(multi_resident<ZB>() ? MultiCfg::LDS_FLOATS_RESIDENT : MultiCfg::LDS_FLOATS);
     if constexpr (D == 64) take(WideCfg<D, 4>::LDS_FLOATS);
     if constexpr (D == 128) take(WideCfg<D, 8>::LDS_FLOATS);
     return n;
@@ -43,7 +43,7 @@ __global__ __launch_bounds__(64) void dual_few_kernel(const int64_t *__restrict_
     switch (c) {  // uniform
         case 0: dual_rows_step<D, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, step, lds); break;
         case 1:
-            if constexpr (D >= 32) dual_multi_step<D, 2, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, step, lds);
+            if constexpr (D >= 32) dual_multi_step<D, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, step, lds);
             break;
         case 2: wide(std::integral_constant<int, 3>{}); break;
         case 3: wide(std::integral_constant<int, 4>{}); break;

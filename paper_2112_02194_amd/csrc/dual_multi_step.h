@@ -1,59 +1,103 @@
 // Dual row update for rows with 16 < k <= 32 stored entries.  The algebra is in the header comment of
-// dual_prepare.hip.  The kernel is written for M rows of S per lane (k <= 16*M); M = 2 is the one in
-// use (for 32 < k <= 48, M = 3 was measured slower than the one-row-per-wavefront kernel).
+// dual_prepare.hip.
 #pragma once
 
 #include "dual_common.h"
 
-
 namespace als {
 
-// Four rows per wavefront, one per group of 16 lanes; lane i of a group owns the M rows i, 16+i, ..
-// of its row's k x k system (k <= K = 16*M), so every broadcast of the elimination stays inside a DPP
-// row and needs no LDS.
-//   1. per row: gather its M tiles into registers, S = I + Z_I Z_I^T tile by tile, packed lower
-//      triangle to LDS; the column ids go to LDS for the second gather;
-//   2. lanes load their rows; elimination S = M P M^T (unit lower M, pivots P) one column per step with
-//      u = M^{-1} y riding along;
-//   3. the factor goes back to LDS and is read transposed; back-substitution column by column;
-//   4. r = Z_I^T t with one lane per pair of output columns, gathering the entries a second time.
+// Four rows per wavefront, one per group of 16 lanes, each with a 32 x 32 system S = I + Z_I Z_I^T in 16 x 16 tiles
+//     S = [ A  B^T ]      A: entries 0..15,  C: entries 16..31
+//         [ B   C  ]
+//   1. per row: gather its two tiles of entries into registers, form A, B, C on the matrix cores.  C stays in the
+//      accumulator layout; A and B go to LDS and come back with lane i of a group holding rows i of A and of B;
+//   2. sixteen steps of elimination on [A; B] in registers.  Every row of A but the pivot's is updated, the rows above
+//      it too (Gauss-Jordan: those lanes would be idle otherwise), so A ends up diagonal and no triangular system is left
+//      for a back-substitution; the right-hand side rides along.  Rows are scaled by the root of the pivot, L = B U^-1 P^1/2,
+//      so that one operand serves both sides of step 3;
+//   3. C -= L L^T on the fp32 matrix instruction, in place; C to one row per lane through LDS; sixteen steps of the same
+//      elimination give t of the entries 16..31;
+//   4. t of the entries 0..15: B^T t (columns of B from LDS, t as a DPP operand), the row operations of step 2 once more
+//      on that vector (their multipliers were left where the eliminated columns were), and the pivots;
+//   5. r = Z_I^T t: bf16 Z from the tiles in registers on the matrix cores; fp32 Z with one lane per group
+//      of four output columns, gathering the entries a second time.
+// What bounds it: bf16 Z (50M power-law rows): the instructions of two wavefronts per SIMD, one every five clocks each, and
+// the latency of the gather; fp32 Z whose rows meet in the caches: the address unit, which takes a clock per lane of the
+// first gather (sixteen rows per instruction, 64 clocks), 94% busy on 10M pages of locality.
+// Against an elimination of all 32 columns with a triangular back-substitution through LDS (616 multiply-adds with a DPP
+// operand, 392 here; LDS accesses of 4 bytes with a select each, 16 bytes here; 3 219 instructions per step, 2 373 here) a
+// half of the power-law rows (d = 128, bf16) takes 41.4 instead of 44.6 ms and one of 10M pages (d = 128, fp32) 7.50 instead
+// of 7.65 ms, the latter 7.15 ms with the 16-byte loads of the second gather; 1M x 1M, d = 64: 705 -> 671 us.
+
 template <int C> __device__ __forceinline__ float bcast16(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + C, 0xf, 0xf, true));
 }
 
-template <int D, int M> struct MultiCfg {
-    static constexpr int K = 16 * M, TRI = K * (K + 1) / 2;
-    static constexpr int OFF_T = 4 * TRI, OFF_ID = OFF_T + 4 * K, OFF_DUMP = OFF_ID + 4 * K;
-    static constexpr int OFF_PARTS = OFF_DUMP + 64;  // one dump slot per lane for stores that must not land
-    // bf16 Z only: t cut into three bf16 parts plus a block of zeros, [4][4 rows][K]; the finished rows r are
-    // staged in the (by then free) triangle area
-    static constexpr int LDS_FLOATS = OFF_PARTS;
-    static constexpr int LDS_FLOATS_RESIDENT = OFF_PARTS + 16 * K;
-    static_assert(4 * TRI >= 4 * D, "the triangle area stages four rows of r");
+// LDS of one wavefront: two regions of four 16 x 16 tiles (P: A, then L, then C, then t; Q: B), one per system.  Rows are
+// sixteen floats without padding; their four blocks of four floats are permuted by the row (tile_block), so that eight lanes
+// which read or write 16 bytes of eight rows meet in eight different groups of banks.  The tiles of two systems lie 16
+// banks apart for the column reads of step 4.
+struct MultiCfg {
+    static constexpr int K = 32, TILE = 16 * 16 + 16, REGION = 4 * TILE;
+    static constexpr int OFF_P = 0, OFF_Q = REGION, OFF_ID = 2 * REGION;
+    static constexpr int LDS_FLOATS = OFF_ID + 4 * K;  // ids of the second gather
+    // bf16 Z: t cut into three bf16 parts plus a block of zeros, [4][4 rows][K], and the lanes' dump slots in P; the
+    // finished rows of r in Q
+    static constexpr int LDS_FLOATS_RESIDENT = 2 * REGION;
+    static_assert(REGION >= 16 * K + 64 && REGION >= 4 * 128, "P and Q hold what step 5 stages");
 };
+// offset of block b (columns 4 b .. 4 b + 3) of row r inside a tile
+__device__ __forceinline__ int tile_block(int r, int b) { return 16 * r + ((b ^ (r >> 1) & 3) << 2); }
 
-// bf16 Z with two tiles per row: the gathered tiles stay in registers (4 rows x 2 tiles x D/32 operands of
-// four registers) until r = Z_I^T t is formed from them on the matrix cores, so nothing is gathered twice.
-template <int D, int M, bool ZB> constexpr bool multi_resident() { return ZB && M == 2; }
+// bf16 Z: the gathered tiles stay in registers (4 rows x 2 tiles x D/32 operands of four registers) until r = Z_I^T t is
+// formed from them on the matrix cores, so nothing is gathered twice.
+template <bool ZB> constexpr bool multi_resident() { return ZB; }
+
+// One step of the eliminations: column c of the lane's row `s` (and of a second row `s2` of the same system, below it) is
+// eliminated; the columns beyond c of all rows but the pivot's are updated.  On return s[c] holds the multiplier of this
+// lane's row (zero in the pivot's), s2[c] the entry of L, and rinv the root of the reciprocal pivot in the pivot's lane.
+template <int c, bool TWO>
+__device__ __forceinline__ void eliminate_column(float (&s)[16], float (&s2)[16], float &y, float &y2, float &rinv, int i, bool &bad) {
+    const float pivot = bcast16<c>(s[c]), uc = bcast16<c>(y);
+    bad |= !(pivot > 0.f);
+    float ri = __builtin_amdgcn_rsqf(pivot);
+    ri = ri * (1.5f - 0.5f * pivot * ri * ri);  // one Newton step on the hardware estimate
+    float l = s[c] * ri, l2 = 0.f;
+    const float own = i == c ? 0.f : l, w = uc * ri;
+    rinv = i == c ? ri : rinv;
+    y -= own * w;
+    if constexpr (TWO) {
+        l2 = s2[c] * ri;
+        y2 -= l2 * w;
+    }
+    dpp_settle(l);  // just written, read through DPP below
+    static_for<c + 1, 16>([&](auto jj) {  // the broadcast of l from the lane that owns row j rides on the multiply-add
+        constexpr int j = decltype(jj)::value;
+        fmac_bcast16_neg<j>(s[j], l, own);
+        if constexpr (TWO) fmac_bcast16_neg<j>(s2[j], l, l2);
+    });
+    s[c] = own * ri;
+    if constexpr (TWO) s2[c] = l2;
+    if constexpr (c + 1 < 16) dpp_settle(s[c + 1]);  // the next step's pivot is read through DPP
+}
 
 // One step: the four rows list[4 blk .. 4 blk + 3] (blk * 4 < count).
-template <int D, int M, bool ZB>
+template <int D, bool ZB>
 __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indptr,
                                                 const int32_t *__restrict__ indices,
                                                 const float *__restrict__ values, const void *__restrict__ Z,
                                                 float *__restrict__ R, int64_t ldr, int64_t r0,
                                                 const int32_t *__restrict__ list, int count,
                                                 int32_t *__restrict__ err_flag, int blk, float *lds) {
-    using C = MultiCfg<D, M>;
-    constexpr int K = C::K, TRI = C::TRI, NJ = z_pieces<D, ZB>(), CPL = D >= 128 ? 2 : 1;
-    float *tri = lds, *tbuf = lds + C::OFF_T;
+    using C = MultiCfg;
+    constexpr int K = C::K, NJ = z_pieces<D, ZB>(), CPL = D >= 128 ? 2 : 1;
+    constexpr bool RES = multi_resident<ZB>();
     int32_t *ids = (int32_t *)(lds + C::OFF_ID);
-    // Accesses to the packed triangle are never put under a lane-dependent branch (a branch per element costs
-    // more than the access): reads go to an in-range address and are selected afterwards, stores of entries
-    // that do not exist go to the lane's dump slot.
     const int lane = opaque_tid(), a = lane & 15, q = lane >> 4;  // MFMA view: entry a of a tile, column group q
-    float *dump = lds + C::OFF_DUMP + lane;
     const int g = lane >> 4, i = lane & 15;                         // solver view: system g, lane i of its group
+    float *mfma_at = lds + tile_block(a, q);        // MFMA view: row a, columns 4 q .. of the first system's tile
+    float *row_at = lds + g * C::TILE + 16 * i;     // solver view: row i of system g
+    const int swz = (i >> 1 & 3) << 2;              // block b of that row lies at row_at + (4 b ^ swz)
 
     // Row descriptors of all four rows first (one 16-byte read of the list entries - the list's workspace is
     // padded for it; past the end of the list the first entry stands in - then the four indptr pairs
@@ -81,31 +125,46 @@ __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indp
         kmax = k[p] > kmax ? k[p] : kmax;
     }
 
-    // ---- 1. S of every row, packed lower triangle in LDS
+    // ---- 1. the tiles of S
     // the column ids of all four rows first: one wait, not one per row.  A slot past the row's k holds the id of
     // the row's first entry with the top bit set: no load for the products, and a harmless, in-range row of the
     // row's own for the second gather (where such a slot meets t = 0)
-    int32_t idv[4][M];
+    int32_t idv[4][2];
 #pragma unroll
     for (int p = 0; p < 4; ++p)
 #pragma unroll
-        for (int t = 0; t < M; ++t) {
+        for (int t = 0; t < 2; ++t) {
             const int e = 16 * t + a;
             const int32_t id = indices[b[p] + (e < k[p] ? e : 0)];  // clamped: unconditional load
             idv[p][t] = e < k[p] ? id : (id | (int32_t)0x80000000);
         }
-    constexpr bool RES = multi_resident<D, M, ZB>();
-    float4 zkeep[RES ? 4 : 1][M][NJ];
+    // labels of the entries i and 16 + i of this lane's system (the class has more than 16 entries per row)
+    float y0 = 1.f, y1 = 0.f;
+    {
+        int myk = 0;
+        int64_t myb = 0;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            myk = g == p ? k[p] : myk;
+            myb = g == p ? b[p] : myb;
+        }
+        if (16 + i < myk) y1 = 1.f;
+        if (values) {
+            y0 = values[myb + i];
+            if (16 + i < myk) y1 = values[myb + 16 + i];
+        }
+    }
+    float4 zkeep[RES ? 4 : 1][2][NJ];
+    floatx4 cc[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        float4 zrow[M][NJ];
-        float4 (&z)[M][NJ] = RES ? zkeep[RES ? p : 0] : zrow;
+        float4 zrow[2][NJ];
+        float4 (&z)[2][NJ] = RES ? zkeep[RES ? p : 0] : zrow;
 #pragma unroll
-        for (int t = 0; t < M; ++t) {
-            const int e = 16 * t + a;
+        for (int t = 0; t < 2; ++t) {
             const int32_t id = idv[p][t];
-            if (!RES && q == 0) ids[p * K + e] = id & 0x7fffffff;
-            if (t < M - 1) {  // every row of the class has more than 16 (M - 1) entries: these tiles are full
+            if (!RES && q == 0) ids[p * K + 16 * t + a] = id & 0x7fffffff;
+            if (t == 0) {  // every row of the class has more than 16 entries: this tile is full
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) z[t][j] = load_piece<D, ZB>(Z, id & 0x7fffffff, j, q);
             } else {
@@ -117,151 +176,100 @@ __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indp
                 }
             }
         }
-        SplitOperand zs[M][NJ / 2 > 0 ? NJ / 2 : 1];
-        if constexpr (!ZB && NJ >= 2) {
-#pragma unroll
-            for (int t = 0; t < M; ++t)
-#pragma unroll
-                for (int h = 0; h < NJ / 2; ++h) zs[t][h] = split_operand(z[t][2 * h], z[t][2 * h + 1]);
-        }
+        TileOperand<D, ZB> op[2];
+        op[0].set(z[0]);
+        op[1].set(z[1]);
         __builtin_amdgcn_s_setprio(1);  // matrix-core work first: other wavefronts fill in with vector work
+        const floatx4 zero = floatx4{0.f, 0.f, 0.f, 0.f};
+        floatx4 ca = tile_product<D, ZB>(op[0], op[0], zero);
+        const floatx4 cb = tile_product<D, ZB>(op[0], op[1], zero);
+        cc[p] = tile_product<D, ZB>(op[1], op[1], zero);
+        // ca[v] = A[a][4 q + v], cb[v] = B[a][4 q + v], cc[p][v] = C[a][4 q + v] (A and C are symmetric)
 #pragma unroll
-        for (int t1 = 0; t1 < M; ++t1)
-#pragma unroll
-            for (int t2 = 0; t2 <= t1; ++t2) {
-                floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-                if constexpr (ZB) {  // bf16 rows are matrix-core operands as loaded
-                    acc = mfma_pieces_bf16<NJ>(z[t2], z[t1], acc);
-                } else if constexpr (NJ >= 2) {
-#pragma unroll
-                    for (int h = 0; h < NJ / 2; ++h) acc = split_mfma(zs[t2][h], zs[t1][h], acc);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(z[t2][j].x, z[t1][j].x, acc, 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(z[t2][j].y, z[t1][j].y, acc, 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(z[t2][j].z, z[t1][j].z, acc, 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(z[t2][j].w, z[t1][j].w, acc, 0, 0, 0);
-                    }
-                }
-                // acc[v] = S[Rr][c], Rr = 16*t1 + a, c = 16*t2 + 4q + v (S is symmetric); keep c <= Rr
-                const int Rr = 16 * t1 + a;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int c = 16 * t2 + 4 * q + v;
-                    float *dst = tri + p * TRI + Rr * (Rr + 1) / 2 + c;
-                    if (t2 == t1) dst = c <= Rr ? dst : dump;  // compile-time test: only diagonal tiles have c > Rr
-                    *dst = acc[v] + (c == Rr ? 1.f : 0.f);
-                }
-            }
+        for (int v = 0; v < 4; ++v) {
+            const float one = 4 * q + v == a ? 1.f : 0.f;
+            ca[v] += one;
+            cc[p][v] += one;
+        }
+        *(floatx4 *)(mfma_at + C::OFF_P + p * C::TILE) = ca;
+        *(floatx4 *)(mfma_at + C::OFF_Q + p * C::TILE) = cb;
         __builtin_amdgcn_s_setprio(0);
     }
     wave_sync();
 
-    // ---- 2. elimination, lane i of group g owns rows 16*bk + i of system g
-    float s[M][K], y[M], rpm[M];
-    int myk = 0;
-    int64_t myb = 0;
+    // ---- 2. elimination of the columns of A
+    auto load_row = [&](int off, float (&s)[16]) {
+#pragma unroll
+        for (int c4 = 0; c4 < 4; ++c4) {
+            const float4 v = *(const float4 *)(row_at + off + (4 * c4 ^ swz));
+            s[4 * c4] = v.x; s[4 * c4 + 1] = v.y; s[4 * c4 + 2] = v.z; s[4 * c4 + 3] = v.w;
+        }
+    };
+    float s0[16], s1[16], ri0 = 1.f, ri1 = 1.f;
+    bool bad = false;
+    load_row(C::OFF_P, s0);
+    load_row(C::OFF_Q, s1);
+    dpp_settle(s0[0]);
+    static_for<0, 16>([&](auto ci) { eliminate_column<decltype(ci)::value, true>(s0, s1, y0, y1, ri0, i, bad); });
+
+    // ---- 3. C - L L^T and its elimination
+    wave_sync();  // every lane has read its rows of A
+#pragma unroll
+    for (int c4 = 0; c4 < 4; ++c4)
+        *(float4 *)(row_at + C::OFF_P + (4 * c4 ^ swz)) = make_float4(s1[4 * c4], s1[4 * c4 + 1], s1[4 * c4 + 2], s1[4 * c4 + 3]);
+    wave_sync();
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        myk = g == p ? k[p] : myk;
-        myb = g == p ? b[p] : myb;
-    }
+        // lane (a, q) supplies L[a][4 q + e] to instruction e on both sides: the contraction runs over all 16 columns
+        const floatx4 o = *(const floatx4 *)(mfma_at + C::OFF_P + p * C::TILE);
 #pragma unroll
-    for (int bk = 0; bk < M; ++bk) {
-        const int Rr = 16 * bk + i;
-#pragma unroll
-        for (int c = 0; c < 16 * (bk + 1); ++c) {
-            const float v = tri[g * TRI + Rr * (Rr + 1) / 2 + c];  // c > Rr reads the next row: in range, unused
-            s[bk][c] = (c < 16 * bk || c <= Rr) ? v : 0.f;
-        }
-        y[bk] = 0.f;
-        if (Rr < myk) y[bk] = values ? values[myb + Rr] : 1.f;
-        rpm[bk] = 1.f;
-    }
-    bool bad = false;
-    dpp_settle(s[0][0], s[1][0]);
-    static_for<0, K>([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        constexpr int cb = c / 16, ci = c % 16;
-        if (c < kmax) {  // steps beyond every row's k only meet identity rows
-            const float pivot = bcast16<ci>(s[cb][c]);
-            const float uc = bcast16<ci>(y[cb]);
-            bad |= !(pivot > 0.f);
-            float rp = __builtin_amdgcn_rcpf(pivot);
-            rp = rp * (2.f - pivot * rp);  // one Newton step on the hardware reciprocal
-            float nf[M];  // -M[Rr][c]
-            static_for<cb, M>([&](auto bb) {
-                constexpr int bk = decltype(bb)::value;
-                const int Rr = 16 * bk + i;
-                rpm[bk] = Rr == c ? rp : rpm[bk];
-                nf[bk] = Rr > c ? -(s[bk][c] * rp) : 0.f;  // rows above stay as they are
-                y[bk] += nf[bk] * uc;
-            });
-            // S'[Rr][j] -= M[Rr][c] S'[j][c]: the broadcast of S'[j][c] from the lane that owns row j rides on
-            // the multiply-add (column c is final since the previous step and has settled)
-            static_for<c + 1, K>([&](auto jj) {
-                constexpr int j = decltype(jj)::value;
-                constexpr int jb = j / 16, ji = j % 16;
-                static_for<jb, M>([&](auto bb) {
-                    constexpr int bk = decltype(bb)::value;
-                    fmac_bcast16<ji>(s[bk][j], s[jb][c], nf[bk]);
-                });
-            });
-            if constexpr (c + 1 < K) {  // the next step reads column c + 1 through DPP
-                if constexpr ((c + 1) / 16 == 0) dpp_settle(s[0][c + 1], s[1][c + 1]);
-                else dpp_settle(s[M - 1][c + 1]);
-            }
-        }
-    });
-    if (bad && myk > 0) atomicOr(err_flag, 1);
-
-    // ---- 3. factor back to LDS, read transposed (lt[bk][Rr] = S'[Rr][16*bk + i]), back-substitution
-#pragma unroll
-    for (int bk = 0; bk < M; ++bk) {
-        const int Rr = 16 * bk + i;
-#pragma unroll
-        for (int c = 0; c < 16 * (bk + 1); ++c) {
-            float *dst = tri + g * TRI + Rr * (Rr + 1) / 2 + c;
-            if (c >= 16 * bk) dst = c <= Rr ? dst : dump;
-            *dst = s[bk][c];
-        }
+        for (int e = 0; e < 4; ++e) cc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(-o[e], o[e], cc[p], 0, 0, 0);
     }
     wave_sync();
 #pragma unroll
-    for (int bk = 0; bk < M; ++bk) {
-        const int col = 16 * bk + i;
+    for (int p = 0; p < 4; ++p) *(floatx4 *)(mfma_at + C::OFF_P + p * C::TILE) = cc[p];
+    float bt[16];  // column i of B
 #pragma unroll
-        for (int Rr = 16 * bk; Rr < K; ++Rr) {
-            const float v = tri[g * TRI + Rr * (Rr + 1) / 2 + col];  // col > Rr reads a later row: in range, unused
-            s[bk][Rr] = (Rr >= 16 * (bk + 1) || Rr > col) ? v : 0.f;
-        }
-    }
-    float t[M];
-#pragma unroll
-    for (int bk = 0; bk < M; ++bk) t[bk] = 0.f;
-    static_for<0, K>([&](auto cc) {
-        constexpr int c = K - 1 - decltype(cc)::value;
-        constexpr int cb = c / 16, ci = c % 16;
-        if (c < kmax) {
-            const float tc = bcast16<ci>(y[cb] * rpm[cb]);
-            t[cb] = i == ci ? tc : t[cb];
-            static_for<0, cb + 1>([&](auto bb) {
-                constexpr int bk = decltype(bb)::value;
-                y[bk] -= s[bk][c] * tc;  // zero unless row c lies below column 16*bk + i
-            });
-        }
+    for (int m = 0; m < 16; ++m)
+        bt[m] = lds[C::OFF_Q + g * C::TILE + 16 * m + (((i >> 2) ^ (m >> 1) & 3) << 2) + (i & 3)];
+    wave_sync();
+    load_row(C::OFF_P, s1);
+    dpp_settle(s1[0]);
+    static_for<0, 16>([&](auto ci) {
+        constexpr int c = decltype(ci)::value;
+        float none = 0.f;
+        if (16 + c < kmax) eliminate_column<c, false>(s1, s1, y1, none, ri1, i, bad);  // beyond every row's k: identity rows
     });
+    if (bad) atomicOr(err_flag, 1);
+
+    // ---- 4. t of both halves
+    float t1 = y1 * ri1 * ri1;
+    float za = 0.f, zb = 0.f;
+    dpp_settle(t1);
+    static_for<0, 8>([&](auto mm) {
+        constexpr int m = decltype(mm)::value;
+        fmac_bcast16<2 * m>(za, t1, bt[2 * m]);
+        fmac_bcast16<2 * m + 1>(zb, t1, bt[2 * m + 1]);
+    });
+    za += zb;
+    static_for<0, 16>([&](auto ci) {
+        constexpr int c = decltype(ci)::value;
+        dpp_settle(za);
+        fmac_bcast16_neg<c>(za, za, s0[c]);
+    });
+    const float t0 = (y0 - za) * ri0 * ri0;
     if constexpr (RES) {
-        // ---- 4. r = Z_I^T t from the tiles in registers (zt_times_t, dual_common.h); parts[x][row][e]: part
-        // x of t, x = 3 a block of zeros; the finished rows are staged in the triangle area for 8-byte stores
-        float *parts = lds + C::OFF_PARTS;
+        // ---- 5. r = Z_I^T t from the tiles in registers (zt_times_t, dual_common.h); parts[x][row][e]: part
+        // x of t, x = 3 a block of zeros; the finished rows are staged for 8-byte stores
+        float *parts = lds + C::OFF_P, *dump = parts + 16 * K + lane;
+        wave_sync();  // every lane has read its rows of C and its column of B
 #pragma unroll
-        for (int bk = 0; bk < M; ++bk) {
+        for (int bk = 0; bk < 2; ++bk) {
             float x1, x2;
-            t_parts(t[bk], x1, x2);
+            const float t = bk ? t1 : t0;
+            t_parts(t, x1, x2);
             const int e = g * K + 16 * bk + i;
-            parts[e] = t[bk];
+            parts[e] = t;
             parts[4 * K + e] = x1;
             parts[8 * K + e] = x2;
             parts[12 * K + e] = 0.f;
@@ -269,7 +277,7 @@ __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indp
         const SelOperands sel = make_sel(lane);
         wave_sync();
         const float *mine = parts + (a < 3 ? a : 3) * 4 * K + 4 * q;
-        float *rbuf = tri;
+        float *rbuf = lds + C::OFF_Q;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
             const bf16x8 top[1] = {t_operand(mine + p * K, true)};
@@ -292,66 +300,64 @@ __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indp
         }
         return;
     }
-#pragma unroll
-    for (int bk = 0; bk < M; ++bk) tbuf[g * K + 16 * bk + i] = t[bk];
+    float *tbuf = lds + C::OFF_P;
+    wave_sync();  // every lane has read its row of C
+    tbuf[g * K + i] = t0;
+    tbuf[g * K + 16 + i] = t1;
     wave_sync();
 
-    // ---- 4. r = Z_I^T t (second gather of the row's entries); the four rows advance together, EPR
-    // entries each per round.  Per round: first the ids and t of all rows from LDS with 16-byte reads,
-    // then the loads, then the products - no wait and no lane-dependent branch between two loads.
+    // ---- 5. r = Z_I^T t (second gather of the row's entries): 16 bytes of an entry per lane, so that one instruction takes
+    // GatherCols<D>::EPI entries; the four rows advance together, EPL entries per lane and round.  Per round: first the
+    // ids and t of all rows from LDS, then the loads, then the products - no wait and no lane-dependent branch between
+    // two loads.
     {
-        float r0v[4] = {0.f, 0.f, 0.f, 0.f}, r1v[4] = {0.f, 0.f, 0.f, 0.f};
-        const bool col_ok = lane * CPL < D;
-        const int zlane = col_ok ? lane : 0;  // lanes without a column (d = 32) read column 0
-        // entries per row and round (measured: 16 eight-byte loads in flight are best at d = 128, 32 four-byte
-        // loads at d <= 64)
-        constexpr int EPR = CPL == 2 ? 4 : 8, NQ = EPR / 4;
-        const int kmaxr = (kmax + EPR - 1) / EPR * EPR;  // padded entries have t = 0 and the id of the row's first entry
-        for (int e0 = 0; e0 < kmaxr; e0 += EPR) {
-            int4 idq[4][NQ];
-            float4 teq[4][NQ];
+        using GC = GatherCols<D>;
+        constexpr int EPL = 2, EPR = EPL * GC::EPI;
+        const int mine = EPL * (lane / GC::LPR);
+        const float *col = (const float *)Z + 4 * (lane % GC::LPR);
+        floatx4 rv[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) rv[p] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int e0 = 0; e0 < kmax; e0 += EPR) {  // padded entries have t = 0 and the id of the row's first entry
+            int2 id[4];
+            float2 te[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                id[p] = *(const int2 *)(ids + p * K + e0 + mine);
+                te[p] = *(const float2 *)(tbuf + p * K + e0 + mine);
+            }
+            floatx4 zz[4][EPL];
 #pragma unroll
             for (int p = 0; p < 4; ++p)
-#pragma unroll
-                for (int h = 0; h < NQ; ++h) {
-                    idq[p][h] = *(const int4 *)(ids + p * K + e0 + 4 * h);
-                    teq[p][h] = *(const float4 *)(tbuf + p * K + e0 + 4 * h);
-                }
-            float zz[4][EPR][CPL];
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
                 if (e0 < k[p]) {  // uniform
-#pragma unroll
-                    for (int h = 0; h < NQ; ++h) {
-                        const int id[4] = {idq[p][h].x, idq[p][h].y, idq[p][h].z, idq[p][h].w};
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) {
-                            row_cols<ZB, CPL>((const char *)Z + (int64_t)id[x] * D * ZT<ZB>::ES, zlane, zz[p][4 * h + x]);
-                        }
-                    }
+                    zz[p][0] = *(const floatx4 *)(col + (int64_t)id[p].x * D);
+                    zz[p][1] = *(const floatx4 *)(col + (int64_t)id[p].y * D);
                 }
-            }
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
+            for (int p = 0; p < 4; ++p)
                 if (e0 < k[p]) {
 #pragma unroll
-                    for (int h = 0; h < NQ; ++h) {
-                        const float te[4] = {teq[p][h].x, teq[p][h].y, teq[p][h].z, teq[p][h].w};
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) {
-                            r0v[p] += te[x] * zz[p][4 * h + x][0];
-                            if constexpr (CPL == 2) r1v[p] += te[x] * zz[p][4 * h + x][1];
-                        }
+                    for (int c = 0; c < 4; ++c) {
+                        rv[p][c] += te[p].x * zz[p][0][c];
+                        rv[p][c] += te[p].y * zz[p][1][c];
                     }
                 }
-            }
         }
+        // sums over the lanes that hold the same columns; the rows are spread over the halves (d = 128) or quarters
+        floatx4 lo = swap_add32(rv[0], rv[1]), hi = swap_add32(rv[2], rv[3]);  // lanes 32..63: the second of each pair
+        if constexpr (D == 128) {
+            const bool up = lane >= 32;
+            const int64_t ua = up ? u[1] : u[0], ub = up ? u[3] : u[2];
+            float *dst = R + 4 * (lane & 31);
+            if (ua >= 0) *(floatx4 *)(dst + ua * ldr) = lo;
+            if (ub >= 0) *(floatx4 *)(dst + ub * ldr) = hi;
+        } else {
+            floatx4 r = swap_add16(lo, hi);  // quarters: rows 0, 2, 1, 3
+            if constexpr (D == 32)
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            if (u[p] >= 0 && col_ok) {
-                if constexpr (CPL == 2) *(float2 *)(R + u[p] * ldr + 2 * lane) = make_float2(r0v[p], r1v[p]);
-                else R[u[p] * ldr + lane] = r0v[p];
-            }
+                for (int c = 0; c < 4; ++c) r[c] += __shfl_xor(r[c], 8);
+            const int64_t ur = q == 0 ? u[0] : (q == 1 ? u[2] : (q == 2 ? u[1] : u[3]));
+            if (ur >= 0 && a < GC::LPR) *(floatx4 *)(R + ur * ldr + 4 * a) = r;
         }
     }
 }

@@ -14,7 +14,7 @@ namespace als {
 //      each finished 16x16 tile goes to LDS, where S is kept as a lower triangle.
 //   2./3. Block elimination S = M P M^T and back-substitution by the wavefront (tri_solve.h).
 //   4. r = Z_I^T t: with bf16 Z from the tiles still in registers, on the matrix cores (zt_times_t,
-//      dual_common.h: bf16 entries are exact operands); with fp32 Z with D/64 adjacent output columns per lane,
+//      dual_common.h: bf16 entries are exact operands); with fp32 Z with four adjacent output columns per lane,
 //      gathering the entries a second time (the hi + lo operands kept for S carry z only to 2^-16, which is
 //      enough for S = I + Z Z^T but would show in r).
 template <int D, int KT, bool ZB> constexpr bool wide_resident() { return ZB; }
@@ -164,30 +164,28 @@ __device__ __forceinline__ void dual_wide_step(const int64_t *__restrict__ indpt
         if constexpr (D >= 128) *(float2 *)(R + u * ldr + 2 * lane) = *(const float2 *)(rbuf + 2 * lane);
         else R[u * ldr + lane] = rbuf[lane];
     } else {
-        constexpr int CPL = D / 64;
-        float rv[CPL];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) rv[c] = 0.f;
-        const int kp8 = (k + 7) & ~7;  // padded entries have t = 0 and the id of the row's first entry
-        for (int e0 = 0; e0 < kp8; e0 += 8) {
-            float zz[8][CPL];
+        // 16 bytes of an entry per lane, GatherCols<D>::EPI entries per instruction, four entries per lane and round
+        using GC = GatherCols<D>;
+        const int mine = 4 * (lane / GC::LPR);
+        const float *col = (const float *)Z + 4 * (lane % GC::LPR);
+        floatx4 rv = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int e0 = 0; e0 < k; e0 += 4 * GC::EPI) {  // padded entries have t = 0 and the id of the row's first entry
             // ids and t of the round with 16-byte LDS reads, before the first load is issued
-            const int4 ia = *(const int4 *)(ids + e0), ib = *(const int4 *)(ids + e0 + 4);
-            const float4 ta = *(const float4 *)(tbuf + e0), tb = *(const float4 *)(tbuf + e0 + 4);
-            const int idr[8] = {ia.x, ia.y, ia.z, ia.w, ib.x, ib.y, ib.z, ib.w};
-            const float te[8] = {ta.x, ta.y, ta.z, ta.w, tb.x, tb.y, tb.z, tb.w};
+            const int4 id4 = *(const int4 *)(ids + e0 + mine);
+            const float4 t4 = *(const float4 *)(tbuf + e0 + mine);
+            const int id[4] = {id4.x, id4.y, id4.z, id4.w};
+            const float te[4] = {t4.x, t4.y, t4.z, t4.w};
+            floatx4 zz[4];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int id = idr[i];
-                row_cols<ZB, CPL>((const char *)Z + (int64_t)id * D * ZT<ZB>::ES, lane, zz[i]);
-            }
+            for (int x = 0; x < 4; ++x) zz[x] = *(const floatx4 *)(col + (int64_t)id[x] * D);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int x = 0; x < 4; ++x)
 #pragma unroll
-                for (int c = 0; c < CPL; ++c) rv[c] += te[i] * zz[i][c];
+                for (int c = 0; c < 4; ++c) rv[c] += te[x] * zz[x][c];
         }
-        if constexpr (CPL == 2) *(float2 *)(R + u * ldr + 2 * lane) = make_float2(rv[0], rv[1]);
-        else R[u * ldr + lane] = rv[0];
+        rv = swap_add32(rv, rv);
+        if constexpr (D == 64) rv = swap_add16(rv, rv);
+        if (lane < GC::LPR) *(floatx4 *)(R + u * ldr + 4 * lane) = rv;
     }
 }
 

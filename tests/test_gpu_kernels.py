@@ -467,3 +467,36 @@ def test_topk_on_a_nearly_full_card(gpu_device):
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
     assert c.lib.als_last_error(c.handle) == b""
     c.close()
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("alpha", [0.1, 1e-4])
+def test_rows_of_17_to_32_entries(ctx, gpu_device, d, dtype, alpha):
+    """Both 16-entry tiles of the class at every fill of the second one, steps of the list that are not full, entries that
+    repeat (Z_I Z_I^T is singular then), labels of both signs and zero.  alpha = 1e-4: eigenvalues of S up to 1e4 apart.
+    Tolerance: the products of S carry 2^-16 of |z||z'| (fp32; bf16: Z itself carries 2^-9), so S is off by 2^-16 of its
+    trace at most and t by 2^-16 of S's largest eigenvalue, which is below 1 + k max |z|^2."""
+    say(f"rows of 17 to 32 entries d={d} {dtype} alpha={alpha}")
+    gen = torch.Generator().manual_seed(d + 1)
+    n, lam = 700, 1e-2
+    H = (torch.randn((n, d), generator=gen) * 0.3 / np.sqrt(d)).to(dtype)
+    lens = torch.cat([torch.arange(17, 33), torch.randint(17, 33, (43,), generator=gen), torch.tensor([17, 32, 3])])
+    ptr = torch.zeros(len(lens) + 1, dtype=torch.int64)
+    ptr[1:] = torch.cumsum(lens, 0)
+    idx = torch.randint(0, n, (int(ptr[-1]),), generator=gen).to(torch.int32)
+    idx[ptr[20] + 3:ptr[20] + 17] = idx[ptr[20]]
+    val = torch.randn(int(ptr[-1]), generator=gen)
+    val[ptr[5]:ptr[6]] = 0
+    G = (H.double().T @ H.double()).float()
+    B = alpha * G.double().numpy() + lam * np.eye(d)
+    X = torch.empty((len(lens), d), device=gpu_device, dtype=dtype)
+    als.als_solve_rows(ctx, als.Csr(len(lens), n, ptr.to(gpu_device), idx.to(gpu_device), val.to(gpu_device)), H.to(gpu_device),
+                       G.to(gpu_device), als.make_params(alpha, lam), X)
+    als.als_status_sync(ctx)
+    got, unit = f64(X), 2.0 ** -16 if dtype == torch.float32 else 2.0 ** -9
+    for r in range(len(lens)):
+        v, y = f64(H)[idx[ptr[r]:ptr[r + 1]].numpy()], val[ptr[r]:ptr[r + 1]].double().numpy()
+        ref = np.linalg.solve(B + v.T @ v, v.T @ y)
+        z2 = np.max(np.sum(v * np.linalg.solve(B, v.T).T, axis=1))  # max |z|^2
+        assert np.linalg.norm(got[r] - ref) <= 4 * unit * (1 + len(v) * z2) * np.linalg.norm(ref), (r, len(v))
