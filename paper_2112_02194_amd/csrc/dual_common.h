@@ -22,6 +22,15 @@ template <class T> __device__ __forceinline__ T opaque(T v) {
     asm volatile("" : "+s"(v));
     return v;
 }
+// Pointers by way of an opaque offset of zero: the compiler still knows which memory they point to (a pointer that went through
+// the asm itself is accessed with flat instructions, which wait for LDS and memory alike).
+template <class T> __device__ __forceinline__ T *opaque(T *p) {
+    int zero = 0;
+    asm volatile("" : "+s"(zero));
+    return p + zero;
+}
+__device__ __forceinline__ const void *opaque(const void *p) { return opaque((const char *)p); }
+__device__ __forceinline__ void *opaque(void *p) { return opaque((char *)p); }
 __device__ __forceinline__ int opaque_tid() {
     int lane = threadIdx.x;
     asm volatile("" : "+v"(lane));
@@ -71,6 +80,53 @@ template <int C> __device__ __forceinline__ void fmac_bcast16_neg(float &acc, fl
 }
 __device__ __forceinline__ void dpp_settle(float &a) { asm volatile("s_nop 1" : "+v"(a)); }
 __device__ __forceinline__ void dpp_settle(float &a, float &b) { asm volatile("s_nop 1" : "+v"(a), "+v"(b)); }
+
+// ---------------------------------------------------------------------------------------------- 16 x 16 systems
+// Four 16 x 16 tiles in LDS, one per system of a wavefront.  Rows are sixteen floats without padding; their four blocks of
+// four floats are permuted by the row, so that eight lanes which read or write 16 bytes of eight rows meet in eight different
+// groups of banks.  The tiles lie 16 banks apart for column reads.
+constexpr int TILE_FLOATS = 16 * 16 + 16;
+__device__ __forceinline__ int tile_block(int r, int b) { return 16 * r + ((b ^ (r >> 1) & 3) << 2); }  // block b (columns 4 b ..) of row r
+__device__ __forceinline__ void load_tile_row(const float *row, int i, float (&s)[16]) {  // row i, at `row`
+    const int swz = (i >> 1 & 3) << 2;
+#pragma unroll
+    for (int c4 = 0; c4 < 4; ++c4) {
+        const float4 v = *(const float4 *)(row + (4 * c4 ^ swz));
+        s[4 * c4] = v.x; s[4 * c4 + 1] = v.y; s[4 * c4 + 2] = v.z; s[4 * c4 + 3] = v.w;
+    }
+}
+
+template <int C> __device__ __forceinline__ float bcast16(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + C, 0xf, 0xf, true));
+}
+
+// One step of the eliminations: column c of the lane's row `s` (and of a second row `s2` of the same system, below it) is
+// eliminated; the columns beyond c of all rows but the pivot's are updated.  On return s[c] holds the multiplier of this
+// lane's row (zero in the pivot's), s2[c] the entry of L, and rinv the root of the reciprocal pivot in the pivot's lane.
+template <int c, bool TWO>
+__device__ __forceinline__ void eliminate_column(float (&s)[16], float (&s2)[16], float &y, float &y2, float &rinv, int i, bool &bad) {
+    const float pivot = bcast16<c>(s[c]), uc = bcast16<c>(y);
+    bad |= !(pivot > 0.f);
+    float ri = __builtin_amdgcn_rsqf(pivot);
+    ri = ri * (1.5f - 0.5f * pivot * ri * ri);  // one Newton step on the hardware estimate
+    float l = s[c] * ri, l2 = 0.f;
+    const float own = i == c ? 0.f : l, w = uc * ri;
+    rinv = i == c ? ri : rinv;
+    y -= own * w;
+    if constexpr (TWO) {
+        l2 = s2[c] * ri;
+        y2 -= l2 * w;
+    }
+    dpp_settle(l);  // just written, read through DPP below
+    static_for<c + 1, 16>([&](auto jj) {  // the broadcast of l from the lane that owns row j rides on the multiply-add
+        constexpr int j = decltype(jj)::value;
+        fmac_bcast16_neg<j>(s[j], l, own);
+        if constexpr (TWO) fmac_bcast16_neg<j>(s2[j], l, l2);
+    });
+    s[c] = own * ri;
+    if constexpr (TWO) s2[c] = l2;
+    if constexpr (c + 1 < 16) dpp_settle(s[c + 1]);  // the next step's pivot is read through DPP
+}
 
 // ---------------------------------------------------------------------------------------------- split products
 // S = I + Z_I Z_I^T on the bf16 matrix cores at fp32-like accuracy: every fp32 entry z is cut into
@@ -191,6 +247,65 @@ __device__ __forceinline__ floatx4 swap_add16(floatx4 x, floatx4 y) {
     return r;
 }
 
+// r of four rows from partial sums: lane l holds, for each row, 4 NV columns starting at 4 NV (l % LPR), summed over every
+// 64 / LPR-th entry.  The sums over the lanes with the same columns leave whole rows in the halves (LPR = 32) or quarters of
+// the wavefront, which store them 16 bytes a lane.  u < 0: not stored.
+template <int LPR, int NV>
+__device__ __forceinline__ void store_rows(const floatx4 (&rv)[4][NV], float *R, int64_t ldr, const int64_t (&u)[4], int lane) {
+    const int a = lane & 15, q = lane >> 4;
+    const int64_t u01 = lane >= 32 ? u[1] : u[0], u23 = lane >= 32 ? u[3] : u[2];
+    const int64_t uq = q & 1 ? u23 : u01;
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+        const floatx4 lo = swap_add32(rv[0][n], rv[1][n]), hi = swap_add32(rv[2][n], rv[3][n]);
+        if constexpr (LPR == 32) {
+            float *dst = R + 4 * NV * (lane & 31) + 4 * n;
+            if (u01 >= 0) *(floatx4 *)(dst + u01 * ldr) = lo;
+            if (u23 >= 0) *(floatx4 *)(dst + u23 * ldr) = hi;
+        } else {
+            floatx4 r = swap_add16(lo, hi);  // quarters: rows 0, 2, 1, 3
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if constexpr (LPR <= 8) r[c] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(r[c]), 0x128, 0xf, 0xf, true));  // row_ror:8
+                if constexpr (LPR <= 4) r[c] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(r[c]), 0x124, 0xf, 0xf, true));  // row_ror:4
+            }
+            if (uq >= 0 && a < LPR) *(floatx4 *)(R + uq * ldr + 4 * NV * a + 4 * n) = r;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------- gather through LDS
+// The matrix core wants sixteen different rows of Z in the sixteen lanes a of an operand, and loads that go straight into such
+// an operand touch 64 places of 16 bytes per instruction: the address unit works them off one a clock, which bounds the
+// gathers where Z is cached (the HBM bounds them otherwise).  Here side-by-side lanes load side-by-side 16-byte pieces of a
+// row (LPR lanes a row, EPI rows an instruction, four lanes a clock), and a tile of sixteen rows goes through LDS into the
+// operand layout.  In LDS the pieces of a row are permuted by the row number so that eight lanes that access eight rows meet
+// in eight different groups of banks.
+template <int D, bool ZB> struct RowGather {
+    static constexpr int RB = D * ZT<ZB>::ES, LPR = RB / 16, EPI = 64 / LPR, N = 16 / EPI;  // N instructions per tile
+    static constexpr int STAGE_FLOATS = 16 * RB / 4, ZERO_FLOATS = RB / 4;
+    // entry whose id `lane` holds for bcast_id
+    static __device__ __forceinline__ int id_entry(int lane) {
+        const int s = LPR >= 16 ? lane & (N - 1) : (LPR == 8 ? lane & 1 : 0);
+        return EPI * s + lane / LPR;
+    }
+    // id of the entry that this lane loads a piece of in instruction s of a tile
+    template <int s> static __device__ __forceinline__ int32_t bcast_id(int32_t id) {
+        if constexpr (LPR >= 16) return __builtin_amdgcn_update_dpp(0, id, 0x150 + s, 0xf, 0xf, true);
+        else if constexpr (LPR == 8) return __builtin_amdgcn_update_dpp(0, id, 0x55 * s, 0xf, 0xf, true);  // quad_perm
+        else return id;
+    }
+    static __device__ __forceinline__ int swizzle(int row) { return 16 * (RB >= 128 ? row & 7 : (row >> 1) & 3); }
+    // where this lane's piece of instruction 0 goes (bytes from the stage's start), and the offset of instruction s
+    static __device__ __forceinline__ int put_base(int lane) { return lane / LPR * RB + (16 * (lane % LPR) ^ swizzle(lane / LPR)); }
+    template <int s> static __device__ __forceinline__ int put_at(int base) {
+        return (EPI < 8 ? base ^ (16 * (EPI * s & 7)) : base) + s * EPI * RB;
+    }
+    // where lane (a, q) finds piece 4 j + q of row a
+    static __device__ __forceinline__ int get_base(int a, int q) { return a * RB + (16 * q ^ swizzle(a)); }
+    template <int j> static __device__ __forceinline__ int get_at(int base) { return (j & 1 ? base ^ 64 : base) + 128 * (j >> 1); }
+};
+
 // acc += A B^T over all columns of two entries' bf16 rows held as NP pieces each
 template <int NP> __device__ __forceinline__ floatx4 mfma_pieces_bf16(const float4 (&A)[NP], const float4 (&B)[NP], floatx4 acc) {
 #pragma unroll
@@ -286,11 +401,5 @@ struct WideSolver {
     int iters;
     float tol;
 };
-
-// per-class launchers, one translation unit each (they compile in parallel)
-// (`count_dev`: device address of the list's length; `g`: see StepGrid)
-// `zb16`: Z is stored as bf16
-void launch_dual_k16(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
-                     const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
 
 }  // namespace als

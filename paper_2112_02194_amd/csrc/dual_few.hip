@@ -12,7 +12,7 @@
 namespace als {
 
 template <int D, bool ZB> constexpr int few_lds_floats() {
-    int n = DualCfg<D>::LDS_FLOATS;
+    int n = RowsCfg<D, ZB>::LDS_FLOATS;
     auto take = [&](int x) { n = x > n ? x : n; };
     take(SmallCfg<D, 4>::LDS_FLOATS);
     take(SmallCfg<D, 8>::LDS_FLOATS);

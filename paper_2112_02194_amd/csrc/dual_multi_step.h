@@ -29,16 +29,9 @@ namespace als {
 // half of the power-law rows (d = 128, bf16) takes 41.4 instead of 44.6 ms and one of 10M pages (d = 128, fp32) 7.50 instead
 // of 7.65 ms, the latter 7.15 ms with the 16-byte loads of the second gather; 1M x 1M, d = 64: 705 -> 671 us.
 
-template <int C> __device__ __forceinline__ float bcast16(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + C, 0xf, 0xf, true));
-}
-
-// LDS of one wavefront: two regions of four 16 x 16 tiles (P: A, then L, then C, then t; Q: B), one per system.  Rows are
-// sixteen floats without padding; their four blocks of four floats are permuted by the row (tile_block), so that eight lanes
-// which read or write 16 bytes of eight rows meet in eight different groups of banks.  The tiles of two systems lie 16
-// banks apart for the column reads of step 4.
+// LDS of one wavefront: two regions of four 16 x 16 tiles (P: A, then L, then C, then t; Q: B), one per system.
 struct MultiCfg {
-    static constexpr int K = 32, TILE = 16 * 16 + 16, REGION = 4 * TILE;
+    static constexpr int K = 32, TILE = TILE_FLOATS, REGION = 4 * TILE;
     static constexpr int OFF_P = 0, OFF_Q = REGION, OFF_ID = 2 * REGION;
     static constexpr int LDS_FLOATS = OFF_ID + 4 * K;  // ids of the second gather
     // bf16 Z: t cut into three bf16 parts plus a block of zeros, [4][4 rows][K], and the lanes' dump slots in P; the
@@ -46,40 +39,9 @@ struct MultiCfg {
     static constexpr int LDS_FLOATS_RESIDENT = 2 * REGION;
     static_assert(REGION >= 16 * K + 64 && REGION >= 4 * 128, "P and Q hold what step 5 stages");
 };
-// offset of block b (columns 4 b .. 4 b + 3) of row r inside a tile
-__device__ __forceinline__ int tile_block(int r, int b) { return 16 * r + ((b ^ (r >> 1) & 3) << 2); }
-
 // bf16 Z: the gathered tiles stay in registers (4 rows x 2 tiles x D/32 operands of four registers) until r = Z_I^T t is
 // formed from them on the matrix cores, so nothing is gathered twice.
 template <bool ZB> constexpr bool multi_resident() { return ZB; }
-
-// One step of the eliminations: column c of the lane's row `s` (and of a second row `s2` of the same system, below it) is
-// eliminated; the columns beyond c of all rows but the pivot's are updated.  On return s[c] holds the multiplier of this
-// lane's row (zero in the pivot's), s2[c] the entry of L, and rinv the root of the reciprocal pivot in the pivot's lane.
-template <int c, bool TWO>
-__device__ __forceinline__ void eliminate_column(float (&s)[16], float (&s2)[16], float &y, float &y2, float &rinv, int i, bool &bad) {
-    const float pivot = bcast16<c>(s[c]), uc = bcast16<c>(y);
-    bad |= !(pivot > 0.f);
-    float ri = __builtin_amdgcn_rsqf(pivot);
-    ri = ri * (1.5f - 0.5f * pivot * ri * ri);  // one Newton step on the hardware estimate
-    float l = s[c] * ri, l2 = 0.f;
-    const float own = i == c ? 0.f : l, w = uc * ri;
-    rinv = i == c ? ri : rinv;
-    y -= own * w;
-    if constexpr (TWO) {
-        l2 = s2[c] * ri;
-        y2 -= l2 * w;
-    }
-    dpp_settle(l);  // just written, read through DPP below
-    static_for<c + 1, 16>([&](auto jj) {  // the broadcast of l from the lane that owns row j rides on the multiply-add
-        constexpr int j = decltype(jj)::value;
-        fmac_bcast16_neg<j>(s[j], l, own);
-        if constexpr (TWO) fmac_bcast16_neg<j>(s2[j], l, l2);
-    });
-    s[c] = own * ri;
-    if constexpr (TWO) s2[c] = l2;
-    if constexpr (c + 1 < 16) dpp_settle(s[c + 1]);  // the next step's pivot is read through DPP
-}
 
 // One step: the four rows list[4 blk .. 4 blk + 3] (blk * 4 < count).
 template <int D, bool ZB>
@@ -198,17 +160,10 @@ __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indp
     wave_sync();
 
     // ---- 2. elimination of the columns of A
-    auto load_row = [&](int off, float (&s)[16]) {
-#pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) {
-            const float4 v = *(const float4 *)(row_at + off + (4 * c4 ^ swz));
-            s[4 * c4] = v.x; s[4 * c4 + 1] = v.y; s[4 * c4 + 2] = v.z; s[4 * c4 + 3] = v.w;
-        }
-    };
     float s0[16], s1[16], ri0 = 1.f, ri1 = 1.f;
     bool bad = false;
-    load_row(C::OFF_P, s0);
-    load_row(C::OFF_Q, s1);
+    load_tile_row(row_at + C::OFF_P, i, s0);
+    load_tile_row(row_at + C::OFF_Q, i, s1);
     dpp_settle(s0[0]);
     static_for<0, 16>([&](auto ci) { eliminate_column<decltype(ci)::value, true>(s0, s1, y0, y1, ri0, i, bad); });
 
@@ -233,7 +188,7 @@ __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indp
     for (int m = 0; m < 16; ++m)
         bt[m] = lds[C::OFF_Q + g * C::TILE + 16 * m + (((i >> 2) ^ (m >> 1) & 3) << 2) + (i & 3)];
     wave_sync();
-    load_row(C::OFF_P, s1);
+    load_tile_row(row_at + C::OFF_P, i, s1);
     dpp_settle(s1[0]);
     static_for<0, 16>([&](auto ci) {
         constexpr int c = decltype(ci)::value;
@@ -315,9 +270,9 @@ __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indp
         constexpr int EPL = 2, EPR = EPL * GC::EPI;
         const int mine = EPL * (lane / GC::LPR);
         const float *col = (const float *)Z + 4 * (lane % GC::LPR);
-        floatx4 rv[4];
+        floatx4 rv[4][1];
 #pragma unroll
-        for (int p = 0; p < 4; ++p) rv[p] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int p = 0; p < 4; ++p) rv[p][0] = floatx4{0.f, 0.f, 0.f, 0.f};
         for (int e0 = 0; e0 < kmax; e0 += EPR) {  // padded entries have t = 0 and the id of the row's first entry
             int2 id[4];
             float2 te[4];
@@ -338,27 +293,12 @@ __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indp
                 if (e0 < k[p]) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        rv[p][c] += te[p].x * zz[p][0][c];
-                        rv[p][c] += te[p].y * zz[p][1][c];
+                        rv[p][0][c] += te[p].x * zz[p][0][c];
+                        rv[p][0][c] += te[p].y * zz[p][1][c];
                     }
                 }
         }
-        // sums over the lanes that hold the same columns; the rows are spread over the halves (d = 128) or quarters
-        floatx4 lo = swap_add32(rv[0], rv[1]), hi = swap_add32(rv[2], rv[3]);  // lanes 32..63: the second of each pair
-        if constexpr (D == 128) {
-            const bool up = lane >= 32;
-            const int64_t ua = up ? u[1] : u[0], ub = up ? u[3] : u[2];
-            float *dst = R + 4 * (lane & 31);
-            if (ua >= 0) *(floatx4 *)(dst + ua * ldr) = lo;
-            if (ub >= 0) *(floatx4 *)(dst + ub * ldr) = hi;
-        } else {
-            floatx4 r = swap_add16(lo, hi);  // quarters: rows 0, 2, 1, 3
-            if constexpr (D == 32)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) r[c] += __shfl_xor(r[c], 8);
-            const int64_t ur = q == 0 ? u[0] : (q == 1 ? u[2] : (q == 2 ? u[1] : u[3]));
-            if (ur >= 0 && a < GC::LPR) *(floatx4 *)(R + ur * ldr + 4 * a) = r;
-        }
+        store_rows<GC::LPR>(rv, R, ldr, u, lane);
     }
 }
 

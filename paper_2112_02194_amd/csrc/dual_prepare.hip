@@ -14,13 +14,14 @@
 //                     operand registers, form S = I + Z_I Z_I^T on the matrix cores, solve the k x k
 //                     system on the vector ALU, then r = Z_I^T t
 //       dual_small_kernel  k <= 4 and 5 <= k <= 8: several rows share one 16-entry MFMA tile
-//       dual_rows_kernel   8 < k <= 16: four rows per wavefront, one lane per row of S, DPP broadcasts
-//       dual_multi_kernel  16 < k <= 32: four rows per wavefront, two rows of S per lane, DPP only
+//       dual_rows_kernel   8 < k <= 16: four rows per wavefront, one lane per row of S, gather through LDS
+//       dual_multi_kernel  16 < k <= 32: four rows per wavefront, S in two blocks of 16
 //       dual_wide_kernel   32 < k <= 128 (d >= 64; k <= 64 at d = 64): one row per wavefront, S as a
 //                          lower triangle in LDS, blocked elimination with MFMA trailing updates
 //   transform_kernel  X = R L^{-1}   (rows r -> L^{-T} r), rounding to the table's element type
 #include "dual_common.h"
 #include "dual_few.h"
+#include "dual_walk.h"
 
 namespace als {
 
@@ -28,6 +29,9 @@ void launch_dual_small4(int d, const als_csr *Y, const void *Z, bool zb16, float
                         const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
 void launch_dual_small8(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
                         const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
+// per-class launchers (`count_dev`: device address of the list's length; `g`, `w`: see StepGrid, WalkSize; `zb16`: Z is bf16)
+void launch_dual_k16(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
+                     const int32_t *list, const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
 void launch_dual_multi2(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
                         const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
 #define ALS_DECL_WIDE(kt)                                                                                          \
@@ -602,6 +606,9 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
         const int64_t hint = hints[cls] < 0 ? -1 : ((int64_t)hints[cls] + rpw - 1) / rpw;
         return step_grid(ctx->num_cu, 64, cap, hint, 32, rpw > 1 ? 1 << 24 : 1 << 22);  // one wavefront per workgroup
     };
+    auto walk = [&](int cls, int rpw) {
+        return WalkSize{ctx->num_cu, (caps[cls] + rpw - 1) / rpw, hints[cls] < 0 ? -1 : ((int64_t)hints[cls] + rpw - 1) / rpw};
+    };
 #define ALS_TIMED_CLASS(slot, cls, rpw, call)           \
     if (caps[cls] > 0 && stb == ALS_OK) {               \
         const StepGrid g = grid(cls, rpw);              \
@@ -637,7 +644,7 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
         ALS_TIMED_CLASS(T_SMALL4, 8, 1, (stb = launch_dual_wide3(ctx, D, Y, Z, zb16, R, ldr, r0, lists[8], counts_dev[8], g, err, ws, s)))
     } else {
     ALS_TIMED_CLASS(T_DUAL_CLASS0 + 1, 1, 4, (launch_dual_multi2(D, Y, Z, zb16, R, ldr, r0, lists[1], counts_dev[1], g, err, s)))
-    ALS_TIMED_CLASS(T_DUAL_CLASS0, 0, 4, (launch_dual_k16(D, Y, Z, zb16, R, ldr, r0, lists[0], counts_dev[0], g, err, s)))
+    ALS_TIMED_CLASS(T_DUAL_CLASS0, 0, 4, (launch_dual_k16(D, Y, Z, zb16, R, ldr, r0, lists[0], counts_dev[0], walk(0, 4), err, s)))
     // 5 <= k <= 8 and k <= 4: several rows per MFMA tile
     ALS_TIMED_CLASS(T_SMALL8, 9, 8, (launch_dual_small8(D, Y, Z, zb16, R, ldr, r0, lists[9], counts_dev[9], g, err, s)))
     ALS_TIMED_CLASS(T_SMALL4, 8, 16, (launch_dual_small4(D, Y, Z, zb16, R, ldr, r0, lists[8], counts_dev[8], g, err, s)))

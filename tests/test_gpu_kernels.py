@@ -469,23 +469,23 @@ def test_topk_on_a_nearly_full_card(gpu_device):
     c.close()
 
 
-@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("d,lo,hi", [(16, 9, 16), (32, 9, 16), (64, 9, 16), (128, 9, 16), (32, 17, 32), (64, 17, 32), (128, 17, 32)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("alpha", [0.1, 1e-4])
-def test_rows_of_17_to_32_entries(ctx, gpu_device, d, dtype, alpha):
-    """Both 16-entry tiles of the class at every fill of the second one, steps of the list that are not full, entries that
+def test_rows_of_9_to_32_entries(ctx, gpu_device, d, lo, hi, dtype, alpha):
+    """The 16-entry tiles of the two classes at every fill, steps of the list that are not full, entries that
     repeat (Z_I Z_I^T is singular then), labels of both signs and zero.  alpha = 1e-4: eigenvalues of S up to 1e4 apart.
     Tolerance: the products of S carry 2^-16 of |z||z'| (fp32; bf16: Z itself carries 2^-9), so S is off by 2^-16 of its
     trace at most and t by 2^-16 of S's largest eigenvalue, which is below 1 + k max |z|^2."""
-    say(f"rows of 17 to 32 entries d={d} {dtype} alpha={alpha}")
+    say(f"rows of {lo} to {hi} entries d={d} {dtype} alpha={alpha}")
     gen = torch.Generator().manual_seed(d + 1)
     n, lam = 700, 1e-2
     H = (torch.randn((n, d), generator=gen) * 0.3 / np.sqrt(d)).to(dtype)
-    lens = torch.cat([torch.arange(17, 33), torch.randint(17, 33, (43,), generator=gen), torch.tensor([17, 32, 3])])
+    lens = torch.cat([torch.arange(lo, hi + 1), torch.randint(lo, hi + 1, (43,), generator=gen), torch.tensor([lo, hi, 3])])
     ptr = torch.zeros(len(lens) + 1, dtype=torch.int64)
     ptr[1:] = torch.cumsum(lens, 0)
     idx = torch.randint(0, n, (int(ptr[-1]),), generator=gen).to(torch.int32)
-    idx[ptr[20] + 3:ptr[20] + 17] = idx[ptr[20]]
+    idx[ptr[20] + 3:ptr[20] + lo] = idx[ptr[20]]
     val = torch.randn(int(ptr[-1]), generator=gen)
     val[ptr[5]:ptr[6]] = 0
     G = (H.double().T @ H.double()).float()

@@ -15,8 +15,11 @@ def step_grid(tmp_path_factory):
     src.write_text('#include "launch_size.h"\n'
                    'extern "C" void grid(int cu, int threads, int64_t cap, int64_t hint, int per_cu, int64_t blind, unsigned *out) {\n'
                    '    const als::StepGrid g = als::step_grid(cu, threads, cap, hint, per_cu, blind); out[0] = g.known; out[1] = g.rest; }\n'
+                   'extern "C" unsigned walk(int64_t resident, int64_t cap, int64_t hint) { return als::walk_grid(resident, cap, hint); }\n'
                    'extern "C" int xcd(int b, int grid, int steps) { return als::xcd_step(b, grid, steps); }\n')
     subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, "-o", str(lib), str(src)])
+    walk_grid.f = ctypes.CDLL(str(lib)).walk
+    walk_grid.f.argtypes, walk_grid.f.restype = [ctypes.c_int64] * 3, ctypes.c_uint
     xcd.f = ctypes.CDLL(str(lib)).xcd
     f = ctypes.CDLL(str(lib)).grid
     f.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_void_p]
@@ -30,6 +33,10 @@ def step_grid(tmp_path_factory):
 
 def xcd(b, grid, steps):
     return xcd.f(b, grid, steps)
+
+
+def walk_grid(resident, cap, hint):
+    return walk_grid.f(resident, cap, hint)
 
 
 SIZES = [0, 1, 4095, 4096, 4097, 100_000, (1 << 24) - 1, 1 << 24, 25_000_000, 50_000_000, (1 << 26) - 1, 1 << 26, (1 << 31) - 1]
@@ -68,3 +75,13 @@ def test_steps_are_dealt_out_once_each_in_eight_parts(step_grid, grid):
         for die in range(8):  # what one die gets of the divisible part is contiguous and in order
             part = [s for s in order[die::8] if s < min(steps, grid) // 8 * 8]
             assert part == list(range(part[0], part[0] + len(part))) if part else True
+
+
+def test_a_walked_list_gets_enough_workgroups_and_no_more_than_a_launch_holds(step_grid):
+    for cap in SIZES[1:]:
+        for hint in [-1] + SIZES:
+            g = walk_grid(3072, cap, hint)
+            assert g % 8 == 0 and g > 0 and g * 64 < 1 << 32
+            steps = cap if hint < 0 else min(cap, hint)
+            assert g >= min(cap, 3072) and (g >= steps / 4 or g * 64 >= (1 << 32) - 512)  # at most four steps each, if a launch can hold that
+            assert g <= max(steps / 4, min(cap, 3072)) + 8
