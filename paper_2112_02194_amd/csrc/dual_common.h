@@ -281,29 +281,32 @@ __device__ __forceinline__ void store_rows(const floatx4 (&rv)[4][NV], float *R,
 // row (LPR lanes a row, EPI rows an instruction, four lanes a clock), and a tile of sixteen rows goes through LDS into the
 // operand layout.  In LDS the pieces of a row are permuted by the row number so that eight lanes that access eight rows meet
 // in eight different groups of banks.
-template <int D, bool ZB> struct RowGather {
-    static constexpr int RB = D * ZT<ZB>::ES, LPR = RB / 16, EPI = 64 / LPR, N = 16 / EPI;  // N instructions per tile
-    static constexpr int STAGE_FLOATS = 16 * RB / 4, ZERO_FLOATS = RB / 4;
-    // entry whose id `lane` holds for bcast_id
-    static __device__ __forceinline__ int id_entry(int lane) {
-        const int s = LPR >= 16 ? lane & (N - 1) : (LPR == 8 ? lane & 1 : 0);
-        return EPI * s + lane / LPR;
+template <int CB> struct PieceGather {  // CB: bytes of a row that go through the stage at a time
+    static constexpr int LPR = CB / 16, EPI = 64 / LPR, N = 16 / EPI;  // N instructions per tile
+    static constexpr int STAGE_FLOATS = 16 * CB / 4, ZERO_FLOATS = CB / 4;
+    // instructions (of the same or the next tile) whose ids one register can hold, spread over the lanes for bcast_id
+    static constexpr int IDS = LPR >= 16 ? 16 : (LPR == 8 ? 4 : 1);
+    // entry of which `lane` holds the id, counted from the first of the register's first `used` instructions
+    static __device__ __forceinline__ int id_entry(int lane, int used = N) {
+        return EPI * (lane & (IDS - 1) & (used - 1)) + lane / LPR;  // used: a power of two
     }
-    // id of the entry that this lane loads a piece of in instruction s of a tile
+    // id of the entry that this lane loads a piece of in the register's instruction s
     template <int s> static __device__ __forceinline__ int32_t bcast_id(int32_t id) {
         if constexpr (LPR >= 16) return __builtin_amdgcn_update_dpp(0, id, 0x150 + s, 0xf, 0xf, true);
         else if constexpr (LPR == 8) return __builtin_amdgcn_update_dpp(0, id, 0x55 * s, 0xf, 0xf, true);  // quad_perm
         else return id;
     }
-    static __device__ __forceinline__ int swizzle(int row) { return 16 * (RB >= 128 ? row & 7 : (row >> 1) & 3); }
+    static __device__ __forceinline__ int swizzle(int row) { return 16 * (CB >= 128 ? row & 7 : (row >> 1) & 3); }
     // where this lane's piece of instruction 0 goes (bytes from the stage's start), and the offset of instruction s
-    static __device__ __forceinline__ int put_base(int lane) { return lane / LPR * RB + (16 * (lane % LPR) ^ swizzle(lane / LPR)); }
+    static __device__ __forceinline__ int put_base(int lane) { return lane / LPR * CB + (16 * (lane % LPR) ^ swizzle(lane / LPR)); }
     template <int s> static __device__ __forceinline__ int put_at(int base) {
-        return (EPI < 8 ? base ^ (16 * (EPI * s & 7)) : base) + s * EPI * RB;
+        return (EPI < 8 ? base ^ (16 * (EPI * s & 7)) : base) + s * EPI * CB;
     }
-    // where lane (a, q) finds piece 4 j + q of row a
-    static __device__ __forceinline__ int get_base(int a, int q) { return a * RB + (16 * q ^ swizzle(a)); }
-    template <int j> static __device__ __forceinline__ int get_at(int base) { return (j & 1 ? base ^ 64 : base) + 128 * (j >> 1); }
+    // where lane (a, q) finds piece 4 j + q of row a; pieces with odd j: ^ 64, two pieces on: + 128
+    static __device__ __forceinline__ int get_base(int a, int q) { return a * CB + (16 * q ^ swizzle(a)); }
+};
+template <int D, bool ZB> struct RowGather : PieceGather<D * ZT<ZB>::ES> {
+    static constexpr int RB = D * ZT<ZB>::ES;
 };
 
 // acc += A B^T over all columns of two entries' bf16 rows held as NP pieces each

@@ -16,7 +16,7 @@ template <int D, bool ZB> constexpr int few_lds_floats() {
     auto take = [&](int x) { n = x > n ? x : n; };
     take(SmallCfg<D, 4>::LDS_FLOATS);
     take(SmallCfg<D, 8>::LDS_FLOATS);
-    if constexpr (D >= 32) take(multi_resident<ZB>() ? MultiCfg::LDS_FLOATS_RESIDENT : MultiCfg::LDS_FLOATS);
+    if constexpr (D >= 32) take(MultiCfg<D, ZB>::LDS_FLOATS);
     if constexpr (D == 64) take(WideCfg<D, 4>::LDS_FLOATS);
     if constexpr (D == 128) take(WideCfg<D, 8>::LDS_FLOATS);
     return n;

@@ -2,7 +2,7 @@
 // dual_prepare.hip.
 #pragma once
 
-#include "dual_common.h"
+#include "dual_walk.h"
 
 namespace als {
 
@@ -19,287 +19,334 @@ namespace als {
 //      elimination give t of the entries 16..31;
 //   4. t of the entries 0..15: B^T t (columns of B from LDS, t as a DPP operand), the row operations of step 2 once more
 //      on that vector (their multipliers were left where the eliminated columns were), and the pivots;
-//   5. r = Z_I^T t: bf16 Z from the tiles in registers on the matrix cores; fp32 Z with one lane per group
-//      of four output columns, gathering the entries a second time.
-// What bounds it: bf16 Z (50M power-law rows): the instructions of two wavefronts per SIMD, one every five clocks each, and
-// the latency of the gather; fp32 Z whose rows meet in the caches: the address unit, which takes a clock per lane of the
-// first gather (sixteen rows per instruction, 64 clocks), 94% busy on 10M pages of locality.
-// Against an elimination of all 32 columns with a triangular back-substitution through LDS (616 multiply-adds with a DPP
-// operand, 392 here; LDS accesses of 4 bytes with a select each, 16 bytes here; 3 219 instructions per step, 2 373 here) a
-// half of the power-law rows (d = 128, bf16) takes 41.4 instead of 44.6 ms and one of 10M pages (d = 128, fp32) 7.50 instead
-// of 7.65 ms, the latter 7.15 ms with the 16-byte loads of the second gather; 1M x 1M, d = 64: 705 -> 671 us.
+//   5. r = Z_I^T t, four (bf16: eight) columns per lane, from the registers of step 1, or (fp32, d = 128, whose tiles do not fit
+//      the registers) gathering the entries a second time.
+// Every row goes through LDS into the operand layout (PieceGather), and the walk over the list loads the next step's ids ahead
+// (dual_walk.h).
+// What bounds it: HBM and the instructions of two wavefronts per SIMD, one every five clocks each, where the tiles stay in
+// registers; with a second gather (fp32, d = 128) the latency of about twelve rounds of loads at three wavefronts per SIMD.
+// Per half, an elimination of all 32 columns in one block with a triangular back-substitution (616 multiply-adds with a DPP
+// operand, 392 here) / this one with loads straight into the operand layout, 64 places per instruction / as it is:
+//   50M power-law rows, bf16, d = 128  44.6 / 41.4 / 36.5 ms      10M pages, fp32, d = 128  8.12 / 7.05 / 6.35 ms
+//   1M x 1M, fp32, d = 64 (second gather before)  705 / 671 / 525 us      300k rows, bf16, d = 128  129 / 115 / 107 us
 
-// LDS of one wavefront: two regions of four 16 x 16 tiles (P: A, then L, then C, then t; Q: B), one per system.
-struct MultiCfg {
-    static constexpr int K = 32, TILE = TILE_FLOATS, REGION = 4 * TILE;
-    static constexpr int OFF_P = 0, OFF_Q = REGION, OFF_ID = 2 * REGION;
-    static constexpr int LDS_FLOATS = OFF_ID + 4 * K;  // ids of the second gather
-    // bf16 Z: t cut into three bf16 parts plus a block of zeros, [4][4 rows][K], and the lanes' dump slots in P; the
-    // finished rows of r in Q
-    static constexpr int LDS_FLOATS_RESIDENT = 2 * REGION;
-    static_assert(REGION >= 16 * K + 64 && REGION >= 4 * 128, "P and Q hold what step 5 stages");
+// LDS of one wavefront: P holds four 16 x 16 tiles (A, then L, then C, then t), U the stage of two tiles of entries and later
+// four tiles again (B); a block of zeros for slots beyond a row's k, the ids of the second gather.
+template <int D, bool ZB> struct MultiCfg {
+    static constexpr int RB = D * ZT<ZB>::ES, CB = RB < 256 ? RB : 256, NCH = RB / CB;
+    using PG = PieceGather<CB>;
+    static constexpr int K = 32, TILE = TILE_FLOATS;
+    static constexpr int OFF_P = 0, OFF_Q = 4 * TILE, U = 2 * PG::STAGE_FLOATS > 4 * TILE ? 2 * PG::STAGE_FLOATS : 4 * TILE;
+    static constexpr int OFF_ZERO = OFF_Q + U, OFF_ID = OFF_ZERO + PG::ZERO_FLOATS;
+    // what is loaded at a time: the chunk h of both tiles of row p is unit p * NCH + h.  Rows of up to 256 bytes: all units are
+    // loaded at once (128 registers at most) and stay in registers until r = Z_I^T t is formed from them, so nothing is gathered
+    // twice.  Longer ones (fp32, d = 128): two units are under way.
+    static constexpr bool RES = NCH == 1;
+    static constexpr int UNITS = 4 * NCH, DEPTH = RES ? UNITS : 2;
+    static constexpr int LDS_FLOATS = OFF_ID + (RES ? 0 : 4 * K);
+    static constexpr int IDR = 2 * PG::N <= PG::IDS ? 1 : 2;  // id registers per row
 };
-// bf16 Z: the gathered tiles stay in registers (4 rows x 2 tiles x D/32 operands of four registers) until r = Z_I^T t is
-// formed from them on the matrix cores, so nothing is gathered twice.
-template <bool ZB> constexpr bool multi_resident() { return ZB; }
 
-// One step: the four rows list[4 blk .. 4 blk + 3] (blk * 4 < count).
+// (the members are what walk_steps and single_step want, see dual_walk.h)
+template <int D, bool ZB> struct MultiStep {
+    using C = MultiCfg<D, ZB>;
+    using PG = typename C::PG;
+    static constexpr int NIDS = 4 * C::IDR, N = PG::N, EPI = PG::EPI;
+
+    static __device__ __forceinline__ void init(float *lds, int lane) {
+        if (lane < PG::ZERO_FLOATS) lds[C::OFF_ZERO + lane] = 0.f;
+        static_assert(PG::ZERO_FLOATS <= 64, "one store a lane");
+        wave_sync();
+    }
+    static __device__ __forceinline__ int id_entry(int lane, int r) { return C::IDR == 1 ? PG::id_entry(lane, 2 * N) : 16 * r + PG::id_entry(lane); }
+    static __device__ __forceinline__ void ids(const int32_t *__restrict__ indices, const RowsDesc &d, int lane, int32_t (&idv)[NIDS]) {
+#pragma unroll
+        for (int n = 0; n < NIDS; ++n) {
+            const int p = n / C::IDR, e = id_entry(lane, n % C::IDR);
+            idv[n] = indices[d.b[p] + (e < d.k[p] ? e : 0)];  // clamped: a slot beyond k holds the row's first entry
+        }
+    }
+
+    template <class Loaded, class Between, class Last>
+    static __device__ __forceinline__ void solve(const float *__restrict__ values, const void *__restrict__ Z, float *__restrict__ R,
+                                                 int64_t ldr, int32_t *__restrict__ err_flag, float *lds, const RowsDesc &d,
+                                                 const int32_t (&idv)[NIDS], Loaded &&loaded, Between &&between, Last &&last) {
+        constexpr int K = C::K;
+        const int (&k)[4] = d.k;
+        int kmax = 0;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) kmax = k[p] > kmax ? k[p] : kmax;
+
+        // ---- 1. gather and the tiles of S
+        floatx4 z[C::DEPTH][2][N];  // (a float4 would be copied by way of scratch memory)
+        const char *zlane = (const char *)Z + 16 * (opaque_tid() % PG::LPR);
+        auto load = [&](auto uu) {
+            constexpr int unit = decltype(uu)::value, p = unit / C::NCH, h = unit % C::NCH;
+            static_for<0, 2>([&](auto tt) {
+                static_for<0, N>([&](auto ss) {
+                    constexpr int t = decltype(tt)::value, s = decltype(ss)::value;
+                    // instructions that only meet slots beyond the row's k are left out (the first tile is full: k > 16)
+                    if (t == 0 || 16 + s * EPI < k[p]) {
+                        const int32_t id = C::IDR == 1 ? PG::template bcast_id<t * N + s>(idv[p]) : PG::template bcast_id<s>(idv[2 * p + t]);
+                        z[unit % C::DEPTH][t][s] = *(const floatx4 *)(zlane + (int64_t)id * C::RB + h * C::CB);
+                    }
+                });
+            });
+        };
+        static_for<0, C::DEPTH>(load);
+        loaded();
+        const int lane = opaque_tid();  // after the loads: what derives from it is not kept across them
+        const int a = lane & 15, q = lane >> 4;  // MFMA view: entry a of a tile, column group q
+        const int g = lane >> 4, i = lane & 15;  // solver view: system g, lane i of its group
+        // labels of the entries i and 16 + i of this lane's system
+        float y0 = 0.f, y1 = 0.f;
+        {
+            int myk = 0;
+            int64_t myb = 0;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                myk = g == p ? k[p] : myk;
+                myb = g == p ? d.b[p] : myb;
+            }
+            y0 = i < myk ? 1.f : 0.f;
+            y1 = 16 + i < myk ? 1.f : 0.f;
+            if (values) {
+                int at = i;
+                asm volatile("" : "+v"(at));  // no zero-extended copy of i across the step
+                if (i < myk) y0 = values[myb + at];
+                if (16 + i < myk) y1 = values[myb + at + 16];
+            }
+        }
+        if constexpr (!C::RES) {
+            int32_t *idl = (int32_t *)(lds + C::OFF_ID);
+#pragma unroll
+            for (int n = 0; n < NIDS; ++n) idl[n / C::IDR * K + id_entry(lane, n % C::IDR)] = idv[n];
+        }
+        float *mfma_at = lds + tile_block(a, q);     // MFMA view: row a, columns 4 q .. of the first system's tile
+        char *stage = (char *)(lds + C::OFF_Q);
+        floatx4 cb[4], cc[4];
+        static_for<0, 4>([&](auto pp) {
+            constexpr int p = decltype(pp)::value;
+            const floatx4 zero4 = floatx4{0.f, 0.f, 0.f, 0.f};
+            floatx4 ca = zero4;
+            cb[p] = zero4;
+            cc[p] = zero4;
+            static_for<0, C::NCH>([&](auto hh) {
+                constexpr int unit = p * C::NCH + decltype(hh)::value;
+                // what derives from the lane is formed again for each unit rather than kept
+                const int lane = opaque_tid(), a = lane & 15, q = lane >> 4;
+                const int put = PG::put_base(lane), get = PG::get_base(a, q);
+                static_for<0, 2>([&](auto tt) {
+                    static_for<0, N>([&](auto ss) {
+                        constexpr int t = decltype(tt)::value, s = decltype(ss)::value;
+                        if (t == 0 || 16 + s * EPI < k[p])
+                            *(floatx4 *)(stage + t * 16 * C::CB + PG::template put_at<s>(put)) = z[unit % C::DEPTH][t][s];
+                    });
+                });
+                wave_sync();
+                if constexpr (unit + C::DEPTH < C::UNITS) load(std::integral_constant<int, unit + C::DEPTH>{});
+                // slots of the second tile beyond the row's k read zeros
+                const bool have = 16 + a < k[p];
+                const char *const zero = (const char *)(lds + C::OFF_ZERO);
+                const char *at0[2] = {stage + get, stage + (get ^ 64)};
+                const char *at1[2] = {have ? stage + 16 * C::CB + get : zero, have ? stage + 16 * C::CB + (get ^ 64) : zero};
+                __builtin_amdgcn_s_setprio(1);  // matrix-core work first: other wavefronts fill in with vector work
+                if constexpr (ZB) {
+#pragma unroll
+                    for (int j = 0; j < N; ++j) {
+                        const bf16x8 o0 = *(const bf16x8 *)(at0[j & 1] + 128 * (j >> 1)), o1 = *(const bf16x8 *)(at1[j & 1] + 128 * (j >> 1));
+                        ca = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o0, o0, ca, 0, 0, 0);
+                        cb[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o0, o1, cb[p], 0, 0, 0);
+                        cc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o1, o1, cc[p], 0, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < N; j += 2) {
+                        const SplitOperand o0 = split_operand(*(const float4 *)(at0[0] + 64 * j), *(const float4 *)(at0[1] + 64 * j));
+                        const SplitOperand o1 = split_operand(*(const float4 *)(at1[0] + 64 * j), *(const float4 *)(at1[1] + 64 * j));
+                        ca = split_mfma(o0, o0, ca);
+                        cb[p] = split_mfma(o0, o1, cb[p]);
+                        cc[p] = split_mfma(o1, o1, cc[p]);
+                    }
+                }
+                __builtin_amdgcn_s_setprio(0);
+                wave_sync();  // the next unit reuses the stage
+            });
+            // ca[v] = A[a][4 q + v], cb[p][v] = B[a][4 q + v], cc[p][v] = C[a][4 q + v] (A and C are symmetric)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float one = 4 * q + v == a ? 1.f : 0.f;
+                ca[v] += one;
+                cc[p][v] += one;
+            }
+            *(floatx4 *)(mfma_at + C::OFF_P + p * C::TILE) = ca;
+        });
+        between();
+#pragma unroll
+        for (int p = 0; p < 4; ++p) *(floatx4 *)(mfma_at + C::OFF_Q + p * C::TILE) = cb[p];
+        wave_sync();
+
+        // ---- 2. elimination of the columns of A
+        float *row_at = lds + g * C::TILE + 16 * i;  // solver view: row i of system g
+        const int swz = (i >> 1 & 3) << 2;           // block b of that row lies at row_at + (4 b ^ swz)
+        float s0[16], s1[16], ri0 = 1.f, ri1 = 1.f;
+        bool bad = false;
+        load_tile_row(row_at + C::OFF_P, i, s0);
+        load_tile_row(row_at + C::OFF_Q, i, s1);
+        dpp_settle(s0[0]);
+        static_for<0, 16>([&](auto ci) { eliminate_column<decltype(ci)::value, true>(s0, s1, y0, y1, ri0, i, bad); });
+
+        // ---- 3. C - L L^T and its elimination
+        wave_sync();  // every lane has read its rows of A
+#pragma unroll
+        for (int c4 = 0; c4 < 4; ++c4)
+            *(float4 *)(row_at + C::OFF_P + (4 * c4 ^ swz)) = make_float4(s1[4 * c4], s1[4 * c4 + 1], s1[4 * c4 + 2], s1[4 * c4 + 3]);
+        wave_sync();
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            // lane (a, q) supplies L[a][4 q + e] to instruction e on both sides: the contraction runs over all 16 columns
+            const floatx4 o = *(const floatx4 *)(mfma_at + C::OFF_P + p * C::TILE);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) cc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(-o[e], o[e], cc[p], 0, 0, 0);
+        }
+        wave_sync();
+#pragma unroll
+        for (int p = 0; p < 4; ++p) *(floatx4 *)(mfma_at + C::OFF_P + p * C::TILE) = cc[p];
+        float bt[16];  // column i of B
+#pragma unroll
+        for (int m = 0; m < 16; ++m)
+            bt[m] = lds[C::OFF_Q + g * C::TILE + 16 * m + (((i >> 2) ^ (m >> 1) & 3) << 2) + (i & 3)];
+        wave_sync();
+        load_tile_row(row_at + C::OFF_P, i, s1);
+        dpp_settle(s1[0]);
+        static_for<0, 16>([&](auto ci) {
+            constexpr int c = decltype(ci)::value;
+            float none = 0.f;
+            if (16 + c < kmax) eliminate_column<c, false>(s1, s1, y1, none, ri1, i, bad);  // beyond every row's k: identity rows
+        });
+        if (bad) atomicOr(err_flag, 1);
+
+        // ---- 4. t of both halves
+        float t1 = y1 * ri1 * ri1;
+        float za = 0.f, zb = 0.f;
+        dpp_settle(t1);
+        static_for<0, 8>([&](auto mm) {
+            constexpr int m = decltype(mm)::value;
+            fmac_bcast16<2 * m>(za, t1, bt[2 * m]);
+            fmac_bcast16<2 * m + 1>(zb, t1, bt[2 * m + 1]);
+        });
+        za += zb;
+        static_for<0, 16>([&](auto ci) {
+            constexpr int c = decltype(ci)::value;
+            dpp_settle(za);
+            fmac_bcast16_neg<c>(za, za, s0[c]);
+        });
+        const float t0 = (y0 - za) * ri0 * ri0;
+        wave_sync();  // every lane has read its row of C
+        if constexpr (C::RES) {
+            // ---- 5. r = Z_I^T t from the registers of step 1, four (bf16: eight) columns per lane
+            float *tb = lds + C::OFF_P;  // t of the entries of one lane side by side
+            tb[g * K + i % EPI * 2 * N + i / EPI] = t0;
+            tb[g * K + i % EPI * 2 * N + N + i / EPI] = t1;
+            wave_sync();
+            constexpr int NV = ZB ? 2 : 1;
+            floatx4 rv[4][NV];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const float *tp = tb + p * K + lane / PG::LPR * 2 * N;
+                float t[2 * N];
+                if constexpr (N >= 2) {
+#pragma unroll
+                    for (int h = 0; h < N / 2; ++h) {
+                        const float4 v = ((const float4 *)tp)[h];
+                        t[4 * h] = v.x; t[4 * h + 1] = v.y; t[4 * h + 2] = v.z; t[4 * h + 3] = v.w;
+                    }
+                } else {
+                    t[0] = tp[0];
+                    t[1] = tp[1];
+                }
+#pragma unroll
+                for (int n = 0; n < NV; ++n) rv[p][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int x = 0; x < 2 * N; ++x) {
+                    if (x >= N && 16 + (x - N) * EPI >= k[p]) continue;  // uniform
+                    const floatx4 w = z[p % C::DEPTH][x / N][x % N];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        if constexpr (ZB) {
+                            rv[p][c / 2][2 * (c & 1)] += t[x] * __uint_as_float(__float_as_uint(w[c]) << 16);
+                            rv[p][c / 2][2 * (c & 1) + 1] += t[x] * __uint_as_float(__float_as_uint(w[c]) & 0xffff0000u);
+                        } else {
+                            rv[p][0][c] += t[x] * w[c];
+                        }
+                    }
+                }
+            }
+            last();
+            const int64_t u[4] = {d.row.rel[0], d.row.rel[1], d.row.rel[2], d.row.rel[3]};
+            store_rows<PG::LPR>(rv, R, ldr, u, lane);
+            return;
+        }
+        if constexpr (!C::RES) {
+        const int32_t *ids = (const int32_t *)(lds + C::OFF_ID);
+        float *tbuf = lds + C::OFF_P;
+        tbuf[g * K + i] = t0;
+        tbuf[g * K + 16 + i] = t1;
+        wave_sync();
+
+        // ---- 5. r = Z_I^T t (second gather of the row's entries): 16 bytes of an entry per lane, so that one instruction takes
+        // GatherCols<D>::EPI entries; the four rows advance together, EPL entries per lane and round.  Per round: first the
+        // ids and t of all rows from LDS, then the loads, then the products - no wait and no lane-dependent branch between
+        // two loads.
+        {
+            using GC = GatherCols<D>;
+            constexpr int EPL = 4, EPR = EPL * GC::EPI;
+            const int mine = EPL * (lane / GC::LPR);
+            const float *col = (const float *)Z + 4 * (lane % GC::LPR);
+            floatx4 rv[4][1];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) rv[p][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int e0 = 0; e0 < kmax; e0 += EPR) {  // padded entries have t = 0 and the id of the row's first entry
+                typedef int intv __attribute__((ext_vector_type(EPL)));
+                typedef float floatv __attribute__((ext_vector_type(EPL)));
+                intv id[4];
+                floatv te[4];
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    id[p] = *(const intv *)(ids + p * K + e0 + mine);
+                    te[p] = *(const floatv *)(tbuf + p * K + e0 + mine);
+                }
+                floatx4 zz[4][EPL];
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    if (e0 < k[p]) {  // uniform
+#pragma unroll
+                        for (int x = 0; x < EPL; ++x) zz[p][x] = *(const floatx4 *)(col + (int64_t)id[p][x] * D);
+                    }
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    if (e0 < k[p]) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+#pragma unroll
+                            for (int x = 0; x < EPL; ++x) rv[p][0][c] += te[p][x] * zz[p][x][c];
+                    }
+            }
+            last();
+            const int64_t u[4] = {d.row.rel[0], d.row.rel[1], d.row.rel[2], d.row.rel[3]};
+            store_rows<GC::LPR>(rv, R, ldr, u, lane);
+        }
+        }
+    }
+};
+
 template <int D, bool ZB>
-__device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indptr,
-                                                const int32_t *__restrict__ indices,
+__device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                 const float *__restrict__ values, const void *__restrict__ Z,
                                                 float *__restrict__ R, int64_t ldr, int64_t r0,
                                                 const int32_t *__restrict__ list, int count,
                                                 int32_t *__restrict__ err_flag, int blk, float *lds) {
-    using C = MultiCfg;
-    constexpr int K = C::K, NJ = z_pieces<D, ZB>(), CPL = D >= 128 ? 2 : 1;
-    constexpr bool RES = multi_resident<ZB>();
-    int32_t *ids = (int32_t *)(lds + C::OFF_ID);
-    const int lane = opaque_tid(), a = lane & 15, q = lane >> 4;  // MFMA view: entry a of a tile, column group q
-    const int g = lane >> 4, i = lane & 15;                         // solver view: system g, lane i of its group
-    float *mfma_at = lds + tile_block(a, q);        // MFMA view: row a, columns 4 q .. of the first system's tile
-    float *row_at = lds + g * C::TILE + 16 * i;     // solver view: row i of system g
-    const int swz = (i >> 1 & 3) << 2;              // block b of that row lies at row_at + (4 b ^ swz)
-
-    // Row descriptors of all four rows first (one 16-byte read of the list entries - the list's workspace is
-    // padded for it; past the end of the list the first entry stands in - then the four indptr pairs
-    // together): one wait per stage instead of one per row.
-    int64_t u[4], b[4], b1[4];
-    int k[4], kmax = 0, rel[4];
-    {
-        const ListQuad r4 = *(const ListQuad *)(list + (int64_t)blk * 4);
-        const int first = blk * 4;
-        rel[0] = r4.x;
-        rel[1] = first + 1 < count ? r4.y : r4.x;
-        rel[2] = first + 2 < count ? r4.z : r4.x;
-        rel[3] = first + 3 < count ? r4.w : r4.x;
-    }
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        b[p] = indptr[r0 + rel[p]];
-        b1[p] = indptr[r0 + rel[p] + 1];
-    }
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const bool have = blk * 4 + p < count;
-        u[p] = have ? r0 + rel[p] : -1;  // past the end of the list: the step's first row once more, not stored
-        k[p] = (int)(b1[p] - b[p]);
-        kmax = k[p] > kmax ? k[p] : kmax;
-    }
-
-    // ---- 1. the tiles of S
-    // the column ids of all four rows first: one wait, not one per row.  A slot past the row's k holds the id of
-    // the row's first entry with the top bit set: no load for the products, and a harmless, in-range row of the
-    // row's own for the second gather (where such a slot meets t = 0)
-    int32_t idv[4][2];
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int e = 16 * t + a;
-            const int32_t id = indices[b[p] + (e < k[p] ? e : 0)];  // clamped: unconditional load
-            idv[p][t] = e < k[p] ? id : (id | (int32_t)0x80000000);
-        }
-    // labels of the entries i and 16 + i of this lane's system (the class has more than 16 entries per row)
-    float y0 = 1.f, y1 = 0.f;
-    {
-        int myk = 0;
-        int64_t myb = 0;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            myk = g == p ? k[p] : myk;
-            myb = g == p ? b[p] : myb;
-        }
-        if (16 + i < myk) y1 = 1.f;
-        if (values) {
-            y0 = values[myb + i];
-            if (16 + i < myk) y1 = values[myb + 16 + i];
-        }
-    }
-    float4 zkeep[RES ? 4 : 1][2][NJ];
-    floatx4 cc[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        float4 zrow[2][NJ];
-        float4 (&z)[2][NJ] = RES ? zkeep[RES ? p : 0] : zrow;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int32_t id = idv[p][t];
-            if (!RES && q == 0) ids[p * K + 16 * t + a] = id & 0x7fffffff;
-            if (t == 0) {  // every row of the class has more than 16 entries: this tile is full
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) z[t][j] = load_piece<D, ZB>(Z, id & 0x7fffffff, j, q);
-            } else {
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) z[t][j] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (id >= 0) {  // one masked region per tile, not one per load
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) z[t][j] = load_piece<D, ZB>(Z, id, j, q);
-                }
-            }
-        }
-        TileOperand<D, ZB> op[2];
-        op[0].set(z[0]);
-        op[1].set(z[1]);
-        __builtin_amdgcn_s_setprio(1);  // matrix-core work first: other wavefronts fill in with vector work
-        const floatx4 zero = floatx4{0.f, 0.f, 0.f, 0.f};
-        floatx4 ca = tile_product<D, ZB>(op[0], op[0], zero);
-        const floatx4 cb = tile_product<D, ZB>(op[0], op[1], zero);
-        cc[p] = tile_product<D, ZB>(op[1], op[1], zero);
-        // ca[v] = A[a][4 q + v], cb[v] = B[a][4 q + v], cc[p][v] = C[a][4 q + v] (A and C are symmetric)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const float one = 4 * q + v == a ? 1.f : 0.f;
-            ca[v] += one;
-            cc[p][v] += one;
-        }
-        *(floatx4 *)(mfma_at + C::OFF_P + p * C::TILE) = ca;
-        *(floatx4 *)(mfma_at + C::OFF_Q + p * C::TILE) = cb;
-        __builtin_amdgcn_s_setprio(0);
-    }
-    wave_sync();
-
-    // ---- 2. elimination of the columns of A
-    float s0[16], s1[16], ri0 = 1.f, ri1 = 1.f;
-    bool bad = false;
-    load_tile_row(row_at + C::OFF_P, i, s0);
-    load_tile_row(row_at + C::OFF_Q, i, s1);
-    dpp_settle(s0[0]);
-    static_for<0, 16>([&](auto ci) { eliminate_column<decltype(ci)::value, true>(s0, s1, y0, y1, ri0, i, bad); });
-
-    // ---- 3. C - L L^T and its elimination
-    wave_sync();  // every lane has read its rows of A
-#pragma unroll
-    for (int c4 = 0; c4 < 4; ++c4)
-        *(float4 *)(row_at + C::OFF_P + (4 * c4 ^ swz)) = make_float4(s1[4 * c4], s1[4 * c4 + 1], s1[4 * c4 + 2], s1[4 * c4 + 3]);
-    wave_sync();
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        // lane (a, q) supplies L[a][4 q + e] to instruction e on both sides: the contraction runs over all 16 columns
-        const floatx4 o = *(const floatx4 *)(mfma_at + C::OFF_P + p * C::TILE);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) cc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(-o[e], o[e], cc[p], 0, 0, 0);
-    }
-    wave_sync();
-#pragma unroll
-    for (int p = 0; p < 4; ++p) *(floatx4 *)(mfma_at + C::OFF_P + p * C::TILE) = cc[p];
-    float bt[16];  // column i of B
-#pragma unroll
-    for (int m = 0; m < 16; ++m)
-        bt[m] = lds[C::OFF_Q + g * C::TILE + 16 * m + (((i >> 2) ^ (m >> 1) & 3) << 2) + (i & 3)];
-    wave_sync();
-    load_tile_row(row_at + C::OFF_P, i, s1);
-    dpp_settle(s1[0]);
-    static_for<0, 16>([&](auto ci) {
-        constexpr int c = decltype(ci)::value;
-        float none = 0.f;
-        if (16 + c < kmax) eliminate_column<c, false>(s1, s1, y1, none, ri1, i, bad);  // beyond every row's k: identity rows
-    });
-    if (bad) atomicOr(err_flag, 1);
-
-    // ---- 4. t of both halves
-    float t1 = y1 * ri1 * ri1;
-    float za = 0.f, zb = 0.f;
-    dpp_settle(t1);
-    static_for<0, 8>([&](auto mm) {
-        constexpr int m = decltype(mm)::value;
-        fmac_bcast16<2 * m>(za, t1, bt[2 * m]);
-        fmac_bcast16<2 * m + 1>(zb, t1, bt[2 * m + 1]);
-    });
-    za += zb;
-    static_for<0, 16>([&](auto ci) {
-        constexpr int c = decltype(ci)::value;
-        dpp_settle(za);
-        fmac_bcast16_neg<c>(za, za, s0[c]);
-    });
-    const float t0 = (y0 - za) * ri0 * ri0;
-    if constexpr (RES) {
-        // ---- 5. r = Z_I^T t from the tiles in registers (zt_times_t, dual_common.h); parts[x][row][e]: part
-        // x of t, x = 3 a block of zeros; the finished rows are staged for 8-byte stores
-        float *parts = lds + C::OFF_P, *dump = parts + 16 * K + lane;
-        wave_sync();  // every lane has read its rows of C and its column of B
-#pragma unroll
-        for (int bk = 0; bk < 2; ++bk) {
-            float x1, x2;
-            const float t = bk ? t1 : t0;
-            t_parts(t, x1, x2);
-            const int e = g * K + 16 * bk + i;
-            parts[e] = t;
-            parts[4 * K + e] = x1;
-            parts[8 * K + e] = x2;
-            parts[12 * K + e] = 0.f;
-        }
-        const SelOperands sel = make_sel(lane);
-        wave_sync();
-        const float *mine = parts + (a < 3 ? a : 3) * 4 * K + 4 * q;
-        float *rbuf = lds + C::OFF_Q;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const bf16x8 top[1] = {t_operand(mine + p * K, true)};
-            floatx4 out[2 * NJ];
-#pragma unroll
-            for (int x = 0; x < 2 * NJ; ++x) out[x] = floatx4{0.f, 0.f, 0.f, 0.f};
-            zt_times_t<2, NJ>([&](int tt, int j) { return __builtin_bit_cast(bf16x8, zkeep[RES ? p : 0][tt][j]); }, top, sel, out);
-#pragma unroll
-            for (int x = 0; x < 2 * NJ; ++x)
-                *(q == 0 ? rbuf + p * D + column_of_result(x >> 1, x & 1, a) : dump) = out[x][0] + out[x][1] + out[x][2];
-        }
-        wave_sync();
-        const bool col_ok = lane * CPL < D;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            if (u[p] >= 0 && col_ok) {
-                if constexpr (CPL == 2) *(float2 *)(R + u[p] * ldr + 2 * lane) = *(const float2 *)(rbuf + p * D + 2 * lane);
-                else R[u[p] * ldr + lane] = rbuf[p * D + lane];
-            }
-        }
-        return;
-    }
-    float *tbuf = lds + C::OFF_P;
-    wave_sync();  // every lane has read its row of C
-    tbuf[g * K + i] = t0;
-    tbuf[g * K + 16 + i] = t1;
-    wave_sync();
-
-    // ---- 5. r = Z_I^T t (second gather of the row's entries): 16 bytes of an entry per lane, so that one instruction takes
-    // GatherCols<D>::EPI entries; the four rows advance together, EPL entries per lane and round.  Per round: first the
-    // ids and t of all rows from LDS, then the loads, then the products - no wait and no lane-dependent branch between
-    // two loads.
-    {
-        using GC = GatherCols<D>;
-        constexpr int EPL = 2, EPR = EPL * GC::EPI;
-        const int mine = EPL * (lane / GC::LPR);
-        const float *col = (const float *)Z + 4 * (lane % GC::LPR);
-        floatx4 rv[4][1];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) rv[p][0] = floatx4{0.f, 0.f, 0.f, 0.f};
-        for (int e0 = 0; e0 < kmax; e0 += EPR) {  // padded entries have t = 0 and the id of the row's first entry
-            int2 id[4];
-            float2 te[4];
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                id[p] = *(const int2 *)(ids + p * K + e0 + mine);
-                te[p] = *(const float2 *)(tbuf + p * K + e0 + mine);
-            }
-            floatx4 zz[4][EPL];
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-                if (e0 < k[p]) {  // uniform
-                    zz[p][0] = *(const floatx4 *)(col + (int64_t)id[p].x * D);
-                    zz[p][1] = *(const floatx4 *)(col + (int64_t)id[p].y * D);
-                }
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-                if (e0 < k[p]) {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        rv[p][0][c] += te[p].x * zz[p][0][c];
-                        rv[p][0][c] += te[p].y * zz[p][1][c];
-                    }
-                }
-        }
-        store_rows<GC::LPR>(rv, R, ldr, u, lane);
-    }
+    single_step<MultiStep<D, ZB>>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
 }
 
 }  // namespace als

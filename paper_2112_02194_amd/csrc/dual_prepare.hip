@@ -33,7 +33,7 @@ void launch_dual_small8(int d, const als_csr *Y, const void *Z, bool zb16, float
 void launch_dual_k16(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
                      const int32_t *list, const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
 void launch_dual_multi2(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
-                        const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
+                        const int32_t *list, const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
 #define ALS_DECL_WIDE(kt)                                                                                          \
     als_status launch_dual_wide##kt(als_ctx *ctx, int d, const als_csr *Y, const void *Z, bool zb16, float *R,     \
                                     int64_t ldr, int64_t r0, const int32_t *list, const int32_t *count_dev,        \
@@ -643,7 +643,7 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
         ALS_TIMED_CLASS(T_SMALL8, 9, 1, (stb = launch_dual_wide3(ctx, D, Y, Z, zb16, R, ldr, r0, lists[9], counts_dev[9], g, err, ws, s)))
         ALS_TIMED_CLASS(T_SMALL4, 8, 1, (stb = launch_dual_wide3(ctx, D, Y, Z, zb16, R, ldr, r0, lists[8], counts_dev[8], g, err, ws, s)))
     } else {
-    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 1, 1, 4, (launch_dual_multi2(D, Y, Z, zb16, R, ldr, r0, lists[1], counts_dev[1], g, err, s)))
+    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 1, 1, 4, (launch_dual_multi2(D, Y, Z, zb16, R, ldr, r0, lists[1], counts_dev[1], walk(1, 4), err, s)))
     ALS_TIMED_CLASS(T_DUAL_CLASS0, 0, 4, (launch_dual_k16(D, Y, Z, zb16, R, ldr, r0, lists[0], counts_dev[0], walk(0, 4), err, s)))
     // 5 <= k <= 8 and k <= 4: several rows per MFMA tile
     ALS_TIMED_CLASS(T_SMALL8, 9, 8, (launch_dual_small8(D, Y, Z, zb16, R, ldr, r0, lists[9], counts_dev[9], g, err, s)))
