@@ -9,9 +9,10 @@
 namespace als {
 
 // One wavefront per row with k <= K = 16*KT entries (KT = 3..8).
-//   1. S = I + Z_I Z_I^T tile by tile: the wavefront keeps the 16 entries of tile t1 in registers (B
-//      operand) and streams the tiles t2 <= t1 past them (A operand, fetched again from the caches);
-//      each finished 16x16 tile goes to LDS, where S is kept as a lower triangle.
+//   1. S = I + Z_I Z_I^T tile by tile, into a lower triangle in LDS.  The first wide_tiles() tiles of sixteen entries are
+//      loaded together and stay in registers as operands; tiles beyond them (fp32, k > 64) are loaded whenever they are
+//      needed, from the caches mostly.  Where wide_staged(), side-by-side lanes load side-by-side pieces of a row
+//      (PieceGather, dual_common.h), and the tiles go through the triangle's place in LDS into the operand layout.
 //   2./3. Block elimination S = M P M^T and back-substitution by the wavefront (tri_solve.h).
 //   4. r = Z_I^T t: with bf16 Z from the tiles still in registers, on the matrix cores (zt_times_t,
 //      dual_common.h: bf16 entries are exact operands); with fp32 Z with four adjacent output columns per lane,
@@ -19,13 +20,21 @@ namespace als {
 //      enough for S = I + Z Z^T but would show in r).
 template <int D, int KT, bool ZB> constexpr bool wide_resident() { return ZB; }
 
+// tiles that stay in registers
+template <int KT, bool ZB> constexpr int wide_tiles() { return ZB ? KT : (KT < 5 ? KT : (KT < 7 ? 5 : 4)); }
+// Long rows of Z only.  10M pages with host locality (d = 128, fp32), KT = 3 .. 8, ms per epoch, straight into the operand
+// layout / staged: 5.66 / 5.48, 4.25 / 4.07, 2.98 / 2.91, 2.35 / 2.12, 1.93 / 1.86, 1.24 / 1.16; shorter rows lose: 1M x 1M
+// (d = 64) 1.22 / 1.26, 300k bf16 rows (d = 128, KT = 3) 76 / 81 us.
+template <int D, bool ZB> constexpr bool wide_staged() { return D == 128 && !ZB; }
+
 template <int D, int KT> struct WideCfg {
     static constexpr int K = 16 * KT;
     static constexpr int TRI = tri_row<K>(K);           // lower triangle, rows padded (tri_solve.h)
     static constexpr int OFF_COL = TRI;              // solver's auxiliary buffer
     static constexpr int OFF_T = OFF_COL + TRI_AUX_FLOATS<K>;  // tbuf[K]
     static constexpr int OFF_ID = OFF_T + K;         // ids[K]
-    static constexpr int LDS_FLOATS = OFF_ID + K;
+    static constexpr int STAGE_FLOATS = wide_staged<D, false>() ? RowGather<D, false>::STAGE_FLOATS : 0;  // over everything else, before anything is there
+    static constexpr int LDS_FLOATS = OFF_ID + K > STAGE_FLOATS ? OFF_ID + K : STAGE_FLOATS;
 };
 
 // CG: the k x k system is solved by conjugate gradients (tri_cg.h) instead of the panel elimination.
@@ -46,36 +55,74 @@ __device__ __forceinline__ void dual_wide_step(const int64_t *__restrict__ indpt
     const int k = (int)(indptr[u + 1] - b);  // <= K by the list's class
 
     // ---- 1. S tiles
-    int32_t myid[KT];
-#pragma unroll
-    for (int t = 0; t < KT; ++t) {
-        const int e = 16 * t + a;
-        const int32_t id = indices[b + (e < k ? e : 0)];  // a slot past k: the row's first entry (meets t = 0 below)
-        myid[t] = e < k ? id : (id | (int32_t)0x80000000);  // a padded slot: negative, and still a row of the table
-        if (!RES && q == 0) ids[e] = id;
-    }
-    // the first RT tiles stay in registers for the whole phase (one round of loads, all in flight
-    // together), already cut into the hi/lo bf16 operands of the split products (dual_common.h); later
-    // tiles are fetched and cut when they are needed
-    constexpr int RT = RES ? KT : (KT < 5 ? KT : (KT < 7 ? 5 : 4));
+    // With the direct solver the class holds rows with more than 16 (KT - 1) entries only: all tiles but the last are full
+    // (under CG shorter rows come through the same kernel).  A slot past k has the id of the row's first entry (and meets t = 0
+    // below); its operand is zero.
+    using RG = RowGather<D, ZB>;
+    constexpr bool STAGED = wide_staged<D, ZB>();
+    constexpr int RT = wide_tiles<KT, ZB>(), N = RG::N, T0 = STAGED ? RT : 0;  // tiles from T0 on are loaded in operand layout
+    static_assert(N == NJ, "as many registers as loaded and as operand");
     typedef TileOperand<D, ZB> Op;
-    auto fetch = [&](int t, float4 (&raw)[NJ]) {
-        // with the direct solver the class holds rows with more than 16 (KT - 1) entries only: all tiles but the
-        // last are full (under CG shorter rows come through the same kernel)
+    int32_t idv[STAGED ? RT : 1], myid[T0 < KT ? KT - T0 : 1];
+    const int in_tile = RG::id_entry(lane);
+#pragma unroll
+    for (int t = 0; t < T0; ++t) {
+        const int e = 16 * t + in_tile;
+        idv[t] = indices[b + (e < k ? e : 0)];
+    }
+#pragma unroll
+    for (int t = T0; t < KT; ++t) {
+        const int e = 16 * t + a;
+        const int32_t id = indices[b + (e < k ? e : 0)];
+        myid[t - T0] = e < k ? id : (id | (int32_t)0x80000000);  // a padded slot: negative, and still a row of the table
+        if (!RES && q == 0) ids[e] = id;  // beyond what a stage takes, where there are such tiles
+    }
+    auto fetch = [&](int t, float4 (&raw)[NJ]) {  // t >= T0
+        const int32_t id = myid[t < T0 ? 0 : t - T0];
         if (!CG && t < KT - 1) {
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) raw[j] = load_piece<D, ZB>(Z, myid[t] & 0x7fffffff, j, q);
+            for (int j = 0; j < NJ; ++j) raw[j] = load_piece<D, ZB>(Z, id & 0x7fffffff, j, q);
         } else {
 #pragma unroll
             for (int j = 0; j < NJ; ++j) raw[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (myid[t] >= 0) {  // one masked region per tile, not one per load
+            if (id >= 0) {  // one masked region per tile, not one per load
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) raw[j] = load_piece<D, ZB>(Z, myid[t], j, q);
+                for (int j = 0; j < NJ; ++j) raw[j] = load_piece<D, ZB>(Z, id, j, q);
             }
         }
     };
     Op zop[RT];
-    {
+    if constexpr (STAGED) {
+        static_assert(KT == RT || C::OFF_ID >= C::STAGE_FLOATS, "ids of tiles beyond the staged ones are in LDS already");
+        floatx4 raw[RT][N];  // (the plain vector type: as float4 they are copied by way of scratch memory)
+        const char *zlane = (const char *)Z + 16 * (lane % RG::LPR);
+        static_for<0, RT * N>([&](auto ii) {
+            constexpr int t = decltype(ii)::value / N, s = decltype(ii)::value % N;
+            raw[t][s] = *(const floatx4 *)(zlane + (int64_t)RG::template bcast_id<s>(idv[t]) * RG::RB);
+        });
+        char *stage = (char *)lds;
+        const int put = RG::put_base(lane), get = RG::get_base(a, q);
+        static_for<0, RT>([&](auto tt) {
+            constexpr int t = decltype(tt)::value;
+            static_for<0, N>([&](auto ss) {
+                constexpr int s = decltype(ss)::value;
+                *(floatx4 *)(stage + RG::template put_at<s>(put)) = raw[t][s];
+            });
+            wave_sync();
+            const bool have = 16 * t + a < k;
+            float4 o[NJ];
+            static_for<0, NJ>([&](auto jj) {
+                constexpr int j = decltype(jj)::value;
+                float4 x = *(const float4 *)(stage + (j & 1 ? get ^ 64 : get) + 128 * (j >> 1));
+                if constexpr (CG || t == KT - 1) x = make_float4(have ? x.x : 0.f, have ? x.y : 0.f, have ? x.z : 0.f, have ? x.w : 0.f);
+                o[j] = x;
+            });
+            zop[t].set(o);
+            wave_sync();  // the next tile, or the triangle, takes the place
+        });
+#pragma unroll
+        for (int t = 0; t < RT; ++t) ids[16 * t + in_tile] = idv[t];  // several lanes, the same value
+    } else {
         float4 raw[RT][NJ];
 #pragma unroll
         for (int t = 0; t < RT; ++t) fetch(t, raw[t]);
