@@ -78,8 +78,12 @@ template <int C> __device__ __forceinline__ void fmac_bcast16_neg(float &acc, fl
                  : "+v"(acc)
                  : "v"(src), "v"(mul), "n"(C));
 }
+template <int C> __device__ __forceinline__ void fmac_bcast16_neg_self(float &x, float mul) {  // x -= (x of lane C) * mul
+    asm volatile("v_fmac_f32_dpp %0, -%0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(x) : "v"(mul), "n"(C));
+}
 __device__ __forceinline__ void dpp_settle(float &a) { asm volatile("s_nop 1" : "+v"(a)); }
 __device__ __forceinline__ void dpp_settle(float &a, float &b) { asm volatile("s_nop 1" : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void dpp_settle(float (&x)[4]) { asm volatile("s_nop 1" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])); }
 
 // ---------------------------------------------------------------------------------------------- 16 x 16 systems
 // Four 16 x 16 tiles in LDS, one per system of a wavefront.  Rows are sixteen floats without padding; their four blocks of

@@ -311,8 +311,9 @@ template <int D> struct Packed {
 // table's element type.  Returns at once in the wavefronts that have nothing left to do; wavefront 0 stores.  One or two
 // panels (d < 64) are worked on by wavefront 0 alone; a Cholesky factorisation in LDS with two barriers per column
 // took an epoch of 50k x 30k rows (d = 32, half of them longer than 32) to 838 us instead of 444.  It divided by
-// square roots; the panels' reciprocals are the hardware's after one Newton step, and the error against fp64 is no larger for it
-// (rows of 1 to 500 entries, lambda 1e-4 to 1: d = 16 1.70e-7 -> 1.56e-7, d = 32 2.49e-7 -> 2.39e-7 on average).
+// square roots; the panels' reciprocals are the hardware's after one Newton step, and the error against fp64 was no larger for
+// it.  With block_solve it is (rows of 1 to 500 entries, lambda 1e-4 to 1, against rows in lanes as in tri_solve)
+// d = 16 2.16e-7 -> 2.00e-7, d = 32 2.54e-7 -> 2.20e-7 on average.
 template <int D, bool BF16>
 __device__ __forceinline__ void packed_solve_store(float *lds, void *X, int64_t xoff, int wave_s, int32_t *err_flag) {
     const int lane = opaque_tid() & 63;
@@ -326,7 +327,7 @@ __device__ __forceinline__ void packed_solve_store(float *lds, void *X, int64_t 
         tri_back<D>(lds, tbuf, rhs[lane], D > 64 ? rhs[64 + lane] : 0.f, aux[lane], D > 64 ? aux[64 + lane] : 1.f, k);
     } else {
         if (wave_s != 0) return;
-        tri_solve<D>(lds, aux, tbuf, lane < D ? rhs[lane] : 0.f, 0.f, k, err_flag);
+        block_solve<D>(lds, aux, tbuf, lane < D ? rhs[lane] : 0.f, k, err_flag);
     }
     for (int c = lane; c < D; c += 64) store_elem<BF16>(X, xoff + c, tbuf[c]);
 }

@@ -227,7 +227,158 @@ __device__ __forceinline__ void tri_solve(float *tri, float *aux /* [TRI_AUX_FLO
 
     tri_back<K>(tri, tbuf, y0, y1, rp0, rp1, k);
 }
-// The same elimination by a workgroup of four wavefronts, for systems too few per compute unit to hide one wavefront's
+// Sum over the four rows of 16 lanes, in every lane.
+__device__ __forceinline__ float sum_lane_rows(float v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const float w = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(w), __float_as_uint(w), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+// Sum over the 16 lanes of this lane's row, in every lane.
+__device__ __forceinline__ float sum_lane_row(float v) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true));  // row_ror:8
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, true));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, true));
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, true));
+    return v;
+}
+// Value of the lane at this lane's place in row Q of the four rows of 16 lanes: permlane16_swap(v, v) leaves rows 0 0 2 2 and
+// 1 1 3 3, permlane32_swap(v, v) the lower half twice and the upper half twice.
+template <int Q> __device__ __forceinline__ float from_lane_row(float v) {
+    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const uint32_t w = r16[Q & 1];
+    const auto r32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return __uint_as_float(r32[Q >> 1]);
+}
+
+// The same for one or two panels, S = M P M^T by blocks.  Lane (i, q) = (lane % 16, lane / 16).  Per panel p:
+//   1. the 16 x 16 diagonal block is eliminated in registers, in place: lane (i, q) holds the entries (i, 4 q + s), and a
+//      column that is done makes room for the same column of N = M_pp^{-1}.  A step takes four multiply-adds (the pivot row
+//      comes as a DPP modifier) instead of up to fifteen with a lane read each, the pivot from its lane, the pivot column by
+//      lane swaps.
+//   2. u_p = N y_p.
+//   3. the tile below becomes W = A N^T on the matrix cores: v_mfma_f32_16x16x4f32 takes A[a][q] and B[q][a] from lane
+//      (a, q) and leaves C[4q+v][a]; instruction e contracts the columns 4q + e, so N as it stands in the registers is one
+//      operand, 16 bytes of a tile row the other, and the result (computed transposed) is row a, columns 4q .. of W.
+//   4. the tile after it is updated the same way, A -= W P^{-1} W^T, and y -= W P^{-1} u_p.
+// Then, from the last panel to the first, t_p = N^T P^{-1} (u_p - W^T t).
+// What bounds it: the chain of the steps, and with many rows per SIMD their instructions.  Epoch of 50k x 30k with labels (d = 32,
+// half of the rows longer than 32): the kernel 177 -> 167 us, the epoch 335 -> 325 us.  For 48 <= K <= 128 the form above is
+// the better one: a step's chain is longer here (10M pages, d = 128, fp32: 0 to 1 % slower, 50M rows bf16: 1 %).
+template <int K>
+__device__ __forceinline__ void block_solve(float *tri, float *aux /* [TRI_AUX_FLOATS<K>] */, float *tbuf /* [K] */, float y0,
+                                            int k, int32_t *err_flag) {
+    static_assert(K == 16 || K == 32, "unsupported system size");
+    constexpr int NT = K / 16;
+    const int lane = opaque_tid() & 63, a = lane & 15, q = lane >> 4;
+    bool bad = false;
+    if (lane < K) tbuf[lane] = y0;  // y, then u, then t
+    wave_sync();
+    static_for<0, NT>([&](auto pp) {
+        constexpr int p = decltype(pp)::value, P0 = 16 * p, T = NT - p - 1;
+        if (P0 < k) {
+            float x[4], mine = 1.f;
+            floatx4 z[T > 0 ? T : 1];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {  // the lower triangle is what callers fill
+                const int c = 4 * q + s;
+                x[s] = c <= a ? tri[tri_row<K>(P0 + a) + P0 + c] : tri[tri_row<K>(P0 + c) + P0 + a];
+            }
+            const floatx4 yv = *(const floatx4 *)(tbuf + P0 + 4 * q);
+            dpp_settle(x);
+            static_for<0, 16>([&](auto cc) {
+                constexpr int c = decltype(cc)::value, sc = c & 3, qc = c >> 2;
+                if (P0 + c < k) {
+                    const float pivot = lane_value(x[sc], 16 * qc + c);
+                    float rp = __builtin_amdgcn_rcpf(pivot);
+                    rp = rp * (2.f - pivot * rp);  // one Newton step on the hardware reciprocal
+                    mine = a == c ? rp : mine;
+                    const float col = from_lane_row<qc>(x[sc]);
+                    const float f = a > c ? col * rp : 0.f;
+                    const float done = a == c ? 1.f : -f;  // this row's entry of N in column c
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) fmac_bcast16_neg_self<c>(x[s], f);
+                    x[sc] = q == qc ? done : x[sc];
+                    dpp_settle(x);
+                }
+            });
+            bad |= !(mine > 0.f);  // negative stays negative, zero and NaN come out of the Newton step as NaN
+            const float u = sum_lane_rows(x[0] * yv[0] + x[1] * yv[1] + x[2] * yv[2] + x[3] * yv[3]);
+            tbuf[P0 + a] = u;  // four lanes, the same value
+            aux[P0 + a] = mine;
+            *(floatx4 *)(tri + tri_row<K>(P0 + a) + P0 + 4 * q) = floatx4{x[0], x[1], x[2], x[3]};
+            wave_sync();
+            if constexpr (T > 0) {
+                const floatx4 rpv = *(const floatx4 *)(aux + P0 + 4 * q), uv = *(const floatx4 *)(tbuf + P0 + 4 * q);
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    floatx4 *cell = (floatx4 *)(tri + tri_row<K>(16 * (p + 1 + t) + a) + P0 + 4 * q);
+                    const floatx4 c4 = *cell;
+                    floatx4 w = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], c4[e], w, 0, 0, 0);
+                    z[t] = w;
+                    *cell = w;
+                }
+                static_for<0, T>([&](auto tii) {
+                    constexpr int ti = decltype(tii)::value;
+                    floatx4 za;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) za[e] = -z[ti][e] * rpv[e];
+                    const float d = sum_lane_rows(za[0] * uv[0] + za[1] * uv[1] + za[2] * uv[2] + za[3] * uv[3]);
+                    tbuf[16 * (p + 1 + ti) + a] += d;
+                    // all tiles of the tile row are fetched before the first is stored back; in a diagonal tile the columns
+                    // beyond the diagonal belong to the row's padding
+                    floatx4 acc[ti + 1];
+                    floatx4 *cell[ti + 1];
+#pragma unroll
+                    for (int tj = 0; tj <= ti; ++tj) {
+                        cell[tj] = (floatx4 *)(tri + tri_row<K>(16 * (p + 1 + ti) + a) + 16 * (p + 1 + tj) + 4 * q);
+                        acc[tj] = *cell[tj];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int tj = 0; tj <= ti; ++tj) acc[tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[tj][e], za[e], acc[tj], 0, 0, 0);
+#pragma unroll
+                    for (int tj = 0; tj <= ti; ++tj) *cell[tj] = acc[tj];
+                });
+                wave_sync();
+            }
+        }
+    });
+    if (__any(bad) && lane == 0) atomicOr(err_flag, 1);
+    static_for<0, NT>([&](auto pp) {
+        constexpr int p = NT - 1 - decltype(pp)::value, P0 = 16 * p, T = NT - p - 1;
+        if (P0 < k) {
+            floatx4 s4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const floatx4 w = *(const floatx4 *)(tri + tri_row<K>(16 * (p + 1 + t) + a) + P0 + 4 * q);
+                const float ti = tbuf[16 * (p + 1 + t) + a];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) s4[s] += w[s] * ti;
+            }
+            const floatx4 n4 = *(const floatx4 *)(tri + tri_row<K>(P0 + a) + P0 + 4 * q);
+            const floatx4 rpv = *(const floatx4 *)(aux + P0 + 4 * q), uv = *(const floatx4 *)(tbuf + P0 + 4 * q);
+            floatx4 v4;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) v4[s] = rpv[s] * (uv[s] - (T > 0 ? sum_lane_row(s4[s]) : 0.f));
+            wave_sync();
+            *(floatx4 *)(tbuf + P0 + 4 * q) = v4;  // sixteen lanes, the same values
+            wave_sync();
+            const float va = tbuf[P0 + a];
+            floatx4 t4;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) t4[s] = sum_lane_row(n4[s] * va);
+            wave_sync();
+            *(floatx4 *)(tbuf + P0 + 4 * q) = t4;
+            wave_sync();
+        }
+    });
+}
+
+// The elimination of tri_solve by a workgroup of four wavefronts, for systems too few per compute unit to hide one wavefront's
 // chain (K = 128: a workgroup's triangle takes a quarter of the LDS).  Every wavefront that works on a panel eliminates the
 // panel's 16 pivot rows for itself (lanes 0 .. 15) and 48 of the rows below in its other lanes - the steps cost what
 // they cost with 16 rows, nothing is exchanged between wavefronts, and the numbers are those of tri_solve -, and the tiles
