@@ -37,6 +37,10 @@ __global__ void clear_counters_kernel(int32_t *counters, long long *long_stat) {
 }
 
 constexpr int CLS_THREADS = 256, CLS_RPT = 8, CLS_ROWS = CLS_THREADS * CLS_RPT;  // rows per workgroup
+// Up to this many rows one large workgroup does what takes four dependent launches otherwise (clearing, the long rows' sums, the
+// lists, their lengths for the host).  Epoch of 2000 x 1500 113 -> 95 us, 256 folded-in rows (d = 128) 85.7 -> 80.4 us; eight
+// rows a thread are all it can hold in registers.
+constexpr int CLS_ONE_THREADS = 1024, CLS_ONE_ROWS = CLS_ONE_THREADS * CLS_RPT;
 struct ListOffsets { int64_t v[11]; };  // start of each dual class list (and the end of the last), passed by value
 
 // Entries and rows beyond the requested split threshold, summed per workgroup and added with one atomic
@@ -92,6 +96,33 @@ __device__ __forceinline__ int32_t decide_split(const unsigned long long *__rest
     return (int32_t)(s > 0x7fffffffull ? 0x7fffffffull : s);
 }
 
+// 0 = mid list, 1..8 = dual classes by ceil(k/16), 9 = k <= 4, 10 = 5 <= k <= 8
+__device__ __forceinline__ int row_class(int64_t k, int64_t dual_max) {
+    return k > dual_max ? 0 : (k <= 4 ? 9 : (k <= 8 ? 10 : (int)((k + 15) / 16)));
+}
+// where the length of list `cls` stands among the counters
+__device__ __forceinline__ int class_counter(int cls) { return cls == 0 ? 3 : (cls <= 8 ? 8 + cls - 1 : cls - 4); }
+
+// Row u with k > split entries from b on: its record and its balanced segments; false where they do not fit.
+__device__ __forceinline__ bool add_long_row(int64_t u, int64_t b, int64_t k, int64_t split, int32_t *n_long, int32_t *n_seg,
+                                             LongRow *__restrict__ long_rows, Segment *__restrict__ segs) {
+    int nseg = (int)((k + split - 1) / split);
+    if (nseg > MAX_SEGS_PER_ROW) nseg = MAX_SEGS_PER_ROW;
+    const int64_t len = (k + nseg - 1) / nseg, e = b + k;
+    const int slot = atomicAdd(n_long, 1);
+    const int first = atomicAdd(n_seg, nseg);
+    if (slot >= SEG_CAPACITY / 2 || first + nseg > SEG_CAPACITY) return false;
+    long_rows[slot].row = u;
+    long_rows[slot].seg_first = first;
+    long_rows[slot].nseg = nseg;
+    for (int g = 0; g < nseg; ++g) {
+        const int64_t start = b + g * len, stop = b + (g + 1) * len;
+        segs[first + g].begin = start < e ? start : e;
+        segs[first + g].end = stop < e ? stop : e;
+    }
+    return true;
+}
+
 // One workgroup per CLS_ROWS consecutive rows of [r0, r1):
 //   k = 0               X[u] = 0
 //   0 < k <= dual_max   appended to the dual list of its class: k <= 4, 5..8, else ceil(k/16) in 1..8
@@ -134,32 +165,15 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
             } else if (k <= 0) {
                 for (int c = 0; c < d; ++c) store_elem<BF16>(X, u * ldx + c, 0.f);
             } else if (k > split) {
-                int nseg = (int)((k + split - 1) / split);
-                if (nseg > MAX_SEGS_PER_ROW) nseg = MAX_SEGS_PER_ROW;
-                const int64_t len = (k + nseg - 1) / nseg;
-                const int slot = atomicAdd(&counters[0], 1);
-                const int first = atomicAdd(&counters[1], nseg);
-                if (slot < SEG_CAPACITY / 2 && first + nseg <= SEG_CAPACITY) {
-                    long_rows[slot].row = u;
-                    long_rows[slot].seg_first = first;
-                    long_rows[slot].nseg = nseg;
-                    for (int g = 0; g < nseg; ++g) {
-                        const int64_t start = b + g * len, stop = b + (g + 1) * len;
-                        segs[first + g].begin = start < e ? start : e;
-                        segs[first + g].end = stop < e ? stop : e;
-                    }
-                } else {
-                    atomicOr(&counters[2], 2);
-                }
+                if (!add_long_row(u, b, k, split, &counters[0], &counters[1], long_rows, segs)) atomicOr(&counters[2], 2);
             } else {
-                // 0 = mid list, 1..8 = dual classes by ceil(k/16), 9 = k <= 4, 10 = 5 <= k <= 8
-                cls[i] = k > dual_max ? 0 : (k <= 4 ? 9 : (k <= 8 ? 10 : (int)((k + 15) / 16)));
+                cls[i] = row_class(k, dual_max);
                 pos[i] = atomicAdd(&cnt[cls[i]], 1);
             }
         }
     }
     __syncthreads();
-    if (t < 11 && cnt[t] > 0) base[t] = atomicAdd(&counters[t == 0 ? 3 : (t <= 8 ? 8 + t - 1 : t - 4)], cnt[t]);
+    if (t < 11 && cnt[t] > 0) base[t] = atomicAdd(&counters[class_counter(t)], cnt[t]);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < CLS_RPT; ++i) {
@@ -198,6 +212,83 @@ __global__ void publish_counts_kernel(int32_t *__restrict__ counters, int64_t ca
     if (t < 16) hint[t] = counters[t];
     __threadfence_system();
     __syncthreads();
+    if (t == 0) {
+        ((volatile int32_t *)hint)[16] = (int32_t)seq;
+        __threadfence_system();
+    }
+}
+
+// The four kernels above in one, for at most CLS_ONE_ROWS rows: one workgroup, everything counted in LDS.  The same lists,
+// segments, counters and hint.
+template <bool BF16>
+__global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
+    const int64_t *__restrict__ indptr, int64_t r0, int64_t r1, int64_t dual_max, int d,
+    void *__restrict__ X, int64_t ldx, int32_t *__restrict__ counters, LongRow *__restrict__ long_rows,
+    Segment *__restrict__ segs, int32_t *__restrict__ mid_list, int64_t cap_mid, int32_t *__restrict__ dual_lists,
+    ListOffsets list_off, int64_t entry_limit, int64_t split_wanted, int32_t *__restrict__ hint, uint32_t seq) {
+    __shared__ int32_t n[16];  // as in `counters`; [2]: flag bits set here
+    __shared__ unsigned long long long_stat[2];
+    const int t = threadIdx.x;
+    if (t < 16) n[t] = 0;
+    if (t < 2) long_stat[t] = 0;
+    const bool by_entry = entry_limit != INT64_MAX;
+    const int64_t first_entry = by_entry && indptr[r0] > 0 ? indptr[r0] : 0;
+    const int64_t end_entry = by_entry && indptr[r1] < entry_limit ? indptr[r1] : entry_limit;
+    int64_t b[CLS_RPT], e[CLS_RPT];
+#pragma unroll
+    for (int i = 0; i < CLS_RPT; ++i) {
+        const int64_t u = r0 + (int64_t)i * CLS_ONE_THREADS + t;
+        b[i] = e[i] = 0;
+        if (u < r1) {
+            b[i] = indptr[u];
+            e[i] = indptr[u + 1];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < CLS_RPT; ++i) {  // few rows are long
+        if (e[i] - b[i] > split_wanted) {
+            atomicAdd(&long_stat[0], (unsigned long long)(e[i] - b[i]));
+            atomicAdd(&long_stat[1], 1ull);
+        }
+    }
+    __syncthreads();
+    const int64_t split = decide_split(long_stat, split_wanted);
+#pragma unroll
+    for (int i = 0; i < CLS_RPT; ++i) {
+        const int64_t u = r0 + (int64_t)i * CLS_ONE_THREADS + t, k = e[i] - b[i];
+        if (u >= r1) continue;
+        if (b[i] < first_entry || e[i] > end_entry) {
+            atomicOr(&n[2], 2);
+        } else if (k <= 0) {
+            for (int c = 0; c < d; ++c) store_elem<BF16>(X, u * ldx + c, 0.f);
+        } else if (k > split) {
+            if (!add_long_row(u, b[i], k, split, &n[0], &n[1], long_rows, segs)) atomicOr(&n[2], 2);
+        } else {
+            const int c = row_class(k, dual_max);
+            const int64_t at = atomicAdd(&n[class_counter(c)], 1);
+            const int64_t cap = c == 0 ? cap_mid : list_off.v[c] - list_off.v[c - 1];
+            if (at < cap) (c == 0 ? mid_list : dual_lists + list_off.v[c - 1])[at] = (int32_t)(u - r0);
+            else atomicOr(&n[2], 2);
+        }
+    }
+    __syncthreads();
+    if (t < 16 && t != 4) {  // [4] is the CSR check flag
+        const int32_t flag = counters[2] | n[2];  // the error flag is sticky
+        int32_t v = n[t];
+        if (t == 2) v = flag;
+        if (t == 7) v = (int32_t)split;
+        if (t < 2 && (flag & 2)) v = 0;  // something was dropped: no long rows at all rather than half-written ones
+        if (t == 3 && v > cap_mid) v = (int32_t)cap_mid;
+        const int c = t >= 8 ? t - 8 : t + 3;  // list whose length stands here
+        if (t == 5 || t == 6 || t >= 8) {
+            const int64_t cap = list_off.v[c + 1] - list_off.v[c];
+            if (v > cap) v = (int32_t)cap;
+        }
+        counters[t] = v;
+        hint[t] = v;
+    }
+    if (t < 64) __threadfence_system();
     if (t == 0) {
         ((volatile int32_t *)hint)[16] = (int32_t)seq;
         __threadfence_system();
@@ -286,19 +377,22 @@ als_status launch_solve_rows(als_ctx *ctx, const als_csr *Y, const als_table *V,
     als_csr by_position = *Y;
 
     timer_begin(ctx, T_CLASSIFY, s);
-    hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, counters, (long long *)long_stat);
-    const unsigned cblocks = (unsigned)((nrows + CLS_ROWS - 1) / CLS_ROWS);
-    hipLaunchKernelGGL(long_stat_kernel, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr, r0, r1, split, long_stat);
-    if (V->dtype == ALS_BF16)
-        hipLaunchKernelGGL(classify_kernel<true>, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr, r0, r1,
-                           (int64_t)dual_max, V->d, X->data, X->ld, counters, long_rows, segs, mid_list, cap_mid,
-                           dual_lists, list_off, by_entry ? Y->nnz : INT64_MAX, (const unsigned long long *)long_stat, split);
-    else
-        hipLaunchKernelGGL(classify_kernel<false>, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr, r0, r1,
-                           (int64_t)dual_max, V->d, X->data, X->ld, counters, long_rows, segs, mid_list, cap_mid,
-                           dual_lists, list_off, by_entry ? Y->nnz : INT64_MAX, (const unsigned long long *)long_stat, split);
-    hipLaunchKernelGGL(publish_counts_kernel, dim3(1), dim3(64), 0, s, counters, cap_mid, list_off,
-                       ctx->hint_counts_dev + (size_t)slot * HINT_INTS, hs.seq);
+    const bool bf = V->dtype == ALS_BF16;
+    const int64_t entry_limit = by_entry ? Y->nnz : INT64_MAX;
+    int32_t *hint_out = ctx->hint_counts_dev + (size_t)slot * HINT_INTS;
+    if (nrows <= CLS_ONE_ROWS) {
+        hipLaunchKernelGGL(bf ? classify_one_kernel<true> : classify_one_kernel<false>, dim3(1), dim3(CLS_ONE_THREADS), 0, s,
+                           Y->indptr, r0, r1, (int64_t)dual_max, V->d, X->data, X->ld, counters, long_rows, segs, mid_list,
+                           cap_mid, dual_lists, list_off, entry_limit, split, hint_out, hs.seq);
+    } else {
+        hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, counters, (long long *)long_stat);
+        const unsigned cblocks = (unsigned)((nrows + CLS_ROWS - 1) / CLS_ROWS);
+        hipLaunchKernelGGL(long_stat_kernel, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr, r0, r1, split, long_stat);
+        hipLaunchKernelGGL(bf ? classify_kernel<true> : classify_kernel<false>, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr,
+                           r0, r1, (int64_t)dual_max, V->d, X->data, X->ld, counters, long_rows, segs, mid_list, cap_mid,
+                           dual_lists, list_off, entry_limit, (const unsigned long long *)long_stat, split);
+        hipLaunchKernelGGL(publish_counts_kernel, dim3(1), dim3(64), 0, s, counters, cap_mid, list_off, hint_out, hs.seq);
+    }
     timer_end(ctx, s);
     ALS_HIP(ctx, hipGetLastError());
 
