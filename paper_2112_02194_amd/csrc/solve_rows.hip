@@ -103,14 +103,16 @@ __device__ __forceinline__ int row_class(int64_t k, int64_t dual_max) {
 // where the length of list `cls` stands among the counters
 __device__ __forceinline__ int class_counter(int cls) { return cls == 0 ? 3 : (cls <= 8 ? 8 + cls - 1 : cls - 4); }
 
-// Row u with k > split entries from b on: its record and its balanced segments; false where they do not fit.
-__device__ __forceinline__ bool add_long_row(int64_t u, int64_t b, int64_t k, int64_t split, int32_t *n_long, int32_t *n_seg,
+__device__ __forceinline__ int segments_of(int64_t k, int64_t split) {
+    const int64_t nseg = (k + split - 1) / split;
+    return (int)(nseg < MAX_SEGS_PER_ROW ? nseg : MAX_SEGS_PER_ROW);
+}
+// Row u with k > split entries from b on becomes long row `slot` with its balanced segments from `first` on; false where they
+// do not fit.
+__device__ __forceinline__ bool put_long_row(int64_t u, int64_t b, int64_t k, int64_t split, int slot, int first,
                                              LongRow *__restrict__ long_rows, Segment *__restrict__ segs) {
-    int nseg = (int)((k + split - 1) / split);
-    if (nseg > MAX_SEGS_PER_ROW) nseg = MAX_SEGS_PER_ROW;
+    const int nseg = segments_of(k, split);
     const int64_t len = (k + nseg - 1) / nseg, e = b + k;
-    const int slot = atomicAdd(n_long, 1);
-    const int first = atomicAdd(n_seg, nseg);
     if (slot >= SEG_CAPACITY / 2 || first + nseg > SEG_CAPACITY) return false;
     long_rows[slot].row = u;
     long_rows[slot].seg_first = first;
@@ -131,7 +133,8 @@ __device__ __forceinline__ bool add_long_row(int64_t u, int64_t b, int64_t k, in
 //   k > split           becomes a long row cut into balanced segments of about `split` entries
 //                       (at most MAX_SEGS_PER_ROW of them); split is the threshold of decide_split, left in
 //                       counters[7] too
-// List positions are reserved with one atomic per workgroup and list (counts gathered in LDS), and
+// Positions are reserved with one atomic per workgroup and list (counts gathered in LDS; with two per long row, whose answers a
+// wavefront waited for up to eight times, the 1M rows of a heavy-tailed half took 74 us instead of 17), and
 // rows keep their order inside a workgroup's slice.  A matrix whose indptr does not fit its nnz can ask
 // for more long rows or segments than the workspace holds; those rows are dropped and the error flag is set.  So are, when Z
 // holds one row per entry (entry_limit = nnz, else INT64_MAX), rows with entries outside those that Gather walks, from
@@ -142,9 +145,9 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
     void *__restrict__ X, int64_t ldx, int32_t *__restrict__ counters, LongRow *__restrict__ long_rows,
     Segment *__restrict__ segs, int32_t *__restrict__ mid_list, int64_t cap_mid, int32_t *__restrict__ dual_lists,
     ListOffsets list_off, int64_t entry_limit, const unsigned long long *__restrict__ long_stat, int64_t split_wanted) {
-    __shared__ int32_t cnt[11], base[11];
+    __shared__ int32_t cnt[13], base[13];  // lists 0..10, long rows, their segments
     const int t = threadIdx.x;
-    if (t < 11) cnt[t] = 0;
+    if (t < 13) cnt[t] = 0;
     __syncthreads();
     const int64_t split = decide_split(long_stat, split_wanted);
     if (blockIdx.x == 0 && t == 0) counters[7] = (int32_t)split;
@@ -152,12 +155,12 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
     const int64_t first_entry = by_entry && indptr[r0] > 0 ? indptr[r0] : 0;
     const int64_t end_entry = by_entry && indptr[r1] < entry_limit ? indptr[r1] : entry_limit;
     const int64_t u0 = r0 + (int64_t)blockIdx.x * CLS_ROWS;
-    int cls[CLS_RPT], pos[CLS_RPT];
+    int cls[CLS_RPT], pos[CLS_RPT], seg[CLS_RPT];
 #pragma unroll
     for (int i = 0; i < CLS_RPT; ++i) {
         const int64_t u = u0 + (int64_t)i * CLS_THREADS + t;  // coalesced indptr reads
         cls[i] = -1;
-        pos[i] = 0;
+        pos[i] = seg[i] = 0;
         if (u < r1) {
             const int64_t b = indptr[u], e = indptr[u + 1], k = e - b;
             if (b < first_entry || e > end_entry) {
@@ -165,7 +168,9 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
             } else if (k <= 0) {
                 for (int c = 0; c < d; ++c) store_elem<BF16>(X, u * ldx + c, 0.f);
             } else if (k > split) {
-                if (!add_long_row(u, b, k, split, &counters[0], &counters[1], long_rows, segs)) atomicOr(&counters[2], 2);
+                cls[i] = 11;
+                pos[i] = atomicAdd(&cnt[11], 1);
+                seg[i] = atomicAdd(&cnt[12], segments_of(k, split));
             } else {
                 cls[i] = row_class(k, dual_max);
                 pos[i] = atomicAdd(&cnt[cls[i]], 1);
@@ -173,11 +178,16 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
         }
     }
     __syncthreads();
-    if (t < 11 && cnt[t] > 0) base[t] = atomicAdd(&counters[class_counter(t)], cnt[t]);
+    if (t < 13 && cnt[t] > 0) base[t] = atomicAdd(&counters[t < 11 ? class_counter(t) : t - 11], cnt[t]);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < CLS_RPT; ++i) {
         if (cls[i] < 0) continue;
+        if (cls[i] == 11) {
+            const int64_t u = u0 + (int64_t)i * CLS_THREADS + t, b = indptr[u];
+            if (!put_long_row(u, b, indptr[u + 1] - b, split, base[11] + pos[i], base[12] + seg[i], long_rows, segs)) atomicOr(&counters[2], 2);
+            continue;
+        }
         const int32_t rel = (int32_t)(u0 + (int64_t)i * CLS_THREADS + t - r0);
         const int64_t at = (int64_t)base[cls[i]] + pos[i];
         if (cls[i] == 0) {
@@ -263,7 +273,8 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
         } else if (k <= 0) {
             for (int c = 0; c < d; ++c) store_elem<BF16>(X, u * ldx + c, 0.f);
         } else if (k > split) {
-            if (!add_long_row(u, b[i], k, split, &n[0], &n[1], long_rows, segs)) atomicOr(&n[2], 2);
+            const int slot = atomicAdd(&n[0], 1), first = atomicAdd(&n[1], segments_of(k, split));
+            if (!put_long_row(u, b[i], k, split, slot, first, long_rows, segs)) atomicOr(&n[2], 2);
         } else {
             const int c = row_class(k, dual_max);
             const int64_t at = atomicAdd(&n[class_counter(c)], 1);
