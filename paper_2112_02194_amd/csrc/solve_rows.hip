@@ -4,6 +4,8 @@
 // counts stay in device memory, every row kernel walks its list with a grid-stride loop bounded by
 // the count it reads there, and grids are sized from the counts of the previous call on the same
 // matrix when there was one (a hint: a wrong or missing hint costs speed, never correctness).
+#include <type_traits>
+
 #include "als_internal.h"
 
 namespace als {
@@ -36,23 +38,28 @@ __global__ void clear_counters_kernel(int32_t *counters, long long *long_stat) {
     if (t < 2) long_stat[t] = 0;
 }
 
-constexpr int CLS_THREADS = 256, CLS_RPT = 8, CLS_ROWS = CLS_THREADS * CLS_RPT;  // rows per workgroup
+constexpr int CLS_THREADS = 256;
+// Rows per thread: eight, so that few workgroups reserve places with atomics, but two while each of those workgroups has a
+// compute unit to itself, where the rounds of a thread, one after the other, are what is waited for.  Epoch of 50k x 30k, eight / two:
+// 325 / 312 us; the kernel for 2 x 1M rows 35 / 59 us, for 2 x 10M rows 191 / 465 us.
+constexpr int CLS_RPT_MANY = 8, CLS_RPT_FEW = 2;
 // Up to this many rows one large workgroup does what takes four dependent launches otherwise (clearing, the long rows' sums, the
 // lists, their lengths for the host).  Epoch of 2000 x 1500 113 -> 95 us, 256 folded-in rows (d = 128) 85.7 -> 80.4 us; eight
 // rows a thread are all it can hold in registers.
-constexpr int CLS_ONE_THREADS = 1024, CLS_ONE_ROWS = CLS_ONE_THREADS * CLS_RPT;
+constexpr int CLS_ONE_THREADS = 1024, CLS_ONE_RPT = 8, CLS_ONE_ROWS = CLS_ONE_THREADS * CLS_ONE_RPT;
 struct ListOffsets { int64_t v[11]; };  // start of each dual class list (and the end of the last), passed by value
 
 // Entries and rows beyond the requested split threshold, summed per workgroup and added with one atomic
 // each (integer sums: the order does not matter).
+template <int RPT>
 __global__ __launch_bounds__(CLS_THREADS) void long_stat_kernel(const int64_t *__restrict__ indptr, int64_t r0,
                                                                int64_t r1, int64_t split,
                                                                unsigned long long *__restrict__ long_stat) {
     __shared__ unsigned long long red[2][CLS_THREADS / 64];
     unsigned long long ent = 0, cnt = 0;
-    const int64_t u0 = r0 + (int64_t)blockIdx.x * CLS_ROWS;
+    const int64_t u0 = r0 + (int64_t)blockIdx.x * (CLS_THREADS * RPT);
 #pragma unroll
-    for (int i = 0; i < CLS_RPT; ++i) {
+    for (int i = 0; i < RPT; ++i) {
         const int64_t u = u0 + (int64_t)i * CLS_THREADS + threadIdx.x;
         if (u < r1) {
             const int64_t k = indptr[u + 1] - indptr[u];
@@ -125,7 +132,7 @@ __device__ __forceinline__ bool put_long_row(int64_t u, int64_t b, int64_t k, in
     return true;
 }
 
-// One workgroup per CLS_ROWS consecutive rows of [r0, r1):
+// One workgroup per CLS_THREADS * RPT consecutive rows of [r0, r1):
 //   k = 0               X[u] = 0
 //   0 < k <= dual_max   appended to the dual list of its class: k <= 4, 5..8, else ceil(k/16) in 1..8
 //                       (row id relative to r0)
@@ -139,7 +146,7 @@ __device__ __forceinline__ bool put_long_row(int64_t u, int64_t b, int64_t k, in
 // for more long rows or segments than the workspace holds; those rows are dropped and the error flag is set.  So are, when Z
 // holds one row per entry (entry_limit = nnz, else INT64_MAX), rows with entries outside those that Gather walks, from
 // indptr[r0] to indptr[r1] and below entry_limit: an indptr that is not monotone has such rows, and Z has nothing for them.
-template <bool BF16>
+template <bool BF16, int RPT>
 __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
     const int64_t *__restrict__ indptr, int64_t r0, int64_t r1, int64_t dual_max, int d,
     void *__restrict__ X, int64_t ldx, int32_t *__restrict__ counters, LongRow *__restrict__ long_rows,
@@ -154,10 +161,10 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
     const bool by_entry = entry_limit != INT64_MAX;
     const int64_t first_entry = by_entry && indptr[r0] > 0 ? indptr[r0] : 0;
     const int64_t end_entry = by_entry && indptr[r1] < entry_limit ? indptr[r1] : entry_limit;
-    const int64_t u0 = r0 + (int64_t)blockIdx.x * CLS_ROWS;
-    int cls[CLS_RPT], pos[CLS_RPT], seg[CLS_RPT];
+    const int64_t u0 = r0 + (int64_t)blockIdx.x * (CLS_THREADS * RPT);
+    int cls[RPT], pos[RPT], seg[RPT];
 #pragma unroll
-    for (int i = 0; i < CLS_RPT; ++i) {
+    for (int i = 0; i < RPT; ++i) {
         const int64_t u = u0 + (int64_t)i * CLS_THREADS + t;  // coalesced indptr reads
         cls[i] = -1;
         pos[i] = seg[i] = 0;
@@ -181,7 +188,7 @@ __global__ __launch_bounds__(CLS_THREADS) void classify_kernel(
     if (t < 13 && cnt[t] > 0) base[t] = atomicAdd(&counters[t < 11 ? class_counter(t) : t - 11], cnt[t]);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < CLS_RPT; ++i) {
+    for (int i = 0; i < RPT; ++i) {
         if (cls[i] < 0) continue;
         if (cls[i] == 11) {
             const int64_t u = u0 + (int64_t)i * CLS_THREADS + t, b = indptr[u];
@@ -244,9 +251,9 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
     const bool by_entry = entry_limit != INT64_MAX;
     const int64_t first_entry = by_entry && indptr[r0] > 0 ? indptr[r0] : 0;
     const int64_t end_entry = by_entry && indptr[r1] < entry_limit ? indptr[r1] : entry_limit;
-    int64_t b[CLS_RPT], e[CLS_RPT];
+    int64_t b[CLS_ONE_RPT], e[CLS_ONE_RPT];
 #pragma unroll
-    for (int i = 0; i < CLS_RPT; ++i) {
+    for (int i = 0; i < CLS_ONE_RPT; ++i) {
         const int64_t u = r0 + (int64_t)i * CLS_ONE_THREADS + t;
         b[i] = e[i] = 0;
         if (u < r1) {
@@ -256,7 +263,7 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < CLS_RPT; ++i) {  // few rows are long
+    for (int i = 0; i < CLS_ONE_RPT; ++i) {  // few rows are long
         if (e[i] - b[i] > split_wanted) {
             atomicAdd(&long_stat[0], (unsigned long long)(e[i] - b[i]));
             atomicAdd(&long_stat[1], 1ull);
@@ -265,7 +272,7 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
     __syncthreads();
     const int64_t split = decide_split(long_stat, split_wanted);
 #pragma unroll
-    for (int i = 0; i < CLS_RPT; ++i) {
+    for (int i = 0; i < CLS_ONE_RPT; ++i) {
         const int64_t u = r0 + (int64_t)i * CLS_ONE_THREADS + t, k = e[i] - b[i];
         if (u >= r1) continue;
         if (b[i] < first_entry || e[i] > end_entry) {
@@ -397,11 +404,16 @@ als_status launch_solve_rows(als_ctx *ctx, const als_csr *Y, const als_table *V,
                            cap_mid, dual_lists, list_off, entry_limit, split, hint_out, hs.seq);
     } else {
         hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, counters, (long long *)long_stat);
-        const unsigned cblocks = (unsigned)((nrows + CLS_ROWS - 1) / CLS_ROWS);
-        hipLaunchKernelGGL(long_stat_kernel, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr, r0, r1, split, long_stat);
-        hipLaunchKernelGGL(bf ? classify_kernel<true> : classify_kernel<false>, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr,
-                           r0, r1, (int64_t)dual_max, V->d, X->data, X->ld, counters, long_rows, segs, mid_list, cap_mid,
-                           dual_lists, list_off, entry_limit, (const unsigned long long *)long_stat, split);
+        auto sort = [&](auto rows_per_thread) {
+            constexpr int RPT = decltype(rows_per_thread)::value;
+            const unsigned cblocks = (unsigned)((nrows + CLS_THREADS * RPT - 1) / (CLS_THREADS * RPT));
+            hipLaunchKernelGGL(long_stat_kernel<RPT>, dim3(cblocks), dim3(CLS_THREADS), 0, s, Y->indptr, r0, r1, split, long_stat);
+            hipLaunchKernelGGL((bf ? classify_kernel<true, RPT> : classify_kernel<false, RPT>), dim3(cblocks), dim3(CLS_THREADS), 0,
+                               s, Y->indptr, r0, r1, (int64_t)dual_max, V->d, X->data, X->ld, counters, long_rows, segs, mid_list,
+                               cap_mid, dual_lists, list_off, entry_limit, (const unsigned long long *)long_stat, split);
+        };
+        if (nrows <= (int64_t)ctx->num_cu * CLS_THREADS * CLS_RPT_FEW) sort(std::integral_constant<int, CLS_RPT_FEW>{});
+        else sort(std::integral_constant<int, CLS_RPT_MANY>{});
         hipLaunchKernelGGL(publish_counts_kernel, dim3(1), dim3(64), 0, s, counters, cap_mid, list_off, hint_out, hs.seq);
     }
     timer_end(ctx, s);

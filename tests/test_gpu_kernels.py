@@ -503,30 +503,28 @@ def test_rows_of_9_to_32_entries(ctx, gpu_device, d, lo, hi, dtype, alpha):
 
 
 @pytest.mark.parametrize("d,dtype", [(32, torch.float32), (64, torch.bfloat16)])
-def test_rows_are_sorted_alike_by_one_workgroup_and_by_many(ctx, gpu_device, d, dtype):
-    """8192 rows are the most that one workgroup sorts into the lists by itself.  8193 rows of every class (empty, each side of
-    the class boundaries, beyond the split threshold) in one call, and the same rows as ranges of 8192, 1 and 4097 rows: which
-    list place a row gets does not enter its result, so the bits are the same."""
-    say(f"one workgroup's lists d={d} {dtype}")
+@pytest.mark.parametrize("most", [8192, 512 * 256])
+def test_rows_are_sorted_alike_on_both_sides_of_a_line(ctx, gpu_device, d, dtype, most):
+    """8192 rows are the most that one workgroup sorts into the lists by itself, 512 per compute unit the most that are sorted two
+    a thread.  One row more, rows of every class (empty, each side of the class boundaries, beyond the split threshold) in one
+    call, and the same rows in two ranges: which list place a row gets does not enter its result, so the bits are the same."""
+    say(f"lists d={d} {dtype} {most}")
     ks = [0, 1, 4, 5, 8, 9, 16, 17, 32, 33, 48, 64, 65, 3, 2, 7]
-    k = torch.tensor(ks, device=gpu_device).repeat(513)[:8193]
-    k[[5, 1024, 4096, 8191, 8192]] = torch.tensor([513, 700, 1025, 2000, 512], device=gpu_device)
+    k = torch.tensor(ks, device=gpu_device).repeat(most // 16 + 1)[:most + 1]
+    k[[5, 1024, 4096, most - 1, most]] = torch.tensor([513, 700, 1025, 2000, 512], device=gpu_device)
     n, nnz = 3000, int(k.sum())
-    indptr = torch.zeros(8194, dtype=torch.int64, device=gpu_device)
+    indptr = torch.zeros(most + 2, dtype=torch.int64, device=gpu_device)
     indptr[1:] = torch.cumsum(k, 0)
     gen = torch.Generator(device=gpu_device).manual_seed(d)
-    Y = als.Csr(8193, n, indptr, torch.randint(0, n, (nnz,), device=gpu_device, generator=gen).to(torch.int32),
+    Y = als.Csr(most + 1, n, indptr, torch.randint(0, n, (nnz,), device=gpu_device, generator=gen).to(torch.int32),
                 torch.rand(nnz, device=gpu_device, generator=gen) + 0.5)
     H = (0.1 * torch.randn((n, d), device=gpu_device, generator=gen)).to(dtype)
     G = als.als_gramian(ctx, H)
     prm = als.make_params(0.1, 1e-2)
-    whole, parts = (torch.full((8193, d), 7.0, dtype=dtype, device=gpu_device) for _ in range(2))
+    whole, parts = (torch.full((most + 1, d), 7.0, dtype=dtype, device=gpu_device) for _ in range(2))
     als.als_solve_rows(ctx, Y, H, G, prm, whole)
-    als.als_solve_rows(ctx, Y, H, G, prm, parts, 0, 8192)
-    als.als_solve_rows(ctx, Y, H, G, prm, parts, 8192, 8193)
+    als.als_solve_rows(ctx, Y, H, G, prm, parts, 0, most)
+    als.als_solve_rows(ctx, Y, H, G, prm, parts, most, most + 1)
     als.als_status_sync(ctx)
     assert torch.equal(whole, parts)
     assert not whole[k == 0].any()
-    als.als_solve_rows(ctx, Y, H, G, prm, parts, 2048, 6145)
-    als.als_status_sync(ctx)
-    assert torch.equal(whole, parts)
