@@ -204,7 +204,7 @@ def main():
     bft = "true" if es == 2 else "false"  # the kernels' template arguments as rocprofv3 prints them
     zbt = "true" if (es == 2 and d >= 32) else "false"  # Z kept as bf16
     kernel_names = {"dual_k4": f"dual_small_kernel<{d},4,{zbt},false>", "dual_k8": f"dual_small_kernel<{d},8,{zbt},false>",
-                    "dual_k16": f"dual_rows_kernel<{d},{zbt},false>", "dual_k32": f"dual_multi_kernel<{d},2,{zbt},false>"}
+                    "dual_k16": f"dual_rows_kernel<{d},{zbt}>", "dual_k32": f"dual_multi_kernel<{d},{zbt}>"}
     for c in range(2, 8):
         kernel_names[f"dual_k{16 * (c + 1)}"] = f"dual_wide_kernel<{d},{c + 1},{zbt},false,false>"
     if args.solver == "cg" and d >= 64:  # every class runs the one-row-per-wavefront kernel with the CG solver
