@@ -224,7 +224,10 @@ template <int D, bool ZB> struct MultiStep {
             float none = 0.f;
             if (16 + c < kmax) eliminate_column<c, false>(s1, s1, y1, none, ri1, i, bad);  // beyond every row's k: identity rows
         });
-        if (bad) atomicOr(err_flag, 1);
+        // a row past the end of the list stands for the step's first entry sixteen times over (its first tile is not masked): its
+        // pivots mean nothing
+        const int rel_lo = g & 1 ? d.row.rel[1] : d.row.rel[0], rel_hi = g & 1 ? d.row.rel[3] : d.row.rel[2];
+        if (bad && (g & 2 ? rel_hi : rel_lo) >= 0) atomicOr(err_flag, 1);
 
         // ---- 4. t of both halves
         float t1 = y1 * ri1 * ri1;

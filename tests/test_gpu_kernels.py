@@ -528,3 +528,37 @@ def test_rows_are_sorted_alike_on_both_sides_of_a_line(ctx, gpu_device, d, dtype
     als.als_status_sync(ctx)
     assert torch.equal(whole, parts)
     assert not whole[k == 0].any()
+
+
+@pytest.mark.parametrize("d,dtype", [(32, torch.float32), (64, torch.float32), (128, torch.float32), (32, torch.bfloat16), (128, torch.bfloat16)])
+@pytest.mark.parametrize("walked", [False, True])
+def test_places_past_the_end_of_a_list_raise_no_flag(ctx, gpu_device, d, dtype, walked):
+    """alpha = 0 and a tiny lambda: |z|^2 about 1e9, where a system of one entry repeated is singular in fp32.  Rows of 9 to 16 and
+    of 17 and 18 distinct entries are regular; lists of every length modulo four, by the launch that small calls share and (300 000
+    empty rows more) by the launches of their own.  fp32 rows are compared too: S is off by 2^-16 of its trace at most."""
+    say(f"past the end of a list d={d} {dtype} walked={walked}")
+    gen = torch.Generator().manual_seed(d)
+    n, lam = 4000, 1e-10
+    H = (torch.randn((n, d), generator=gen) * 0.3 / np.sqrt(d)).to(dtype)
+    G = torch.zeros((d, d), device=gpu_device)
+    some = 17_000 if walked else 4
+    for more in range(4):
+        lens = torch.cat([torch.full((some + more,), 17), torch.tensor([18]), torch.full((1 + more,), 9 + 2 * more),
+                          torch.zeros(300_000 if walked else 0, dtype=torch.int64)])
+        ptr = torch.zeros(len(lens) + 1, dtype=torch.int64)
+        ptr[1:] = torch.cumsum(lens, 0)
+        nnz = int(ptr[-1])
+        start = torch.repeat_interleave(torch.randint(0, n - 18, (len(lens),), generator=gen), lens)
+        idx = (start + torch.arange(nnz) - torch.repeat_interleave(ptr[:-1], lens)).to(torch.int32)  # distinct in a row
+        X = torch.empty((len(lens), d), device=gpu_device, dtype=dtype)
+        Y = als.Csr(len(lens), n, ptr.to(gpu_device), idx.to(gpu_device))
+        als.als_solve_rows(ctx, Y, H.to(gpu_device), G, als.make_params(0.0, lam), X)
+        als.als_status_sync(ctx)
+        got = f64(X)
+        assert np.isfinite(got).all()
+        if dtype == torch.float32:
+            for r in range(some, some + 2 * more + 2):
+                v = f64(H)[idx[ptr[r]:ptr[r + 1]].numpy()]
+                s = lam * np.eye(len(v)) + v @ v.T
+                ref, ev = v.T @ np.linalg.solve(s, np.ones(len(v))), np.linalg.eigvalsh(s)
+                assert np.linalg.norm(got[r] - ref) <= 4 * 2.0 ** -16 * np.trace(s) / ev[0] * np.linalg.norm(ref), (r, len(v))
