@@ -34,7 +34,7 @@ __global__ __launch_bounds__(64) void dual_few_kernel(const int64_t *__restrict_
     const int step = b - few.start[c], count = *few.count[c];
     const int32_t *list = few.list[c];
     // lists 0..7: ceil(k / 16) - 1, lists 8 and 9: k <= 4 and 5 <= k <= 8
-    if (step >= (count + FEW_ROWS[c] - 1) / FEW_ROWS[c]) return;
+    if (step >= list_steps(count, FEW_ROWS[c])) return;
     auto wide = [&](auto kt) {
         constexpr int KT = decltype(kt)::value;
         if constexpr (16 * KT <= (D == 128 ? 128 : 64) && D >= 64)

@@ -20,12 +20,13 @@ __global__ __launch_bounds__(64) void dual_small_kernel(const int64_t *__restric
     extern __shared__ float lds[];
     constexpr int NR = SmallCfg<D, G>::NR;
     const int count = *count_ptr;
+    const int steps = list_steps(count, NR);  // compared with instead of blk * NR, which does not fit beyond the end of a list of 2^31 rows
     int blk = first_blk + blockIdx.x;
     if constexpr (!LOOP) {
-        blk = xcd_step(blk, gridDim.x, (count + NR - 1) / NR);
-        if (blk * NR < count) dual_small_step<D, G, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
+        blk = xcd_step(blk, gridDim.x, steps);
+        if (blk < steps) dual_small_step<D, G, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
     } else {
-        for (; blk * NR < count; blk += gridDim.x) {
+        for (; blk < steps; blk += gridDim.x) {
             dual_small_step<D, G, ZB>(opaque(indptr), opaque(indices), opaque(values), opaque(Z), opaque(R), opaque(ldr), opaque(r0),
                               opaque(list), opaque(count), opaque(err_flag), blk, opaque(lds));
             wave_sync();  // the next step reuses the LDS buffers

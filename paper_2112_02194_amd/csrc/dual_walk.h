@@ -78,9 +78,9 @@ __device__ __forceinline__ void walk_steps(const int64_t *__restrict__ indptr, c
                                            const float *__restrict__ values, const void *__restrict__ Z, float *__restrict__ R,
                                            int64_t ldr, int64_t r0, const int32_t *__restrict__ list, int count,
                                            int32_t *__restrict__ err_flag, float *lds) {
-    const int steps = (count + 3) / 4, part = (steps + 7) / 8, stride = gridDim.x / 8;
-    const int first = (blockIdx.x & 7) * part, end = first + part < steps ? first + part : steps;
-    int blk = first + (blockIdx.x >> 3);
+    const WalkRange range = walk_range(blockIdx.x, gridDim.x, count);
+    const int end = range.end, stride = range.stride;
+    int blk = range.blk;
     if (blk >= end) return;
     S::init(lds, opaque_tid());
     R += r0 * ldr;

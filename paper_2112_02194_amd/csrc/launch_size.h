@@ -34,6 +34,9 @@ inline StepGrid step_grid(int num_cu, int threads, int64_t capacity, int64_t hin
     return g;
 }
 
+// Steps of `rows` rows that a list of `count` rows takes, for every count (count + rows - 1 does not fit near 2^31 rows).
+constexpr int list_steps(int count, int rows) { return count / rows + (count % rows != 0); }
+
 // Step that workgroup `b` of a launch of `grid` workgroups takes of a list of `steps` steps.  Workgroups go to the eight
 // dies (XCDs) in turn, each with an L2 of its own, so the steps are dealt out in eight contiguous parts, one per die, each
 // in order: neighbouring rows of a list then meet in one L2.  Rows of a link matrix that belong to one host share most of
@@ -44,6 +47,14 @@ inline StepGrid step_grid(int num_cu, int threads, int64_t capacity, int64_t hin
 constexpr int xcd_step(int b, int grid, int steps) {
     const int chunk = (steps < grid ? steps : grid) >> 3;
     return b < 8 * chunk ? (b & 7) * chunk + (b >> 3) : b;
+}
+
+// What workgroup `b` of `grid` (a multiple of eight) takes of a list of `count` rows walked four at a time: the steps blk,
+// blk + stride, .. below end.  Each die takes a contiguous eighth of the list, its workgroups in turn.
+struct WalkRange { int blk, end, stride; };
+constexpr WalkRange walk_range(int b, int grid, int count) {
+    const int steps = list_steps(count, 4), part = list_steps(steps, 8), first = (b & 7) * part;
+    return {first + (b >> 3), first + part < steps ? first + part : steps, grid / 8};
 }
 
 // Workgroups (one wavefront each) that walk a list, each in strides of the grid: a multiple of eight, for any list.  Four steps each

@@ -16,11 +16,16 @@ def step_grid(tmp_path_factory):
                    'extern "C" void grid(int cu, int threads, int64_t cap, int64_t hint, int per_cu, int64_t blind, unsigned *out) {\n'
                    '    const als::StepGrid g = als::step_grid(cu, threads, cap, hint, per_cu, blind); out[0] = g.known; out[1] = g.rest; }\n'
                    'extern "C" unsigned walk(int64_t resident, int64_t cap, int64_t hint) { return als::walk_grid(resident, cap, hint); }\n'
-                   'extern "C" int xcd(int b, int grid, int steps) { return als::xcd_step(b, grid, steps); }\n')
+                   'extern "C" int xcd(int b, int grid, int steps) { return als::xcd_step(b, grid, steps); }\n'
+                   'extern "C" int list_steps(int count, int rows) { return als::list_steps(count, rows); }\n'
+                   'extern "C" void walk_range(int b, int grid, int count, int *out) {\n'
+                   '    const als::WalkRange w = als::walk_range(b, grid, count); out[0] = w.blk; out[1] = w.end; out[2] = w.stride; }\n')
     subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, "-o", str(lib), str(src)])
     walk_grid.f = ctypes.CDLL(str(lib)).walk
     walk_grid.f.argtypes, walk_grid.f.restype = [ctypes.c_int64] * 3, ctypes.c_uint
     xcd.f = ctypes.CDLL(str(lib)).xcd
+    list_steps.f = ctypes.CDLL(str(lib)).list_steps
+    walk_range.f = ctypes.CDLL(str(lib)).walk_range
     f = ctypes.CDLL(str(lib)).grid
     f.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_void_p]
 
@@ -33,6 +38,16 @@ def step_grid(tmp_path_factory):
 
 def xcd(b, grid, steps):
     return xcd.f(b, grid, steps)
+
+
+def list_steps(count, rows):
+    return list_steps.f(count, rows)
+
+
+def walk_range(b, grid, count):
+    out = (ctypes.c_int * 3)()
+    walk_range.f(b, grid, count, out)
+    return tuple(out)
 
 
 def walk_grid(resident, cap, hint):
@@ -85,3 +100,26 @@ def test_a_walked_list_gets_enough_workgroups_and_no_more_than_a_launch_holds(st
             steps = cap if hint < 0 else min(cap, hint)
             assert g >= min(cap, 3072) and (g >= steps / 4 or g * 64 >= (1 << 32) - 512)  # at most four steps each, if a launch can hold that
             assert g <= max(steps / 4, min(cap, 3072)) + 8
+
+
+@pytest.mark.parametrize("rows", [1, 4, 8, 16])
+def test_steps_of_a_list_up_to_the_longest_range(step_grid, rows):
+    """count + rows - 1 would be negative for the longest lists, which a kernel then takes for empty ones."""
+    for count in [0, 1, rows - 1, rows, rows + 1, 1000, (1 << 31) - 1 - rows, (1 << 31) - rows, (1 << 31) - 2, (1 << 31) - 1]:
+        assert list_steps(count, rows) == -(-count // rows)
+
+
+@pytest.mark.parametrize("count", [0, 1, 4, 5, 31, 32, 33, 100_003, (1 << 31) - 4, (1 << 31) - 3, (1 << 31) - 1])
+def test_a_walk_covers_its_list_once(step_grid, count):
+    """The parts of the eight dies join without a gap, and the workgroups of a die take every place of a stride."""
+    steps = -(-count // 4)
+    for grid in [8, 64, 1 << 20, walk_grid(3072, steps, -1) or 8]:
+        end = 0
+        for die in range(8):
+            first, stop, stride = walk_range(die, grid, count)
+            assert first == min(end, steps) or first >= stop
+            end = max(end, stop)
+            assert stride == grid // 8
+            for w in {0, 1, stride - 1} & set(range(stride)):
+                assert walk_range(die + 8 * w, grid, count) == (first + w, stop, stride)
+        assert end == steps
