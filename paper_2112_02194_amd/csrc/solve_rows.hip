@@ -45,7 +45,8 @@ constexpr int CLS_THREADS = 256;
 constexpr int CLS_RPT_MANY = 8, CLS_RPT_FEW = 2;
 // Up to this many rows one large workgroup does what takes four dependent launches otherwise (clearing, the long rows' sums, the
 // lists, their lengths for the host).  Epoch of 2000 x 1500 113 -> 95 us, 256 folded-in rows (d = 128) 85.7 -> 80.4 us; eight
-// rows a thread are all it can hold in registers.
+// rows a thread are all it can hold in registers.  At the line, 8192 rows of 12 entries / without entries, one launch against
+// four with two rows a thread: d = 16 35 / 31 against 38 / 38 us a call, d = 128 101 / 89 against 100 / 93 us.
 constexpr int CLS_ONE_THREADS = 1024, CLS_ONE_RPT = 8, CLS_ONE_ROWS = CLS_ONE_THREADS * CLS_ONE_RPT;
 struct ListOffsets { int64_t v[11]; };  // start of each dual class list (and the end of the last), passed by value
 
@@ -235,6 +236,19 @@ __global__ void publish_counts_kernel(int32_t *__restrict__ counters, int64_t ca
     }
 }
 
+// The rows u0 + j of X with bit j of the wavefront-uniform `which` become zero, 16 bytes a lane, as many rows at a time as the
+// wavefront spans.  (With one thread per row, one element after the other, as in classify_kernel, a call with 8192 empty rows took 574 us
+// for d = 128, fp32, and 75 us for d = 16: all of them wait for one compute unit.  So it takes 89 and 31 us.)
+template <bool BF16> __device__ __forceinline__ void zero_rows(void *X, int64_t ldx, int d, int64_t u0, unsigned long long which) {
+    constexpr int ES = BF16 ? 2 : 4;
+    const int per_row = d * ES / 16, lane = threadIdx.x & 63, at_once = 64 / per_row;  // lanes per row: 2 to 32
+    for (int j = 0; which && j < 64; j += at_once) {
+        const int64_t u = u0 + j + lane / per_row;
+        if (which >> (j + lane / per_row) & 1)
+            *(float4 *)((char *)X + u * ldx * ES + 16 * (lane % per_row)) = make_float4(0.f, 0.f, 0.f, 0.f);  // (rows are 16-byte aligned)
+    }
+}
+
 // The four kernels above in one, for at most CLS_ONE_ROWS rows: one workgroup, everything counted in LDS.  The same lists,
 // segments, counters and hint.
 template <bool BF16>
@@ -271,6 +285,7 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
     }
     __syncthreads();
     const int64_t split = decide_split(long_stat, split_wanted);
+    unsigned empty = 0;  // bit i: this thread's row i
 #pragma unroll
     for (int i = 0; i < CLS_ONE_RPT; ++i) {
         const int64_t u = r0 + (int64_t)i * CLS_ONE_THREADS + t, k = e[i] - b[i];
@@ -278,7 +293,7 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
         if (b[i] < first_entry || e[i] > end_entry) {
             atomicOr(&n[2], 2);
         } else if (k <= 0) {
-            for (int c = 0; c < d; ++c) store_elem<BF16>(X, u * ldx + c, 0.f);
+            empty |= 1u << i;
         } else if (k > split) {
             const int slot = atomicAdd(&n[0], 1), first = atomicAdd(&n[1], segments_of(k, split));
             if (!put_long_row(u, b[i], k, split, slot, first, long_rows, segs)) atomicOr(&n[2], 2);
@@ -290,6 +305,9 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
             else atomicOr(&n[2], 2);
         }
     }
+#pragma unroll 1
+    for (int i = 0; i < CLS_ONE_RPT; ++i)
+        zero_rows<BF16>(X, ldx, d, r0 + (int64_t)i * CLS_ONE_THREADS + (t & ~63), __ballot(empty >> i & 1));
     __syncthreads();
     if (t < 16 && t != 4) {  // [4] is the CSR check flag
         const int32_t flag = counters[2] | n[2];  // the error flag is sticky
