@@ -111,8 +111,12 @@ __device__ __forceinline__ int row_class(int64_t k, int64_t dual_max) {
 // where the length of list `cls` stands among the counters
 __device__ __forceinline__ int class_counter(int cls) { return cls == 0 ? 3 : (cls <= 8 ? 8 + cls - 1 : cls - 4); }
 
+// a / b rounded up, for 0 < a and 0 < b < 2^31 (a 64-bit division takes about five times the instructions of a 32-bit one)
+__device__ __forceinline__ int64_t divide_up(int64_t a, int64_t b) {
+    return a <= 0x7fffffff ? (int64_t)(((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b) : (a + b - 1) / b;
+}
 __device__ __forceinline__ int segments_of(int64_t k, int64_t split) {
-    const int64_t nseg = (k + split - 1) / split;
+    const int64_t nseg = divide_up(k, split);
     return (int)(nseg < MAX_SEGS_PER_ROW ? nseg : MAX_SEGS_PER_ROW);
 }
 // Row u with k > split entries from b on becomes long row `slot` with its balanced segments from `first` on; false where they
@@ -120,7 +124,7 @@ __device__ __forceinline__ int segments_of(int64_t k, int64_t split) {
 __device__ __forceinline__ bool put_long_row(int64_t u, int64_t b, int64_t k, int64_t split, int slot, int first,
                                              LongRow *__restrict__ long_rows, Segment *__restrict__ segs) {
     const int nseg = segments_of(k, split);
-    const int64_t len = (k + nseg - 1) / nseg, e = b + k;
+    const int64_t len = divide_up(k, nseg), e = b + k;
     if (slot >= SEG_CAPACITY / 2 || first + nseg > SEG_CAPACITY) return false;
     long_rows[slot].row = u;
     long_rows[slot].seg_first = first;
@@ -258,10 +262,10 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
     Segment *__restrict__ segs, int32_t *__restrict__ mid_list, int64_t cap_mid, int32_t *__restrict__ dual_lists,
     ListOffsets list_off, int64_t entry_limit, int64_t split_wanted, int32_t *__restrict__ hint, uint32_t seq) {
     __shared__ int32_t n[16];  // as in `counters`; [2]: flag bits set here
-    __shared__ unsigned long long long_stat[2];
+    __shared__ unsigned long long long_stat;  // entries of the rows beyond the requested split
     const int t = threadIdx.x;
     if (t < 16) n[t] = 0;
-    if (t < 2) long_stat[t] = 0;
+    if (t == 0) long_stat = 0;
     const bool by_entry = entry_limit != INT64_MAX;
     const int64_t first_entry = by_entry && indptr[r0] > 0 ? indptr[r0] : 0;
     const int64_t end_entry = by_entry && indptr[r1] < entry_limit ? indptr[r1] : entry_limit;
@@ -276,16 +280,14 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
         }
     }
     __syncthreads();
+    unsigned long long beyond = 0;
 #pragma unroll
-    for (int i = 0; i < CLS_ONE_RPT; ++i) {  // few rows are long
-        if (e[i] - b[i] > split_wanted) {
-            atomicAdd(&long_stat[0], (unsigned long long)(e[i] - b[i]));
-            atomicAdd(&long_stat[1], 1ull);
-        }
-    }
+    for (int i = 0; i < CLS_ONE_RPT; ++i) beyond += e[i] - b[i] > split_wanted ? (unsigned long long)(e[i] - b[i]) : 0ull;
+    if (beyond) atomicAdd(&long_stat, beyond);
     __syncthreads();
-    const int64_t split = decide_split(long_stat, split_wanted);
-    unsigned empty = 0;  // bit i: this thread's row i
+    const int64_t split = decide_split(&long_stat, split_wanted);
+    unsigned empty = 0, longs = 0;  // bit i: this thread's row i
+    int nsegs = 0;                  // segments of its long rows
 #pragma unroll
     for (int i = 0; i < CLS_ONE_RPT; ++i) {
         const int64_t u = r0 + (int64_t)i * CLS_ONE_THREADS + t, k = e[i] - b[i];
@@ -295,8 +297,8 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
         } else if (k <= 0) {
             empty |= 1u << i;
         } else if (k > split) {
-            const int slot = atomicAdd(&n[0], 1), first = atomicAdd(&n[1], segments_of(k, split));
-            if (!put_long_row(u, b[i], k, split, slot, first, long_rows, segs)) atomicOr(&n[2], 2);
+            longs |= 1u << i;
+            nsegs += segments_of(k, split);
         } else {
             const int c = row_class(k, dual_max);
             const int64_t at = atomicAdd(&n[class_counter(c)], 1);
@@ -305,9 +307,23 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
             else atomicOr(&n[2], 2);
         }
     }
+    // what most calls have few of, in a loop of its own (unrolled with the rest it would cost the kernel its registers)
+    int slot = 0, first = 0;
+    if (longs) {
+        slot = atomicAdd(&n[0], __popc(longs));
+        first = atomicAdd(&n[1], nsegs);
+    }
 #pragma unroll 1
-    for (int i = 0; i < CLS_ONE_RPT; ++i)
-        zero_rows<BF16>(X, ldx, d, r0 + (int64_t)i * CLS_ONE_THREADS + (t & ~63), __ballot(empty >> i & 1));
+    for (int i = 0; __any((longs | empty) >> i); ++i) {
+        const int64_t u = r0 + (int64_t)i * CLS_ONE_THREADS + t;
+        if (longs >> i & 1) {
+            const int64_t from = indptr[u], k = indptr[u + 1] - from;
+            if (!put_long_row(u, from, k, split, slot, first, long_rows, segs)) atomicOr(&n[2], 2);
+            ++slot;
+            first += segments_of(k, split);
+        }
+        zero_rows<BF16>(X, ldx, d, u - (t & 63), __ballot(empty >> i & 1));
+    }
     __syncthreads();
     if (t < 16 && t != 4) {  // [4] is the CSR check flag
         const int32_t flag = counters[2] | n[2];  // the error flag is sticky
