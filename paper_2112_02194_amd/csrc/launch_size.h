@@ -34,8 +34,8 @@ inline StepGrid step_grid(int num_cu, int threads, int64_t capacity, int64_t hin
     return g;
 }
 
-// Steps of `rows` rows that a list of `count` rows takes, for every count (count + rows - 1 does not fit near 2^31 rows).
-constexpr int list_steps(int count, int rows) { return count / rows + (count % rows != 0); }
+// Steps of `rows` rows that a list of `count` rows takes, for every count (near 2^31 rows the sum only fits unsigned).
+constexpr int list_steps(int count, int rows) { return (int)(((unsigned)count + (unsigned)rows - 1u) / (unsigned)rows); }
 
 // Step that workgroup `b` of a launch of `grid` workgroups takes of a list of `steps` steps.  Workgroups go to the eight
 // dies (XCDs) in turn, each with an L2 of its own, so the steps are dealt out in eight contiguous parts, one per die, each
@@ -52,9 +52,9 @@ constexpr int xcd_step(int b, int grid, int steps) {
 // What workgroup `b` of `grid` (a multiple of eight) takes of a list of `count` rows walked four at a time: the steps blk,
 // blk + stride, .. below end.  Each die takes a contiguous eighth of the list, its workgroups in turn.
 struct WalkRange { int blk, end, stride; };
-constexpr WalkRange walk_range(int b, int grid, int count) {
-    const int steps = list_steps(count, 4), part = list_steps(steps, 8), first = (b & 7) * part;
-    return {first + (b >> 3), first + part < steps ? first + part : steps, grid / 8};
+constexpr WalkRange walk_range(unsigned b, unsigned grid, int count) {
+    const int steps = list_steps(count, 4), part = list_steps(steps, 8), first = (int)(b & 7) * part;
+    return {first + (int)(b >> 3), first + part < steps ? first + part : steps, (int)(grid / 8)};
 }
 
 // Workgroups (one wavefront each) that walk a list, each in strides of the grid: a multiple of eight, for any list.  Four steps each
