@@ -11,12 +11,19 @@
 
 namespace als {
 
+// 16 < k <= 32 keeps the tiles of its four rows in registers in the launch of its own.  This kernel takes the registers and LDS of its
+// largest class, and with fp32 Z those tiles took it from 87 to 166 registers at d = 32 and from 105 to 240 at d = 64, for all classes:
+// 300k rows of 3 entries (d = 32) 115 -> 122 us, 40k rows of 40 / 56 entries (d = 64) 221 / 303 -> 244 / 325 us.  With a second gather
+// and one chunk of the tiles under way, 122 registers either way: 113 and 205 / 282 us; 40k rows of 25 entries 76 -> 76 us (d = 32) and
+// 120 -> 124 us (d = 64), the price.
+template <bool ZB> constexpr bool few_keeps_tiles() { return ZB; }
+
 template <int D, bool ZB> constexpr int few_lds_floats() {
     int n = RowsCfg<D, ZB>::LDS_FLOATS;
     auto take = [&](int x) { n = x > n ? x : n; };
     take(SmallCfg<D, 4>::LDS_FLOATS);
     take(SmallCfg<D, 8>::LDS_FLOATS);
-    if constexpr (D >= 32) take(MultiCfg<D, ZB>::LDS_FLOATS);
+    if constexpr (D >= 32) take(MultiCfg<D, ZB, few_keeps_tiles<ZB>()>::LDS_FLOATS);
     if constexpr (D == 64) take(WideCfg<D, 4>::LDS_FLOATS);
     if constexpr (D == 128) take(WideCfg<D, 8>::LDS_FLOATS);
     return n;
@@ -43,7 +50,7 @@ __global__ __launch_bounds__(64) void dual_few_kernel(const int64_t *__restrict_
     switch (c) {  // uniform
         case 0: dual_rows_step<D, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, step, lds); break;
         case 1:
-            if constexpr (D >= 32) dual_multi_step<D, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, step, lds);
+            if constexpr (D >= 32) dual_multi_step<D, ZB, few_keeps_tiles<ZB>()>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, step, lds);
             break;
         case 2: wide(std::integral_constant<int, 3>{}); break;
         case 3: wide(std::integral_constant<int, 4>{}); break;

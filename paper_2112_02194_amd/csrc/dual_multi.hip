@@ -18,7 +18,7 @@ __global__ __launch_bounds__(64) void dual_multi_kernel(const int64_t *__restric
 template <int D, bool ZB>
 static void launch_multi_typed(const als_csr *Y, const void *Z, float *R, int64_t ldr, int64_t r0, const int32_t *list,
                               const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s) {
-    constexpr size_t lds_bytes = MultiCfg<D, ZB>::LDS_FLOATS * sizeof(float);
+    constexpr size_t lds_bytes = MultiStep<D, ZB>::C::LDS_FLOATS * sizeof(float);
     static const int resident = resident_waves(dual_multi_kernel<D, ZB>, lds_bytes, w.num_cu);
     hipLaunchKernelGGL((dual_multi_kernel<D, ZB>), dim3(walk_grid(resident, w.capacity, w.hint)), dim3(64), lds_bytes, s, Y->indptr,
                        Y->indices, Y->values, Z, R, ldr, r0, list, count_dev, err);

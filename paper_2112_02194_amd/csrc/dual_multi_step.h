@@ -32,24 +32,30 @@ namespace als {
 
 // LDS of one wavefront: P holds four 16 x 16 tiles (A, then L, then C, then t), U the stage of two tiles of entries and later
 // four tiles again (B); a block of zeros for slots beyond a row's k, the ids of the second gather.
-template <int D, bool ZB> struct MultiCfg {
-    static constexpr int RB = D * ZT<ZB>::ES, CB = RB < 256 ? RB : 256, NCH = RB / CB;
+// KEEP: rows of up to 256 bytes stay in registers.
+template <int D, bool ZB, bool KEEP> struct MultiCfg {
+    static constexpr int RB = D * ZT<ZB>::ES, CB = RB > 256 ? 256 : (KEEP || RB < 128 ? RB : 128), NCH = RB / CB;
     using PG = PieceGather<CB>;
     static constexpr int K = 32, TILE = TILE_FLOATS;
     static constexpr int OFF_P = 0, OFF_Q = 4 * TILE, U = 2 * PG::STAGE_FLOATS > 4 * TILE ? 2 * PG::STAGE_FLOATS : 4 * TILE;
     static constexpr int OFF_ZERO = OFF_Q + U, OFF_ID = OFF_ZERO + PG::ZERO_FLOATS;
-    // what is loaded at a time: the chunk h of both tiles of row p is unit p * NCH + h.  Rows of up to 256 bytes: all units are
-    // loaded at once (128 registers at most) and stay in registers until r = Z_I^T t is formed from them, so nothing is gathered
-    // twice.  Longer ones (fp32, d = 128): two units are under way.
-    static constexpr bool RES = NCH == 1;
+    // what is loaded at a time: the chunk h of both tiles of row p is unit p * NCH + h.  RES: all units are loaded at once (128
+    // registers at most) and stay in registers until r = Z_I^T t is formed from them, so nothing is gathered twice.  Otherwise
+    // (fp32 with d = 128, whose rows are longer, and fp32 in the launch that small calls share, see dual_few.hip) two units are under way.
+    static constexpr bool RES = KEEP && RB <= 256;
     static constexpr int UNITS = 4 * NCH, DEPTH = RES ? UNITS : 2;
     static constexpr int LDS_FLOATS = OFF_ID + (RES ? 0 : 4 * K);
     static constexpr int IDR = 2 * PG::N <= PG::IDS ? 1 : 2;  // id registers per row
+    // where t and the id of entry e stand; with rows of up to 256 bytes the entries that a lane adds up stand side by side, in the
+    // order in which RES has them, so that both forms have the same bits
+    static constexpr bool SIDE = RB <= 256;
+    static constexpr int PER_LANE = 2 * RowGather<D, ZB>::N;
+    static __device__ __forceinline__ constexpr int slot(int e) { return SIDE ? e % RowGather<D, ZB>::EPI * PER_LANE + e / RowGather<D, ZB>::EPI : e; }
 };
 
 // (the members are what walk_steps and single_step want, see dual_walk.h)
-template <int D, bool ZB> struct MultiStep {
-    using C = MultiCfg<D, ZB>;
+template <int D, bool ZB, bool KEEP = true> struct MultiStep {
+    using C = MultiCfg<D, ZB, KEEP>;
     using PG = typename C::PG;
     static constexpr int NIDS = 4 * C::IDR, N = PG::N, EPI = PG::EPI;
 
@@ -87,7 +93,9 @@ template <int D, bool ZB> struct MultiStep {
                     constexpr int t = decltype(tt)::value, s = decltype(ss)::value;
                     // instructions that only meet slots beyond the row's k are left out (the first tile is full: k > 16)
                     if (t == 0 || 16 + s * EPI < k[p]) {
-                        const int32_t id = C::IDR == 1 ? PG::template bcast_id<t * N + s>(idv[p]) : PG::template bcast_id<s>(idv[2 * p + t]);
+                        int32_t id;
+                        if constexpr (C::IDR == 1) id = PG::template bcast_id<t * N + s>(idv[p]);
+                        else id = PG::template bcast_id<s>(idv[2 * p + t]);
                         z[unit % C::DEPTH][t][s] = *(const floatx4 *)(zlane + (int64_t)id * C::RB + h * C::CB);
                     }
                 });
@@ -120,7 +128,7 @@ template <int D, bool ZB> struct MultiStep {
         if constexpr (!C::RES) {
             int32_t *idl = (int32_t *)(lds + C::OFF_ID);
 #pragma unroll
-            for (int n = 0; n < NIDS; ++n) idl[n / C::IDR * K + id_entry(lane, n % C::IDR)] = idv[n];
+            for (int n = 0; n < NIDS; ++n) idl[n / C::IDR * K + C::slot(id_entry(lane, n % C::IDR))] = idv[n];
         }
         float *mfma_at = lds + tile_block(a, q);     // MFMA view: row a, columns 4 q .. of the first system's tile
         char *stage = (char *)(lds + C::OFF_Q);
@@ -249,8 +257,8 @@ template <int D, bool ZB> struct MultiStep {
         if constexpr (C::RES) {
             // ---- 5. r = Z_I^T t from the registers of step 1, four (bf16: eight) columns per lane
             float *tb = lds + C::OFF_P;  // t of the entries of one lane side by side
-            tb[g * K + i % EPI * 2 * N + i / EPI] = t0;
-            tb[g * K + i % EPI * 2 * N + N + i / EPI] = t1;
+            tb[g * K + C::slot(i)] = t0;
+            tb[g * K + C::slot(i) + C::slot(16)] = t1;
             wave_sync();
             constexpr int NV = ZB ? 2 : 1;
             floatx4 rv[4][NV];
@@ -293,8 +301,8 @@ template <int D, bool ZB> struct MultiStep {
         if constexpr (!C::RES) {
         const int32_t *ids = (const int32_t *)(lds + C::OFF_ID);
         float *tbuf = lds + C::OFF_P;
-        tbuf[g * K + i] = t0;
-        tbuf[g * K + 16 + i] = t1;
+        tbuf[g * K + C::slot(i)] = t0;
+        tbuf[g * K + C::slot(i) + C::slot(16)] = t1;
         wave_sync();
 
         // ---- 5. r = Z_I^T t (second gather of the row's entries): 16 bytes of an entry per lane, so that one instruction takes
@@ -304,7 +312,8 @@ template <int D, bool ZB> struct MultiStep {
         {
             using GC = GatherCols<D>;
             constexpr int EPL = 4, EPR = EPL * GC::EPI;
-            const int mine = EPL * (lane / GC::LPR);
+            // round e0 / EPR takes the entries e0 .. e0 + EPR - 1
+            const int mine = (C::SIDE ? C::PER_LANE : EPL) * (lane / GC::LPR);
             const float *col = (const float *)Z + 4 * (lane % GC::LPR);
             floatx4 rv[4][1];
 #pragma unroll
@@ -316,8 +325,9 @@ template <int D, bool ZB> struct MultiStep {
                 floatv te[4];
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
-                    id[p] = *(const intv *)(ids + p * K + e0 + mine);
-                    te[p] = *(const floatv *)(tbuf + p * K + e0 + mine);
+                    const int at = p * K + mine + (C::SIDE ? e0 / GC::EPI : e0);
+                    id[p] = *(const intv *)(ids + at);
+                    te[p] = *(const floatv *)(tbuf + at);
                 }
                 floatx4 zz[4][EPL];
 #pragma unroll
@@ -343,13 +353,13 @@ template <int D, bool ZB> struct MultiStep {
     }
 };
 
-template <int D, bool ZB>
+template <int D, bool ZB, bool KEEP>
 __device__ __forceinline__ void dual_multi_step(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                 const float *__restrict__ values, const void *__restrict__ Z,
                                                 float *__restrict__ R, int64_t ldr, int64_t r0,
                                                 const int32_t *__restrict__ list, int count,
                                                 int32_t *__restrict__ err_flag, int blk, float *lds) {
-    single_step<MultiStep<D, ZB>>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
+    single_step<MultiStep<D, ZB, KEEP>>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
 }
 
 }  // namespace als

@@ -340,7 +340,8 @@ def test_primal_rows_beyond_a_launch_hint_that_is_too_small(gpu_device, d, dtype
 @pytest.mark.parametrize("d,dtype", [(16, torch.float32), (32, torch.float32), (32, torch.bfloat16), (64, torch.float32),
                                      (128, torch.float32), (128, torch.bfloat16)])
 def test_dual_rows_beyond_a_launch_hint_that_is_too_small(gpu_device, d, dtype):
-    """The same for every dual class: 8192 workgroups walk the steps (of 16, 8, 4 and 1 rows) that no hint announced."""
+    """The same for every dual class: 8192 workgroups walk the steps (of 16, 8 and 1 rows) that no hint announced; rows of 9 to 32 entries have
+    one kernel, whose wavefronts walk about thirty steps of four rows each instead of four."""
     say(f"hint too small: dual classes d={d} {dtype}")
     counts = {3: 140_000, 7: 70_000, 13: 36_000}
     if d >= 32:
@@ -656,3 +657,37 @@ def test_long_rows_are_cut_as_fast_in_one_workgroup_as_in_many(ctx, gpu_device):
         best.append(_fastest_call(ctx, Y, H, G, X))
     say(f"us {best}")
     assert best[0] <= 1.25 * best[1], best
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_classes_in_launches_of_their_own_and_in_a_common_one(ctx, gpu_device, d, dtype):
+    """300 003 rows have lists for launches of their own (walked lists, tiles kept in registers), 15 000 of them share one launch (single
+    steps, 16 < k <= 32 in fp32 with a second gather): the same labelled rows both ways, bit for bit.  Some rows are compared with fp64."""
+    say(f"own and common launches d={d} {dtype}")
+    rows, part, n, alpha, lam = 300_003, 15_000, 5000, 0.1, 1e-2
+    gen = torch.Generator(device=gpu_device).manual_seed(d)
+    rnd = lambda lo, hi, size: torch.randint(lo, hi, (size,), device=gpu_device, generator=gen)
+    lens = torch.where(rnd(0, 4, rows) == 0, rnd(17, 33, rows), rnd(0, 17, rows))
+    lens = torch.where(rnd(0, 40, rows) == 0, rnd(33, 160, rows), lens)
+    indptr = torch.zeros(rows + 1, dtype=torch.int64, device=gpu_device)
+    indptr[1:] = torch.cumsum(lens, 0)
+    nnz = int(indptr[-1])
+    Y = als.Csr(rows, n, indptr, rnd(0, n, nnz).to(torch.int32), torch.randn(nnz, device=gpu_device, generator=gen))
+    H = (torch.randn((n, d), device=gpu_device, generator=gen) * 0.3 / np.sqrt(d)).to(dtype)
+    G, prm = als.als_gramian(ctx, H), als.make_params(alpha, lam)
+    whole, parts = (torch.full((rows, d), 7.0, device=gpu_device, dtype=dtype) for _ in range(2))
+    als.als_solve_rows(ctx, Y, H, G, prm, whole)
+    for r0 in range(0, rows, part):
+        als.als_solve_rows(ctx, Y, H, G, prm, parts, r0, min(rows, r0 + part))
+    als.als_status_sync(ctx)
+    assert torch.equal(whole, parts)
+    B, h = alpha * f64(G) + lam * np.eye(d), f64(H)
+    for r in range(0, rows, 3001):
+        at = slice(int(indptr[r]), int(indptr[r + 1]))
+        v, y = h[Y.indices[at].cpu().numpy()], f64(Y.values[at])
+        ref = np.linalg.solve(B + v.T @ v, v.T @ y)
+        # the entries of S are off by 2^-16 |z|^2 (fp32) or, as Z is rounded, 2^-8 |z|^2 (bf16), and S has no eigenvalue below 1
+        z2 = np.max(np.sum(v * np.linalg.solve(B, v.T).T, axis=1), initial=0.0)
+        unit = 2.0 ** -16 if dtype == torch.float32 else 2.0 ** -8
+        assert np.linalg.norm(f64(whole[r]) - ref) <= unit * (1 + len(v) * z2) * np.linalg.norm(ref), (r, len(v))
