@@ -48,18 +48,6 @@ template <int B, int E, class F> __device__ __forceinline__ void static_for(F &&
     }
 }
 
-// Value of lane C of this lane's group of GW consecutive lanes (GW = 16: DPP row broadcast,
-// GW = 32: LDS-crossbar swizzle, GW = 64: scalar read of the lane).
-template <int GW, int C> __device__ __forceinline__ float group_bcast(float x) {
-    if constexpr (GW == 16) {
-        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + C, 0xf, 0xf, true));
-    } else if constexpr (GW == 32) {
-        return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), C << 5));
-    } else {
-        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), C));
-    }
-}
-
 // ---------------------------------------------------------------------------------------------- fused broadcasts
 // acc += (src as held by lane C of this lane's row of 16 lanes) * mul in ONE vector instruction: the row
 // broadcast is a DPP modifier of the multiply-add (the compiler emits a separate broadcast move and a

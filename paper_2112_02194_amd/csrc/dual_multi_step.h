@@ -20,14 +20,15 @@ namespace als {
 //   4. t of the entries 0..15: B^T t (columns of B from LDS, t as a DPP operand), the row operations of step 2 once more
 //      on that vector (their multipliers were left where the eliminated columns were), and the pivots;
 //   5. r = Z_I^T t, four (bf16: eight) columns per lane, from the registers of step 1, or (fp32, d = 128, whose tiles do not fit
-//      the registers) gathering the entries a second time.
+//      the registers, and fp32 in the launch that small calls share) gathering the entries a second time.
 // Every row goes through LDS into the operand layout (PieceGather), and the walk over the list loads the next step's ids ahead
 // (dual_walk.h).
 // What bounds it: HBM and the instructions of two wavefronts per SIMD, one every five clocks each, where the tiles stay in
-// registers; with a second gather (fp32, d = 128) the latency of about twelve rounds of loads at three wavefronts per SIMD.
+// registers; with a second gather (fp32, d = 128) the latency of about twelve rounds of loads at three wavefronts per SIMD: on 10M
+// pages 3.2 TB/s are counted.
 // Per half, an elimination of all 32 columns in one block with a triangular back-substitution (616 multiply-adds with a DPP
 // operand, 392 here) / this one with loads straight into the operand layout, 64 places per instruction / as it is:
-//   50M power-law rows, bf16, d = 128  44.6 / 41.4 / 36.5 ms      10M pages, fp32, d = 128  8.12 / 7.05 / 6.35 ms
+//   50M power-law rows, bf16, d = 128  44.6 / 41.4 / 36.5 ms      10M pages, fp32, d = 128  7.65 / 7.15 / 6.35 ms
 //   1M x 1M, fp32, d = 64 (second gather before)  705 / 671 / 525 us      300k rows, bf16, d = 128  129 / 115 / 107 us
 
 // LDS of one wavefront: P holds four 16 x 16 tiles (A, then L, then C, then t), U the stage of two tiles of entries and later

@@ -10,9 +10,9 @@
 // [1, 1 + k/alpha], so fp32 is comfortable.  Steps:
 //   factor_kernel     B -> L^{-1} in fp64 (one workgroup), stored fp32
 //   transform_kernel  Z = V L^{-T}   (fp32 MFMA, table-sized workspace)
-//   row kernels       by class of k (fixed by measurement on MI355X): all gather Z_I straight into MFMA
-//                     operand registers, form S = I + Z_I Z_I^T on the matrix cores, solve the k x k
-//                     system on the vector ALU, then r = Z_I^T t
+//   row kernels       by class of k (fixed by measurement on MI355X): all gather Z_I into MFMA operand
+//                     registers, straight or by way of LDS, form S = I + Z_I Z_I^T on the matrix cores,
+//                     solve the k x k system on the vector ALU, then r = Z_I^T t
 //       dual_small_kernel  k <= 4 and 5 <= k <= 8: several rows share one 16-entry MFMA tile
 //       dual_rows_kernel   8 < k <= 16: four rows per wavefront, one lane per row of S, gather through LDS
 //       dual_multi_kernel  16 < k <= 32: four rows per wavefront, S in two blocks of 16

@@ -1,8 +1,8 @@
 // als_solve_rows orchestration: classify the rows of the requested range by their number of
 // stored entries, then run the kernels each class needs (paper Algorithm 1 lines 3-10; long rows
 // are cut into segments in the spirit of Section 4.3).  Nothing here waits for the GPU: the class
-// counts stay in device memory, every row kernel walks its list with a grid-stride loop bounded by
-// the count it reads there, and grids are sized from the counts of the previous call on the same
+// counts stay in device memory, every row kernel reads the length of its list there and covers the
+// list whatever its grid, and grids are sized from the counts of the previous call on the same
 // matrix when there was one (a hint: a wrong or missing hint costs speed, never correctness).
 #include <type_traits>
 
@@ -146,8 +146,9 @@ __device__ __forceinline__ bool put_long_row(int64_t u, int64_t b, int64_t k, in
 //                       (at most MAX_SEGS_PER_ROW of them); split is the threshold of decide_split, left in
 //                       counters[7] too
 // Positions are reserved with one atomic per workgroup and list (counts gathered in LDS; with two per long row, whose answers a
-// wavefront waited for up to eight times, the 1M rows of a heavy-tailed half took 74 us instead of 17), and
-// rows keep their order inside a workgroup's slice.  A matrix whose indptr does not fit its nnz can ask
+// wavefront waited for up to eight times, the 1M rows of a heavy-tailed half took 74 us instead of 17).  Rows keep
+// their order inside a wavefront's 64; the wavefronts of a workgroup, and the workgroups, come in any order, which can change from call to
+// call.  No result depends on it, and neighbouring rows still stand near each other.  A matrix whose indptr does not fit its nnz can ask
 // for more long rows or segments than the workspace holds; those rows are dropped and the error flag is set.  So are, when Z
 // holds one row per entry (entry_limit = nnz, else INT64_MAX), rows with entries outside those that Gather walks, from
 // indptr[r0] to indptr[r1] and below entry_limit: an indptr that is not monotone has such rows, and Z has nothing for them.
