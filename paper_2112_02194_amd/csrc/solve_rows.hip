@@ -246,11 +246,11 @@ __global__ void publish_counts_kernel(int32_t *__restrict__ counters, int64_t ca
 // for d = 128, fp32, and 75 us for d = 16: all of them wait for one compute unit.  So it takes 89 and 31 us.)
 template <bool BF16> __device__ __forceinline__ void zero_rows(void *X, int64_t ldx, int d, int64_t u0, unsigned long long which) {
     constexpr int ES = BF16 ? 2 : 4;
-    const int per_row = d * ES / 16, lane = threadIdx.x & 63, at_once = 64 / per_row;  // lanes per row: 2 to 32
-    for (int j = 0; which && j < 64; j += at_once) {
-        const int64_t u = u0 + j + lane / per_row;
-        if (which >> (j + lane / per_row) & 1)
-            *(float4 *)((char *)X + u * ldx * ES + 16 * (lane % per_row)) = make_float4(0.f, 0.f, 0.f, 0.f);  // (rows are 16-byte aligned)
+    const int lane = threadIdx.x & 63, shift = __ffs(d * ES / 16) - 1;  // 2, 4, .. 32 lanes per row
+    const int64_t mine = lane >> shift;
+    for (int j = 0; which && j < 64; j += 64 >> shift) {
+        if (which >> (j + mine) & 1)
+            *(float4 *)((char *)X + (u0 + j + mine) * ldx * ES + 16 * (lane & ((1 << shift) - 1))) = make_float4(0.f, 0.f, 0.f, 0.f);  // (rows are 16-byte aligned)
     }
 }
 
@@ -263,10 +263,10 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
     Segment *__restrict__ segs, int32_t *__restrict__ mid_list, int64_t cap_mid, int32_t *__restrict__ dual_lists,
     ListOffsets list_off, int64_t entry_limit, int64_t split_wanted, int32_t *__restrict__ hint, uint32_t seq) {
     __shared__ int32_t n[16];  // as in `counters`; [2]: flag bits set here
-    __shared__ unsigned long long long_stat;  // entries of the rows beyond the requested split
+    __shared__ unsigned long long long_stat[1];  // entries of the rows beyond the requested split
     const int t = threadIdx.x;
     if (t < 16) n[t] = 0;
-    if (t == 0) long_stat = 0;
+    if (t == 0) long_stat[0] = 0;
     const bool by_entry = entry_limit != INT64_MAX;
     const int64_t first_entry = by_entry && indptr[r0] > 0 ? indptr[r0] : 0;
     const int64_t end_entry = by_entry && indptr[r1] < entry_limit ? indptr[r1] : entry_limit;
@@ -284,9 +284,13 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
     unsigned long long beyond = 0;
 #pragma unroll
     for (int i = 0; i < CLS_ONE_RPT; ++i) beyond += e[i] - b[i] > split_wanted ? (unsigned long long)(e[i] - b[i]) : 0ull;
-    if (beyond) atomicAdd(&long_stat, beyond);
+    // Sums in one place of LDS go there lane by lane: with an address that is known to be the same in all lanes, the compiler adds up the
+    // wavefront's values first, in a loop over its lanes that takes a microsecond.
+    int here = 0;
+    asm volatile("" : "+v"(here));
+    if (beyond) atomicAdd(&long_stat[here], beyond);
     __syncthreads();
-    const int64_t split = decide_split(&long_stat, split_wanted);
+    const int64_t split = decide_split(long_stat, split_wanted);
     unsigned empty = 0, longs = 0;  // bit i: this thread's row i
     int nsegs = 0;                  // segments of its long rows
 #pragma unroll
@@ -311,14 +315,20 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
     // what most calls have few of, in a loop of its own (unrolled with the rest it would cost the kernel its registers)
     int slot = 0, first = 0;
     if (longs) {
-        slot = atomicAdd(&n[0], __popc(longs));
-        first = atomicAdd(&n[1], nsegs);
+        slot = atomicAdd(&n[here], __popc(longs));
+        first = atomicAdd(&n[here + 1], nsegs);
     }
 #pragma unroll 1
     for (int i = 0; __any((longs | empty) >> i); ++i) {
         const int64_t u = r0 + (int64_t)i * CLS_ONE_THREADS + t;
         if (longs >> i & 1) {
-            const int64_t from = indptr[u], k = indptr[u + 1] - from;
+            int64_t from = b[0], to = e[0];  // of row i, without waiting for indptr again
+#pragma unroll
+            for (int j = 1; j < CLS_ONE_RPT; ++j) {
+                from = i == j ? b[j] : from;
+                to = i == j ? e[j] : to;
+            }
+            const int64_t k = to - from;
             if (!put_long_row(u, from, k, split, slot, first, long_rows, segs)) atomicOr(&n[2], 2);
             ++slot;
             first += segments_of(k, split);

@@ -656,7 +656,7 @@ def test_empty_rows_cost_no_more_in_one_workgroup_than_in_many(ctx, gpu_device, 
 
 def test_long_rows_are_cut_as_fast_in_one_workgroup_as_in_many(ctx, gpu_device):
     """8192 rows of 600 entries, two segments each, d = 16: 147 us in one workgroup that reserved places and divided in 64 bits row by row, 95
-    by several; 111 as it is, and a quarter more than by several is allowed."""
+    by several; 103 as it is, and a quarter more than by several is allowed."""
     say("long rows in one workgroup")
     d, n, k, best = 16, 3000, 600, []
     gen = torch.Generator(device=gpu_device).manual_seed(1)
