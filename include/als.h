@@ -194,7 +194,7 @@ als_status als_copy_probe(als_ctx *ctx, const void *src, void *dst, int64_t byte
 
 /* Diagnostics, not part of the method.  GPU time in milliseconds (HIP events on the call's stream) of the
  * kernels launched by the most recent als_gramian / als_solve_rows / als_epoch / als_loss, per kernel:
- *   [0] Gramian (2 or 3 kernels)   [1] row classification (4 kernels)   [2] shared factorisation + Z = V L^-T
+ *   [0] Gramian (2 or 3 kernels)   [1] row classification (4 kernels, 1 up to 8192 rows)   [2] shared factorisation + Z = V L^-T
  *   [3] X = R L^-1   [4] primal fused row kernel   [5] long-row segment accumulation   [6] long-row reduce + solve
  *   [7] dual rows k <= 4   [8] dual rows 5 <= k <= 8   [9 + c] dual rows 16c < k <= 16(c+1), c = 0..7 (c = 0: 8 < k)
  * Small calls, whose dual classes share one launch, have the time of all of them in [9]; [7], [8] and [10] to [16] are 0 then.
