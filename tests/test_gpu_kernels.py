@@ -703,3 +703,31 @@ def test_classes_in_launches_of_their_own_and_in_a_common_one(ctx, gpu_device, d
         z2 = np.max(np.sum(v * np.linalg.solve(B, v.T).T, axis=1), initial=0.0)
         unit = 2.0 ** -16 if dtype == torch.float32 else 2.0 ** -8
         assert np.linalg.norm(f64(whole[r]) - ref) <= unit * (1 + len(v) * z2) * np.linalg.norm(ref), (r, len(v))
+
+
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rows_of_tables_with_a_stride(ctx, gpu_device, d, dtype):
+    """Tables whose rows are further apart than d: the same bits as without, empty rows zeroed one by one and in runs, and neither what
+    lies between the rows nor rows outside the range written (a range that starts and ends inside a wavefront's 64 rows)."""
+    say(f"strided tables d={d} {dtype}")
+    rows, n, r0, r1 = 1500, 300, 3, 1497
+    gen = torch.Generator(device=gpu_device).manual_seed(d)
+    k = torch.randint(0, 40, (rows,), device=gpu_device, generator=gen)
+    k[torch.rand(rows, device=gpu_device, generator=gen) < 0.4] = 0
+    k[400:700] = 0
+    k[[10, 800]] = 600
+    indptr = torch.zeros(rows + 1, dtype=torch.int64, device=gpu_device)
+    indptr[1:] = torch.cumsum(k, 0)
+    Y = als.Csr(rows, n, indptr, torch.randint(0, n, (int(indptr[-1]),), device=gpu_device, generator=gen).to(torch.int32))
+    H = (0.2 * torch.randn((n, d), device=gpu_device, generator=gen)).to(dtype)
+    wide_h = torch.full((n, d + 16), float("nan"), device=gpu_device, dtype=dtype)
+    wide_h[:, :d] = H
+    wide_x = torch.full((rows, d + 8), 7.0, device=gpu_device, dtype=dtype)
+    X = torch.full((rows, d), 7.0, device=gpu_device, dtype=dtype)
+    G, prm = als.als_gramian(ctx, H), als.make_params(0.1, 1e-2)
+    als.als_solve_rows(ctx, Y, H, G, prm, X, r0, r1)
+    als.als_solve_rows(ctx, Y, wide_h[:, :d], G, prm, wide_x[:, :d], r0, r1)
+    als.als_status_sync(ctx)
+    assert torch.equal(wide_x[:, :d], X) and (wide_x[:, d:] == 7).all()
+    assert (X[:r0] == 7).all() and (X[r1:] == 7).all() and torch.equal((X[r0:r1] == 0).all(dim=1), k[r0:r1] == 0)
