@@ -205,6 +205,9 @@ def main():
     zbt = "true" if (es == 2 and d >= 32) else "false"  # Z kept as bf16
     kernel_names = {"dual_k4": f"dual_small_kernel<{d},4,{zbt},false>", "dual_k8": f"dual_small_kernel<{d},8,{zbt},false>",
                     "dual_k16": f"dual_rows_kernel<{d},{zbt}>", "dual_k32": f"dual_multi_kernel<{d},{zbt}>"}
+    small_x = es == 4 and d >= 64 and args.solver == "direct"  # rows of up to 8 entries leave their kernel as X
+    if small_x:
+        kernel_names.update({"dual_k4": f"dual_small_x_kernel<{d},4>", "dual_k8": f"dual_small_x_kernel<{d},8>"})
     for c in range(2, 8):
         kernel_names[f"dual_k{16 * (c + 1)}"] = f"dual_wide_kernel<{d},{c + 1},{zbt},false,false>"
     if args.solver == "cg" and d >= 64:  # every class runs the one-row-per-wavefront kernel with the CG solver
@@ -218,7 +221,7 @@ def main():
                          "transform_z": f"transform16_kernel<{d},true,true,false>" if zbt == "true"      # Z = V L^-T
                          else f"transform_kernel<{d},{bft},false,true,false>",
                          "transform_x": f"transform16_kernel<{d},false,false,false>" if zbt == "true"    # X = R L^-1
-                         else (f"transform_split_kernel<{d},false>" if (es == 4 and d >= 64)
+                         else (f"transform_split_kernel<{d}>" if (es == 4 and d >= 64)
                                else f"transform_kernel<{d},false,{bft},false,false>"),
                          "primal": f"primal_kernel<{d},{bft},0,false>",               # one workgroup per row
                          "segment": f"primal_kernel<{d},{bft},1,false>"})             # segments of long rows
@@ -256,7 +259,11 @@ def main():
     work["transform_x"] = ["hbm", float(m + n) * d * (4 + es)]
     # lists that are short together share one launch, which the library times in the slot of 8 < k <= 16
     dual_names = [name for name, _, _ in bounds]
-    if args.solver == "direct" and [name for name in dual_names if stage_launches.get(name, 0.0) > 0] == ["dual_k16"]:
+    common = args.solver == "direct" and [name for name in dual_names if stage_launches.get(name, 0.0) > 0] == ["dual_k16"]
+    if es == 4 and d >= 64 and args.solver != "cg_free":  # of the rows that are not X yet
+        lo = 8 if small_x and not common else 0
+        work["transform_x"][1] = float(sum(int(((k > lo) & (k <= dual_max)).sum()) for k in deg.values())) * d * (4 + es)
+    if common:
         work["dual_common"] = ["hbm", sum(work.pop(name)[1] for name in dual_names)]
         stage_ms["dual_common"], stage_launches["dual_common"] = stage_ms.pop("dual_k16"), stage_launches.pop("dual_k16")
         kernel_names["dual_common"] = f"dual_few_kernel<{d},{zbt}>"

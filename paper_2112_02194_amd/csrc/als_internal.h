@@ -9,6 +9,7 @@
 
 #include "als.h"
 #include "launch_size.h"
+#include "step_queue.h"
 
 namespace als {
 
@@ -181,7 +182,8 @@ constexpr size_t SM_COUNTERS = 0;       // int32[16]: [0] n_long [1] n_seg [2] e
 constexpr size_t SM_LONGSTAT = 128;     // int64[2]: entries and rows beyond the requested split (sizes the segments)
 constexpr size_t SM_LOSS = 64;          // double[2]
 constexpr size_t SM_FACTOR = 256;       // fp32 [2][128*128]: L^{-1} and scratch for the dual form
-constexpr size_t SM_BYTES = SM_FACTOR + 2 * 128 * 128 * sizeof(float) + 128 * 128 * sizeof(double);
+constexpr size_t SM_QUEUE = SM_FACTOR + 2 * 128 * 128 * sizeof(float);  // int32[2][QUEUE_INTS]: StepQueue counters, cleared with the others
+constexpr size_t SM_BYTES = SM_QUEUE + 2 * QUEUE_INTS * sizeof(int32_t);
 
 struct LongRow {   // a row whose statistics are accumulated by several segments
     int64_t row;

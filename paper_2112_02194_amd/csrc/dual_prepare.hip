@@ -13,7 +13,8 @@
 //   row kernels       by class of k (fixed by measurement on MI355X): all gather Z_I into MFMA operand
 //                     registers, straight or by way of LDS, form S = I + Z_I Z_I^T on the matrix cores,
 //                     solve the k x k system on the vector ALU, then r = Z_I^T t
-//       dual_small_kernel  k <= 4 and 5 <= k <= 8: several rows share one 16-entry MFMA tile
+//       dual_small_kernel  k <= 4 and 5 <= k <= 8: several rows share one 16-entry MFMA tile (fp32 tables with d >= 64:
+//                          dual_small_x_kernel, which takes the next step along)
 //       dual_rows_kernel   8 < k <= 16: four rows per wavefront, one lane per row of S, gather through LDS
 //       dual_multi_kernel  16 < k <= 32: four rows per wavefront, S in two blocks of 16
 //       dual_wide_kernel   32 < k <= 128 (d >= 64; k <= 64 at d = 64): one row per wavefront, S as a
@@ -22,6 +23,8 @@
 #include "dual_common.h"
 #include "dual_few.h"
 #include "dual_walk.h"
+#include "step_queue.h"
+#include "x_rows.h"
 
 namespace als {
 
@@ -29,6 +32,13 @@ void launch_dual_small4(int d, const als_csr *Y, const void *Z, bool zb16, float
                         const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
 void launch_dual_small8(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
                         const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
+// with X = R L^-1 taken along (fp32 tables, d = 64 or 128); `queue`: see StepQueue, zero when the launch begins
+als_status launch_dual_small4_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0,
+                                const int32_t *list, const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue,
+                                int32_t *err, hipStream_t s);
+als_status launch_dual_small8_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0,
+                                const int32_t *list, const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue,
+                                int32_t *err, hipStream_t s);
 // per-class launchers (`count_dev`: device address of the list's length; `g`, `w`: see StepGrid, WalkSize; `zb16`: Z is bf16)
 void launch_dual_k16(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
                      const int32_t *list, const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
@@ -456,107 +466,67 @@ __global__ __launch_bounds__(256, 2) void transform16_kernel(const void *__restr
 }
 
 // ---------------------------------------------------------------------------------------------- transform, fp32 tables
-// fp32 in, fp32 out (d >= 64), with fp32 accuracy on the bf16 matrix cores: the matrix (once per workgroup, LDS)
-// and the table rows (registers) are cut exactly into three bf16 parts each, x = x0 + x1 + x2 with x0 = upper
-// 16 bits of x and so on, and a product keeps the six terms m0 x0, m0 x1, m1 x0, m0 x2, m2 x0, m1 x1 (what is
-// dropped is below the rounding of an fp32 product): 0.375 of the fp32 instruction's matrix-core time, which
-// leaves the pass to the table read and write (used for X = R L^-1: 24.5 against 29.0 ms per epoch on the 50M-row
-// configuration; for Z = V L^-T the fp32 kernel above measured faster, 24.4 against 25.9 ms).  The matrix core's running sum is not rounded to nearest, so
-// only the six products of one 16-column step are summed there, from zero and small terms first; the steps are
-// summed on the vector units.  Operand roles and the store layout are those of transform16_kernel.  All of a
-// tile's input is in registers before its first store, so In == Out is fine.
+// X = R L^-1 in place for fp32 tables (d >= 64), of the rows of some class lists: with fp32 accuracy on the bf16 matrix cores
+// (x_rows.h), 0.375 of the fp32 instruction's matrix-core time, which leaves the pass to the table read and write (for Z = V L^-T
+// the fp32 kernel above measured faster, 24.4 against 25.9 ms per epoch of 50M x 50M).  A wavefront takes 32 rows at a time.
+// What bounds it: HBM (4.5 TB/s of rows read and written).
 constexpr int XFS_THREADS = 512;
-template <int D> struct XfsCfg {
-    static constexpr int MLD = D + 8;  // bf16 elements per LDS row
-    static constexpr size_t LDS_BYTES = (size_t)3 * D * MLD * sizeof(uint16_t);
+struct XLists {
+    const int32_t *list[10], *count[10];
+    int n;
 };
 
-template <int D, bool UPPER>
-__global__ __launch_bounds__(XFS_THREADS, 2) void transform_split_kernel(const float *In, int64_t ldi, float *Out,
-                                                                         int64_t ldo, const float *__restrict__ Mt,
-                                                                         int64_t r0, int64_t r1,
-                                                                         const int64_t *__restrict__ indptr, int64_t k_max) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int MLD = XfsCfg<D>::MLD, NKB = D / 16, NJB = D / 32;
-    extern __shared__ uint16_t mt[];  // part t: mt[t * D * MLD + c * MLD + j] = part t of M[j][c]
-    auto rest = [](float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
-#pragma unroll 4
-    for (int e = threadIdx.x; e < D * D / 4; e += XFS_THREADS) {
-        float4 v = ((const float4 *)Mt)[e];
-        uint16_t *at = mt + e / (D / 4) * MLD + 4 * (e % (D / 4));
-#pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            *(uint2 *)(at + t * D * MLD) = make_uint2(pack_upper(v.x, v.y), pack_upper(v.z, v.w));
-            v = make_float4(rest(v.x), rest(v.y), rest(v.z), rest(v.w));
-        }
-    }
+template <int D>
+__global__ __launch_bounds__(XFS_THREADS, 2) void transform_split_kernel(float *__restrict__ X, int64_t ldx, const float *__restrict__ LinvT,
+                                                                         int64_t r0, XLists xl) {
+    constexpr int NK = D / 32;
+    extern __shared__ char mat[];
+    XMatrix<D>::fill(mat, LinvT, threadIdx.x, XFS_THREADS);
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 31, kq = lane >> 5;
-    const int pi = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);  // see transform16_kernel
-    const int64_t ntiles = (r1 - r0 + 31) / 32;
-    const int64_t nwaves = (int64_t)gridDim.x * (XFS_THREADS / 64);
-    for (int64_t tile = (int64_t)blockIdx.x * (XFS_THREADS / 64) + wave; tile < ntiles; tile += nwaves) {
-        const int64_t row = r0 + tile * 32 + n;
-        bool keep = row < r1;
-        if (keep && indptr) {  // only rows solved in the dual form are written
-            const int64_t k = indptr[row + 1] - indptr[row];
-            keep = k > 0 && k <= k_max;
-        }
-        // this lane's share of its row: columns 16 kb + 8 kq .., as three bf16 operands each
-        bf16x8 xp[3][NKB];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), a = lane & 15, q = lane >> 4;
+    X += r0 * ldx;
+    const int nwaves = (int)gridDim.x * (XFS_THREADS / 64);
+    int tile = (int)blockIdx.x * (XFS_THREADS / 64) + wave;  // counted from the first tile of list i
+    for (int i = 0; i < xl.n; ++i) {
+        const int count = *xl.count[i], tiles = list_steps(count, 32);
+        const int32_t *list = xl.list[i];
+        for (; tile < tiles; tile += nwaves) {
+            int32_t rel[2];
+            bool have[2];
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-            float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (row < r1) {
-                const float4 p = *(const float4 *)(In + row * ldi + 16 * kb + 8 * kq);
-                const float4 q4 = *(const float4 *)(In + row * ldi + 16 * kb + 8 * kq + 4);
-                x[0] = p.x; x[1] = p.y; x[2] = p.z; x[3] = p.w; x[4] = q4.x; x[5] = q4.y; x[6] = q4.z; x[7] = q4.w;
+            for (int n = 0; n < 2; ++n) {
+                const unsigned item = 32u * (unsigned)tile + 16u * n + (unsigned)a;
+                have[n] = item < (unsigned)count;
+                rel[n] = list[have[n] ? item : (unsigned)count - 1u];
             }
+            float4 raw[2][NK][2];
 #pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                u32x4 w;
+            for (int n = 0; n < 2; ++n)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = pack_upper(x[2 * e], x[2 * e + 1]);
-                xp[t][kb] = __builtin_bit_cast(bf16x8, w);
-                if (t < 2) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) x[e] = rest(x[e]);
+                for (int kb = 0; kb < NK; ++kb) {
+                    const float *src = X + rel[n] * ldx + 32 * kb + 8 * q;
+                    raw[n][kb][0] = *(const float4 *)src;
+                    raw[n][kb][1] = *(const float4 *)(src + 4);
                 }
-            }
-        }
+            bf16x8 xp[2][3][NK];
 #pragma unroll
-        for (int J = 0; J < NJB; ++J) {
-            floatx16 acc;
+            for (int n = 0; n < 2; ++n)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-            const uint16_t *mrow = mt + (32 * J + pi) * MLD + 8 * kq;
+                for (int kb = 0; kb < NK; ++kb) {
+                    bf16x8 part[3];
+                    XMatrix<D>::cut(raw[n][kb][0], raw[n][kb][1], part);
 #pragma unroll
-            for (int kb = 0; kb < NKB; ++kb) {
-                if (UPPER ? (kb <= 2 * J + 1) : (kb >= 2 * J)) {  // compile-time after unrolling: other steps only meet zeros
-                    const bf16x8 m0 = *(const bf16x8 *)(mrow + 16 * kb), m1 = *(const bf16x8 *)(mrow + D * MLD + 16 * kb),
-                                 m2 = *(const bf16x8 *)(mrow + 2 * D * MLD + 16 * kb);
-                    floatx16 t16;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) t16[v] = 0.f;
-                    t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m1, xp[1][kb], t16, 0, 0, 0);  // small terms first
-                    t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m2, xp[0][kb], t16, 0, 0, 0);
-                    t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m0, xp[2][kb], t16, 0, 0, 0);
-                    t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m1, xp[0][kb], t16, 0, 0, 0);
-                    t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m0, xp[1][kb], t16, 0, 0, 0);
-                    t16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m0, xp[0][kb], t16, 0, 0, 0);
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[v] += t16[v];
+                    for (int t = 0; t < 3; ++t) xp[n][t][kb] = part[t];
                 }
-            }
-            // acc[v] = Out[row][32 J + 16 kq + v]
-            if (keep) {
-                float4 *dst = (float4 *)(Out + row * ldo + 32 * J + 16 * kq);
-#pragma unroll
-                for (int w = 0; w < 4; ++w) dst[w] = make_float4(acc[4 * w], acc[4 * w + 1], acc[4 * w + 2], acc[4 * w + 3]);
-            }
-            __builtin_amdgcn_sched_barrier(0);  // keep the next column block's operand reads from piling up
+            x_rows<D, 2>(mat, xp, [&](int n, int P, const floatx4 (&v)[2]) {
+                if (have[n]) {
+                    float *dst = X + rel[n] * ldx + 32 * P + 8 * q;
+                    *(floatx4 *)dst = v[0];
+                    *(floatx4 *)(dst + 4) = v[1];
+                }
+            });
         }
+        tile -= tiles;
     }
 }
 
@@ -636,8 +606,10 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     }
     const float *LinvT = (const float *)((char *)ctx->small.p + SM_FACTOR) + 128 * 128;  // transpose of the matrix applied
     int32_t *err = (int32_t *)((char *)ctx->small.p + SM_COUNTERS) + 2;
+    int32_t *queue = (int32_t *)((char *)ctx->small.p + SM_QUEUE);
     const void *Z = ctx->ztable.p;
-    constexpr bool zb16 = z_is_bf16<D, BF16>();
+    constexpr bool zb16 = z_is_bf16<D, BF16>(), X_LISTS = !BF16 && D >= 64;
+    bool small_x = false;  // rows of up to 8 entries are X already
     als_status stb = ALS_OK;
     // workgroups of class `cls` whose kernel takes `rpw` rows per step
     auto grid = [&](int cls, int rpw) {
@@ -685,8 +657,14 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     ALS_TIMED_CLASS(T_DUAL_CLASS0 + 1, 1, 4, (launch_dual_multi2(D, Y, Z, zb16, R, ldr, r0, lists[1], counts_dev[1], walk(1, 4), err, s)))
     ALS_TIMED_CLASS(T_DUAL_CLASS0, 0, 4, (launch_dual_k16(D, Y, Z, zb16, R, ldr, r0, lists[0], counts_dev[0], walk(0, 4), err, s)))
     // 5 <= k <= 8 and k <= 4: several rows per MFMA tile
+    if constexpr (X_LISTS) {
+    small_x = true;
+    ALS_TIMED_CLASS(T_SMALL8, 9, 8, (stb = launch_dual_small8_x(ctx, D, Y, Z, R, ldr, r0, lists[9], counts_dev[9], walk(9, 8), LinvT, queue, err, s)))
+    ALS_TIMED_CLASS(T_SMALL4, 8, 16, (stb = launch_dual_small4_x(ctx, D, Y, Z, R, ldr, r0, lists[8], counts_dev[8], walk(8, 16), LinvT, queue + QUEUE_INTS, err, s)))
+    } else {
     ALS_TIMED_CLASS(T_SMALL8, 9, 8, (launch_dual_small8(D, Y, Z, zb16, R, ldr, r0, lists[9], counts_dev[9], g, err, s)))
     ALS_TIMED_CLASS(T_SMALL4, 8, 16, (launch_dual_small4(D, Y, Z, zb16, R, ldr, r0, lists[8], counts_dev[8], g, err, s)))
+    }
     }
     ALS_TIMED_CLASS(T_DUAL_CLASS0 + 2, 2, 1, (stb = launch_dual_wide3(ctx, D, Y, Z, zb16, R, ldr, r0, lists[2], counts_dev[2], g, err, ws, s)))
     ALS_TIMED_CLASS(T_DUAL_CLASS0 + 3, 3, 1, (stb = launch_dual_wide4(ctx, D, Y, Z, zb16, R, ldr, r0, lists[3], counts_dev[3], g, err, ws, s)))
@@ -706,14 +684,22 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
         ALS_HIP(ctx, attr_x);
         hipLaunchKernelGGL((transform16_kernel<D, false, false, false>), dim3(xblocks), dim3(256), Xf16Cfg<D>::LDS_BYTES, s,
                            (const void *)R, ldr, (uint16_t *)X->data, X->ld, LinvT, r0, r1, Y->indptr, (int64_t)dual_max, Gather{});
-    } else if constexpr (!BF16 && D >= 64) {
-        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_split_kernel<D, false>,
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                             (int)XfsCfg<D>::LDS_BYTES);  // once per process
+    } else if constexpr (X_LISTS) {
+        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_split_kernel<D>,
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, XMatrix<D>::BYTES);  // once per process
         ALS_HIP(ctx, attr_x);
-        const unsigned sblocks = (unsigned)std::min<int64_t>(512, std::max<int64_t>(1, (r1 - r0 + 255) / 256));
-        hipLaunchKernelGGL((transform_split_kernel<D, false>), dim3(sblocks), dim3(XFS_THREADS), XfsCfg<D>::LDS_BYTES, s,
-                           (const float *)R, ldr, (float *)X->data, X->ld, LinvT, r0, r1, Y->indptr, (int64_t)dual_max);
+        XLists xl;
+        xl.n = 0;
+        int64_t tiles = 0;
+        for (int c = 0; c < (small_x ? 8 : 10); ++c)
+            if (caps[c] > 0) {
+                xl.list[xl.n] = lists[c];
+                xl.count[xl.n++] = counts_dev[c];
+                tiles += (caps[c] + 31) / 32;
+            }
+        const unsigned sblocks = (unsigned)std::min<int64_t>(512, (tiles + XFS_THREADS / 64 - 1) / (XFS_THREADS / 64));
+        if (sblocks > 0)
+            hipLaunchKernelGGL((transform_split_kernel<D>), dim3(sblocks), dim3(XFS_THREADS), XMatrix<D>::BYTES, s, R, ldr, LinvT, r0, xl);
     } else {
         static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_kernel<D, false, BF16, false, false>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -1,5 +1,8 @@
 // Row classes k <= 4 and 5 <= k <= 8, compiled once each with -DSMALL_G=4 and -DSMALL_G=8 (step: dual_small_step.h).
 #include "dual_small_step.h"
+#include "dual_walk.h"
+#include "step_queue.h"
+#include "x_rows.h"
 
 #ifndef SMALL_G
 #error "compile with -DSMALL_G=8 or -DSMALL_G=4"
@@ -34,6 +37,179 @@ __global__ __launch_bounds__(64) void dual_small_kernel(const int64_t *__restric
     }
 }
 
+// The same step with X = R L^-1 taken along (fp32 tables, d >= 64): the wavefront's rows of R go from registers through LDS
+// into x_rows and never to memory, where a pass of its own writes and reads each of them once more.  Epoch of 50M x 50M rows (d =
+// 128), 81M of whose 100M solved rows come through here: 132.0 -> 115.2 ms (these kernels 46.0 -> 47.5 ms, the pass over the rows left
+// 24.8 -> 4.3 ms); 10M pages: 55.2 -> 54.1 ms; 1M x 1M (d = 64) the two together 402 -> 324 us.
+// The matrix stands in LDS once per workgroup (60 KB at d = 128), so the launch is persistent and its wavefronts take their
+// steps in turn or, where they get many, from a queue (50M x 50M: 49.7 ms in turn, 47.5 from the queue; 378 000 rows of 5 to 8 entries, d = 64:
+// 142 us in turn, 237 from a queue, whose counters all wavefronts ask at the end).  List entry, row descriptor and column id of the next step are loaded while a step is solved: lane
+// l = 16 p + a of the wavefront keeps those of entry slot a of tile p.
+// What bounds it: HBM (50M rows of c4's kind: 5.0 TB/s with the rows of Z, ids and X; two wavefronts per SIMD).
+constexpr int SMALL_X_THREADS = 512;
+
+template <int D, int G> struct SmallXCfg {
+    static constexpr int RLD = D + 4;  // row stride of the copy of R
+    static constexpr int WAVE_FLOATS = SmallCfg<D, G>::OFF_META;
+    static_assert(16 * RLD <= SmallCfg<D, G>::MAIN, "sixteen rows of R take the place of a tile's entries");
+    static constexpr size_t LDS_BYTES = XMatrix<D>::BYTES + (SMALL_X_THREADS / 64) * WAVE_FLOATS * sizeof(float);
+};
+
+template <int D, int G>
+__global__ __launch_bounds__(SMALL_X_THREADS, 2) void dual_small_x_kernel(const int64_t *__restrict__ indptr,
+                                                                          const int32_t *__restrict__ indices,
+                                                                          const float *__restrict__ values,
+                                                                          const float *__restrict__ Z, float *__restrict__ X,
+                                                                          int64_t ldx, int64_t r0, const int32_t *__restrict__ list,
+                                                                          const int32_t *__restrict__ count_ptr,
+                                                                          const float *__restrict__ LinvT, int32_t *__restrict__ queue,
+                                                                          int32_t *__restrict__ err_flag) {
+    using C = SmallCfg<D, G>;
+    using CX = SmallXCfg<D, G>;
+    constexpr int NR = C::NR, NJ = z_pieces<D, false>(), CPL = D >= 128 ? 2 : 1, NK = D / 32;
+    extern __shared__ float shared[];
+    const int count = *count_ptr;
+    if (count <= 0) return;
+    char *mat = (char *)shared;
+    XMatrix<D>::fill(mat, LinvT, threadIdx.x, SMALL_X_THREADS);
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    float *lds = (float *)(mat + XMatrix<D>::BYTES) + wave * CX::WAVE_FLOATS;
+    const int slot = lane % G;
+    X += r0 * ldx;
+    indptr += r0;
+
+    StepQueue steps = step_queue(queue, list_steps(count, NR), blockIdx.x, gridDim.x, wave, SMALL_X_THREADS / 64);
+    auto next_step = [&]() {
+        return steps.next([](const int32_t *counter) { return __builtin_amdgcn_readfirstlane(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); },
+                          [&](int32_t *counter, int n) {
+                              int at = 0;
+                              if (lane == 0) at = atomicAdd(counter, n);
+                              return __builtin_amdgcn_readfirstlane(at);
+                          });
+    };
+    auto place = [&](int blk) {  // place in the list of the row of which this lane keeps an entry
+        return (unsigned)blk * NR + (unsigned)(lane / G);
+    };
+    auto row_of = [&](int blk) { return list[place(blk) < (unsigned)count ? place(blk) : (unsigned)count - 1u]; };
+
+    int blk = next_step();
+    if (blk < 0) return;
+    int next = next_step();
+    int32_t rel = row_of(blk), rel_next = next < 0 ? rel : row_of(next);
+    int64_t b = indptr[rel];
+    int k = place(blk) < (unsigned)count ? (int)(indptr[rel + 1] - b) : 0;
+    int64_t at = b + (slot < k ? slot : 0);  // a row of the list has k >= 1: always in range
+    int32_t id = indices[at];
+    float y = slot < k ? (values ? values[at] : 1.f) : 0.f;
+    for (;;) {
+        // ---- gather, all loads of the step
+        float4 z[4][NJ];
+        {
+            const int a = lane & 15, q = lane >> 4;
+            const int own = slot < k ? id : -1;
+            int32_t ids[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) ids[p] = __shfl(own, 16 * p + a);
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) z[p][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (ids[p] >= 0) {
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) z[p][j] = load_piece<D, false>(Z, ids[p], j, q);
+                }
+            }
+        }
+        // ---- the next step's row descriptors, the list entries of the one after it
+        const int64_t b_next = indptr[rel_next], e_next = indptr[rel_next + 1];
+        const int after = next < 0 ? -1 : next_step();
+        const int32_t rel_after = after < 0 ? rel_next : row_of(after);
+
+        small_solve<D, G, false>(z, y, lds, err_flag);
+
+        // ---- the next step's column ids
+        const int k_next = next >= 0 && place(next) < (unsigned)count ? (int)(e_next - b_next) : 0;
+        const int64_t at_next = b_next + (slot < k_next ? slot : 0);
+        const int32_t id_next = indices[at_next];
+        const float y_next = slot < k_next ? (values ? values[at_next] : 1.f) : 0.f;
+
+        float r[NR][CPL];
+#pragma unroll
+        for (int n = 0; n < NR; ++n)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) r[n][c] = 0.f;
+        small_rows<D, G, false>(z, lds, [&](int n) { return __builtin_amdgcn_readlane(k, n * G); }, [&](int n, const float (&v)[CPL]) {
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) r[n][c] = v[c];
+        });
+        wave_sync();
+        // ---- X = R L^-1 of the wavefront's rows (with G = 8 the rows 8 .. 15 of the tile are whatever lies there)
+#pragma unroll
+        for (int n = 0; n < NR; ++n) {
+            if constexpr (CPL == 2) *(float2 *)(lds + n * CX::RLD + 2 * lane) = make_float2(r[n][0], r[n][1]);
+            else lds[n * CX::RLD + lane] = r[n][0];
+        }
+        wave_sync();
+        const int a = lane & 15, q = lane >> 4;
+        bf16x8 xp[1][3][NK];
+#pragma unroll
+        for (int kb = 0; kb < NK; ++kb) {
+            const float *src = lds + a * CX::RLD + 32 * kb + 8 * q;
+            bf16x8 part[3];
+            XMatrix<D>::cut(*(const float4 *)src, *(const float4 *)(src + 4), part);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) xp[0][t][kb] = part[t];
+        }
+        const int32_t my_rel = __shfl(rel, a * G & 63);
+        const int my_k = __shfl(k, a * G & 63);  // by all lanes: a lane that is masked out gives nothing
+        const bool mine = a < NR && my_k > 0;
+        float *dst = X + my_rel * ldx + 8 * q;
+        x_rows<D, 1>(mat, xp, [&](int, int P, const floatx4 (&v)[2]) {
+            if (mine) {
+                *(floatx4 *)(dst + 32 * P) = v[0];
+                *(floatx4 *)(dst + 32 * P + 4) = v[1];
+            }
+        });
+        if (next < 0) break;
+        wave_sync();  // the next step reuses the LDS buffers
+        blk = next;
+        next = after;
+        rel = rel_next;
+        rel_next = rel_after;
+        k = k_next;
+        id = id_next;
+        y = y_next;
+    }
+}
+
+template <int D>
+static als_status launch_small_x_typed(als_ctx *ctx, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0, const int32_t *list,
+                                       const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue, int32_t *err,
+                                       hipStream_t s) {
+    using CX = SmallXCfg<D, SMALL_G>;
+    static const hipError_t attr = hipFuncSetAttribute((const void *)dual_small_x_kernel<D, SMALL_G>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)CX::LDS_BYTES);  // once per process
+    ALS_HIP(ctx, attr);
+    constexpr int64_t WAVES = SMALL_X_THREADS / 64, PER_CU = 160 * 1024 / CX::LDS_BYTES;
+    const int64_t most = w.num_cu * PER_CU, wanted = ((w.hint < 0 ? w.capacity : std::min(w.hint, w.capacity)) + WAVES - 1) / WAVES;
+    const unsigned blocks = (unsigned)(std::max<int64_t>(1, std::min(most, wanted)) + 7) / 8 * 8;
+    hipLaunchKernelGGL((dual_small_x_kernel<D, SMALL_G>), dim3(blocks), dim3(SMALL_X_THREADS), CX::LDS_BYTES, s, Y->indptr, Y->indices,
+                       Y->values, (const float *)Z, X, ldx, r0, list, count_dev, LinvT, queue, err);
+    return ALS_OK;
+}
+
+#if SMALL_G == 8
+als_status launch_dual_small8_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0, const int32_t *list,
+                                const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue, int32_t *err, hipStream_t s) {
+#else
+als_status launch_dual_small4_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0, const int32_t *list,
+                                const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue, int32_t *err, hipStream_t s) {
+#endif
+    return d == 128 ? launch_small_x_typed<128>(ctx, Y, Z, X, ldx, r0, list, count_dev, w, LinvT, queue, err, s)
+                    : launch_small_x_typed<64>(ctx, Y, Z, X, ldx, r0, list, count_dev, w, LinvT, queue, err, s);
+}
+
 template <int D, bool ZB>
 static void launch_small_typed(const als_csr *Y, const void *Z, float *R, int64_t ldr, int64_t r0, const int32_t *list,
                                const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s) {
@@ -57,8 +233,8 @@ void launch_dual_small4(int d, const als_csr *Y, const void *Z, bool zb16, float
 #endif
 #define ALS_SMALL_CASE(dd)                                                                              \
     case dd:                                                                                            \
-        if (zb16 && dd >= 32) launch_small_typed<dd, (dd >= 32)>(Y, Z, R, ldr, r0, list, count_dev, g, err, s); \
-        else launch_small_typed<dd, false>(Y, Z, R, ldr, r0, list, count_dev, g, err, s);               \
+        if (dd >= 64 || (zb16 && dd >= 32)) launch_small_typed<dd, (dd >= 32)>(Y, Z, R, ldr, r0, list, count_dev, g, err, s); \
+        else launch_small_typed<dd, (dd >= 64)>(Y, Z, R, ldr, r0, list, count_dev, g, err, s); /* d >= 64 with fp32 Z: launch_small_x_typed */ \
         break;
     switch (d) { ALS_SMALL_CASE(16) ALS_SMALL_CASE(32) ALS_SMALL_CASE(64) ALS_SMALL_CASE(128) }
 #undef ALS_SMALL_CASE

@@ -32,8 +32,9 @@ constexpr int SEG_CAPACITY = 32768;  // segments whose partial statistics the wo
 constexpr int MAX_SEGS_PER_ROW = 128;
 constexpr int64_t BLIND_PRIMAL = 1 << 20;  // see step_grid; workgroups of up to four wavefronts
 
-__global__ void clear_counters_kernel(int32_t *counters, long long *long_stat) {
+__global__ void clear_counters_kernel(int32_t *counters, long long *long_stat, int32_t *queue) {
     const int t = threadIdx.x;
+    if (t < 2 * QUEUE_PARTS) queue[t * QUEUE_STRIDE] = 0;
     if (t < 16 && t != 2 && t != 4) counters[t] = 0;  // [2] is the sticky error flag, [4] the CSR check flag
     if (t < 2) long_stat[t] = 0;
 }
@@ -261,11 +262,13 @@ __global__ __launch_bounds__(CLS_ONE_THREADS) void classify_one_kernel(
     const int64_t *__restrict__ indptr, int64_t r0, int64_t r1, int64_t dual_max, int d,
     void *__restrict__ X, int64_t ldx, int32_t *__restrict__ counters, LongRow *__restrict__ long_rows,
     Segment *__restrict__ segs, int32_t *__restrict__ mid_list, int64_t cap_mid, int32_t *__restrict__ dual_lists,
-    ListOffsets list_off, int64_t entry_limit, int64_t split_wanted, int32_t *__restrict__ hint, uint32_t seq) {
+    ListOffsets list_off, int64_t entry_limit, int64_t split_wanted, int32_t *__restrict__ hint, uint32_t seq,
+    int32_t *__restrict__ queue) {
     __shared__ int32_t n[16];  // as in `counters`; [2]: flag bits set here
     __shared__ unsigned long long long_stat[1];  // entries of the rows beyond the requested split
     const int t = threadIdx.x;
     if (t < 16) n[t] = 0;
+    if (t < 2 * QUEUE_PARTS) queue[t * QUEUE_STRIDE] = 0;
     if (t == 0) long_stat[0] = 0;
     const bool by_entry = entry_limit != INT64_MAX;
     const int64_t first_entry = by_entry && indptr[r0] > 0 ? indptr[r0] : 0;
@@ -402,6 +405,7 @@ als_status launch_solve_rows(als_ctx *ctx, const als_csr *Y, const als_table *V,
     int32_t *dual_lists = mid_list + cap_mid;
     int32_t *counters = (int32_t *)((char *)ctx->small.p + SM_COUNTERS);
     unsigned long long *long_stat = (unsigned long long *)((char *)ctx->small.p + SM_LONGSTAT);
+    int32_t *queue = (int32_t *)((char *)ctx->small.p + SM_QUEUE);
     ListOffsets list_off;
     for (int c = 0; c <= 10; ++c) list_off.v[c] = off[c];
 
@@ -446,9 +450,9 @@ als_status launch_solve_rows(als_ctx *ctx, const als_csr *Y, const als_table *V,
     if (nrows <= CLS_ONE_ROWS) {
         hipLaunchKernelGGL(bf ? classify_one_kernel<true> : classify_one_kernel<false>, dim3(1), dim3(CLS_ONE_THREADS), 0, s,
                            Y->indptr, r0, r1, (int64_t)dual_max, V->d, X->data, X->ld, counters, long_rows, segs, mid_list,
-                           cap_mid, dual_lists, list_off, entry_limit, split, hint_out, hs.seq);
+                           cap_mid, dual_lists, list_off, entry_limit, split, hint_out, hs.seq, queue);
     } else {
-        hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, counters, (long long *)long_stat);
+        hipLaunchKernelGGL(clear_counters_kernel, dim3(1), dim3(64), 0, s, counters, (long long *)long_stat, queue);
         auto sort = [&](auto rows_per_thread) {
             constexpr int RPT = decltype(rows_per_thread)::value;
             const unsigned cblocks = (unsigned)((nrows + CLS_THREADS * RPT - 1) / (CLS_THREADS * RPT));
