@@ -203,11 +203,11 @@ def main():
     bounds = [("dual_k4", 0, 4), ("dual_k8", 4, 8)] + [(f"dual_k{16 * (c + 1)}", max(16 * c, 8), 16 * (c + 1)) for c in range(8)]
     bft = "true" if es == 2 else "false"  # the kernels' template arguments as rocprofv3 prints them
     zbt = "true" if (es == 2 and d >= 32) else "false"  # Z kept as bf16
-    kernel_names = {"dual_k4": f"dual_small_kernel<{d},4,{zbt},false>", "dual_k8": f"dual_small_kernel<{d},8,{zbt},false>",
-                    "dual_k16": f"dual_rows_kernel<{d},{zbt}>", "dual_k32": f"dual_multi_kernel<{d},{zbt}>"}
-    small_x = es == 4 and d >= 64 and args.solver == "direct"  # rows of up to 8 entries leave their kernel as X
-    if small_x:
-        kernel_names.update({"dual_k4": f"dual_small_x_kernel<{d},4>", "dual_k8": f"dual_small_x_kernel<{d},8>"})
+    # rows of up to that many entries leave their kernel as X, not as R
+    is_x = 0 if args.solver != "direct" else (32 if zbt == "true" else (8 if es == 4 and d >= 64 else 0))
+    sx, rx = "_x" if is_x >= 8 else "", "_x" if is_x >= 32 else ""
+    kernel_names = {"dual_k4": f"dual_small{sx}_kernel<{d},4,{zbt if sx else 'false'}>", "dual_k8": f"dual_small{sx}_kernel<{d},8,{zbt if sx else 'false'}>",
+                    "dual_k16": f"dual_rows{rx}_kernel<{d}>", "dual_k32": f"dual_multi{rx}_kernel<{d}>"}
     for c in range(2, 8):
         kernel_names[f"dual_k{16 * (c + 1)}"] = f"dual_wide_kernel<{d},{c + 1},{zbt},false,false>"
     if args.solver == "cg" and d >= 64:  # every class runs the one-row-per-wavefront kernel with the CG solver
@@ -218,11 +218,10 @@ def main():
             kernel_names[name] = f"cg_free_kernel<{d},{bft}>"
     kernel_names.update({"gramian": (f"gramian_bf16_kernel<{d}>" if es == 2 else f"gramian_split_kernel<{d}>") if d >= 64
                          else f"gramian_partial_kernel<{d},{bft}>",
-                         "transform_z": f"transform16_kernel<{d},true,true,false>" if zbt == "true"      # Z = V L^-T
+                         "transform_z": f"transform16_kernel<{d},false>" if zbt == "true"      # Z = V L^-T
                          else f"transform_kernel<{d},{bft},false,true,false>",
-                         "transform_x": f"transform16_kernel<{d},false,false,false>" if zbt == "true"    # X = R L^-1
-                         else (f"transform_split_kernel<{d}>" if (es == 4 and d >= 64)
-                               else f"transform_kernel<{d},false,{bft},false,false>"),
+                         "transform_x": f"transform_lists_kernel<{d},{bft}>" if zbt == "true" or (es == 4 and d >= 64)  # X = R L^-1
+                         else f"transform_kernel<{d},false,{bft},false,false>",
                          "primal": f"primal_kernel<{d},{bft},0,false>",               # one workgroup per row
                          "segment": f"primal_kernel<{d},{bft},1,false>"})             # segments of long rows
     zs = 2 if (es == 2 and d >= 32) else 4  # bytes per element of the transformed table Z the dual kernels gather
@@ -260,8 +259,8 @@ def main():
     # lists that are short together share one launch, which the library times in the slot of 8 < k <= 16
     dual_names = [name for name, _, _ in bounds]
     common = args.solver == "direct" and [name for name in dual_names if stage_launches.get(name, 0.0) > 0] == ["dual_k16"]
-    if es == 4 and d >= 64 and args.solver != "cg_free":  # of the rows that are not X yet
-        lo = 8 if small_x and not common else 0
+    if (zbt == "true" or (es == 4 and d >= 64)) and args.solver != "cg_free":  # of the rows that are not X yet
+        lo = 0 if common else is_x
         work["transform_x"][1] = float(sum(int(((k > lo) & (k <= dual_max)).sum()) for k in deg.values())) * d * (4 + es)
     if common:
         work["dual_common"] = ["hbm", sum(work.pop(name)[1] for name in dual_names)]

@@ -183,7 +183,8 @@ constexpr size_t SM_LONGSTAT = 128;     // int64[2]: entries and rows beyond the
 constexpr size_t SM_LOSS = 64;          // double[2]
 constexpr size_t SM_FACTOR = 256;       // fp32 [2][128*128]: L^{-1} and scratch for the dual form
 constexpr size_t SM_QUEUE = SM_FACTOR + 2 * 128 * 128 * sizeof(float);  // int32[2][QUEUE_INTS]: StepQueue counters, cleared with the others
-constexpr size_t SM_BYTES = SM_QUEUE + 2 * QUEUE_INTS * sizeof(int32_t);
+constexpr size_t SM_XMATRIX = SM_QUEUE + 2 * QUEUE_INTS * sizeof(int32_t);  // L^-1 as operands of x_rows.h, 40 KB at d = 128
+constexpr size_t SM_BYTES = SM_XMATRIX + 40 * 1024;
 
 struct LongRow {   // a row whose statistics are accumulated by several segments
     int64_t row;

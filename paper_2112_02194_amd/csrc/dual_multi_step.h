@@ -20,7 +20,8 @@ namespace als {
 //   4. t of the entries 0..15: B^T t (columns of B from LDS, t as a DPP operand), the row operations of step 2 once more
 //      on that vector (their multipliers were left where the eliminated columns were), and the pivots;
 //   5. r = Z_I^T t, four (bf16: eight) columns per lane, from the registers of step 1, or (fp32, d = 128, whose tiles do not fit
-//      the registers, and fp32 in the launch that small calls share) gathering the entries a second time.
+//      the registers, and fp32 in the launch that small calls share) gathering the entries a second time; bf16 tables in the launch of
+//      their own: X = R L^-1 of four steps' rows at a time (Parked, dual_walk.h).
 // Every row goes through LDS into the operand layout (PieceGather), and the walk over the list loads the next step's ids ahead
 // (dual_walk.h).
 // What bounds it: HBM and the instructions of two wavefronts per SIMD, one every five clocks each, where the tiles stay in
@@ -59,6 +60,7 @@ template <int D, bool ZB, bool KEEP = true> struct MultiStep {
     using C = MultiCfg<D, ZB, KEEP>;
     using PG = typename C::PG;
     static constexpr int NIDS = 4 * C::IDR, N = PG::N, EPI = PG::EPI;
+    static constexpr int LDS_FLOATS = C::LDS_FLOATS, FREE = C::OFF_Q;
 
     static __device__ __forceinline__ void init(float *lds, int lane) {
         if (lane < PG::ZERO_FLOATS) lds[C::OFF_ZERO + lane] = 0.f;
@@ -74,10 +76,10 @@ template <int D, bool ZB, bool KEEP = true> struct MultiStep {
         }
     }
 
-    template <class Loaded, class Between, class Last>
-    static __device__ __forceinline__ void solve(const float *__restrict__ values, const void *__restrict__ Z, float *__restrict__ R,
-                                                 int64_t ldr, int32_t *__restrict__ err_flag, float *lds, const RowsDesc &d,
-                                                 const int32_t (&idv)[NIDS], Loaded &&loaded, Between &&between, Last &&last) {
+    template <class Loaded, class Between, class Last, class Out>
+    static __device__ __forceinline__ void solve(const float *__restrict__ values, const void *__restrict__ Z,
+                                                 int32_t *__restrict__ err_flag, float *lds, const RowsDesc &d,
+                                                 const int32_t (&idv)[NIDS], Loaded &&loaded, Between &&between, Last &&last, const Out &out) {
         constexpr int K = C::K;
         const int (&k)[4] = d.k;
         int kmax = 0;
@@ -295,8 +297,7 @@ template <int D, bool ZB, bool KEEP = true> struct MultiStep {
                 }
             }
             last();
-            const int64_t u[4] = {d.row.rel[0], d.row.rel[1], d.row.rel[2], d.row.rel[3]};
-            store_rows<PG::LPR>(rv, R, ldr, u, lane);
+            out.template store<PG::LPR>(rv, lane);
             return;
         }
         if constexpr (!C::RES) {
@@ -347,8 +348,7 @@ template <int D, bool ZB, bool KEEP = true> struct MultiStep {
                     }
             }
             last();
-            const int64_t u[4] = {d.row.rel[0], d.row.rel[1], d.row.rel[2], d.row.rel[3]};
-            store_rows<GC::LPR>(rv, R, ldr, u, lane);
+            out.template store<GC::LPR>(rv, lane);
         }
         }
     }

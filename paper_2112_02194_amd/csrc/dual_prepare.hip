@@ -13,13 +13,14 @@
 //   row kernels       by class of k (fixed by measurement on MI355X): all gather Z_I into MFMA operand
 //                     registers, straight or by way of LDS, form S = I + Z_I Z_I^T on the matrix cores,
 //                     solve the k x k system on the vector ALU, then r = Z_I^T t
-//       dual_small_kernel  k <= 4 and 5 <= k <= 8: several rows share one 16-entry MFMA tile (fp32 tables with d >= 64:
-//                          dual_small_x_kernel, which takes the next step along)
+//       dual_small_kernel  k <= 4 and 5 <= k <= 8: several rows share one 16-entry MFMA tile (dual_small_x_kernel takes
+//                          the last step along, and so do dual_rows_x_kernel and dual_multi_x_kernel for bf16 tables)
 //       dual_rows_kernel   8 < k <= 16: four rows per wavefront, one lane per row of S, gather through LDS
 //       dual_multi_kernel  16 < k <= 32: four rows per wavefront, S in two blocks of 16
 //       dual_wide_kernel   32 < k <= 128 (d >= 64; k <= 64 at d = 64): one row per wavefront, S as a
 //                          lower triangle in LDS, blocked elimination with MFMA trailing updates
-//   transform_kernel  X = R L^{-1}   (rows r -> L^{-T} r), rounding to the table's element type
+//   transform_lists_kernel, transform_kernel (d = 16, fp32 with d = 32)
+//                     X = R L^{-1}   (rows r -> L^{-T} r), rounding to the table's element type
 #include "dual_common.h"
 #include "dual_few.h"
 #include "dual_walk.h"
@@ -28,22 +29,29 @@
 
 namespace als {
 
-void launch_dual_small4(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
-                        const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
-void launch_dual_small8(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
-                        const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
-// with X = R L^-1 taken along (fp32 tables, d = 64 or 128); `queue`: see StepQueue, zero when the launch begins
-als_status launch_dual_small4_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0,
+// per-class launchers (`count_dev`: device address of the list's length; `g`, `w`: see StepGrid, WalkSize; `zb16`: Z is bf16), fp32 Z with
+// d = 16 or 32
+void launch_dual_small4(int d, const als_csr *Y, const void *Z, float *R, int64_t ldr, int64_t r0, const int32_t *list,
+                        const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
+void launch_dual_small8(int d, const als_csr *Y, const void *Z, float *R, int64_t ldr, int64_t r0, const int32_t *list,
+                        const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s);
+// the other tables, with X = R L^-1 taken along; `queue`: see StepQueue, zero when the launch begins
+als_status launch_dual_small4_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, bool zb16, void *X, int64_t ldx, int64_t r0,
                                 const int32_t *list, const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue,
                                 int32_t *err, hipStream_t s);
-als_status launch_dual_small8_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0,
+als_status launch_dual_small8_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, bool zb16, void *X, int64_t ldx, int64_t r0,
                                 const int32_t *list, const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue,
                                 int32_t *err, hipStream_t s);
-// per-class launchers (`count_dev`: device address of the list's length; `g`, `w`: see StepGrid, WalkSize; `zb16`: Z is bf16)
-void launch_dual_k16(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
-                     const int32_t *list, const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
-void launch_dual_multi2(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
-                        const int32_t *list, const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
+// fp32 Z
+void launch_dual_k16(int d, const als_csr *Y, const void *Z, float *R, int64_t ldr, int64_t r0, const int32_t *list,
+                     const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
+void launch_dual_multi2(int d, const als_csr *Y, const void *Z, float *R, int64_t ldr, int64_t r0, const int32_t *list,
+                        const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
+// bf16 Z, with X = R L^-1 taken along
+void launch_dual_k16_x(int d, const als_csr *Y, const void *Z, const XTable &x, int64_t r0, const int32_t *list,
+                       const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
+void launch_dual_multi2_x(int d, const als_csr *Y, const void *Z, const XTable &x, int64_t r0, const int32_t *list,
+                          const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
 #define ALS_DECL_WIDE(kt)                                                                                          \
     als_status launch_dual_wide##kt(als_ctx *ctx, int d, const als_csr *Y, const void *Z, bool zb16, float *R,     \
                                     int64_t ldr, int64_t r0, const int32_t *list, const int32_t *count_dev,        \
@@ -352,11 +360,10 @@ __global__ __launch_bounds__(256) void transform_kernel(const void *In, int64_t 
 }
 
 // ---------------------------------------------------------------------------------------------- transform, bf16 output
-// The same product for bf16 tables (d >= 32), where both passes write bf16 (Z and X): on the bf16 matrix cores,
+// Z = V L^-T for bf16 tables (d >= 32), where Z is bf16 too: on the bf16 matrix cores,
 // which turns the pass from matrix-core-bound (fp32 instruction) into HBM-bound.  M is cut once per workgroup
-// into hi = bf16(M) and lo = bf16(M - hi) (LDS, transposed); bf16 input rows are exact operands (two products
-// per step: x hi + x lo), fp32 input rows (the dual solutions R) are cut the same way (three products,
-// dropping lo lo).  The error of the cut, 2^-17 relative, is far below the bf16 rounding of the output.
+// into hi = bf16(M) and lo = bf16(M - hi) (LDS, transposed); the table's rows are exact operands (two products
+// per step: x hi + x lo).  The error of the cut, 2^-17 relative, is far below the bf16 rounding of the output.
 // The roles of the operands are swapped against transform_kernel: the matrix supplies the M dimension
 // (output columns) and the table rows the N dimension, so that a lane ends up with 16 consecutive output
 // columns of ONE table row (the output columns are assigned to the instruction's row index in the order
@@ -366,25 +373,21 @@ template <int D> struct Xf16Cfg {
     static constexpr size_t LDS_BYTES = (size_t)2 * D * MLD * sizeof(uint16_t);
 };
 
-template <int D, bool IN_BF16, bool UPPER, bool GATHER>
-__global__ __launch_bounds__(256, 2) void transform16_kernel(const void *__restrict__ In, int64_t ldi,
+template <int D, bool GATHER>
+__global__ __launch_bounds__(256, 2) void transform16_kernel(const uint16_t *__restrict__ In, int64_t ldi,
                                                           uint16_t *__restrict__ Out, int64_t ldo,
-                                                          const float *__restrict__ Mt, int64_t r0, int64_t r1,
-                                                          const int64_t *__restrict__ indptr, int64_t k_max, Gather ga) {
+                                                          const float *__restrict__ Mt, int64_t r0, int64_t r1, Gather ga) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    typedef float floatx2 __attribute__((ext_vector_type(2)));
     constexpr int MLD = Xf16Cfg<D>::MLD, NKB = D / 16, NJB = D / 32;
     extern __shared__ uint16_t mt[];  // hi: mt[c * MLD + j] = bf16(M[j][c]); lo: the same at offset D * MLD
-    auto rne = [](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){x, y}, bf16x2)); };
 #pragma unroll 4
     for (int e = threadIdx.x; e < D * D / 4; e += 256) {
         const float4 v = ((const float4 *)Mt)[e];
-        const uint32_t h0 = rne(v.x, v.y), h1 = rne(v.z, v.w);
+        const uint32_t h0 = pack_nearest(v.x, v.y), h1 = pack_nearest(v.z, v.w);
         uint16_t *at = mt + e / (D / 4) * MLD + 4 * (e % (D / 4));
         *(uint2 *)at = make_uint2(h0, h1);
-        *(uint2 *)(at + D * MLD) = make_uint2(rne(v.x - __uint_as_float(h0 << 16), v.y - __uint_as_float(h0 & 0xffff0000u)),
-                                              rne(v.z - __uint_as_float(h1 << 16), v.w - __uint_as_float(h1 & 0xffff0000u)));
+        *(uint2 *)(at + D * MLD) = make_uint2(pack_nearest(v.x - __uint_as_float(h0 << 16), v.y - __uint_as_float(h0 & 0xffff0000u)),
+                                              pack_nearest(v.z - __uint_as_float(h1 << 16), v.w - __uint_as_float(h1 & 0xffff0000u)));
     }
     if constexpr (GATHER) {
         r0 = ga.begin();
@@ -399,40 +402,19 @@ __global__ __launch_bounds__(256, 2) void transform16_kernel(const void *__restr
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntiles; tile += nwaves) {
         const int64_t row = r0 + tile * 32 + n;
-        bool keep = row < r1;
-        if (keep && indptr) {  // only rows solved in the dual form are written
-            const int64_t k = indptr[row + 1] - indptr[row];
-            keep = k > 0 && k <= k_max;
-        }
-        // this lane's share of its row: columns 16 kb + 8 kq .., as bf16 operands (hi and, for fp32 input, lo)
+        const bool keep = row < r1;
+        // this lane's share of its row: columns 16 kb + 8 kq .., operands as they are
         int64_t src = row;
         if constexpr (GATHER) {
             src = row < r1 ? ga.ids[row] : 0;
             if (kq == 0 && row < r1) ga.entry_ids[row] = (int32_t)row;
         }
-        bf16x8 xh[NKB], xl[IN_BF16 ? 1 : NKB];
+        bf16x8 xh[NKB];
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
-            if constexpr (IN_BF16) {
-                u32x4 w = {0u, 0u, 0u, 0u};
-                if (row < r1) w = *(const u32x4 *)((const uint16_t *)In + src * ldi + 16 * kb + 8 * kq);
-                xh[kb] = __builtin_bit_cast(bf16x8, w);
-            } else {
-                float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                if (row < r1) {
-                    const float4 p = *(const float4 *)((const float *)In + src * ldi + 16 * kb + 8 * kq);
-                    const float4 q4 = *(const float4 *)((const float *)In + src * ldi + 16 * kb + 8 * kq + 4);
-                    x[0] = p.x; x[1] = p.y; x[2] = p.z; x[3] = p.w; x[4] = q4.x; x[5] = q4.y; x[6] = q4.z; x[7] = q4.w;
-                }
-                u32x4 h, l;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    h[w] = rne(x[2 * w], x[2 * w + 1]);
-                    l[w] = rne(x[2 * w] - __uint_as_float(h[w] << 16), x[2 * w + 1] - __uint_as_float(h[w] & 0xffff0000u));
-                }
-                xh[kb] = __builtin_bit_cast(bf16x8, h);
-                xl[kb] = __builtin_bit_cast(bf16x8, l);
-            }
+            u32x4 w = {0u, 0u, 0u, 0u};
+            if (keep) w = *(const u32x4 *)(In + src * ldi + 16 * kb + 8 * kq);
+            xh[kb] = __builtin_bit_cast(bf16x8, w);
         }
 #pragma unroll
         for (int J = 0; J < NJB; ++J) {
@@ -442,11 +424,10 @@ __global__ __launch_bounds__(256, 2) void transform16_kernel(const void *__restr
             const uint16_t *mrow = mt + (32 * J + pi) * MLD + 8 * kq;
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb) {
-                if (UPPER ? (kb <= 2 * J + 1) : (kb >= 2 * J)) {  // compile-time after unrolling: other steps only meet zeros
+                if (kb <= 2 * J + 1) {  // compile-time after unrolling: other steps only meet zeros
                     const bf16x8 mh = *(const bf16x8 *)(mrow + 16 * kb), ml = *(const bf16x8 *)(mrow + D * MLD + 16 * kb);
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mh, xh[kb], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ml, xh[kb], acc, 0, 0, 0);
-                    if constexpr (!IN_BF16) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mh, xl[kb], acc, 0, 0, 0);
                 }
             }
             // acc[v] = Out[row][32 J + 16 kq + v]
@@ -454,8 +435,8 @@ __global__ __launch_bounds__(256, 2) void transform16_kernel(const void *__restr
                 u32x4 lo4, hi4;
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
-                    lo4[w] = rne(acc[2 * w], acc[2 * w + 1]);
-                    hi4[w] = rne(acc[8 + 2 * w], acc[8 + 2 * w + 1]);
+                    lo4[w] = pack_nearest(acc[2 * w], acc[2 * w + 1]);
+                    hi4[w] = pack_nearest(acc[8 + 2 * w], acc[8 + 2 * w + 1]);
                 }
                 u32x4 *dst = (u32x4 *)(Out + row * ldo + 32 * J + 16 * kq);
                 dst[0] = lo4;
@@ -465,10 +446,10 @@ __global__ __launch_bounds__(256, 2) void transform16_kernel(const void *__restr
     }
 }
 
-// ---------------------------------------------------------------------------------------------- transform, fp32 tables
-// X = R L^-1 in place for fp32 tables (d >= 64), of the rows of some class lists: with fp32 accuracy on the bf16 matrix cores
-// (x_rows.h), 0.375 of the fp32 instruction's matrix-core time, which leaves the pass to the table read and write (for Z = V L^-T
-// the fp32 kernel above measured faster, 24.4 against 25.9 ms per epoch of 50M x 50M).  A wavefront takes 32 rows at a time.
+// ---------------------------------------------------------------------------------------------- X = R L^-1 of class lists
+// x_rows.h over the rows of some class lists, 32 rows per wavefront at a time, fp32 tables (d >= 64) in place, bf16 tables (d >= 32)
+// from the fp32 rows of R.  fp32: 0.375 of the fp32 instruction's matrix-core time, which leaves the pass to the table read and
+// write (for Z = V L^-T the fp32 kernel above measured faster, 24.4 against 25.9 ms per epoch of 50M x 50M).
 // What bounds it: HBM (4.5 TB/s of rows read and written).
 constexpr int XFS_THREADS = 512;
 struct XLists {
@@ -476,14 +457,17 @@ struct XLists {
     int n;
 };
 
-template <int D>
-__global__ __launch_bounds__(XFS_THREADS, 2) void transform_split_kernel(float *__restrict__ X, int64_t ldx, const float *__restrict__ LinvT,
-                                                                         int64_t r0, XLists xl) {
+template <int D, bool BF>
+__global__ __launch_bounds__(XFS_THREADS, 2) void transform_lists_kernel(const float *R, int64_t ldr,
+                                                                         typename std::conditional<BF, uint16_t, float>::type *X, int64_t ldx,
+                                                                         const float *__restrict__ LinvT, int64_t r0, XLists xl) {
+    using M = XMatrix<D, BF>;
     constexpr int NK = D / 32;
     extern __shared__ char mat[];
-    XMatrix<D>::fill(mat, LinvT, threadIdx.x, XFS_THREADS);
+    M::fill(mat, LinvT, threadIdx.x, XFS_THREADS);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), a = lane & 15, q = lane >> 4;
+    R += r0 * ldr;
     X += r0 * ldx;
     const int nwaves = (int)gridDim.x * (XFS_THREADS / 64);
     int tile = (int)blockIdx.x * (XFS_THREADS / 64) + wave;  // counted from the first tile of list i
@@ -504,30 +488,31 @@ __global__ __launch_bounds__(XFS_THREADS, 2) void transform_split_kernel(float *
             for (int n = 0; n < 2; ++n)
 #pragma unroll
                 for (int kb = 0; kb < NK; ++kb) {
-                    const float *src = X + rel[n] * ldx + 32 * kb + 8 * q;
+                    const float *src = R + rel[n] * ldr + 32 * kb + 8 * q;
                     raw[n][kb][0] = *(const float4 *)src;
                     raw[n][kb][1] = *(const float4 *)(src + 4);
                 }
-            bf16x8 xp[2][3][NK];
+            bf16x8 xp[2][M::PARTS][NK];
 #pragma unroll
             for (int n = 0; n < 2; ++n)
 #pragma unroll
                 for (int kb = 0; kb < NK; ++kb) {
-                    bf16x8 part[3];
-                    XMatrix<D>::cut(raw[n][kb][0], raw[n][kb][1], part);
+                    bf16x8 part[M::PARTS];
+                    M::cut(raw[n][kb][0], raw[n][kb][1], part);
 #pragma unroll
-                    for (int t = 0; t < 3; ++t) xp[n][t][kb] = part[t];
+                    for (int t = 0; t < M::PARTS; ++t) xp[n][t][kb] = part[t];
                 }
-            x_rows<D, 2>(mat, xp, [&](int n, int P, const floatx4 (&v)[2]) {
-                if (have[n]) {
-                    float *dst = X + rel[n] * ldx + 32 * P + 8 * q;
-                    *(floatx4 *)dst = v[0];
-                    *(floatx4 *)(dst + 4) = v[1];
-                }
+            x_rows<D, BF, 2>(mat, xp, [&](int n, int P, const floatx4 (&v)[2]) {
+                if (have[n]) store_x8<BF>(X + rel[n] * ldx + 32 * P + 8 * q, v);
             });
         }
         tile -= tiles;
     }
+}
+
+// XMatrix for the kernels that read it from device memory
+template <int D> __global__ __launch_bounds__(64) void x_matrix_kernel(const float *__restrict__ LinvT, char *__restrict__ mat) {
+    XMatrix<D, true>::fill(mat, LinvT, blockIdx.x * 64 + threadIdx.x, gridDim.x * 64);
 }
 
 // ---------------------------------------------------------------------------------------------- launchers
@@ -563,13 +548,13 @@ static als_status dual_prepare_typed(als_ctx *ctx, const als_table *V, const flo
     auto transform = [&](auto gather) {  // L^{-1} is the transpose of the matrix applied
         constexpr bool GA = decltype(gather)::value;
         if constexpr (ZB) {
-            static const hipError_t attr = hipFuncSetAttribute((const void *)transform16_kernel<D, true, true, GA>,
+            static const hipError_t attr = hipFuncSetAttribute((const void *)transform16_kernel<D, GA>,
                                                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                                                (int)Xf16Cfg<D>::LDS_BYTES);  // once per process
             if (attr == hipSuccess)
-                hipLaunchKernelGGL((transform16_kernel<D, true, true, GA>), dim3(tblocks), dim3(256), Xf16Cfg<D>::LDS_BYTES, s,
-                                   V->data, V->ld, (uint16_t *)ctx->ztable.p, (int64_t)D, (const float *)Linv, (int64_t)0,
-                                   V->rows, (const int64_t *)nullptr, (int64_t)0, ga);
+                hipLaunchKernelGGL((transform16_kernel<D, GA>), dim3(tblocks), dim3(256), Xf16Cfg<D>::LDS_BYTES, s,
+                                   (const uint16_t *)V->data, V->ld, (uint16_t *)ctx->ztable.p, (int64_t)D, (const float *)Linv,
+                                   (int64_t)0, V->rows, ga);
             return attr;
         } else {
             static const hipError_t attr = hipFuncSetAttribute((const void *)transform_kernel<D, BF16, false, true, GA>,
@@ -608,8 +593,8 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     int32_t *err = (int32_t *)((char *)ctx->small.p + SM_COUNTERS) + 2;
     int32_t *queue = (int32_t *)((char *)ctx->small.p + SM_QUEUE);
     const void *Z = ctx->ztable.p;
-    constexpr bool zb16 = z_is_bf16<D, BF16>(), X_LISTS = !BF16 && D >= 64;
-    bool small_x = false;  // rows of up to 8 entries are X already
+    constexpr bool zb16 = z_is_bf16<D, BF16>(), X_LISTS = zb16 || (!BF16 && D >= 64);
+    bool is_x[10] = {false};  // classes whose rows leave their kernel as X
     als_status stb = ALS_OK;
     // workgroups of class `cls` whose kernel takes `rpw` rows per step
     auto grid = [&](int cls, int rpw) {
@@ -654,16 +639,25 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
         ALS_TIMED_CLASS(T_SMALL8, 9, 1, (stb = launch_dual_wide3(ctx, D, Y, Z, zb16, R, ldr, r0, lists[9], counts_dev[9], g, err, ws, s)))
         ALS_TIMED_CLASS(T_SMALL4, 8, 1, (stb = launch_dual_wide3(ctx, D, Y, Z, zb16, R, ldr, r0, lists[8], counts_dev[8], g, err, ws, s)))
     } else {
-    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 1, 1, 4, (launch_dual_multi2(D, Y, Z, zb16, R, ldr, r0, lists[1], counts_dev[1], walk(1, 4), err, s)))
-    ALS_TIMED_CLASS(T_DUAL_CLASS0, 0, 4, (launch_dual_k16(D, Y, Z, zb16, R, ldr, r0, lists[0], counts_dev[0], walk(0, 4), err, s)))
+    if constexpr (zb16) {
+    char *xmat = (char *)ctx->small.p + SM_XMATRIX;
+    is_x[0] = is_x[1] = true;
+    hipLaunchKernelGGL(x_matrix_kernel<D>, dim3(XMatrix<D, true>::BLOCKS), dim3(64), 0, s, LinvT, xmat);
+    const XTable x = {(uint16_t *)X->data, X->ld, xmat};
+    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 1, 1, 4, (launch_dual_multi2_x(D, Y, Z, x, r0, lists[1], counts_dev[1], walk(1, 4), err, s)))
+    ALS_TIMED_CLASS(T_DUAL_CLASS0, 0, 4, (launch_dual_k16_x(D, Y, Z, x, r0, lists[0], counts_dev[0], walk(0, 4), err, s)))
+    } else {
+    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 1, 1, 4, (launch_dual_multi2(D, Y, Z, R, ldr, r0, lists[1], counts_dev[1], walk(1, 4), err, s)))
+    ALS_TIMED_CLASS(T_DUAL_CLASS0, 0, 4, (launch_dual_k16(D, Y, Z, R, ldr, r0, lists[0], counts_dev[0], walk(0, 4), err, s)))
+    }
     // 5 <= k <= 8 and k <= 4: several rows per MFMA tile
     if constexpr (X_LISTS) {
-    small_x = true;
-    ALS_TIMED_CLASS(T_SMALL8, 9, 8, (stb = launch_dual_small8_x(ctx, D, Y, Z, R, ldr, r0, lists[9], counts_dev[9], walk(9, 8), LinvT, queue, err, s)))
-    ALS_TIMED_CLASS(T_SMALL4, 8, 16, (stb = launch_dual_small4_x(ctx, D, Y, Z, R, ldr, r0, lists[8], counts_dev[8], walk(8, 16), LinvT, queue + QUEUE_INTS, err, s)))
+    is_x[8] = is_x[9] = true;
+    ALS_TIMED_CLASS(T_SMALL8, 9, 8, (stb = launch_dual_small8_x(ctx, D, Y, Z, zb16, X->data, X->ld, r0, lists[9], counts_dev[9], walk(9, 8), LinvT, queue, err, s)))
+    ALS_TIMED_CLASS(T_SMALL4, 8, 16, (stb = launch_dual_small4_x(ctx, D, Y, Z, zb16, X->data, X->ld, r0, lists[8], counts_dev[8], walk(8, 16), LinvT, queue + QUEUE_INTS, err, s)))
     } else {
-    ALS_TIMED_CLASS(T_SMALL8, 9, 8, (launch_dual_small8(D, Y, Z, zb16, R, ldr, r0, lists[9], counts_dev[9], g, err, s)))
-    ALS_TIMED_CLASS(T_SMALL4, 8, 16, (launch_dual_small4(D, Y, Z, zb16, R, ldr, r0, lists[8], counts_dev[8], g, err, s)))
+    ALS_TIMED_CLASS(T_SMALL8, 9, 8, (launch_dual_small8(D, Y, Z, R, ldr, r0, lists[9], counts_dev[9], g, err, s)))
+    ALS_TIMED_CLASS(T_SMALL4, 8, 16, (launch_dual_small4(D, Y, Z, R, ldr, r0, lists[8], counts_dev[8], g, err, s)))
     }
     }
     ALS_TIMED_CLASS(T_DUAL_CLASS0 + 2, 2, 1, (stb = launch_dual_wide3(ctx, D, Y, Z, zb16, R, ldr, r0, lists[2], counts_dev[2], g, err, ws, s)))
@@ -677,29 +671,25 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     if (stb != ALS_OK) return stb;
     timer_begin(ctx, T_TRANSFORM_X, s);
     const unsigned xblocks = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(1, (r1 - r0 + 127) / 128));
-    if constexpr (zb16) {
-        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform16_kernel<D, false, false, false>,
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                             (int)Xf16Cfg<D>::LDS_BYTES);  // once per process
-        ALS_HIP(ctx, attr_x);
-        hipLaunchKernelGGL((transform16_kernel<D, false, false, false>), dim3(xblocks), dim3(256), Xf16Cfg<D>::LDS_BYTES, s,
-                           (const void *)R, ldr, (uint16_t *)X->data, X->ld, LinvT, r0, r1, Y->indptr, (int64_t)dual_max, Gather{});
-    } else if constexpr (X_LISTS) {
-        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_split_kernel<D>,
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, XMatrix<D>::BYTES);  // once per process
+    if constexpr (X_LISTS) {
+        using M = XMatrix<D, BF16>;
+        typedef typename std::conditional<BF16, uint16_t, float>::type elem;
+        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_lists_kernel<D, BF16>,
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, M::BYTES);  // once per process
         ALS_HIP(ctx, attr_x);
         XLists xl;
         xl.n = 0;
         int64_t tiles = 0;
-        for (int c = 0; c < (small_x ? 8 : 10); ++c)
-            if (caps[c] > 0) {
+        for (int c = 0; c < 10; ++c)
+            if (caps[c] > 0 && !is_x[c]) {
                 xl.list[xl.n] = lists[c];
                 xl.count[xl.n++] = counts_dev[c];
                 tiles += (caps[c] + 31) / 32;
             }
         const unsigned sblocks = (unsigned)std::min<int64_t>(512, (tiles + XFS_THREADS / 64 - 1) / (XFS_THREADS / 64));
         if (sblocks > 0)
-            hipLaunchKernelGGL((transform_split_kernel<D>), dim3(sblocks), dim3(XFS_THREADS), XMatrix<D>::BYTES, s, R, ldr, LinvT, r0, xl);
+            hipLaunchKernelGGL((transform_lists_kernel<D, BF16>), dim3(sblocks), dim3(XFS_THREADS), M::BYTES, s, (const float *)R, ldr,
+                               (elem *)X->data, X->ld, LinvT, r0, xl);
     } else {
         static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_kernel<D, false, BF16, false, false>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -28,7 +28,7 @@ template <int D, bool ZB> struct RowsCfg {
 
 // (the members are what walk_steps and single_step want, see dual_walk.h)
 template <int D, bool ZB> struct RowsStep {
-    static constexpr int NIDS = 4;
+    static constexpr int NIDS = 4, LDS_FLOATS = RowsCfg<D, ZB>::LDS_FLOATS, FREE = 0;
     // Where S is formed in full fp32 precision (d = 16), the rounding of the elimination is what is left, and the Gauss-Jordan form
     // rounds a little more than triangular solves do.  Error against fp64, 8 < k <= 16, fp32, alpha = 0.05 / 1e-4 / 1e-5: triangular
     // 1.79e-7 / 3.80e-7 / 1.12e-6, Gauss-Jordan 1.76e-7 / 4.04e-7 / 1.15e-6, with one step of refinement 1.32e-7 / 3.25e-7 / 0.97e-6;
@@ -49,10 +49,10 @@ template <int D, bool ZB> struct RowsStep {
 #pragma unroll
         for (int p = 0; p < 4; ++p) idv[p] = indices[d.b[p] + (e < d.k[p] ? e : 0)];  // clamped: rows of the class have k >= 1
     }
-    template <class Loaded, class Between, class Last>
-    static __device__ __forceinline__ void solve(const float *__restrict__ values, const void *__restrict__ Z, float *__restrict__ R,
-                                                 int64_t ldr, int32_t *__restrict__ err_flag, float *lds, const RowsDesc &d,
-                                                 const int32_t (&idv)[NIDS], Loaded &&loaded, Between &&between, Last &&last) {
+    template <class Loaded, class Between, class Last, class Out>
+    static __device__ __forceinline__ void solve(const float *__restrict__ values, const void *__restrict__ Z,
+                                                 int32_t *__restrict__ err_flag, float *lds, const RowsDesc &d,
+                                                 const int32_t (&idv)[NIDS], Loaded &&loaded, Between &&between, Last &&last, const Out &out) {
         using C = RowsCfg<D, ZB>;
         using RG = RowGather<D, ZB>;
         constexpr int RPW = C::RPW, N = RG::N, EPI = RG::EPI;
@@ -220,8 +220,7 @@ template <int D, bool ZB> struct RowsStep {
             }
         }
         last();
-        const int64_t u[4] = {d.row.rel[0], d.row.rel[1], d.row.rel[2], d.row.rel[3]};
-        store_rows<RG::LPR>(rv, R, ldr, u, lane);
+        out.template store<RG::LPR>(rv, lane);
     }
 };
 

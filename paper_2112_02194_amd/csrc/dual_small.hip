@@ -12,7 +12,7 @@ namespace als {
 
 // The two launch forms of a step kernel (see StepGrid): one step per workgroup, or a grid-stride walk from
 // step first_blk to the end of the list.
-template <int D, int G, bool ZB, bool LOOP>
+template <int D, int G, bool LOOP>
 __global__ __launch_bounds__(64) void dual_small_kernel(const int64_t *__restrict__ indptr,
                                                         const int32_t *__restrict__ indices,
                                                         const float *__restrict__ values,
@@ -27,17 +27,17 @@ __global__ __launch_bounds__(64) void dual_small_kernel(const int64_t *__restric
     int blk = first_blk + blockIdx.x;
     if constexpr (!LOOP) {
         blk = xcd_step(blk, gridDim.x, steps);
-        if (blk < steps) dual_small_step<D, G, ZB>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
+        if (blk < steps) dual_small_step<D, G, false>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, blk, lds);
     } else {
         for (; blk < steps; blk += gridDim.x) {
-            dual_small_step<D, G, ZB>(opaque(indptr), opaque(indices), opaque(values), opaque(Z), opaque(R), opaque(ldr), opaque(r0),
+            dual_small_step<D, G, false>(opaque(indptr), opaque(indices), opaque(values), opaque(Z), opaque(R), opaque(ldr), opaque(r0),
                               opaque(list), opaque(count), opaque(err_flag), blk, opaque(lds));
             wave_sync();  // the next step reuses the LDS buffers
         }
     }
 }
 
-// The same step with X = R L^-1 taken along (fp32 tables, d >= 64): the wavefront's rows of R go from registers through LDS
+// The same step with X = R L^-1 taken along (fp32 tables with d >= 64, bf16 tables with d >= 32): the wavefront's rows of R go from registers through LDS
 // into x_rows and never to memory, where a pass of its own writes and reads each of them once more.  Epoch of 50M x 50M rows (d =
 // 128), 81M of whose 100M solved rows come through here: 132.0 -> 115.2 ms (these kernels 46.0 -> 47.5 ms, the pass over the rows left
 // 24.8 -> 4.3 ms); 10M pages: 55.2 -> 54.1 ms; 1M x 1M (d = 64) the two together 402 -> 324 us.
@@ -45,41 +45,41 @@ __global__ __launch_bounds__(64) void dual_small_kernel(const int64_t *__restric
 // steps in turn or, where they get many, from a queue (50M x 50M: 49.7 ms in turn, 47.5 from the queue; 378 000 rows of 5 to 8 entries, d = 64:
 // 142 us in turn, 237 from a queue, whose counters all wavefronts ask at the end).  List entry, row descriptor and column id of the next step are loaded while a step is solved: lane
 // l = 16 p + a of the wavefront keeps those of entry slot a of tile p.
-// What bounds it: HBM (50M rows of c4's kind: 5.0 TB/s with the rows of Z, ids and X; two wavefronts per SIMD).
-constexpr int SMALL_X_THREADS = 512;
-
-template <int D, int G> struct SmallXCfg {
+// bf16 tables: 20M x 20M rows of 6 entries (d = 128) 10.8 -> 9.9 ms and 6.7 -> 0.02 ms of the pass, the epoch 31.6 -> 24.3; 3M x 2M (d = 64)
+// 2.53 -> 2.18 ms, 2M x 3M (d = 32) 1.59 -> 1.35 ms (with 8 < k <= 32, dual_walk.h).
+// What bounds it: HBM (50M rows of 1 to 8 entries, fp32: 5.0 TB/s with the rows of Z, ids and X; two wavefronts per SIMD, three with bf16).
+template <int D, int G, bool ZB> struct SmallXCfg {
+    static constexpr int THREADS = ZB ? 768 : 512;
+    using M = XMatrix<D, ZB>;
+    typedef typename std::conditional<ZB, uint16_t, float>::type elem;
     static constexpr int RLD = D + 4;  // row stride of the copy of R
     static constexpr int WAVE_FLOATS = SmallCfg<D, G>::OFF_META;
     static_assert(16 * RLD <= SmallCfg<D, G>::MAIN, "sixteen rows of R take the place of a tile's entries");
-    static constexpr size_t LDS_BYTES = XMatrix<D>::BYTES + (SMALL_X_THREADS / 64) * WAVE_FLOATS * sizeof(float);
+    static constexpr size_t LDS_BYTES = M::BYTES + (THREADS / 64) * WAVE_FLOATS * sizeof(float);
 };
 
-template <int D, int G>
-__global__ __launch_bounds__(SMALL_X_THREADS, 2) void dual_small_x_kernel(const int64_t *__restrict__ indptr,
-                                                                          const int32_t *__restrict__ indices,
-                                                                          const float *__restrict__ values,
-                                                                          const float *__restrict__ Z, float *__restrict__ X,
-                                                                          int64_t ldx, int64_t r0, const int32_t *__restrict__ list,
-                                                                          const int32_t *__restrict__ count_ptr,
-                                                                          const float *__restrict__ LinvT, int32_t *__restrict__ queue,
-                                                                          int32_t *__restrict__ err_flag) {
+template <int D, int G, bool ZB>
+__global__ __launch_bounds__((SmallXCfg<D, G, ZB>::THREADS)) void dual_small_x_kernel(
+    const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices, const float *__restrict__ values, const void *__restrict__ Z,
+    typename SmallXCfg<D, G, ZB>::elem *__restrict__ X, int64_t ldx, int64_t r0, const int32_t *__restrict__ list,
+    const int32_t *__restrict__ count_ptr, const float *__restrict__ LinvT, int32_t *__restrict__ queue, int32_t *__restrict__ err_flag) {
     using C = SmallCfg<D, G>;
-    using CX = SmallXCfg<D, G>;
-    constexpr int NR = C::NR, NJ = z_pieces<D, false>(), CPL = D >= 128 ? 2 : 1, NK = D / 32;
+    using CX = SmallXCfg<D, G, ZB>;
+    using M = typename CX::M;
+    constexpr int NR = C::NR, NJ = z_pieces<D, ZB>(), CPL = D >= 128 ? 2 : 1, NK = D / 32;
     extern __shared__ float shared[];
     const int count = *count_ptr;
     if (count <= 0) return;
     char *mat = (char *)shared;
-    XMatrix<D>::fill(mat, LinvT, threadIdx.x, SMALL_X_THREADS);
+    M::fill(mat, LinvT, threadIdx.x, CX::THREADS);
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    float *lds = (float *)(mat + XMatrix<D>::BYTES) + wave * CX::WAVE_FLOATS;
+    float *lds = (float *)(mat + M::BYTES) + wave * CX::WAVE_FLOATS;
     const int slot = lane % G;
     X += r0 * ldx;
     indptr += r0;
 
-    StepQueue steps = step_queue(queue, list_steps(count, NR), blockIdx.x, gridDim.x, wave, SMALL_X_THREADS / 64);
+    StepQueue steps = step_queue(queue, list_steps(count, NR), blockIdx.x, gridDim.x, wave, CX::THREADS / 64);
     auto next_step = [&]() {
         return steps.next([](const int32_t *counter) { return __builtin_amdgcn_readfirstlane(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); },
                           [&](int32_t *counter, int n) {
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(SMALL_X_THREADS, 2) void dual_small_x_kernel(const 
                 for (int j = 0; j < NJ; ++j) z[p][j] = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (ids[p] >= 0) {
 #pragma unroll
-                    for (int j = 0; j < NJ; ++j) z[p][j] = load_piece<D, false>(Z, ids[p], j, q);
+                    for (int j = 0; j < NJ; ++j) z[p][j] = load_piece<D, ZB>(Z, ids[p], j, q);
                 }
             }
         }
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(SMALL_X_THREADS, 2) void dual_small_x_kernel(const 
         const int after = next < 0 ? -1 : next_step();
         const int32_t rel_after = after < 0 ? rel_next : row_of(after);
 
-        small_solve<D, G, false>(z, y, lds, err_flag);
+        small_solve<D, G, ZB>(z, y, lds, err_flag);
 
         // ---- the next step's column ids
         const int k_next = next >= 0 && place(next) < (unsigned)count ? (int)(e_next - b_next) : 0;
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(SMALL_X_THREADS, 2) void dual_small_x_kernel(const 
         for (int n = 0; n < NR; ++n)
 #pragma unroll
             for (int c = 0; c < CPL; ++c) r[n][c] = 0.f;
-        small_rows<D, G, false>(z, lds, [&](int n) { return __builtin_amdgcn_readlane(k, n * G); }, [&](int n, const float (&v)[CPL]) {
+        small_rows<D, G, ZB>(z, lds, [&](int n) { return __builtin_amdgcn_readlane(k, n * G); }, [&](int n, const float (&v)[CPL]) {
 #pragma unroll
             for (int c = 0; c < CPL; ++c) r[n][c] = v[c];
         });
@@ -152,24 +152,21 @@ __global__ __launch_bounds__(SMALL_X_THREADS, 2) void dual_small_x_kernel(const 
         }
         wave_sync();
         const int a = lane & 15, q = lane >> 4;
-        bf16x8 xp[1][3][NK];
+        bf16x8 xp[1][M::PARTS][NK];
 #pragma unroll
         for (int kb = 0; kb < NK; ++kb) {
             const float *src = lds + a * CX::RLD + 32 * kb + 8 * q;
-            bf16x8 part[3];
-            XMatrix<D>::cut(*(const float4 *)src, *(const float4 *)(src + 4), part);
+            bf16x8 part[M::PARTS];
+            M::cut(*(const float4 *)src, *(const float4 *)(src + 4), part);
 #pragma unroll
-            for (int t = 0; t < 3; ++t) xp[0][t][kb] = part[t];
+            for (int t = 0; t < M::PARTS; ++t) xp[0][t][kb] = part[t];
         }
         const int32_t my_rel = __shfl(rel, a * G & 63);
         const int my_k = __shfl(k, a * G & 63);  // by all lanes: a lane that is masked out gives nothing
         const bool mine = a < NR && my_k > 0;
-        float *dst = X + my_rel * ldx + 8 * q;
-        x_rows<D, 1>(mat, xp, [&](int, int P, const floatx4 (&v)[2]) {
-            if (mine) {
-                *(floatx4 *)(dst + 32 * P) = v[0];
-                *(floatx4 *)(dst + 32 * P + 4) = v[1];
-            }
+        typename CX::elem *dst = X + my_rel * ldx + 8 * q;
+        x_rows<D, ZB, 1>(mat, xp, [&](int, int P, const floatx4 (&v)[2]) {
+            if (mine) store_x8<ZB>(dst + 32 * P, v);
         });
         if (next < 0) break;
         wave_sync();  // the next step reuses the LDS buffers
@@ -183,61 +180,58 @@ __global__ __launch_bounds__(SMALL_X_THREADS, 2) void dual_small_x_kernel(const 
     }
 }
 
-template <int D>
-static als_status launch_small_x_typed(als_ctx *ctx, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0, const int32_t *list,
+template <int D, bool ZB>
+static als_status launch_small_x_typed(als_ctx *ctx, const als_csr *Y, const void *Z, void *X, int64_t ldx, int64_t r0, const int32_t *list,
                                        const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue, int32_t *err,
                                        hipStream_t s) {
-    using CX = SmallXCfg<D, SMALL_G>;
-    static const hipError_t attr = hipFuncSetAttribute((const void *)dual_small_x_kernel<D, SMALL_G>,
+    using CX = SmallXCfg<D, SMALL_G, ZB>;
+    static const hipError_t attr = hipFuncSetAttribute((const void *)dual_small_x_kernel<D, SMALL_G, ZB>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)CX::LDS_BYTES);  // once per process
     ALS_HIP(ctx, attr);
-    constexpr int64_t WAVES = SMALL_X_THREADS / 64, PER_CU = 160 * 1024 / CX::LDS_BYTES;
+    constexpr int64_t WAVES = CX::THREADS / 64, PER_CU = 160 * 1024 / CX::LDS_BYTES;
     const int64_t most = w.num_cu * PER_CU, wanted = ((w.hint < 0 ? w.capacity : std::min(w.hint, w.capacity)) + WAVES - 1) / WAVES;
     const unsigned blocks = (unsigned)(std::max<int64_t>(1, std::min(most, wanted)) + 7) / 8 * 8;
-    hipLaunchKernelGGL((dual_small_x_kernel<D, SMALL_G>), dim3(blocks), dim3(SMALL_X_THREADS), CX::LDS_BYTES, s, Y->indptr, Y->indices,
-                       Y->values, (const float *)Z, X, ldx, r0, list, count_dev, LinvT, queue, err);
+    hipLaunchKernelGGL((dual_small_x_kernel<D, SMALL_G, ZB>), dim3(blocks), dim3(CX::THREADS), CX::LDS_BYTES, s, Y->indptr, Y->indices,
+                       Y->values, Z, (typename CX::elem *)X, ldx, r0, list, count_dev, LinvT, queue, err);
     return ALS_OK;
 }
 
 #if SMALL_G == 8
-als_status launch_dual_small8_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0, const int32_t *list,
-                                const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue, int32_t *err, hipStream_t s) {
+als_status launch_dual_small8_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, bool zb16, void *X, int64_t ldx, int64_t r0,
+                                const int32_t *list, const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue, int32_t *err, hipStream_t s) {
 #else
-als_status launch_dual_small4_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, float *X, int64_t ldx, int64_t r0, const int32_t *list,
-                                const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue, int32_t *err, hipStream_t s) {
+als_status launch_dual_small4_x(als_ctx *ctx, int d, const als_csr *Y, const void *Z, bool zb16, void *X, int64_t ldx, int64_t r0,
+                                const int32_t *list, const int32_t *count_dev, WalkSize w, const float *LinvT, int32_t *queue, int32_t *err, hipStream_t s) {
 #endif
-    return d == 128 ? launch_small_x_typed<128>(ctx, Y, Z, X, ldx, r0, list, count_dev, w, LinvT, queue, err, s)
-                    : launch_small_x_typed<64>(ctx, Y, Z, X, ldx, r0, list, count_dev, w, LinvT, queue, err, s);
+#define ALS_SMALL_CASE(dd, zb) launch_small_x_typed<dd, zb>(ctx, Y, Z, X, ldx, r0, list, count_dev, w, LinvT, queue, err, s)
+    if (zb16) return d == 128 ? ALS_SMALL_CASE(128, true) : (d == 64 ? ALS_SMALL_CASE(64, true) : ALS_SMALL_CASE(32, true));
+    return d == 128 ? ALS_SMALL_CASE(128, false) : ALS_SMALL_CASE(64, false);
+#undef ALS_SMALL_CASE
 }
 
-template <int D, bool ZB>
+template <int D>
 static void launch_small_typed(const als_csr *Y, const void *Z, float *R, int64_t ldr, int64_t r0, const int32_t *list,
                                const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s) {
     using C = SmallCfg<D, SMALL_G>;
     if (g.known > 0)
-        hipLaunchKernelGGL((dual_small_kernel<D, SMALL_G, ZB, false>), dim3(g.known), dim3(64),
+        hipLaunchKernelGGL((dual_small_kernel<D, SMALL_G, false>), dim3(g.known), dim3(64),
                            C::LDS_FLOATS * sizeof(float), s, Y->indptr, Y->indices, Y->values, Z, R, ldr, r0, list,
                            count_dev, 0, err);
     if (g.rest > 0)
-        hipLaunchKernelGGL((dual_small_kernel<D, SMALL_G, ZB, true>), dim3(g.rest), dim3(64),
+        hipLaunchKernelGGL((dual_small_kernel<D, SMALL_G, true>), dim3(g.rest), dim3(64),
                            C::LDS_FLOATS * sizeof(float), s, Y->indptr, Y->indices, Y->values, Z, R, ldr, r0, list,
                            count_dev, (int)g.known, err);
 }
 
 #if SMALL_G == 8
-void launch_dual_small8(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
-                        const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s) {
+void launch_dual_small8(int d, const als_csr *Y, const void *Z, float *R, int64_t ldr, int64_t r0, const int32_t *list,
+                        const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s) {
 #else
-void launch_dual_small4(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0,
-                        const int32_t *list, const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s) {
+void launch_dual_small4(int d, const als_csr *Y, const void *Z, float *R, int64_t ldr, int64_t r0, const int32_t *list,
+                        const int32_t *count_dev, StepGrid g, int32_t *err, hipStream_t s) {
 #endif
-#define ALS_SMALL_CASE(dd)                                                                              \
-    case dd:                                                                                            \
-        if (dd >= 64 || (zb16 && dd >= 32)) launch_small_typed<dd, (dd >= 32)>(Y, Z, R, ldr, r0, list, count_dev, g, err, s); \
-        else launch_small_typed<dd, (dd >= 64)>(Y, Z, R, ldr, r0, list, count_dev, g, err, s); /* d >= 64 with fp32 Z: launch_small_x_typed */ \
-        break;
-    switch (d) { ALS_SMALL_CASE(16) ALS_SMALL_CASE(32) ALS_SMALL_CASE(64) ALS_SMALL_CASE(128) }
-#undef ALS_SMALL_CASE
+    if (d == 16) launch_small_typed<16>(Y, Z, R, ldr, r0, list, count_dev, g, err, s);
+    else launch_small_typed<32>(Y, Z, R, ldr, r0, list, count_dev, g, err, s);
 }
 
 }  // namespace als

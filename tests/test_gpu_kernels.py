@@ -731,3 +731,29 @@ def test_rows_of_tables_with_a_stride(ctx, gpu_device, d, dtype):
     als.als_status_sync(ctx)
     assert torch.equal(wide_x[:, :d], X) and (wide_x[:, d:] == 7).all()
     assert (X[:r0] == 7).all() and (X[r1:] == 7).all() and torch.equal((X[r0:r1] == 0).all(dim=1), k[r0:r1] == 0)
+
+
+@pytest.mark.parametrize("d,dtype", [(64, torch.float32), (128, torch.float32), (32, torch.bfloat16), (64, torch.bfloat16), (128, torch.bfloat16)])
+@pytest.mark.parametrize("rows", [1, 4, 5, 15, 16, 17, 35])
+def test_rows_that_leave_their_kernel_as_solutions(ctx, gpu_device, d, dtype, rows):
+    """Launches of their own take X = R L^-1 along, sixteen rows at a time: `rows` rows of each class, which do not fill the last sixteen,
+    in a strided table, against the launch that small calls share and its pass over the lists, bit for bit."""
+    say(f"solved in their kernel d={d} {dtype} rows={rows}")
+    gen = torch.Generator(device=gpu_device).manual_seed(rows)
+    n, few = 700, rows * 5
+    lens = torch.cat([torch.full((rows,), k) for k in (2, 7, 13, min(d, 25), min(d, 45))] + [torch.zeros(320_000, dtype=torch.int64)])
+    lens = lens.to(gpu_device)
+    indptr = torch.zeros(len(lens) + 1, dtype=torch.int64, device=gpu_device)
+    indptr[1:] = torch.cumsum(lens, 0)
+    nnz = int(indptr[-1])
+    Y = als.Csr(len(lens), n, indptr, torch.randint(0, n, (nnz,), device=gpu_device, generator=gen).to(torch.int32),
+                torch.rand(nnz, device=gpu_device, generator=gen) + 0.5)
+    H = (torch.randn((n, d), device=gpu_device, generator=gen) * 0.3 / np.sqrt(d)).to(dtype)
+    G, prm = als.als_gramian(ctx, H), als.make_params(0.1, 1e-2)
+    own = torch.full((len(lens), d + 16), 7.0, device=gpu_device, dtype=dtype)
+    common = torch.full((len(lens), d), 7.0, device=gpu_device, dtype=dtype)
+    als.als_solve_rows(ctx, Y, H, G, prm, own[:, :d])
+    als.als_solve_rows(ctx, Y, H, G, prm, common, 0, few)
+    als.als_status_sync(ctx)
+    assert torch.equal(own[:few, :d], common[:few]) and (own[:, d:] == 7).all()
+    assert not own[few:, :d].any() and (common[few:] == 7).all() and torch.isfinite(common[:few]).all()
