@@ -209,10 +209,10 @@ def main():
     kernel_names = {"dual_k4": f"dual_small{sx}_kernel<{d},4,{zbt if sx else 'false'}>", "dual_k8": f"dual_small{sx}_kernel<{d},8,{zbt if sx else 'false'}>",
                     "dual_k16": f"dual_rows{rx}_kernel<{d}>", "dual_k32": f"dual_multi{rx}_kernel<{d}>"}
     for c in range(2, 8):
-        kernel_names[f"dual_k{16 * (c + 1)}"] = f"dual_wide_kernel<{d},{c + 1},{zbt},false,false>"
+        kernel_names[f"dual_k{16 * (c + 1)}"] = f"dual_wide_kernel<{d},{c + 1},{zbt},false>"  # (short classes: dual_wide_rest_kernel, timed with the longest)
     if args.solver == "cg" and d >= 64:  # every class runs the one-row-per-wavefront kernel with the CG solver
         for name, _, hi in bounds:
-            kernel_names[name] = f"dual_wide_kernel<{d},{max(3, hi // 16)},{zbt},true,true>"
+            kernel_names[name] = f"dual_wide_kernel<{d},{max(3, hi // 16)},{zbt},true>"
     if args.solver == "cg_free":
         for name, _, _ in bounds:
             kernel_names[name] = f"cg_free_kernel<{d},{bft}>"

@@ -24,6 +24,7 @@
 #include "dual_common.h"
 #include "dual_few.h"
 #include "dual_walk.h"
+#include "dual_wide_rest.h"
 #include "step_queue.h"
 #include "x_rows.h"
 
@@ -516,6 +517,10 @@ template <int D> __global__ __launch_bounds__(64) void x_matrix_kernel(const flo
 }
 
 // ---------------------------------------------------------------------------------------------- launchers
+// Rows of 32 < k <= 128 that one launch takes for several classes where an earlier call saw so few (or that no hint announced): as many as
+// find a SIMD to themselves.
+inline int64_t wide_rest_limit(int num_cu) { return 8 * (int64_t)num_cu; }
+
 int dual_supported_max_k(int d) { return d < 128 ? (d < 64 ? d : 64) : 128; }
 
 // bf16 tables with d >= 32: Z is stored as bf16 too (one more rounding, to the tables' own element type, of a
@@ -660,12 +665,44 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     ALS_TIMED_CLASS(T_SMALL4, 8, 16, (launch_dual_small4(D, Y, Z, R, ldr, r0, lists[8], counts_dev[8], g, err, s)))
     }
     }
-    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 2, 2, 1, (stb = launch_dual_wide3(ctx, D, Y, Z, zb16, R, ldr, r0, lists[2], counts_dev[2], g, err, ws, s)))
-    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 3, 3, 1, (stb = launch_dual_wide4(ctx, D, Y, Z, zb16, R, ldr, r0, lists[3], counts_dev[3], g, err, ws, s)))
-    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 4, 4, 1, (stb = launch_dual_wide5(ctx, D, Y, Z, zb16, R, ldr, r0, lists[4], counts_dev[4], g, err, ws, s)))
-    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 5, 5, 1, (stb = launch_dual_wide6(ctx, D, Y, Z, zb16, R, ldr, r0, lists[5], counts_dev[5], g, err, ws, s)))
-    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 6, 6, 1, (stb = launch_dual_wide7(ctx, D, Y, Z, zb16, R, ldr, r0, lists[6], counts_dev[6], g, err, ws, s)))
-    ALS_TIMED_CLASS(T_DUAL_CLASS0 + 7, 7, 1, (stb = launch_dual_wide8(ctx, D, Y, Z, zb16, R, ldr, r0, lists[7], counts_dev[7], g, err, ws, s)))
+    if constexpr (D >= 64) {
+    // direct solver: short classes, longest rows first, have no launch of their own (see wide_rest_limit)
+    WideRest rest;
+    int64_t room = wide_rest_limit(ctx->num_cu), joint = 0, beyond = 0;
+    StepGrid wide[6];
+    for (int i = 5; i >= 0; --i) {
+        const int c = 2 + i;
+        wide[i] = grid(c, 1);
+        if (!ws.cg) {
+            if (hints[c] >= 0 && hints[c] <= room) {
+                room -= hints[c];
+                joint += std::min<int64_t>(hints[c], caps[c]);
+                wide[i].known = 0;
+            } else {
+                room = 0;
+            }
+            wide[i].rest = 0;
+        }
+        rest.list[i] = lists[c];
+        rest.count[i] = counts_dev[c];
+        rest.known[i] = (int32_t)wide[i].known;
+        beyond += std::max<int64_t>(0, caps[c] - (int64_t)wide[i].known);
+    }
+#define ALS_WIDE(kt) \
+    if (caps[kt - 1] > 0 && wide[kt - 3].known + wide[kt - 3].rest > 0 && stb == ALS_OK) { \
+        timer_begin(ctx, T_DUAL_CLASS0 + kt - 1, s); \
+        stb = launch_dual_wide##kt(ctx, D, Y, Z, zb16, R, ldr, r0, lists[kt - 1], counts_dev[kt - 1], wide[kt - 3], err, ws, s); \
+        timer_end(ctx, s); \
+    }
+    ALS_WIDE(3) ALS_WIDE(4) ALS_WIDE(5) ALS_WIDE(6) ALS_WIDE(7) ALS_WIDE(8)
+#undef ALS_WIDE
+    if (!ws.cg && beyond > 0 && stb == ALS_OK) {
+        timer_begin(ctx, D == 128 ? T_DUAL_CLASS0 + 7 : T_DUAL_CLASS0 + 3, s);
+        stb = launch_dual_wide_rest(ctx, D, Y, Z, zb16, R, ldr, r0, rest,
+                                    (unsigned)std::min<int64_t>(beyond, std::max<int64_t>(joint, 4 * ctx->num_cu)), err, s);
+        timer_end(ctx, s);
+    }
+    }
     }
 #undef ALS_TIMED_CLASS
     if (stb != ALS_OK) return stb;

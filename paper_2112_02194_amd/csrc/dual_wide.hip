@@ -7,20 +7,20 @@
 
 namespace als {
 
-// The two launch forms of a step kernel (see StepGrid): one row per workgroup, or a grid-stride walk from
-// row first_item to the end of the list.
-template <int D, int KT, bool ZB, bool LOOP, bool CG>
-__global__ __launch_bounds__(64, (LOOP || KT >= 7) ? 1 : (KT <= 4 ? 3 : 2)) void dual_wide_kernel(const int64_t *__restrict__ indptr,
+// Direct solver: one row per workgroup (what no hint announced: dual_wide_rest.hip); conjugate gradients: a grid-stride walk over
+// the list.
+template <int D, int KT, bool ZB, bool CG>
+__global__ __launch_bounds__(64, (CG || KT >= 7) ? 1 : (KT <= 4 ? 3 : 2)) void dual_wide_kernel(const int64_t *__restrict__ indptr,
                                                           const int32_t *__restrict__ indices,
                                                           const float *__restrict__ values,
                                                           const void *__restrict__ Z, float *__restrict__ R,
                                                           int64_t ldr, int64_t r0, const int32_t *__restrict__ list,
-                                                          const int32_t *__restrict__ count_ptr, int first_item,
+                                                          const int32_t *__restrict__ count_ptr,
                                                           int32_t *__restrict__ err_flag, int cg_iters, float cg_tol) {
     extern __shared__ float lds[];
     const int count = *count_ptr;
-    int item = first_item + blockIdx.x;
-    if constexpr (!LOOP) {
+    int item = blockIdx.x;
+    if constexpr (!CG) {
         item = xcd_step(item, gridDim.x, count);
         if (item < count)
             dual_wide_step<D, KT, ZB, CG>(indptr, indices, values, Z, R, ldr, r0, list, err_flag, item, lds, cg_iters, cg_tol);
@@ -43,35 +43,28 @@ static als_status wide_typed(als_ctx *ctx, const als_csr *Y, const void *Z, floa
                              hipStream_t s) {
     using C = WideCfg<D, WIDE_KT>;
     constexpr int lds_bytes = (int)(C::LDS_FLOATS * sizeof(float));
-    if (ws.cg) {  // only the grid-stride form exists with this solver: one launch covers the list
-        auto kern_cg = dual_wide_kernel<D, WIDE_KT, ZB, true, true>;
-        static const hipError_t attr_cg =
-            hipFuncSetAttribute((const void *)kern_cg, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    auto launch = [&](auto kern, unsigned blocks) {
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(64), lds_bytes, s, Y->indptr, Y->indices, Y->values, Z, R, ldr, r0, list, count_dev,
+                           err, ws.iters, ws.tol);
+    };
+    if (ws.cg) {  // one launch covers the list
+        static const hipError_t attr_cg = hipFuncSetAttribute((const void *)dual_wide_kernel<D, WIDE_KT, ZB, true>,
+                                                              hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);  // once per process
         ALS_HIP(ctx, attr_cg);
-        hipLaunchKernelGGL(kern_cg, dim3(g.known + g.rest), dim3(64), lds_bytes, s, Y->indptr, Y->indices, Y->values, Z,
-                           R, ldr, r0, list, count_dev, 0, err, ws.iters, ws.tol);
-        return ALS_OK;
+        launch(dual_wide_kernel<D, WIDE_KT, ZB, true>, g.known + g.rest);
+    } else {
+        static const hipError_t attr = hipFuncSetAttribute((const void *)dual_wide_kernel<D, WIDE_KT, ZB, false>,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);  // once per process
+        ALS_HIP(ctx, attr);
+        launch(dual_wide_kernel<D, WIDE_KT, ZB, false>, g.known);
     }
-    auto kern = dual_wide_kernel<D, WIDE_KT, ZB, false, false>;
-    auto kern_loop = dual_wide_kernel<D, WIDE_KT, ZB, true, false>;
-    static const hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-    static const hipError_t attr_loop =
-        hipFuncSetAttribute((const void *)kern_loop, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);  // both once per process
-    ALS_HIP(ctx, attr);
-    ALS_HIP(ctx, attr_loop);
-    if (g.known > 0)
-        hipLaunchKernelGGL(kern, dim3(g.known), dim3(64), lds_bytes, s, Y->indptr, Y->indices, Y->values, Z, R, ldr, r0,
-                           list, count_dev, 0, err, 0, 0.f);
-    if (g.rest > 0)
-        hipLaunchKernelGGL(kern_loop, dim3(g.rest), dim3(64), lds_bytes, s, Y->indptr, Y->indices, Y->values, Z, R, ldr,
-                           r0, list, count_dev, (int)g.known, err, 0, 0.f);
     return ALS_OK;
 }
 
 als_status ALS_WIDE_NAME(WIDE_KT)(als_ctx *ctx, int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr,
                                   int64_t r0, const int32_t *list, const int32_t *count_dev, StepGrid g,
                                   int32_t *err, const WideSolver &ws, hipStream_t s) {
-    if (g.known == 0 && g.rest == 0) return ALS_OK;
+    if (g.known + (ws.cg ? g.rest : 0u) == 0) return ALS_OK;
     if (d == 128)
         return zb16 ? wide_typed<128, true>(ctx, Y, Z, R, ldr, r0, list, count_dev, g, err, ws, s)
                     : wide_typed<128, false>(ctx, Y, Z, R, ldr, r0, list, count_dev, g, err, ws, s);

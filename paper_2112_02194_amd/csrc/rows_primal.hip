@@ -660,26 +660,21 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
     return true;
 }
 
-template <int D, bool BF16, bool LOOP>
+// Long rows in strides of the grid (the walk costs eight registers here; a launch of its own for the rows that no hint announced
+// was one more that mostly found nothing).
+template <int D, bool BF16>
 __global__ __launch_bounds__(Team<D>::THREADS) void reduce_solve_kernel(
     const LongRow *__restrict__ long_rows, const float *__restrict__ partials, const float *__restrict__ G,
-    float alpha, float lambda, void *__restrict__ X, int64_t ldx, const int32_t *__restrict__ n_long_ptr, int first,
+    float alpha, float lambda, void *__restrict__ X, int64_t ldx, const int32_t *__restrict__ n_long_ptr,
     int32_t *__restrict__ err_flag, int solver, int cg_iters, float cg_tol) {
     extern __shared__ float lds[];
     const int n_long = *n_long_ptr;
-    int row = first + (int)blockIdx.x;
-    if constexpr (!LOOP) {
-        if (row < n_long)
-            reduce_solve_step<D, BF16>(long_rows[row], partials, G, alpha, lambda, X, ldx, err_flag, solver, cg_iters,
-                                       cg_tol, true, lds);
-    } else {
-        for (; row < n_long; row += gridDim.x) {
-            const bool last = row + (int)gridDim.x >= n_long;
-            if (!reduce_solve_step<D, BF16>(long_rows[row], opaque(partials), opaque(G), opaque(alpha), opaque(lambda),
-                                            opaque(X), opaque(ldx), opaque(err_flag), opaque(solver), opaque(cg_iters),
-                                            opaque(cg_tol), last, opaque(lds)))
-                return;
-        }
+    for (int row = blockIdx.x; row < n_long; row += gridDim.x) {
+        const bool last = row + (int)gridDim.x >= n_long;
+        if (!reduce_solve_step<D, BF16>(long_rows[row], opaque(partials), opaque(G), opaque(alpha), opaque(lambda),
+                                        opaque(X), opaque(ldx), opaque(err_flag), opaque(solver), opaque(cg_iters),
+                                        opaque(cg_tol), last, opaque(lds)))
+            return;
     }
 }
 
@@ -737,14 +732,10 @@ static als_status long_typed(als_ctx *ctx, const als_csr *Y, const als_table *V,
     int32_t *err = (int32_t *)((char *)ctx->small.p + SM_COUNTERS) + 2;
     const int cg_iters = prm->cg_max_iters > 0 ? prm->cg_max_iters : 2 * D;
     const float cg_tol = prm->cg_tol > 0.f ? prm->cg_tol : 1e-6f;
-    auto kred = reduce_solve_kernel<D, BF16, false>;
-    auto kred_loop = reduce_solve_kernel<D, BF16, true>;
+    auto kred = reduce_solve_kernel<D, BF16>;
     static const hipError_t attr = hipFuncSetAttribute((const void *)kred, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       (int)Team<D>::LDS_BYTES);
-    static const hipError_t attr_loop = hipFuncSetAttribute(
-        (const void *)kred_loop, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Team<D>::LDS_BYTES);  // both once per process
+                                                       (int)Team<D>::LDS_BYTES);  // once per process
     ALS_HIP(ctx, attr);
-    ALS_HIP(ctx, attr_loop);
     float *partials = (float *)ctx->seg_partials.p;
     constexpr size_t seg_lds = staging_lds_bytes<D, BF16>();  // at most 24 KB: no attribute needed
     timer_begin(ctx, T_SEGMENT, s);
@@ -763,14 +754,8 @@ static als_status long_typed(als_ctx *ctx, const als_csr *Y, const als_table *V,
     if constexpr (!sums_segments<D>()) hipLaunchKernelGGL(reduce_partials_kernel<D>, dim3(red_blocks, (D * D + D + 255) / 256), dim3(256), 0, s, long_rows,
                        partials, counters);
     const size_t lds_bytes = solve_lds_bytes<D>(prm->solver);
-    if (g_long.known > 0)
-        hipLaunchKernelGGL(kred, dim3(g_long.known), dim3(Team<D>::THREADS), lds_bytes, s, long_rows,
-                           (const float *)partials, G, prm->alpha, prm->lambda, X->data, X->ld, counters, 0, err,
-                           prm->solver, cg_iters, cg_tol);
-    if (g_long.rest > 0)
-        hipLaunchKernelGGL(kred_loop, dim3(g_long.rest), dim3(Team<D>::THREADS), lds_bytes, s, long_rows,
-                           (const float *)partials, G, prm->alpha, prm->lambda, X->data, X->ld, counters,
-                           (int)g_long.known, err, prm->solver, cg_iters, cg_tol);
+    hipLaunchKernelGGL(kred, dim3(red_blocks), dim3(Team<D>::THREADS), lds_bytes, s, long_rows, (const float *)partials, G, prm->alpha,
+                       prm->lambda, X->data, X->ld, counters, err, prm->solver, cg_iters, cg_tol);
     timer_end(ctx, s);
     ALS_HIP(ctx, hipGetLastError());
     return ALS_OK;
