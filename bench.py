@@ -222,8 +222,8 @@ def main():
                          else f"transform_kernel<{d},{bft},false,true,false>",
                          "transform_x": f"transform_lists_kernel<{d},{bft}>" if zbt == "true" or (es == 4 and d >= 64)  # X = R L^-1
                          else f"transform_kernel<{d},false,{bft},false,false>",
-                         "primal": f"primal_kernel<{d},{bft},0,false>",               # one workgroup per row
-                         "segment": f"primal_kernel<{d},{bft},1,false>"})             # segments of long rows
+                         "primal": f"primal_kernel<{d},{bft},0>",               # one workgroup per row
+                         "segment": f"primal_kernel<{d},{bft},1>"})             # segments of long rows
     zs = 2 if (es == 2 and d >= 32) else 4  # bytes per element of the transformed table Z the dual kernels gather
     if args.solver == "cg_free":
         zs = es  # the matrix-free solver gathers the fixed table itself (at least once)
@@ -254,6 +254,10 @@ def main():
         work["primal"] = ["alu", prim_rows * (d ** 3 / 3.0 + 2.0 * d * d)]
         work["segment"] = ["hbm", float(long_nnz) * (d * es + 4)]
         work["gramian"] = ["hbm", float(m + n) * d * es]
+    if stage_launches.get("segment", 0.0) == 0:  # segments and whole rows share a launch, timed as the rows
+        kernel_names["primal"] = f"primal_both_kernel<{d},{bft},false>"
+        if work["segment"][0] == work["primal"][0]:
+            work["primal"][1] += work["segment"][1]
     work["transform_z"] = ["hbm", float(m + n) * d * (es + zs)]
     work["transform_x"] = ["hbm", float(m + n) * d * (4 + es)]
     # lists that are short together share one launch, which the library times in the slot of 8 < k <= 16

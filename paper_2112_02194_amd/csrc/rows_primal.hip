@@ -539,36 +539,63 @@ __device__ __forceinline__ bool primal_step(
     }
 }
 
-// MODE_FUSED:   work item = the whole row u = row_begin + row_list[item].
-// MODE_SEGMENT: work item = segment `item` of segs[]; raw partial statistics are written to
-//               partials[item][D*D + D] (row-major D x D, then b).
-// The two launch forms (see StepGrid): LOOP = false, workgroup b takes item first + b if there is one;
-// LOOP = true, grid-stride walk from item `first` on.  *count_ptr is the number of items (device memory).
+// What the workgroups of a primal kernel share.
+struct PrimalArgs {
+    const int64_t *indptr;
+    const int32_t *indices;
+    const float *values;
+    const void *V;
+    int64_t ldv;
+    const float *G;
+    float alpha, lambda;
+    void *X;
+    int64_t ldx, row_begin;
+    const int32_t *row_list, *row_count;  // MODE_FUSED: work item = the whole row u = row_begin + row_list[item]
+    const Segment *segs;                  // MODE_SEGMENT: segment `item`; raw partial statistics are written to
+    const int32_t *seg_count;             // partials[item][D*D + D] (row-major D x D, then b)
+    float *partials;
+    int32_t *err_flag;
+    int solver, cg_iters;
+    float cg_tol;
+};
+
+// Workgroup `b` of `blocks` of the items from `first` on.  The two launch forms (see StepGrid): LOOP = false, item first + b if
+// there is one; LOOP = true, grid-stride walk.
 template <int D, bool BF16, int MODE, bool LOOP>
-__global__ __launch_bounds__(Team<D>::THREADS, D < 64 ? (LOOP ? 1 : 2) : (D == 128 && !BF16 ? (LOOP ? 2 : 3) : 4 - LOOP)) void primal_kernel(
-    const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices, const float *__restrict__ values,
-    const void *__restrict__ V, int64_t ldv, const float *__restrict__ G, float alpha, float lambda,
-    void *__restrict__ X, int64_t ldx, int64_t row_begin, const int32_t *__restrict__ row_list,
-    const Segment *__restrict__ segs, float *__restrict__ partials, const int32_t *__restrict__ count_ptr, int first,
-    int32_t *__restrict__ err_flag, int solver, int cg_iters, float cg_tol) {
-    extern __shared__ float lds[];
-    const int64_t nitems = *count_ptr;
-    int64_t item = (int64_t)first + blockIdx.x;
+__device__ __forceinline__ void primal_items(const PrimalArgs &p, int first, int b, int blocks, float *lds) {
+    const int64_t nitems = MODE == MODE_FUSED ? *p.row_count : *p.seg_count;
+    int64_t item = (int64_t)first + b;
     if constexpr (!LOOP) {
         if (item < nitems)
-            primal_step<D, BF16, MODE>(indptr, indices, values, V, ldv, G, alpha, lambda, X, ldx, row_begin, row_list, segs,
-                                       partials, err_flag, solver, cg_iters, cg_tol, item, true, lds);
+            primal_step<D, BF16, MODE>(p.indptr, p.indices, p.values, p.V, p.ldv, p.G, p.alpha, p.lambda, p.X, p.ldx, p.row_begin, p.row_list,
+                                       p.segs, p.partials, p.err_flag, p.solver, p.cg_iters, p.cg_tol, item, true, lds);
     } else {
-        for (; item < nitems; item += gridDim.x) {
-            const bool last = item + gridDim.x >= nitems;
-            if (!primal_step<D, BF16, MODE>(opaque(indptr), opaque(indices), opaque(values), opaque(V), opaque(ldv),
-                                            opaque(G), opaque(alpha), opaque(lambda), opaque(X), opaque(ldx),
-                                            opaque(row_begin), opaque(row_list), opaque(segs), opaque(partials),
-                                            opaque(err_flag), opaque(solver), opaque(cg_iters), opaque(cg_tol), item, last,
-                                            opaque(lds)))
+        for (; item < nitems; item += blocks) {
+            const bool last = item + blocks >= nitems;
+            if (!primal_step<D, BF16, MODE>(opaque(p.indptr), opaque(p.indices), opaque(p.values), opaque(p.V), opaque(p.ldv), opaque(p.G),
+                                            opaque(p.alpha), opaque(p.lambda), opaque(p.X), opaque(p.ldx), opaque(p.row_begin),
+                                            opaque(p.row_list), opaque(p.segs), opaque(p.partials), opaque(p.err_flag), opaque(p.solver),
+                                            opaque(p.cg_iters), opaque(p.cg_tol), item, last, opaque(lds)))
                 return;
         }
     }
+}
+
+template <int D, bool BF16, int MODE>
+__global__ __launch_bounds__(Team<D>::THREADS, D < 64 ? 2 : (D == 128 && !BF16 ? 3 : 4)) void primal_kernel(PrimalArgs p) {
+    extern __shared__ float lds[];
+    primal_items<D, BF16, MODE, false>(p, 0, blockIdx.x, gridDim.x, lds);
+}
+// Segments (the first `seg_blocks` workgroups) and whole rows in one launch: neither waits for the other's last ones.  The segments' workgroups
+// take the LDS of the solver too, so for d >= 64 only where all find a place at a time.  Epoch of 2000 x 1500 (d = 16)
+// 103 -> 90 us, of 50k x 30k (d = 32) 315 -> 300 us (150 us of rows and 25 of segments before), 256 rows folded in (d = 128) 81.9 -> 80.8 us.
+template <int D, bool BF16, bool LOOP>
+__global__ __launch_bounds__(Team<D>::THREADS, D < 64 ? (LOOP ? 1 : 2) : (D == 128 && !BF16 ? (LOOP ? 2 : 3) : 4 - LOOP)) void primal_both_kernel(
+    PrimalArgs p, int first_seg, int seg_blocks, int first_row) {
+    extern __shared__ float lds[];
+    const int b = blockIdx.x;
+    if (b < seg_blocks) primal_items<D, BF16, MODE_SEGMENT, LOOP>(p, first_seg, b, seg_blocks, lds);
+    else primal_items<D, BF16, MODE_FUSED, LOOP>(p, first_row, b - seg_blocks, (int)gridDim.x - seg_blocks, lds);
 }
 
 // One element of a long row's partials, summed in a fixed order.
@@ -688,75 +715,70 @@ template <int D> static size_t solve_lds_bytes(int solver) {
     return solver == ALS_SOLVER_DIRECT ? Packed<D>::LDS_BYTES : Team<D>::LDS_BYTES;
 }
 
+// counters[0] = number of long rows, counters[1] = number of their segments (device memory); row_list: rows solved whole.
 template <int D, bool BF16>
-static als_status primal_typed(als_ctx *ctx, const als_csr *Y, const als_table *V, const float *G,
-                               const als_params *prm, als_table *X, int64_t r0, const int32_t *row_list,
-                               const int32_t *count_dev, StepGrid g, hipStream_t s) {
-    if (g.known == 0 && g.rest == 0) return ALS_OK;
+static als_status primal_typed(als_ctx *ctx, const als_csr *Y, const als_table *V, const float *G, const als_params *prm, als_table *X,
+                               int64_t r0, const LongRow *long_rows, const Segment *segs, const int32_t *counters, int64_t seg_capacity,
+                               StepGrid g_long, StepGrid g_seg, const int32_t *row_list, const int32_t *row_count, StepGrid g_row, hipStream_t s) {
+    const bool any_long = g_seg.known + g_seg.rest > 0;
+    if (any_long) {
+        als_status st = ensure(ctx, ctx->seg_partials, (size_t)seg_capacity * (D * D + D) * sizeof(float));
+        if (st != ALS_OK) return st;
+    }
     int32_t *err = (int32_t *)((char *)ctx->small.p + SM_COUNTERS) + 2;
     const int cg_iters = prm->cg_max_iters > 0 ? prm->cg_max_iters : 2 * D;
     const float cg_tol = prm->cg_tol > 0.f ? prm->cg_tol : 1e-6f;
-    auto kern = primal_kernel<D, BF16, MODE_FUSED, false>;
-    auto kern_loop = primal_kernel<D, BF16, MODE_FUSED, true>;
-    static const hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       (int)Team<D>::LDS_BYTES);
-    static const hipError_t attr_loop = hipFuncSetAttribute(
-        (const void *)kern_loop, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Team<D>::LDS_BYTES);  // both once per process
-    ALS_HIP(ctx, attr);
-    ALS_HIP(ctx, attr_loop);
-    const size_t lds_bytes = std::max(solve_lds_bytes<D>(prm->solver), staging_lds_bytes<D, BF16>());
-    timer_begin(ctx, T_PRIMAL, s);
-    if (g.known > 0)
-        hipLaunchKernelGGL(kern, dim3(g.known), dim3(Team<D>::THREADS), lds_bytes, s, Y->indptr, Y->indices, Y->values,
-                           V->data, V->ld, G, prm->alpha, prm->lambda, X->data, X->ld, r0, row_list,
-                           (const Segment *)nullptr, (float *)nullptr, count_dev, 0, err, prm->solver, cg_iters, cg_tol);
-    if (g.rest > 0)
-        hipLaunchKernelGGL(kern_loop, dim3(g.rest), dim3(Team<D>::THREADS), lds_bytes, s, Y->indptr, Y->indices,
-                           Y->values, V->data, V->ld, G, prm->alpha, prm->lambda, X->data, X->ld, r0, row_list,
-                           (const Segment *)nullptr, (float *)nullptr, count_dev, (int)g.known, err, prm->solver,
-                           cg_iters, cg_tol);
-    timer_end(ctx, s);
-    ALS_HIP(ctx, hipGetLastError());
-    return ALS_OK;
-}
-
-// counters[0] = number of long rows, counters[1] = number of their segments (device memory).
-template <int D, bool BF16>
-static als_status long_typed(als_ctx *ctx, const als_csr *Y, const als_table *V, const float *G,
-                             const als_params *prm, als_table *X, const LongRow *long_rows, const Segment *segs,
-                             const int32_t *counters, int64_t seg_capacity, StepGrid g_long, StepGrid g_seg,
-                             hipStream_t s) {
-    if (g_seg.known == 0 && g_seg.rest == 0) return ALS_OK;
-    als_status st = ensure(ctx, ctx->seg_partials, (size_t)seg_capacity * (D * D + D) * sizeof(float));
-    if (st != ALS_OK) return st;
-    int32_t *err = (int32_t *)((char *)ctx->small.p + SM_COUNTERS) + 2;
-    const int cg_iters = prm->cg_max_iters > 0 ? prm->cg_max_iters : 2 * D;
-    const float cg_tol = prm->cg_tol > 0.f ? prm->cg_tol : 1e-6f;
-    auto kred = reduce_solve_kernel<D, BF16>;
-    static const hipError_t attr = hipFuncSetAttribute((const void *)kred, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       (int)Team<D>::LDS_BYTES);  // once per process
-    ALS_HIP(ctx, attr);
     float *partials = (float *)ctx->seg_partials.p;
+    const PrimalArgs args = {Y->indptr, Y->indices, Y->values, V->data, V->ld, G, prm->alpha, prm->lambda, X->data, X->ld, r0, row_list,
+                             row_count, segs, counters + 1, partials, err, prm->solver, cg_iters, cg_tol};
+    constexpr int T = Team<D>::THREADS;
     constexpr size_t seg_lds = staging_lds_bytes<D, BF16>();  // at most 24 KB: no attribute needed
-    timer_begin(ctx, T_SEGMENT, s);
-    if (g_seg.known > 0)
-        hipLaunchKernelGGL((primal_kernel<D, BF16, MODE_SEGMENT, false>), dim3(g_seg.known), dim3(Team<D>::THREADS), seg_lds, s,
-                           Y->indptr, Y->indices, Y->values, V->data, V->ld, G, prm->alpha, prm->lambda, X->data, X->ld,
-                           (int64_t)0, (const int32_t *)nullptr, segs, partials, counters + 1, 0, err, 0, 0, 0.f);
-    if (g_seg.rest > 0)
-        hipLaunchKernelGGL((primal_kernel<D, BF16, MODE_SEGMENT, true>), dim3(g_seg.rest), dim3(Team<D>::THREADS), seg_lds, s,
-                           Y->indptr, Y->indices, Y->values, V->data, V->ld, G, prm->alpha, prm->lambda, X->data, X->ld,
-                           (int64_t)0, (const int32_t *)nullptr, segs, partials, counters + 1, (int)g_seg.known, err, 0,
-                           0, 0.f);
-    timer_end(ctx, s);
-    timer_begin(ctx, T_REDUCE, s);
-    const unsigned red_blocks = std::max(1u, g_long.known + g_long.rest);  // grid-stride over the long rows
-    if constexpr (!sums_segments<D>()) hipLaunchKernelGGL(reduce_partials_kernel<D>, dim3(red_blocks, (D * D + D + 255) / 256), dim3(256), 0, s, long_rows,
-                       partials, counters);
-    const size_t lds_bytes = solve_lds_bytes<D>(prm->solver);
-    hipLaunchKernelGGL(kred, dim3(red_blocks), dim3(Team<D>::THREADS), lds_bytes, s, long_rows, (const float *)partials, G, prm->alpha,
-                       prm->lambda, X->data, X->ld, counters, err, prm->solver, cg_iters, cg_tol);
-    timer_end(ctx, s);
+    const size_t solve_lds = solve_lds_bytes<D>(prm->solver), row_lds = std::max(solve_lds, seg_lds);
+#define ALS_LDS(kern)                                                                                                               \
+    {                                                                                                                               \
+        static const hipError_t attr = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,          \
+                                                           (int)Team<D>::LDS_BYTES); /* once per process */                         \
+        ALS_HIP(ctx, attr);                                                                                                         \
+    }
+    auto both = primal_both_kernel<D, BF16, false>, both_loop = primal_both_kernel<D, BF16, true>;
+    const bool together = D < 64 || (int64_t)g_seg.known + g_row.known <= 4 * ctx->num_cu;
+    if (together) {
+        ALS_LDS(both)
+        ALS_LDS(both_loop)
+        timer_begin(ctx, T_PRIMAL, s);
+        if (g_seg.known + g_row.known > 0)
+            hipLaunchKernelGGL(both, dim3(g_seg.known + g_row.known), dim3(T), row_lds, s, args, 0, (int)g_seg.known, 0);
+        if (g_seg.rest + g_row.rest > 0)
+            hipLaunchKernelGGL(both_loop, dim3(g_seg.rest + g_row.rest), dim3(T), row_lds, s, args, (int)g_seg.known, (int)g_seg.rest,
+                               (int)g_row.known);
+        timer_end(ctx, s);
+    } else if constexpr (D >= 64) {
+        auto rows = primal_kernel<D, BF16, MODE_FUSED>;
+        timer_begin(ctx, T_SEGMENT, s);
+        if (g_seg.known > 0)
+            hipLaunchKernelGGL((primal_kernel<D, BF16, MODE_SEGMENT>), dim3(g_seg.known), dim3(T), seg_lds, s, args);
+        timer_end(ctx, s);
+        ALS_LDS(rows)
+        ALS_LDS(both_loop)
+        timer_begin(ctx, T_PRIMAL, s);
+        if (g_row.known > 0) hipLaunchKernelGGL(rows, dim3(g_row.known), dim3(T), row_lds, s, args);
+        if (g_seg.rest + g_row.rest > 0)
+            hipLaunchKernelGGL(both_loop, dim3(g_seg.rest + g_row.rest), dim3(T), row_lds, s, args, (int)g_seg.known, (int)g_seg.rest,
+                               (int)g_row.known);
+        timer_end(ctx, s);
+    }
+    if (any_long) {
+        timer_begin(ctx, T_REDUCE, s);
+        const unsigned red_blocks = std::max(1u, g_long.known + g_long.rest);  // grid-stride over the long rows
+        if constexpr (!sums_segments<D>())
+            hipLaunchKernelGGL(reduce_partials_kernel<D>, dim3(red_blocks, (D * D + D + 255) / 256), dim3(256), 0, s, long_rows, partials, counters);
+        auto kred = reduce_solve_kernel<D, BF16>;
+        ALS_LDS(kred)
+        hipLaunchKernelGGL(kred, dim3(red_blocks), dim3(T), solve_lds, s, long_rows, (const float *)partials, G, prm->alpha, prm->lambda, X->data,
+                           X->ld, counters, err, prm->solver, cg_iters, cg_tol);
+        timer_end(ctx, s);
+    }
+#undef ALS_LDS
     ALS_HIP(ctx, hipGetLastError());
     return ALS_OK;
 }
@@ -770,19 +792,11 @@ static als_status long_typed(als_ctx *ctx, const als_csr *Y, const als_table *V,
     }                                                                                      \
     return fail(ctx, ALS_EDTYPE, "unsupported d")
 
-als_status launch_primal_fused(als_ctx *ctx, const als_csr *Y, const als_table *V, const float *G,
-                               const als_params *prm, als_table *X, int64_t r0, const int32_t *row_list,
-                               const int32_t *count_dev, StepGrid g, hipStream_t s) {
+als_status launch_primal(als_ctx *ctx, const als_csr *Y, const als_table *V, const float *G, const als_params *prm, als_table *X,
+                         int64_t r0, const LongRow *long_rows, const Segment *segs, const int32_t *counters, int64_t seg_capacity,
+                         StepGrid g_long, StepGrid g_seg, const int32_t *row_list, const int32_t *row_count, StepGrid g_row, hipStream_t s) {
     const bool bf = V->dtype == ALS_BF16;
-    ALS_DISPATCH(primal_typed, V->d, bf, ctx, Y, V, G, prm, X, r0, row_list, count_dev, g, s);
-}
-
-als_status launch_primal_long(als_ctx *ctx, const als_csr *Y, const als_table *V, const float *G,
-                              const als_params *prm, als_table *X, const LongRow *long_rows, const Segment *segs,
-                              const int32_t *counters, int64_t seg_capacity, StepGrid g_long, StepGrid g_seg,
-                              hipStream_t s) {
-    const bool bf = V->dtype == ALS_BF16;
-    ALS_DISPATCH(long_typed, V->d, bf, ctx, Y, V, G, prm, X, long_rows, segs, counters, seg_capacity, g_long, g_seg, s);
+    ALS_DISPATCH(primal_typed, V->d, bf, ctx, Y, V, G, prm, X, r0, long_rows, segs, counters, seg_capacity, g_long, g_seg, row_list, row_count, g_row, s);
 }
 
 }  // namespace als

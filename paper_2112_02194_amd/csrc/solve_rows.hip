@@ -10,13 +10,9 @@
 
 namespace als {
 
-als_status launch_primal_fused(als_ctx *ctx, const als_csr *Y, const als_table *V, const float *G,
-                               const als_params *prm, als_table *X, int64_t r0, const int32_t *row_list,
-                               const int32_t *count_dev, StepGrid g, hipStream_t s);
-als_status launch_primal_long(als_ctx *ctx, const als_csr *Y, const als_table *V, const float *G,
-                              const als_params *prm, als_table *X, const LongRow *long_rows,
-                              const Segment *segs, const int32_t *counters, int64_t seg_capacity, StepGrid g_long,
-                              StepGrid g_seg, hipStream_t s);
+als_status launch_primal(als_ctx *ctx, const als_csr *Y, const als_table *V, const float *G, const als_params *prm, als_table *X,
+                         int64_t r0, const LongRow *long_rows, const Segment *segs, const int32_t *counters, int64_t seg_capacity,
+                         StepGrid g_long, StepGrid g_seg, const int32_t *row_list, const int32_t *row_count, StepGrid g_row, hipStream_t s);
 als_status launch_dual_prepare(als_ctx *ctx, const als_table *V, const float *G, const als_params *prm,
                                const als_csr *entries, int64_t r0, int64_t r1, hipStream_t s);
 als_status launch_dual_rows(als_ctx *ctx, const als_csr *Y, als_table *X, int64_t r0, int64_t r1, int dual_max,
@@ -480,10 +476,8 @@ als_status launch_solve_rows(als_ctx *ctx, const als_csr *Y, const als_table *V,
     const int pt = primal_threads(V->d);
     const StepGrid g_long = step_grid(ctx->num_cu, pt, std::min<int64_t>(SEG_CAPACITY / 2, Y->nnz / split + 1), hint[0], 4, SEG_CAPACITY);
     const StepGrid g_seg = step_grid(ctx->num_cu, pt, seg_capacity, hint[1], 8, SEG_CAPACITY);
-    if ((st = launch_primal_long(ctx, Y, V, G, prm, X, long_rows, segs, counters, seg_capacity, g_long, g_seg, s)) != ALS_OK)
-        return st;
-    if ((st = launch_primal_fused(ctx, Y, V, G, prm, X, r0, mid_list, counters + 3,
-                                  step_grid(ctx->num_cu, pt, cap_mid, hint[3], 8, BLIND_PRIMAL), s)) != ALS_OK)
+    if ((st = launch_primal(ctx, Y, V, G, prm, X, r0, long_rows, segs, counters, seg_capacity, g_long, g_seg, mid_list, counters + 3,
+                            step_grid(ctx->num_cu, pt, cap_mid, hint[3], 8, BLIND_PRIMAL), s)) != ALS_OK)
         return st;
     if (dual_max > 0) {
         const int32_t *lists[10], *counts_dev[10];
