@@ -21,7 +21,7 @@ namespace als {
 template <int D, int KT, bool ZB> constexpr bool wide_resident() { return ZB; }
 
 // tiles that stay in registers
-template <int KT, bool ZB> constexpr int wide_tiles() { return ZB ? KT : (KT < 5 ? KT : (KT < 7 ? 5 : 4)); }
+template <int KT, bool ZB> constexpr int wide_tiles() { return ZB || KT < 5 || KT > 6 ? KT : 5; }
 // Long rows of Z only.  10M pages with host locality (d = 128, fp32), KT = 3 .. 8, ms per epoch, straight into the operand
 // layout / staged: 5.66 / 5.48, 4.25 / 4.07, 2.98 / 2.91, 2.35 / 2.12, 1.93 / 1.86, 1.24 / 1.16; shorter rows lose: 1M x 1M
 // (d = 64) 1.22 / 1.26, 300k bf16 rows (d = 128, KT = 3) 76 / 81 us.
@@ -215,24 +215,42 @@ __device__ __forceinline__ void dual_wide_step(const int64_t *__restrict__ indpt
         if constexpr (D >= 128) *(float2 *)(R + u * ldr + 2 * lane) = *(const float2 *)(rbuf + 2 * lane);
         else R[u * ldr + lane] = rbuf[lane];
     } else {
-        // 16 bytes of an entry per lane, GatherCols<D>::EPI entries per instruction, four entries per lane and round
+        // 16 bytes of an entry per lane, GatherCols<D>::EPI entries per instruction, four entries per lane and round, the loads of
+        // four rounds under way together (10M pages, d = 128, KT = 4 .. 8: a round at a time 3.71, 2.63, 1.89, 1.65, 1.00 ms; so, and with all tiles resident
+        // from KT = 7 on, where a wavefront has its SIMD to itself anyway, 3.59, 2.50, 1.73, 1.39, 0.94)
         using GC = GatherCols<D>;
+        constexpr int ROUND = 4 * GC::EPI, AHEAD = K / ROUND < 4 ? K / ROUND : 4;
         const int mine = 4 * (lane / GC::LPR);
         const float *col = (const float *)Z + 4 * (lane % GC::LPR);
         floatx4 rv = floatx4{0.f, 0.f, 0.f, 0.f};
-        for (int e0 = 0; e0 < k; e0 += 4 * GC::EPI) {  // padded entries have t = 0 and the id of the row's first entry
-            // ids and t of the round with 16-byte LDS reads, before the first load is issued
-            const int4 id4 = *(const int4 *)(ids + e0 + mine);
-            const float4 t4 = *(const float4 *)(tbuf + e0 + mine);
-            const int id[4] = {id4.x, id4.y, id4.z, id4.w};
-            const float te[4] = {t4.x, t4.y, t4.z, t4.w};
-            floatx4 zz[4];
+#pragma unroll 1
+        for (int e0 = 0; e0 < k; e0 += AHEAD * ROUND) {  // padded entries have t = 0 and the id of the row's first entry
+            // ids and t with 16-byte LDS reads, before the first load is issued
+            int4 id4[AHEAD];
+            float4 t4[AHEAD];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) zz[x] = *(const floatx4 *)(col + (int64_t)id[x] * D);
+            for (int u = 0; u < AHEAD; ++u) {
+                const int e = K % (AHEAD * ROUND) == 0 || e0 + u * ROUND < K ? e0 + u * ROUND : 0;  // beyond the last place: not used
+                id4[u] = *(const int4 *)(ids + e + mine);
+                t4[u] = *(const float4 *)(tbuf + e + mine);
+            }
+            floatx4 zz[AHEAD][4];
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
+            for (int u = 0; u < AHEAD; ++u)
+                if (u == 0 || e0 + u * ROUND < k) {  // uniform
+                    const int id[4] = {id4[u].x, id4[u].y, id4[u].z, id4[u].w};
 #pragma unroll
-                for (int c = 0; c < 4; ++c) rv[c] += te[x] * zz[x][c];
+                    for (int x = 0; x < 4; ++x) zz[u][x] = *(const floatx4 *)(col + (int64_t)id[x] * D);
+                }
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+                if (u == 0 || e0 + u * ROUND < k) {
+                    const float te[4] = {t4[u].x, t4[u].y, t4[u].z, t4[u].w};
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) rv[c] += te[x] * zz[u][x][c];
+                }
         }
         rv = swap_add32(rv, rv);
         if constexpr (D == 64) rv = swap_add16(rv, rv);
