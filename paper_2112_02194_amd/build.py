@@ -35,6 +35,7 @@ UNITS = [
     ("dual_small.hip", "dual_small_g8", ["-DSMALL_G=8"] + VGPR_FORM),
     ("dual_small.hip", "dual_small_g4", ["-DSMALL_G=4"] + VGPR_FORM),
     ("dual_multi.hip", "dual_multi", VGPR_FORM),
+    ("dual_triple.hip", "dual_triple", VGPR_FORM),
     ("dual_few.hip", "dual_few", VGPR_FORM),
     ("dual_wide_rest.hip", "dual_wide_rest", VGPR_FORM),
     ("dual_wide.hip", "dual_wide_3", ["-DWIDE_KT=3"] + VGPR_FORM),

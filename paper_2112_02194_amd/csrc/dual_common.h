@@ -92,31 +92,35 @@ template <int C> __device__ __forceinline__ float bcast16(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + C, 0xf, 0xf, true));
 }
 
-// One step of the eliminations: column c of the lane's row `s` (and of a second row `s2` of the same system, below it) is
+// One step of the eliminations: column c of the lane's row `s` (and of further rows of the same system, below it) is
 // eliminated; the columns beyond c of all rows but the pivot's are updated.  On return s[c] holds the multiplier of this
-// lane's row (zero in the pivot's), s2[c] the entry of L, and rinv the root of the reciprocal pivot in the pivot's lane.
-template <int c, bool TWO>
-__device__ __forceinline__ void eliminate_column(float (&s)[16], float (&s2)[16], float &y, float &y2, float &rinv, int i, bool &bad) {
+// lane's row (zero in the pivot's), that of a row below the entry of L, and rinv the root of the reciprocal pivot in the pivot's lane.
+struct RowBelow {
+    float (&s)[16];
+    float &y;
+};
+template <int c, class... Below>
+__device__ __forceinline__ void eliminate_column(float (&s)[16], float &y, float &rinv, int i, bool &bad, const Below &...below) {
     const float pivot = bcast16<c>(s[c]), uc = bcast16<c>(y);
     bad |= !(pivot > 0.f);
     float ri = __builtin_amdgcn_rsqf(pivot);
     ri = ri * (1.5f - 0.5f * pivot * ri * ri);  // one Newton step on the hardware estimate
-    float l = s[c] * ri, l2 = 0.f;
+    float l = s[c] * ri, lb[sizeof...(Below) + 1];
     const float own = i == c ? 0.f : l, w = uc * ri;
     rinv = i == c ? ri : rinv;
     y -= own * w;
-    if constexpr (TWO) {
-        l2 = s2[c] * ri;
-        y2 -= l2 * w;
-    }
+    int n = 0;
+    ((lb[n] = below.s[c] * ri, below.y -= lb[n] * w, ++n), ...);
     dpp_settle(l);  // just written, read through DPP below
     static_for<c + 1, 16>([&](auto jj) {  // the broadcast of l from the lane that owns row j rides on the multiply-add
         constexpr int j = decltype(jj)::value;
         fmac_bcast16_neg<j>(s[j], l, own);
-        if constexpr (TWO) fmac_bcast16_neg<j>(s2[j], l, l2);
+        int m = 0;
+        (fmac_bcast16_neg<j>(below.s[j], l, lb[m++]), ...);
     });
     s[c] = own * ri;
-    if constexpr (TWO) s2[c] = l2;
+    n = 0;
+    ((below.s[c] = lb[n++]), ...);
     if constexpr (c + 1 < 16) dpp_settle(s[c + 1]);  // the next step's pivot is read through DPP
 }
 

@@ -14,6 +14,12 @@ constexpr int FEW_ROWS[10] = {4, 4, 1, 1, 1, 1, 1, 1, 16, 8};
 // 34 000 rows gain 5 to 40 %.
 constexpr int64_t FEW_STEPS = 1 << 17;
 
+// Rows of 33 to 48 entries (d >= 64) that an earlier call saw, or that there can be, from which on they have the launch that takes
+// four of them per wavefront, the same operations on each.  Calls with rows of 40 entries only, in the common launch / their own, us:
+// d = 64 2500 rows 69 / 76, 5000 88 / 86, 40 000 231 / 207 (bf16: 2500 63 / 67, 30 000 172 / 140); d = 128 2500 rows 129 / 129, 5000 179 / 167
+// (bf16: 2500 106 / 100, 5000 134 / 117).
+constexpr int64_t few_triple_rows(int d) { return d == 64 ? 16384 : 4096; }
+
 struct FewLists {
     const int32_t *list[10], *count[10];
     int32_t start[11];  // first workgroup of each list; the last: the number of workgroups

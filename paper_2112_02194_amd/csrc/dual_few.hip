@@ -7,6 +7,7 @@
 #include "dual_multi_step.h"
 #include "dual_rows_step.h"
 #include "dual_small_step.h"
+#include "dual_triple_step.h"
 #include "dual_wide_step.h"
 
 namespace als {
@@ -24,6 +25,7 @@ template <int D, bool ZB> constexpr int few_lds_floats() {
     take(SmallCfg<D, 4>::LDS_FLOATS);
     take(SmallCfg<D, 8>::LDS_FLOATS);
     if constexpr (D >= 32) take(MultiCfg<D, ZB, few_keeps_tiles<ZB>()>::LDS_FLOATS);
+    if constexpr (D >= 64) take(TripleCfg<D, ZB, 1>::LDS_FLOATS);
     if constexpr (D == 64) take(WideCfg<D, 4>::LDS_FLOATS);
     if constexpr (D == 128) take(WideCfg<D, 8>::LDS_FLOATS);
     return n;
@@ -52,7 +54,9 @@ __global__ __launch_bounds__(64) void dual_few_kernel(const int64_t *__restrict_
         case 1:
             if constexpr (D >= 32) dual_multi_step<D, ZB, few_keeps_tiles<ZB>()>(indptr, indices, values, Z, R, ldr, r0, list, count, err_flag, step, lds);
             break;
-        case 2: wide(std::integral_constant<int, 3>{}); break;
+        case 2:
+            if constexpr (D >= 64) dual_triple_row<D, ZB>(indptr, indices, values, Z, R, ldr, r0, list, err_flag, step, lds);
+            break;
         case 3: wide(std::integral_constant<int, 4>{}); break;
         case 4: wide(std::integral_constant<int, 5>{}); break;
         case 5: wide(std::integral_constant<int, 6>{}); break;

@@ -14,7 +14,7 @@ __global__ __launch_bounds__(64) void dual_multi_kernel(const int64_t *__restric
 
 // bf16 Z, with X = R L^-1 taken along
 template <int D>
-__global__ __launch_bounds__(64) void dual_multi_x_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
+__global__ __launch_bounds__(64, D == 128 ? 2 : 3) void dual_multi_x_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                          const float *__restrict__ values, const void *__restrict__ Z, XTable x,
                                                          int64_t r0, const int32_t *__restrict__ list,
                                                          const int32_t *__restrict__ count_ptr, int32_t *__restrict__ err_flag) {
@@ -27,7 +27,7 @@ static void launch_multi_typed(const als_csr *Y, const void *Z, float *R, int64_
                               const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s) {
     constexpr size_t lds_bytes = MultiStep<D, false>::LDS_FLOATS * sizeof(float);
     static const int resident = resident_waves(dual_multi_kernel<D>, lds_bytes, w.num_cu);
-    hipLaunchKernelGGL(dual_multi_kernel<D>, dim3(walk_grid(resident, w.capacity, w.hint)), dim3(64), lds_bytes, s, Y->indptr,
+    hipLaunchKernelGGL(dual_multi_kernel<D>, dim3(walk_blocks(resident, w.capacity, w.hint)), dim3(64), lds_bytes, s, Y->indptr,
                        Y->indices, Y->values, Z, R, ldr, r0, list, count_dev, err);
 }
 template <int D>
@@ -35,7 +35,7 @@ static void launch_multi_typed_x(const als_csr *Y, const void *Z, const XTable &
                                 WalkSize w, int32_t *err, hipStream_t s) {
     constexpr size_t lds_bytes = Parked<MultiStep<D, true>, D>::LDS_FLOATS * sizeof(float);
     static const int resident = resident_waves(dual_multi_x_kernel<D>, lds_bytes, w.num_cu);
-    hipLaunchKernelGGL(dual_multi_x_kernel<D>, dim3(walk_grid(resident, w.capacity, w.hint)), dim3(64), lds_bytes, s, Y->indptr,
+    hipLaunchKernelGGL(dual_multi_x_kernel<D>, dim3(walk_blocks(resident, w.capacity, w.hint)), dim3(64), lds_bytes, s, Y->indptr,
                        Y->indices, Y->values, Z, x, r0, list, count_dev, err);
 }
 

@@ -205,7 +205,7 @@ template <int D, bool ZB, bool KEEP = true> struct MultiStep {
         load_tile_row(row_at + C::OFF_P, i, s0);
         load_tile_row(row_at + C::OFF_Q, i, s1);
         dpp_settle(s0[0]);
-        static_for<0, 16>([&](auto ci) { eliminate_column<decltype(ci)::value, true>(s0, s1, y0, y1, ri0, i, bad); });
+        static_for<0, 16>([&](auto ci) { eliminate_column<decltype(ci)::value>(s0, y0, ri0, i, bad, RowBelow{s1, y1}); });
 
         // ---- 3. C - L L^T and its elimination
         wave_sync();  // every lane has read its rows of A
@@ -232,8 +232,7 @@ template <int D, bool ZB, bool KEEP = true> struct MultiStep {
         dpp_settle(s1[0]);
         static_for<0, 16>([&](auto ci) {
             constexpr int c = decltype(ci)::value;
-            float none = 0.f;
-            if (16 + c < kmax) eliminate_column<c, false>(s1, s1, y1, none, ri1, i, bad);  // beyond every row's k: identity rows
+            if (16 + c < kmax) eliminate_column<c>(s1, y1, ri1, i, bad);  // beyond every row's k: identity rows
         });
         // a row past the end of the list stands for the step's first entry sixteen times over (its first tile is not masked): its
         // pivots mean nothing

@@ -53,6 +53,9 @@ void launch_dual_k16_x(int d, const als_csr *Y, const void *Z, const XTable &x, 
                        const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
 void launch_dual_multi2_x(int d, const als_csr *Y, const void *Z, const XTable &x, int64_t r0, const int32_t *list,
                           const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
+// direct solver
+void launch_dual_triple(int d, const als_csr *Y, const void *Z, bool zb16, float *R, int64_t ldr, int64_t r0, const int32_t *list,
+                        const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s);
 #define ALS_DECL_WIDE(kt)                                                                                          \
     als_status launch_dual_wide##kt(als_ctx *ctx, int d, const als_csr *Y, const void *Z, bool zb16, float *R,     \
                                     int64_t ldr, int64_t r0, const int32_t *list, const int32_t *count_dev,        \
@@ -454,7 +457,7 @@ __global__ __launch_bounds__(256, 2) void transform16_kernel(const uint16_t *__r
 // What bounds it: HBM (4.5 TB/s of rows read and written).
 constexpr int XFS_THREADS = 512;
 struct XLists {
-    const int32_t *list[10], *count[10];
+    const int32_t *list[10], *count[10];  // beyond n: the first once more
     int n;
 };
 
@@ -465,59 +468,78 @@ __global__ __launch_bounds__(XFS_THREADS, 2) void transform_lists_kernel(const f
     using M = XMatrix<D, BF>;
     constexpr int NK = D / 32;
     extern __shared__ char mat[];
-    M::fill(mat, LinvT, threadIdx.x, XFS_THREADS);
-    __syncthreads();
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), a = lane & 15, q = lane >> 4;
     R += r0 * ldr;
     X += r0 * ldx;
     const int nwaves = (int)gridDim.x * (XFS_THREADS / 64);
-    int tile = (int)blockIdx.x * (XFS_THREADS / 64) + wave;  // counted from the first tile of list i
-    for (int i = 0; i < xl.n; ++i) {
-        const int count = *xl.count[i], tiles = list_steps(count, 32);
-        const int32_t *list = xl.list[i];
-        for (; tile < tiles; tile += nwaves) {
-            int32_t rel[2];
-            bool have[2];
+    int counts[10], total = 0;  // all loads at once
 #pragma unroll
-            for (int n = 0; n < 2; ++n) {
-                const unsigned item = 32u * (unsigned)tile + 16u * n + (unsigned)a;
-                have[n] = item < (unsigned)count;
-                rel[n] = list[have[n] ? item : (unsigned)count - 1u];
-            }
-            float4 raw[2][NK][2];
+    for (int c = 0; c < 10; ++c) counts[c] = *xl.count[c];
 #pragma unroll
-            for (int n = 0; n < 2; ++n)
+    for (int c = 0; c < 10; ++c) {
+        if (c >= xl.n) counts[c] = 0;
+        total += list_steps(counts[c], 32);
+    }
+    int tile = (int)blockIdx.x * (XFS_THREADS / 64) + wave;  // counted from the first tile of the first list
+    int32_t rel[2] = {0, 0};
+    bool have[2] = {false, false};
+    float4 raw[2][NK][2];
+    auto load = [&] {
+        const int32_t *list = nullptr;
+        int count = 0, in_list = 0, first = 0;
 #pragma unroll
-                for (int kb = 0; kb < NK; ++kb) {
-                    const float *src = R + rel[n] * ldr + 32 * kb + 8 * q;
-                    raw[n][kb][0] = *(const float4 *)src;
-                    raw[n][kb][1] = *(const float4 *)(src + 4);
-                }
-            bf16x8 xp[2][M::PARTS][NK];
-#pragma unroll
-            for (int n = 0; n < 2; ++n)
-#pragma unroll
-                for (int kb = 0; kb < NK; ++kb) {
-                    bf16x8 part[M::PARTS];
-                    M::cut(raw[n][kb][0], raw[n][kb][1], part);
-#pragma unroll
-                    for (int t = 0; t < M::PARTS; ++t) xp[n][t][kb] = part[t];
-                }
-            x_rows<D, BF, 2>(mat, xp, [&](int n, int P, const floatx4 (&v)[2]) {
-                if (have[n]) store_x8<BF>(X + rel[n] * ldx + 32 * P + 8 * q, v);
-            });
+        for (int c = 0; c < 10; ++c) {
+            const bool here = tile >= first;  // the last list that begins at or before the tile, and is not empty
+            const int steps = list_steps(counts[c], 32);
+            list = here && steps > 0 ? xl.list[c] : list;
+            count = here && steps > 0 ? counts[c] : count;
+            in_list = here && steps > 0 ? tile - first : in_list;
+            first += steps;
         }
-        tile -= tiles;
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const unsigned item = 32u * (unsigned)in_list + 16u * n + (unsigned)a;
+            have[n] = item < (unsigned)count;
+            rel[n] = list[have[n] ? item : (unsigned)count - 1u];
+        }
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int kb = 0; kb < NK; ++kb) {
+                const float *src = R + rel[n] * ldr + 32 * kb + 8 * q;
+                raw[n][kb][0] = *(const float4 *)src;
+                raw[n][kb][1] = *(const float4 *)(src + 4);
+            }
+    };
+    if (tile < total) load();  // the first rows are on their way while the matrix is laid out
+    M::template fill<XFS_THREADS>(mat, LinvT, threadIdx.x);
+    __syncthreads();
+    while (tile < total) {
+        bf16x8 xp[2][M::PARTS][NK];
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+            for (int kb = 0; kb < NK; ++kb) {
+                bf16x8 part[M::PARTS];
+                M::cut(raw[n][kb][0], raw[n][kb][1], part);
+#pragma unroll
+                for (int t = 0; t < M::PARTS; ++t) xp[n][t][kb] = part[t];
+            }
+        x_rows<D, BF, 2>(mat, xp, [&](int n, int P, const floatx4 (&v)[2]) {
+            if (have[n]) store_x8<BF>(X + rel[n] * ldx + 32 * P + 8 * q, v);
+        });
+        tile += nwaves;
+        if (tile < total) load();
     }
 }
 
 // XMatrix for the kernels that read it from device memory
 template <int D> __global__ __launch_bounds__(64) void x_matrix_kernel(const float *__restrict__ LinvT, char *__restrict__ mat) {
-    XMatrix<D, true>::fill(mat, LinvT, blockIdx.x * 64 + threadIdx.x, gridDim.x * 64);
+    XMatrix<D, true>::template fill<XMatrix<D, true>::BLOCKS * 64>(mat, LinvT, blockIdx.x * 64 + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------- launchers
-// Rows of 32 < k <= 128 that one launch takes for several classes where an earlier call saw so few (or that no hint announced): as many as
+// Rows of 48 < k <= 128 that one launch takes for several classes where an earlier call saw so few (or that no hint announced): as many as
 // find a SIMD to themselves.
 inline int64_t wide_rest_limit(int num_cu) { return 8 * (int64_t)num_cu; }
 
@@ -622,16 +644,24 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     const WideSolver ws = {prm->solver == ALS_SOLVER_CG, prm->cg_max_iters > 0 ? prm->cg_max_iters : 2 * D,
                            prm->cg_tol > 0.f ? prm->cg_tol : 1e-6f};
     FewLists few;
-    int64_t steps = 0;
+    int64_t steps = 0, listed = 0;  // all, and those in the common launch
+    const bool own_triple = D >= 64 && !ws.cg && (hints[2] < 0 ? caps[2] : hints[2]) >= few_triple_rows(D);
     for (int c = 0; c < 10; ++c) {
         few.list[c] = lists[c];
         few.count[c] = counts_dev[c];
-        few.start[c] = (int32_t)std::min<int64_t>(steps, INT32_MAX);
-        steps += (caps[c] + FEW_ROWS[c] - 1) / FEW_ROWS[c];
+        few.start[c] = (int32_t)std::min<int64_t>(listed, INT32_MAX);
+        const int64_t n = (caps[c] + FEW_ROWS[c] - 1) / FEW_ROWS[c];
+        steps += n;
+        listed += c == 2 && own_triple ? 0 : n;
     }
-    few.start[10] = (int32_t)std::min<int64_t>(steps, INT32_MAX);
+    few.start[10] = (int32_t)std::min<int64_t>(listed, INT32_MAX);
     if (!ws.cg && steps <= FEW_STEPS) {
-        if (steps > 0) {
+        if constexpr (D >= 64) {
+            if (own_triple) {
+                ALS_TIMED_CLASS(T_DUAL_CLASS0 + 2, 2, 4, (launch_dual_triple(D, Y, Z, zb16, R, ldr, r0, lists[2], counts_dev[2], walk(2, 4), err, s)))
+            }
+        }
+        if (listed > 0) {
             timer_begin(ctx, T_DUAL_CLASS0, s);
             stb = launch_dual_few(ctx, D, Y, Z, zb16, R, ldr, r0, few, err, s);
             timer_end(ctx, s);
@@ -666,35 +696,38 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     }
     }
     if constexpr (D >= 64) {
-    // direct solver: short classes, longest rows first, have no launch of their own (see wide_rest_limit)
+    // direct solver: short classes beyond k = 48 have no launch of their own (see wide_rest_limit)
     WideRest rest;
     int64_t room = wide_rest_limit(ctx->num_cu), joint = 0, beyond = 0;
-    StepGrid wide[6];
-    for (int i = 5; i >= 0; --i) {
-        const int c = 2 + i;
-        wide[i] = grid(c, 1);
-        if (!ws.cg) {
-            if (hints[c] >= 0 && hints[c] <= room) {
-                room -= hints[c];
-                joint += std::min<int64_t>(hints[c], caps[c]);
-                wide[i].known = 0;
-            } else {
-                room = 0;
-            }
-            wide[i].rest = 0;
+    StepGrid wide[8];
+    for (int c = 7; c >= 2; --c) {
+        wide[c] = grid(c, 1);
+        if (ws.cg || c == 2) continue;
+        if (hints[c] >= 0 && hints[c] <= room) {
+            room -= hints[c];
+            joint += std::min<int64_t>(hints[c], caps[c]);
+            wide[c].known = 0;
+        } else {
+            room = 0;
         }
-        rest.list[i] = lists[c];
-        rest.count[i] = counts_dev[c];
-        rest.known[i] = (int32_t)wide[i].known;
-        beyond += std::max<int64_t>(0, caps[c] - (int64_t)wide[i].known);
+        wide[c].rest = 0;
+        rest.list[c - 3] = lists[c];
+        rest.count[c - 3] = counts_dev[c];
+        rest.known[c - 3] = (int32_t)wide[c].known;
+        beyond += std::max<int64_t>(0, caps[c] - (int64_t)wide[c].known);
     }
 #define ALS_WIDE(kt) \
-    if (caps[kt - 1] > 0 && wide[kt - 3].known + wide[kt - 3].rest > 0 && stb == ALS_OK) { \
+    if (caps[kt - 1] > 0 && wide[kt - 1].known + wide[kt - 1].rest > 0 && stb == ALS_OK) { \
         timer_begin(ctx, T_DUAL_CLASS0 + kt - 1, s); \
-        stb = launch_dual_wide##kt(ctx, D, Y, Z, zb16, R, ldr, r0, lists[kt - 1], counts_dev[kt - 1], wide[kt - 3], err, ws, s); \
+        stb = launch_dual_wide##kt(ctx, D, Y, Z, zb16, R, ldr, r0, lists[kt - 1], counts_dev[kt - 1], wide[kt - 1], err, ws, s); \
         timer_end(ctx, s); \
     }
-    ALS_WIDE(3) ALS_WIDE(4) ALS_WIDE(5) ALS_WIDE(6) ALS_WIDE(7) ALS_WIDE(8)
+    if (!ws.cg) {
+        ALS_TIMED_CLASS(T_DUAL_CLASS0 + 2, 2, 4, (launch_dual_triple(D, Y, Z, zb16, R, ldr, r0, lists[2], counts_dev[2], walk(2, 4), err, s)))
+    } else {
+        ALS_WIDE(3)
+    }
+    ALS_WIDE(4) ALS_WIDE(5) ALS_WIDE(6) ALS_WIDE(7) ALS_WIDE(8)
 #undef ALS_WIDE
     if (!ws.cg && beyond > 0 && stb == ALS_OK) {
         timer_begin(ctx, D == 128 ? T_DUAL_CLASS0 + 7 : T_DUAL_CLASS0 + 3, s);
@@ -714,8 +747,7 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
         static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_lists_kernel<D, BF16>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, M::BYTES);  // once per process
         ALS_HIP(ctx, attr_x);
-        XLists xl;
-        xl.n = 0;
+        XLists xl = {};
         int64_t tiles = 0;
         for (int c = 0; c < 10; ++c)
             if (caps[c] > 0 && !is_x[c]) {
@@ -723,6 +755,10 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
                 xl.count[xl.n++] = counts_dev[c];
                 tiles += (caps[c] + 31) / 32;
             }
+        for (int c = xl.n; c < 10; ++c) {
+            xl.list[c] = xl.list[0];
+            xl.count[c] = xl.count[0];
+        }
         const unsigned sblocks = (unsigned)std::min<int64_t>(512, (tiles + XFS_THREADS / 64 - 1) / (XFS_THREADS / 64));
         if (sblocks > 0)
             hipLaunchKernelGGL((transform_lists_kernel<D, BF16>), dim3(sblocks), dim3(XFS_THREADS), M::BYTES, s, (const float *)R, ldr,

@@ -27,7 +27,7 @@ static void launch_rows_typed(const als_csr *Y, const void *Z, float *R, int64_t
                               const int32_t *count_dev, WalkSize w, int32_t *err, hipStream_t s) {
     constexpr size_t lds_bytes = RowsStep<D, false>::LDS_FLOATS * sizeof(float);
     static const int resident = resident_waves(dual_rows_kernel<D>, lds_bytes, w.num_cu);
-    hipLaunchKernelGGL(dual_rows_kernel<D>, dim3(walk_grid(resident, w.capacity, w.hint)), dim3(64), lds_bytes, s, Y->indptr,
+    hipLaunchKernelGGL(dual_rows_kernel<D>, dim3(walk_blocks(resident, w.capacity, w.hint)), dim3(64), lds_bytes, s, Y->indptr,
                        Y->indices, Y->values, Z, R, ldr, r0, list, count_dev, err);
 }
 template <int D>
@@ -35,7 +35,7 @@ static void launch_rows_typed_x(const als_csr *Y, const void *Z, const XTable &x
                                 WalkSize w, int32_t *err, hipStream_t s) {
     constexpr size_t lds_bytes = Parked<RowsStep<D, true>, D>::LDS_FLOATS * sizeof(float);
     static const int resident = resident_waves(dual_rows_x_kernel<D>, lds_bytes, w.num_cu);
-    hipLaunchKernelGGL(dual_rows_x_kernel<D>, dim3(walk_grid(resident, w.capacity, w.hint)), dim3(64), lds_bytes, s, Y->indptr,
+    hipLaunchKernelGGL(dual_rows_x_kernel<D>, dim3(walk_blocks(resident, w.capacity, w.hint)), dim3(64), lds_bytes, s, Y->indptr,
                        Y->indices, Y->values, Z, x, r0, list, count_dev, err);
 }
 

@@ -150,8 +150,7 @@ template <int D, bool ZB> struct RowsStep {
         dpp_settle(s[0]);
         static_for<0, 16>([&](auto ci) {
             constexpr int c = decltype(ci)::value;
-            float none = 0.f;
-            if (c < kmax) eliminate_column<c, false>(s, s, y, none, ri, i, bad);  // beyond every row's k: identity rows
+            if (c < kmax) eliminate_column<c>(s, y, ri, i, bad);  // beyond every row's k: identity rows
         });
         if (bad) atomicOr(err_flag, 1);
         float t = y * ri * ri;

@@ -71,7 +71,7 @@ __global__ __launch_bounds__((SmallXCfg<D, G, ZB>::THREADS)) void dual_small_x_k
     const int count = *count_ptr;
     if (count <= 0) return;
     char *mat = (char *)shared;
-    M::fill(mat, LinvT, threadIdx.x, CX::THREADS);
+    M::template fill<CX::THREADS>(mat, LinvT, threadIdx.x);
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     float *lds = (float *)(mat + M::BYTES) + wave * CX::WAVE_FLOATS;

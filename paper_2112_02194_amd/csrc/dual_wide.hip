@@ -1,4 +1,5 @@
-// Row classes 32 < k <= 128, compiled once per class with -DWIDE_KT=3..8 (step: dual_wide_step.h).
+// Row classes 48 < k <= 128, compiled once per class with -DWIDE_KT=4..8, and with -DWIDE_KT=3 all rows of up to 48 entries under conjugate
+// gradients (step: dual_wide_step.h).
 #include "dual_wide_step.h"
 
 #ifndef WIDE_KT
@@ -52,7 +53,7 @@ static als_status wide_typed(als_ctx *ctx, const als_csr *Y, const void *Z, floa
                                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);  // once per process
         ALS_HIP(ctx, attr_cg);
         launch(dual_wide_kernel<D, WIDE_KT, ZB, true>, g.known + g.rest);
-    } else {
+    } else if constexpr (WIDE_KT > 3) {
         static const hipError_t attr = hipFuncSetAttribute((const void *)dual_wide_kernel<D, WIDE_KT, ZB, false>,
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);  // once per process
         ALS_HIP(ctx, attr);

@@ -1,4 +1,4 @@
-// Rows of 32 < k <= 128 beyond those that the launches per class take (direct solver; step: dual_wide_step.h).
+// Rows of 48 < k <= 128 beyond those that the launches per class take (direct solver; step: dual_wide_step.h).
 #include "dual_wide_rest.h"
 #include "dual_wide_step.h"
 
@@ -15,7 +15,7 @@ __global__ __launch_bounds__(64, 1) void dual_wide_rest_kernel(const int64_t *__
                                                                float *__restrict__ R, int64_t ldr, int64_t r0, WideRest w,
                                                                int32_t *__restrict__ err_flag) {
     extern __shared__ float lds[];
-    constexpr int LAST = D == 128 ? 5 : 1;  // list i: rows of class KT = 3 + i
+    constexpr int LAST = D == 128 ? 4 : 0;  // list i: rows of class KT = 4 + i
     int64_t at = blockIdx.x;                // counted from the first row of list i that no other launch takes
     for (int i = LAST; i >= 0; --i) {
         const int64_t first = w.known[i], left = *w.count[i] - first;
@@ -28,13 +28,12 @@ __global__ __launch_bounds__(64, 1) void dual_wide_rest_kernel(const int64_t *__
                                                                   opaque(lds), 0, 0.f);
             };
             switch (i) {  // uniform
-                case 0: step(std::integral_constant<int, 3>{}); break;
-                case 1: step(std::integral_constant<int, 4>{}); break;
+                case 0: step(std::integral_constant<int, 4>{}); break;
                 default:
                     if constexpr (D == 128) {
-                        if (i == 2) step(std::integral_constant<int, 5>{});
-                        else if (i == 3) step(std::integral_constant<int, 6>{});
-                        else if (i == 4) step(std::integral_constant<int, 7>{});
+                        if (i == 1) step(std::integral_constant<int, 5>{});
+                        else if (i == 2) step(std::integral_constant<int, 6>{});
+                        else if (i == 3) step(std::integral_constant<int, 7>{});
                         else step(std::integral_constant<int, 8>{});
                     }
             }

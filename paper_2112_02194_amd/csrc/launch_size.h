@@ -68,4 +68,15 @@ inline unsigned walk_grid(int64_t resident, int64_t capacity, int64_t hint) {
     return (unsigned)std::min((grid + 7) / 8 * 8, LAUNCH_MAX);
 }
 
+// The same in whole rounds of as many workgroups as the device holds at a time, so that a short list has no last round of a few workgroups
+// with four steps each.  300k rows folded in (d = 128, bf16; 17 024 steps of 16 < k <= 32 on 2048 places): 115 -> 107 us; 40 000 rows of
+// 40 entries (d = 64; 10 000 steps of 20 us): the call 225 -> 208 us; one round only, of up to sixteen steps, was slower where a list had more than a few (300k rows of up to 30 entries, d = 128, fp32: 499 -> 579 us).
+inline unsigned walk_blocks(int64_t resident, int64_t capacity, int64_t hint) {
+    constexpr int64_t PER_WAVE = 4, ROUNDS = 8;
+    const int64_t steps = hint < 0 ? capacity : std::min(hint, capacity);
+    const int64_t rounds = (steps + PER_WAVE * resident - 1) / (PER_WAVE * resident);
+    if (steps > resident && rounds <= ROUNDS) return (unsigned)((rounds * resident + 7) / 8 * 8);
+    return walk_grid(resident, capacity, hint);
+}
+
 }  // namespace als

@@ -30,22 +30,34 @@ template <int D, bool BF> struct XMatrix {
     static constexpr int BYTES = PARTS * 1024 * BLOCKS;  // per block and part: one operand, 16 bytes a lane
     // block o of pair P, step kb >= P
     static constexpr int block(int P, int o, int kb) { return 2 * P * NK - P * (P - 1) + o * (NK - P) + kb - P; }
-    // the matrix as operands, from its transpose, by `threads` threads; a barrier is the caller's
-    static __device__ __forceinline__ void fill(char *to, const float *__restrict__ LinvT, int thread, int threads) {
-        for (int e = thread; e < BLOCKS * 64; e += threads) {
-            const int b = e >> 6, m = e & 15, q = e >> 4 & 3;
+    // the matrix as operands, from its transpose, by THREADS threads, all loads at once; a barrier is the caller's
+    template <int THREADS> static __device__ __forceinline__ void fill(char *to, const float *__restrict__ LinvT, int thread) {
+        constexpr int N = (BLOCKS * 64 + THREADS - 1) / THREADS;
+        float4 u[N], v[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            const int e = n * THREADS + thread, b = e >> 6, m = e & 15, q = e >> 4 & 3;
+            if (e >= BLOCKS * 64) continue;
             int P = 0, first = 0;  // the pair and its first block
-            while (P + 1 < NK && b >= first + 2 * (NK - P)) {
-                first += 2 * (NK - P);
-                ++P;
-            }
+#pragma unroll
+            for (int p = 1; p < NK; ++p)
+                if (b >= block(p, 0, p)) {
+                    P = p;
+                    first = block(p, 0, p);
+                }
             const int o = b - first >= NK - P, kb = P + b - first - o * (NK - P);
             const float *src = LinvT + (32 * P + 8 * (m >> 2) + 4 * o + (m & 3)) * D + 32 * kb + 8 * q;
-            const float4 u = *(const float4 *)src, v = *(const float4 *)(src + 4);
-            bf16x8 part[PARTS];
-            cut(u, v, part);
+            u[n] = *(const float4 *)src;
+            v[n] = *(const float4 *)(src + 4);
+        }
 #pragma unroll
-            for (int t = 0; t < PARTS; ++t) *(bf16x8 *)(to + (PARTS * b + t) * 1024 + (e & 63) * 16) = part[t];
+        for (int n = 0; n < N; ++n) {
+            const int e = n * THREADS + thread;
+            if (e >= BLOCKS * 64) continue;
+            bf16x8 part[PARTS];
+            cut(u[n], v[n], part);
+#pragma unroll
+            for (int t = 0; t < PARTS; ++t) *(bf16x8 *)(to + (PARTS * (e >> 6) + t) * 1024 + (e & 63) * 16) = part[t];
         }
     }
     static __device__ __forceinline__ void cut(const float4 &u, const float4 &v, bf16x8 (&part)[PARTS]) {
