@@ -1,6 +1,7 @@
 // Row classes k <= 4 and 5 <= k <= 8, compiled once each with -DSMALL_G=4 and -DSMALL_G=8 (step: dual_small_step.h).
 #include "dual_small_step.h"
 #include "dual_walk.h"
+#include "row_copy.h"
 #include "step_queue.h"
 #include "x_rows.h"
 
@@ -52,7 +53,7 @@ template <int D, int G, bool ZB> struct SmallXCfg {
     static constexpr int THREADS = ZB ? 768 : 512;
     using M = XMatrix<D, ZB>;
     typedef typename std::conditional<ZB, uint16_t, float>::type elem;
-    static constexpr int RLD = D + 4;  // row stride of the copy of R
+    static constexpr int RLD = row_copy_stride(D);  // of the copy of R
     static constexpr int WAVE_FLOATS = SmallCfg<D, G>::OFF_META;
     static_assert(16 * RLD <= SmallCfg<D, G>::MAIN, "sixteen rows of R take the place of a tile's entries");
     static constexpr size_t LDS_BYTES = M::BYTES + (THREADS / 64) * WAVE_FLOATS * sizeof(float);
@@ -66,7 +67,7 @@ __global__ __launch_bounds__((SmallXCfg<D, G, ZB>::THREADS)) void dual_small_x_k
     using C = SmallCfg<D, G>;
     using CX = SmallXCfg<D, G, ZB>;
     using M = typename CX::M;
-    constexpr int NR = C::NR, NJ = z_pieces<D, ZB>(), CPL = D >= 128 ? 2 : 1, NK = D / 32;
+    constexpr int NR = C::NR, NJ = z_pieces<D, ZB>(), CPL = columns_per_lane(D), NK = D / 32;
     extern __shared__ float shared[];
     const int count = *count_ptr;
     if (count <= 0) return;
@@ -145,10 +146,13 @@ __global__ __launch_bounds__((SmallXCfg<D, G, ZB>::THREADS)) void dual_small_x_k
         });
         wave_sync();
         // ---- X = R L^-1 of the wavefront's rows (with G = 8 the rows 8 .. 15 of the tile are whatever lies there)
+        if (holds_columns(D, lane)) {
 #pragma unroll
-        for (int n = 0; n < NR; ++n) {
-            if constexpr (CPL == 2) *(float2 *)(lds + n * CX::RLD + 2 * lane) = make_float2(r[n][0], r[n][1]);
-            else lds[n * CX::RLD + lane] = r[n][0];
+            for (int n = 0; n < NR; ++n) {
+                float *to = lds + row_copy_place(D, n, lane);
+                if constexpr (CPL == 2) *(float2 *)to = make_float2(r[n][0], r[n][1]);
+                else *to = r[n][0];
+            }
         }
         wave_sync();
         const int a = lane & 15, q = lane >> 4;
