@@ -22,12 +22,15 @@ struct StepGrid {
 // `blind_limit` allows: the grid-stride form takes a quarter to a third longer per step (1M x 1M, d = 64, no hint:
 // 7.3 -> 6.5 ms).  A launch holds fewer than 2^32 threads, so the limit depends on the kernel's workgroup: with one limit of
 // 2^24 workgroups for all, the 2.2e7 steps of 16 < k <= 32 of a 100M-row epoch (64 threads each) took the grid-stride form
-// from there on, and 256 threads were too many.  One launch may take both parts together.
-inline StepGrid step_grid(int num_cu, int threads, int64_t capacity, int64_t hint, int per_cu, int64_t blind_limit) {
+// from there on, and 256 threads were too many.  One launch may take both parts together, or the first
+// part with the `beside` workgroups of another list.
+inline StepGrid step_grid(int num_cu, int threads, int64_t capacity, int64_t hint, int per_cu, int64_t blind_limit,
+                          int64_t beside = 0) {
     StepGrid g = {0u, 0u};
     if (capacity <= 0) return g;
     constexpr int64_t WHOLE = 4096;
-    const int64_t walkers = (int64_t)num_cu * per_cu, launch_max = (int64_t)0xffffffff / threads - walkers;
+    const int64_t walkers = (int64_t)num_cu * per_cu;
+    const int64_t launch_max = (int64_t)0xffffffff / threads - walkers - beside;
     const int64_t wanted = capacity <= WHOLE ? capacity : (hint < 0 ? blind_limit : hint);
     g.known = (unsigned)std::min(wanted, std::min(capacity, launch_max));
     g.rest = (unsigned)std::min<int64_t>(capacity - g.known, walkers);

@@ -534,8 +534,9 @@ als_status launch_solve_rows(als_ctx *ctx, const als_csr *Y, const als_table *V,
     const int pt = primal_threads(V->d);
     const StepGrid g_long = step_grid(ctx->num_cu, pt, std::min<int64_t>(SEG_CAPACITY / 2, Y->nnz / split + 1), hint[0], 4, SEG_CAPACITY);
     const StepGrid g_seg = step_grid(ctx->num_cu, pt, seg_capacity, hint[1], 8, SEG_CAPACITY);
+    const StepGrid g_row = step_grid(ctx->num_cu, pt, cap_mid, hint[3], 8, BLIND_PRIMAL, g_seg.known);  // one launch may take both
     if ((st = launch_primal(ctx, Y, V, G, prm, X, r0, long_rows, segs, counters, seg_capacity, g_long, g_seg, mid_list, counters + 3,
-                            step_grid(ctx->num_cu, pt, cap_mid, hint[3], 8, BLIND_PRIMAL), s)) != ALS_OK)
+                            g_row, s)) != ALS_OK)
         return st;
     if (dual_max > 0) {
         const int32_t *lists[10], *counts_dev[10];

@@ -15,12 +15,16 @@ def step_grid(tmp_path_factory):
     src.write_text('#include "launch_size.h"\n'
                    'extern "C" void grid(int cu, int threads, int64_t cap, int64_t hint, int per_cu, int64_t blind, unsigned *out) {\n'
                    '    const als::StepGrid g = als::step_grid(cu, threads, cap, hint, per_cu, blind); out[0] = g.known; out[1] = g.rest; }\n'
+                   'extern "C" void beside(int cu, int threads, int64_t cap, int64_t hint, int per_cu, int64_t blind, int64_t other, unsigned *out) {\n'
+                   '    const als::StepGrid g = als::step_grid(cu, threads, cap, hint, per_cu, blind, other); out[0] = g.known; out[1] = g.rest; }\n'
                    'extern "C" unsigned walk(int64_t resident, int64_t cap, int64_t hint) { return als::walk_grid(resident, cap, hint); }\n'
                    'extern "C" int xcd(int b, int grid, int steps) { return als::xcd_step(b, grid, steps); }\n'
                    'extern "C" int list_steps(int count, int rows) { return als::list_steps(count, rows); }\n'
                    'extern "C" void walk_range(int b, int grid, int count, int *out) {\n'
                    '    const als::WalkRange w = als::walk_range(b, grid, count); out[0] = w.blk; out[1] = w.end; out[2] = w.stride; }\n')
     subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, "-o", str(lib), str(src)])
+    beside.f = ctypes.CDLL(str(lib)).beside
+    beside.f.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p]
     walk_grid.f = ctypes.CDLL(str(lib)).walk
     walk_grid.f.argtypes, walk_grid.f.restype = [ctypes.c_int64] * 3, ctypes.c_uint
     xcd.f = ctypes.CDLL(str(lib)).xcd
@@ -34,6 +38,12 @@ def step_grid(tmp_path_factory):
         f(cu, threads, cap, hint, per_cu, blind, out)
         return int(out[0]), int(out[1])
     return call
+
+
+def beside(threads, cap, hint, other, per_cu=8, blind=1 << 20, cu=256):
+    out = (ctypes.c_uint * 2)()
+    beside.f(cu, threads, cap, hint, per_cu, blind, other, out)
+    return int(out[0]), int(out[1])
 
 
 def xcd(b, grid, steps):
@@ -70,6 +80,20 @@ def test_the_two_forms_cover_the_list_and_fit_one_launch(step_grid, threads):
                 assert known == min(hint, cap)  # a hint is followed as far as a launch can hold it
             elif hint < 0:
                 assert known == min(cap, 1 << 22)
+
+
+@pytest.mark.parametrize("threads", [64, 128, 256])
+@pytest.mark.parametrize("segments", [0, 1, 4096, 4097, 10_000, 1 << 15])
+def test_two_lists_that_share_a_launch_fit_it_together(step_grid, threads, segments):
+    """Rows solved whole and segments of long rows, as many as a call before saw: a launch for the first parts."""
+    other, _ = step_grid(threads, 1 << 15, segments, per_cu=8, blind=1 << 15)
+    for cap in SIZES:
+        for hint in [-1] + SIZES:
+            known, rest = beside(threads, cap, hint, other)
+            assert (known + other) * threads < 1 << 32
+            assert known <= cap and (known + rest == cap or rest == 256 * 8)
+            alone, _ = step_grid(threads, cap, hint, per_cu=8, blind=1 << 20)
+            assert known == alone or known + rest + other == 0xffffffff // threads  # no fewer than a launch can hold
 
 
 def test_a_long_list_of_small_workgroups_is_launched_whole(step_grid):
