@@ -220,7 +220,7 @@ def main():
                          else f"gramian_partial_kernel<{d},{bft}>",
                          "transform_z": f"transform16_kernel<{d},false>" if zbt == "true"      # Z = V L^-T
                          else f"transform_kernel<{d},{bft},false,true,false>",
-                         "transform_x": f"transform_lists_kernel<{d},{bft}>" if zbt == "true" or (es == 4 and d >= 64)  # X = R L^-1
+                         "transform_x": f"transform_lists_kernel<{d},{bft},512>" if zbt == "true" or (es == 4 and d >= 64)  # X = R L^-1
                          else f"transform_kernel<{d},false,{bft},false,false>",
                          "primal": f"primal_kernel<{d},{bft},0>",               # one workgroup per row
                          "segment": f"primal_kernel<{d},{bft},1>"})             # segments of long rows

@@ -271,15 +271,17 @@ __global__ __launch_bounds__(256, 2) void transform16_kernel(const uint16_t *__r
 // x_rows.h over the rows of some class lists, 32 rows per wavefront at a time, fp32 tables (d >= 64) in place, bf16 tables (d >= 32)
 // from the fp32 rows of R.  fp32: 0.375 of the fp32 instruction's matrix-core time, which leaves the pass to the table read and
 // write (for Z = V L^-T the fp32 kernel above measured faster, 24.4 against 25.9 ms per epoch of 50M x 50M).
-// What bounds it: HBM (4.5 TB/s of rows read and written).
-constexpr int XFS_THREADS = 512;
+// What bounds it: HBM (4.5 TB/s of rows read and written); in short calls the chain of counts, list entries, rows and the matrix that every
+// workgroup lays out for itself.  Rows of 12 entries, workgroups for all that the lists' capacities come to, eight wavefronts each / as
+// it is (tile_grid), us: d = 128, bf16 9000 rows 10.3 / 7.6, 15 000 11.2 / 7.9, 30 000 12.2 / 9.2, fp32 9000 13.4 / 9.6, 30 000 15.2 / 12.1, 60 000
+// 19.0 / 17.2; d = 64, fp32, 9000 7.9 / 6.0.
 struct XLists {
     const int32_t *list[10], *count[10];  // beyond n: the first once more
     int n;
 };
 
-template <int D, bool BF>
-__global__ __launch_bounds__(XFS_THREADS, 2) void transform_lists_kernel(const float *R, int64_t ldr,
+template <int D, bool BF, int T>
+__global__ __launch_bounds__(T, 2) void transform_lists_kernel(const float *R, int64_t ldr,
                                                                          typename std::conditional<BF, uint16_t, float>::type *X, int64_t ldx,
                                                                          const float *__restrict__ LinvT, int64_t r0, XLists xl) {
     using M = XMatrix<D, BF>;
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(XFS_THREADS, 2) void transform_lists_kernel(const f
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), a = lane & 15, q = lane >> 4;
     R += r0 * ldr;
     X += r0 * ldx;
-    const int nwaves = (int)gridDim.x * (XFS_THREADS / 64);
+    const int nwaves = (int)gridDim.x * (T / 64);
     int counts[10], total = 0;  // all loads at once
 #pragma unroll
     for (int c = 0; c < 10; ++c) counts[c] = *xl.count[c];
@@ -297,7 +299,7 @@ __global__ __launch_bounds__(XFS_THREADS, 2) void transform_lists_kernel(const f
         if (c >= xl.n) counts[c] = 0;
         total += list_steps(counts[c], 32);
     }
-    int tile = (int)blockIdx.x * (XFS_THREADS / 64) + wave;  // counted from the first tile of the first list
+    int tile = (int)blockIdx.x * (T / 64) + wave;  // counted from the first tile of the first list
     int32_t rel[2] = {0, 0};
     bool have[2] = {false, false};
     float4 raw[2][NK][2];
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(XFS_THREADS, 2) void transform_lists_kernel(const f
             }
     };
     if (tile < total) load();  // the first rows are on their way while the matrix is laid out
-    M::template fill<XFS_THREADS>(mat, LinvT, threadIdx.x);
+    M::template fill<T>(mat, LinvT, threadIdx.x);
     __syncthreads();
     while (tile < total) {
         bf16x8 xp[2][M::PARTS][NK];
@@ -563,9 +565,6 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
     if constexpr (X_LISTS) {
         using M = XMatrix<D, BF16>;
         typedef typename std::conditional<BF16, uint16_t, float>::type elem;
-        static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_lists_kernel<D, BF16>,
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, M::BYTES);  // once per process
-        ALS_HIP(ctx, attr_x);
         XLists xl = {};
         int64_t tiles = 0;
         for (int c = 0; c < 10; ++c)
@@ -578,10 +577,17 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
             xl.list[c] = xl.list[0];
             xl.count[c] = xl.count[0];
         }
-        const unsigned sblocks = (unsigned)std::min<int64_t>(512, (tiles + XFS_THREADS / 64 - 1) / (XFS_THREADS / 64));
-        if (sblocks > 0)
-            hipLaunchKernelGGL((transform_lists_kernel<D, BF16>), dim3(sblocks), dim3(XFS_THREADS), M::BYTES, s, (const float *)R, ldr,
-                               (elem *)X->data, X->ld, LinvT, r0, xl);
+        const TileGrid g = tile_grid(ctx->num_cu, tiles, r1 - r0, xl.n);
+        auto launch = [&](auto threads) {
+            constexpr int T = decltype(threads)::value;
+            static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_lists_kernel<D, BF16, T>,
+                                                                 hipFuncAttributeMaxDynamicSharedMemorySize, M::BYTES);  // once per process
+            if (attr_x == hipSuccess)
+                hipLaunchKernelGGL((transform_lists_kernel<D, BF16, T>), dim3(g.blocks), dim3(T), M::BYTES, s, (const float *)R, ldr,
+                                   (elem *)X->data, X->ld, LinvT, r0, xl);
+            return attr_x;
+        };
+        if (xl.n > 0) ALS_HIP(ctx, g.threads == 256 ? launch(std::integral_constant<int, 256>{}) : launch(std::integral_constant<int, 512>{}));
     } else {
         static const hipError_t attr_x = hipFuncSetAttribute((const void *)transform_kernel<D, false, BF16, false, false>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize,

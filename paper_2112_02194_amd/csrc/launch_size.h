@@ -82,4 +82,14 @@ inline unsigned walk_blocks(int64_t resident, int64_t capacity, int64_t hint) {
     return walk_grid(resident, capacity, hint);
 }
 
+// X = R L^-1 over class lists (transform_lists_kernel), 32 rows per wavefront at a time: workgroups, each of which lays out the matrix
+// for itself.  `tiles`: what the lists can hold by their capacities; every one of the `rows` rows is in one of the `lists` lists at most.
+// While a workgroup of four wavefronts per compute unit holds all tiles, that is what is launched, otherwise eight share a matrix.
+struct TileGrid { unsigned blocks, threads; };
+inline TileGrid tile_grid(int num_cu, int64_t tiles, int64_t rows, int lists) {
+    tiles = std::min(tiles, rows / 32 + lists);
+    const int waves = tiles <= 4 * (int64_t)num_cu ? 4 : 8;
+    return {(unsigned)std::min<int64_t>(2 * num_cu, (tiles + waves - 1) / waves), 64u * (unsigned)waves};
+}
+
 }  // namespace als

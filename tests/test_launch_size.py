@@ -18,6 +18,8 @@ def step_grid(tmp_path_factory):
                    'extern "C" void beside(int cu, int threads, int64_t cap, int64_t hint, int per_cu, int64_t blind, int64_t other, unsigned *out) {\n'
                    '    const als::StepGrid g = als::step_grid(cu, threads, cap, hint, per_cu, blind, other); out[0] = g.known; out[1] = g.rest; }\n'
                    'extern "C" unsigned walk(int64_t resident, int64_t cap, int64_t hint) { return als::walk_grid(resident, cap, hint); }\n'
+                   'extern "C" void tiles(int cu, int64_t tiles, int64_t rows, int lists, unsigned *out) {\n'
+                   '    const als::TileGrid g = als::tile_grid(cu, tiles, rows, lists); out[0] = g.blocks; out[1] = g.threads; }\n'
                    'extern "C" int xcd(int b, int grid, int steps) { return als::xcd_step(b, grid, steps); }\n'
                    'extern "C" int list_steps(int count, int rows) { return als::list_steps(count, rows); }\n'
                    'extern "C" void walk_range(int b, int grid, int count, int *out) {\n'
@@ -25,6 +27,8 @@ def step_grid(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + CSRC, "-o", str(lib), str(src)])
     beside.f = ctypes.CDLL(str(lib)).beside
     beside.f.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p]
+    tile_grid.f = ctypes.CDLL(str(lib)).tiles
+    tile_grid.f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_void_p]
     walk_grid.f = ctypes.CDLL(str(lib)).walk
     walk_grid.f.argtypes, walk_grid.f.restype = [ctypes.c_int64] * 3, ctypes.c_uint
     xcd.f = ctypes.CDLL(str(lib)).xcd
@@ -43,6 +47,12 @@ def step_grid(tmp_path_factory):
 def beside(threads, cap, hint, other, per_cu=8, blind=1 << 20, cu=256):
     out = (ctypes.c_uint * 2)()
     beside.f(cu, threads, cap, hint, per_cu, blind, other, out)
+    return int(out[0]), int(out[1])
+
+
+def tile_grid(tiles, rows, lists, cu=256):
+    out = (ctypes.c_uint * 2)()
+    tile_grid.f(cu, tiles, rows, lists, out)
     return int(out[0]), int(out[1])
 
 
@@ -147,3 +157,16 @@ def test_a_walk_covers_its_list_once(step_grid, count):
             for w in {0, 1, stride - 1} & set(range(stride)):
                 assert walk_range(die + 8 * w, grid, count) == (first + w, stop, stride)
         assert end == steps
+
+
+@pytest.mark.parametrize("rows", [1, 31, 33, 256, 9000, 15_000, 32_000, 33_000, 300_000, 50_000_000, (1 << 31) - 1])
+@pytest.mark.parametrize("mean", [1, 12, 40])
+def test_the_pass_over_the_lists_gets_no_more_workgroups_than_rows_need(step_grid, rows, mean):
+    """Every list can hold all rows, or as many as the entries allow, but a row is in one of them only."""
+    caps = [min(rows, rows * mean // least + 1) for least in (1, 5, 9, 17, 33, 49, 65, 81, 97, 113)]
+    blocks, threads = tile_grid(sum(-(-c // 32) for c in caps), rows, len(caps))
+    waves = threads // 64
+    assert waves in (4, 8) and 1 <= blocks <= 512
+    assert blocks * waves < rows / 32 + len(caps) + waves  # one tile per list that is not full
+    assert blocks == 512 or blocks * waves >= -(-rows // 32)  # a tile a wavefront, or all that find a place at a time
+    assert waves == 8 or blocks <= 256
