@@ -92,6 +92,20 @@ template <int C> __device__ __forceinline__ float bcast16(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + C, 0xf, 0xf, true));
 }
 
+// Values across the rows of 16 lanes.  permlane16_swap(v, v) leaves rows 0 0 2 2 and 1 1 3 3, permlane32_swap(v, v) the lower half twice and
+// the upper half twice.
+template <int Q> __device__ __forceinline__ uint32_t from_lane_row(uint32_t v) {  // of the lane at this lane's place in row Q
+    const auto r16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const uint32_t w = r16[Q & 1];
+    const auto r32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return r32[Q >> 1];
+}
+template <int Q> __device__ __forceinline__ float from_lane_row(float v) { return __uint_as_float(from_lane_row<Q>(__float_as_uint(v))); }
+__device__ __forceinline__ float from_lower_half(float v) {
+    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r32[0]);
+}
+
 // One step of the eliminations: column c of the lane's row `s` (and of further rows of the same system, below it) is
 // eliminated; the columns beyond c of all rows but the pivot's are updated.  On return s[c] holds the multiplier of this
 // lane's row (zero in the pivot's), that of a row below the entry of L, and rinv the root of the reciprocal pivot in the pivot's lane.
@@ -267,6 +281,23 @@ __device__ __forceinline__ void store_rows(const floatx4 (&rv)[4][NV], float *R,
             }
             if (uq >= 0 && a < LPR) *(floatx4 *)(R + uq * ldr + 4 * NV * a + 4 * n) = r;
         }
+    }
+}
+
+// The same for one row, by all lanes of the wavefront.
+template <int LPR, int NV>
+__device__ __forceinline__ void store_row(const floatx4 (&rv)[NV], float *R, int lane) {
+    const floatx4 none = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+        floatx4 r = swap_add32(rv[n], none);
+        if constexpr (LPR <= 16) r = swap_add16(r, none);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if constexpr (LPR <= 8) r[c] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(r[c]), 0x128, 0xf, 0xf, true));  // row_ror:8
+            if constexpr (LPR <= 4) r[c] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(r[c]), 0x124, 0xf, 0xf, true));  // row_ror:4
+        }
+        if (lane < LPR) *(floatx4 *)(R + 4 * NV * lane + 4 * n) = r;
     }
 }
 

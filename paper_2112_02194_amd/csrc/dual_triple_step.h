@@ -5,6 +5,29 @@
 
 namespace als {
 
+// One step of the eliminations with the rows of a block column spread over the wavefront: the lanes below TOP (16 or 32) hold the rows of the
+// pivots' block, 16 lanes each, the others rows below it.  The operations on a row are those of eliminate_column.
+template <int c, int TOP>
+__device__ __forceinline__ void eliminate_shared(float (&s)[16], float &y, float &rinv, int lane, bool &bad) {
+    const float pivot = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s[c]), c));
+    const float uc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), c));
+    bad |= !(pivot > 0.f);
+    float ri = __builtin_amdgcn_rsqf(pivot);
+    ri = ri * (1.5f - 0.5f * pivot * ri * ri);  // one Newton step on the hardware estimate
+    float l = (TOP == 16 ? from_lane_row<0>(s[c]) : from_lower_half(s[c])) * ri;
+    const bool top = lane < TOP, pivots = (lane & 15) == c;
+    const float mine = s[c] * ri, own = top && pivots ? 0.f : mine, w = uc * ri;
+    rinv = pivots ? ri : rinv;
+    y -= own * w;
+    dpp_settle(l);  // just written, read through DPP below
+    static_for<c + 1, 16>([&](auto jj) {
+        constexpr int j = decltype(jj)::value;
+        fmac_bcast16_neg<j>(s[j], l, own);
+    });
+    s[c] = top ? own * ri : mine;
+    if constexpr (c + 1 < 16) dpp_settle(s[c + 1]);  // read across lanes by the next step
+}
+
 // Four rows per wavefront, one per group of 16 lanes, each with a 48 x 48 system S = I + Z_I Z_I^T in 16 x 16 tiles S_ij; the steps
 // of 16 < k <= 32 (dual_multi_step.h) with a block more:
 //   1. per row: the entries go through LDS into the operand layout (PieceGather) and the six tiles of the lower triangle are formed
@@ -16,8 +39,10 @@ namespace als {
 //   3. t of the last block, and backwards t_p = S_pp^-1 (y_p - sum S_ip^T t_i): columns of S_ip from LDS, t as a DPP operand, the
 //      row operations of S_pp once more;
 //   4. r = Z_I^T t, gathering the entries a second time, 16 bytes a lane.
-// R = 1: one row per wavefront, every group of 16 lanes with the same system: for the launch that small calls share, whose rows are too
-// few for more, with the same operations on a row in the same order.
+// R = 1: one row per wavefront, for the launch that small calls share, whose rows are too few for more, with the same operations on a row
+// in the same order: the rows of a block column are spread over the groups of 16 lanes, the last 16 x 16 system stands in all of them.
+// (With the same system in every group, the common launch of 15 000 rows of 40 entries took 67.4 us at d = 64, fp32, and 61.8 for bf16, now 61.6
+// and 57.6, of 9000 rows 45.8 and 40.0, now 42.9 and 37.6; with a triangle in LDS 63.7, 56.3, 43.6 and 38.0.)
 // What bounds it: the instructions of two wavefronts per SIMD (about 16 000 clocks a step of four rows at 64 columns, with 800 multiply-adds
 // with a DPP operand at half rate) and what they wait for memory in between; R = 1: the chain of 48 steps.
 // Against one row per wavefront and a triangle in LDS (tri_solve.h), per epoch: 10M pages, fp32, d = 128 5.15 -> 4.70 ms; 1M x 1M, fp32,
@@ -87,8 +112,10 @@ template <int D, bool ZB, int R> struct TripleStep {
         const int lane = opaque_tid();  // after the loads: what derives from it is not kept across them
         const int a = lane & 15, q = lane >> 4;                 // MFMA view: entry a of a tile, column group q
         const int g = R == 4 ? lane >> 4 : 0, i = lane & 15;    // solver view: system g, lane i of its group
-        float y0, y1, y2;  // labels of the entries i, 16 + i and 32 + i of this lane's system
-        {
+        float y0, y1 = 0.f, y2 = 0.f;  // labels of the entries i, 16 + i and 32 + i of this lane's system; R = 1: y0 of entry `lane`
+        if constexpr (R == 1) {
+            y0 = lane < k[0] ? (values ? values[d.b[0] + lane] : 1.f) : 0.f;
+        } else {
             int myk = 0;
             int64_t myb = 0;
 #pragma unroll
@@ -212,14 +239,28 @@ template <int D, bool ZB, int R> struct TripleStep {
         };
         float s0[16], s1[16], s2[16], ri0 = 1.f, ri1 = 1.f, ri2 = 1.f;
         bool bad = false;
-        load_tile_row(row_at + C::OFF_T, i, s0);
-        load_tile_row(row_at + C::OFF_10, i, s1);
-        load_tile_row(row_at + C::OFF_20, i, s2);
+        // R = 1: the rows of the first block column over the groups 0, 1 and 2, those of the second over the halves of the wavefront
+        float *one_at = lds + 16 * i;
+        if constexpr (R == 1) load_tile_row(one_at + (q == 3 ? 0 : q) * C::AREA, i, s0);  // S_00, S_10, S_20
+        else {
+            load_tile_row(row_at + C::OFF_T, i, s0);
+            load_tile_row(row_at + C::OFF_10, i, s1);
+            load_tile_row(row_at + C::OFF_20, i, s2);
+        }
         dpp_settle(s0[0]);
-        static_for<0, 16>([&](auto ci) { eliminate_column<decltype(ci)::value>(s0, y0, ri0, i, bad, RowBelow{s1, y1}, RowBelow{s2, y2}); });
+        static_for<0, 16>([&](auto ci) {
+            if constexpr (R == 1) eliminate_shared<decltype(ci)::value, 16>(s0, y0, ri0, lane, bad);
+            else eliminate_column<decltype(ci)::value>(s0, y0, ri0, i, bad, RowBelow{s1, y1}, RowBelow{s2, y2});
+        });
         wave_sync();  // every lane has read its rows
-        put_row(C::OFF_T, s1);
-        put_row(C::OFF_21, s2);
+        if constexpr (R == 1) {
+            if (q == 1 || q == 2) put_row(q == 1 ? C::OFF_T : C::OFF_21, s0);
+            y1 = from_lane_row<1>(y0);
+            y2 = from_lane_row<2>(y0);
+        } else {
+            put_row(C::OFF_T, s1);
+            put_row(C::OFF_21, s2);
+        }
         wave_sync();
 #pragma unroll
         for (int p = 0; p < R; ++p) {
@@ -236,12 +277,25 @@ template <int D, bool ZB, int R> struct TripleStep {
         put_tiles(C::OFF_T, c11);
         put_tiles(C::OFF_21, c21);
         wave_sync();
-        load_tile_row(row_at + C::OFF_T, i, s1);
-        load_tile_row(row_at + C::OFF_21, i, s2);
+        if constexpr (R == 1) {
+            load_tile_row(one_at + (q < 2 ? C::OFF_T : C::OFF_21), i, s1);
+            y1 = q < 2 ? y1 : y2;
+        } else {
+            load_tile_row(row_at + C::OFF_T, i, s1);
+            load_tile_row(row_at + C::OFF_21, i, s2);
+        }
         dpp_settle(s1[0]);
-        static_for<0, 16>([&](auto ci) { eliminate_column<decltype(ci)::value>(s1, y1, ri1, i, bad, RowBelow{s2, y2}); });
+        static_for<0, 16>([&](auto ci) {
+            if constexpr (R == 1) eliminate_shared<decltype(ci)::value, 32>(s1, y1, ri1, lane, bad);
+            else eliminate_column<decltype(ci)::value>(s1, y1, ri1, i, bad, RowBelow{s2, y2});
+        });
         wave_sync();
-        put_row(C::OFF_T, s2);
+        if constexpr (R == 1) {
+            if (q == 2) put_row(C::OFF_T, s1);
+            y2 = from_lane_row<2>(y1);
+        } else {
+            put_row(C::OFF_T, s2);
+        }
         wave_sync();
 #pragma unroll
         for (int p = 0; p < R; ++p) {
@@ -298,17 +352,19 @@ template <int D, bool ZB, int R> struct TripleStep {
         const float t0 = (y0 - za) * ri0 * ri0;
         wave_sync();  // every lane has read its row of S_22
         float *tbuf = lds + C::OFF_T;
-        tbuf[g * C::KS + i] = t0;
-        tbuf[g * C::KS + 16 + i] = t1;
-        tbuf[g * C::KS + 32 + i] = t2;
-        tbuf[g * C::KS + 48 + i] = 0.f;
+        if (R == 4 || q == 0) {  // R = 1: t0 is that of the first group, which holds the rows of S_00
+            tbuf[g * C::KS + i] = t0;
+            tbuf[g * C::KS + 16 + i] = t1;
+            tbuf[g * C::KS + 32 + i] = t2;
+            tbuf[g * C::KS + 48 + i] = 0.f;
+        }
         wave_sync();
 
         // ---- 4. r = Z_I^T t
         static_for<R == 4 ? 1 : 0, BUFS>(again);
-        floatx4 rv[4][NV];
+        floatx4 rv[R][NV];
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
+        for (int p = 0; p < R; ++p)
 #pragma unroll
             for (int n = 0; n < NV; ++n) rv[p][n] = floatx4{0.f, 0.f, 0.f, 0.f};
         static_for<0, ROUNDS>([&](auto rr) {
@@ -334,7 +390,8 @@ template <int D, bool ZB, int R> struct TripleStep {
             if constexpr (r + BUFS < ROUNDS) again(std::integral_constant<int, r + BUFS>{});
         });
         last();
-        out.template store<LPR>(rv, lane);
+        if constexpr (R == 1) out.template store_one<LPR>(rv[0], lane);
+        else out.template store<LPR>(rv, lane);
     }
 };
 

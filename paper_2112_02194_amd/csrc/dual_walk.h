@@ -66,6 +66,9 @@ struct RowsOut {
         const int64_t u[4] = {row.rel[0], row.rel[1], row.rel[2], row.rel[3]};
         store_rows<LPR>(rv, R, ldr, u, lane);
     }
+    template <int LPR, int NV> __device__ __forceinline__ void store_one(const floatx4 (&rv)[NV], int lane) const {
+        store_row<LPR>(rv, R + row.rel[0] * ldr, lane);
+    }
 };
 
 // Rows of up to four steps kept in LDS until x_rows_from_memory takes sixteen of them at a time: X = R L^-1 for bf16 tables.  Three

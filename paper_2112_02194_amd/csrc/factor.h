@@ -44,14 +44,6 @@ template <int C> __device__ __forceinline__ double bcast16_f64(double v) {
     return from_words(__builtin_amdgcn_update_dpp(0, (int)low_word(v), 0x150 + C, 0xf, 0xf, true),
                       __builtin_amdgcn_update_dpp(0, (int)high_word(v), 0x150 + C, 0xf, 0xf, true));
 }
-// value of the lane at this lane's place in row Q of the four rows of 16 lanes.  permlane16_swap(v, v) leaves rows 0 0 2 2 and
-// 1 1 3 3, permlane32_swap(v, v) the lower half twice and the upper half twice.
-template <int Q> __device__ __forceinline__ uint32_t from_lane_row(uint32_t v) {
-    const auto r16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    const uint32_t w = r16[Q & 1];
-    const auto r32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-    return r32[Q >> 1];
-}
 template <int Q> __device__ __forceinline__ double from_lane_row_f64(double v) {
     return from_words(from_lane_row<Q>(low_word(v)), from_lane_row<Q>(high_word(v)));
 }

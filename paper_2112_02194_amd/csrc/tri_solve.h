@@ -242,14 +242,6 @@ __device__ __forceinline__ float sum_lane_row(float v) {
     v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, true));
     return v;
 }
-// Value of the lane at this lane's place in row Q of the four rows of 16 lanes: permlane16_swap(v, v) leaves rows 0 0 2 2 and
-// 1 1 3 3, permlane32_swap(v, v) the lower half twice and the upper half twice.
-template <int Q> __device__ __forceinline__ float from_lane_row(float v) {
-    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    const uint32_t w = r16[Q & 1];
-    const auto r32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-    return __uint_as_float(r32[Q >> 1]);
-}
 
 // The same for one or two panels, S = M P M^T by blocks.  Lane (i, q) = (lane % 16, lane / 16).  Per panel p:
 //   1. the 16 x 16 diagonal block is eliminated in registers, in place: lane (i, q) holds the entries (i, 4 q + s), and a

@@ -757,3 +757,43 @@ def test_rows_that_leave_their_kernel_as_solutions(ctx, gpu_device, d, dtype, ro
     als.als_status_sync(ctx)
     assert torch.equal(own[:few, :d], common[:few]) and (own[:, d:] == 7).all()
     assert not own[few:, :d].any() and (common[few:] == 7).all() and torch.isfinite(common[:few]).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("alpha", [0.1, 1e-4])
+def test_rows_of_33_to_48_entries_one_and_four_per_wavefront(ctx, gpu_device, d, dtype, alpha):
+    """20 000 rows take the launch of four rows per wavefront, a few of them the launch that small calls share, where each has a wavefront:
+    the same bits for every length, entries that repeat and labels of both signs and zero.  Tolerance as for rows of 9 to 32 entries."""
+    say(f"rows of 33 to 48 entries d={d} {dtype} alpha={alpha}")
+    rows, n, lam = 20_000, 900, 1e-2
+    gen = torch.Generator(device=gpu_device).manual_seed(d)
+    lens = 33 + torch.randint(0, 16, (rows,), device=gpu_device, generator=gen)
+    lens[:16] = 33 + torch.arange(16, device=gpu_device)
+    indptr = torch.zeros(rows + 1, dtype=torch.int64, device=gpu_device)
+    indptr[1:] = torch.cumsum(lens, 0)
+    idx = torch.randint(0, n, (int(indptr[-1]),), device=gpu_device, generator=gen).to(torch.int32)
+    idx[int(indptr[20]) + 3:int(indptr[21])] = idx[int(indptr[20])]
+    val = torch.randn(len(idx), device=gpu_device, generator=gen)
+    val[int(indptr[5]):int(indptr[6])] = 0
+    Y = als.Csr(rows, n, indptr, idx, val)
+    H = (torch.randn((n, d), device=gpu_device, generator=gen) * 0.3 / np.sqrt(d)).to(dtype)
+    G, prm = als.als_gramian(ctx, H), als.make_params(alpha, lam)
+    whole, parts = (torch.full((rows, d), 7.0, device=gpu_device, dtype=dtype) for _ in range(2))
+    als.als_solve_rows(ctx, Y, H, G, prm, whole)
+    for r0, r1 in ((0, 1), (1, 4), (4, 40), (40, 1500)):
+        als.als_solve_rows(ctx, Y, H, G, prm, parts, r0, r1)
+    als.als_status_sync(ctx)
+    assert torch.equal(whole[:1500], parts[:1500]) and (parts[1500:] == 7).all()
+    bf16, h = dtype == torch.bfloat16, f64(H)
+    L = np.linalg.cholesky(alpha * f64(G) + lam * np.eye(d))
+    Z = np.linalg.solve(L, h.T).T
+    if bf16:
+        Z = f64(torch.tensor(Z).to(torch.bfloat16))
+    unit = 2.0 ** -13 if bf16 else 2.0 ** -16
+    for r in list(range(24)) + [1499, 9999, rows - 1]:
+        at = slice(int(indptr[r]), int(indptr[r + 1]))
+        z, y = Z[idx[at].cpu().numpy()], f64(val[at])
+        ref = np.linalg.solve(L.T, z.T @ np.linalg.solve(np.eye(len(z)) + z @ z.T, y))
+        bound = (2.0 ** -8 if bf16 else 0.0) + (1 if bf16 else 4) * unit * (1 + len(z) * np.max(np.sum(z * z, axis=1)))
+        assert bound < 0.5 and np.linalg.norm(f64(whole[r]) - ref) <= bound * np.linalg.norm(ref), (r, len(z), bound)
