@@ -15,10 +15,13 @@ constexpr int FEW_ROWS[10] = {4, 4, 1, 1, 1, 1, 1, 1, 16, 8};
 constexpr int64_t FEW_STEPS = 1 << 17;
 
 // Rows of 33 to 48 entries (d >= 64) that an earlier call saw, or that there can be, from which on they have the launch that takes
-// four of them per wavefront, the same operations on each.  Calls with rows of 40 entries only, in the common launch / their own, us:
-// d = 64 2500 rows 69 / 76, 5000 88 / 86, 40 000 231 / 207 (bf16: 2500 63 / 67, 30 000 172 / 140); d = 128 2500 rows 129 / 129, 5000 179 / 167
-// (bf16: 2500 106 / 100, 5000 134 / 117).
-constexpr int64_t few_triple_rows(int d) { return d == 64 ? 16384 : 4096; }
+// four of them per wavefront, the same operations on each.  In the common launch / their own, us a call; rows of 40 entries:
+//   d = 64, fp32   8000 87 / 84, 10 000 106 / 105, 13 000 117 / 119, 16 000 128 / 124, 20 000 142 / 147, 30 000 176 / 177: no clear line
+//   d = 64, bf16   4000 59 / 65, 6000 67 / 66, 8000 74 / 69, 16 000 114 / 101
+//   d = 128, fp32  3000 122 / 123, 4000 140 / 136, 8000 198 / 174       d = 128, bf16  2000 83 / 82, 3000 97 / 91, 6000 130 / 110
+// and among others (rows of 20 to 60 entries, 39 in 100 of them in the class): d = 64, bf16 5900 112 / 115, 7800 128 / 125, fp32 5900
+// 132 / 136, 11 700 189 / 194; d = 128, fp32 3100 198 / 199, 3900 234 / 230, bf16 1600 108 / 113, 2300 126 / 126, 3100 145 / 138.
+constexpr int64_t few_triple_rows(int d, bool zb16) { return d == 64 ? (zb16 ? 6144 : 16384) : (zb16 ? 2304 : 3584); }
 
 struct FewLists {
     const int32_t *list[10], *count[10];
