@@ -10,9 +10,9 @@ namespace als {
 
 // One wavefront per row with k <= K = 16*KT entries (KT = 3..8).
 //   1. S = I + Z_I Z_I^T tile by tile, into a lower triangle in LDS.  The first wide_tiles() tiles of sixteen entries are
-//      loaded together and stay in registers as operands; tiles beyond them (fp32, k > 64) are loaded whenever they are
-//      needed, from the caches mostly.  Where wide_staged(), side-by-side lanes load side-by-side pieces of a row
-//      (PieceGather, dual_common.h), and the tiles go through the triangle's place in LDS into the operand layout.
+//      loaded together and stay in registers as operands; the last one (fp32, k > 80) is loaded when it is needed.  Where
+//      wide_staged(), side-by-side lanes load side-by-side pieces of a row (PieceGather, dual_common.h), and the tiles go
+//      through the triangle's place in LDS into the operand layout.
 //   2./3. Block elimination S = M P M^T and back-substitution by the wavefront (tri_solve.h).
 //   4. r = Z_I^T t: with bf16 Z from the tiles still in registers, on the matrix cores (zt_times_t,
 //      dual_common.h: bf16 entries are exact operands); with fp32 Z with four adjacent output columns per lane,
@@ -20,8 +20,10 @@ namespace als {
 //      enough for S = I + Z Z^T but would show in r).
 template <int D, int KT, bool ZB> constexpr bool wide_resident() { return ZB; }
 
-// tiles that stay in registers
-template <int KT, bool ZB> constexpr int wide_tiles() { return ZB || KT < 5 || KT > 6 ? KT : 5; }
+// Tiles that stay in registers.  fp32, d = 128: a tile takes 32 registers as loaded and 32 as operands.  From KT = 6 on the last tile, which is
+// needed last, is loaded then; among the first it left the compiler no registers, which then waited for its eight loads one by
+// one (200 000 rows of 100 / 120 entries 5.23 / 6.72 ms, as it is 4.86 / 5.91; another tile fewer 4.86 / 6.12; with four resident 6.00 / 7.36).
+template <int KT, bool ZB> constexpr int wide_tiles() { return ZB || KT < 6 ? KT : KT - 1; }
 // Long rows of Z only.  10M pages with host locality (d = 128, fp32), KT = 3 .. 8, ms per epoch, straight into the operand
 // layout / staged: 5.66 / 5.48, 4.25 / 4.07, 2.98 / 2.91, 2.35 / 2.12, 1.93 / 1.86, 1.24 / 1.16; shorter rows lose: 1M x 1M
 // (d = 64) 1.22 / 1.26, 300k bf16 rows (d = 128, KT = 3) 76 / 81 us.
@@ -216,8 +218,8 @@ __device__ __forceinline__ void dual_wide_step(const int64_t *__restrict__ indpt
         else R[u * ldr + lane] = rbuf[lane];
     } else {
         // 16 bytes of an entry per lane, GatherCols<D>::EPI entries per instruction, four entries per lane and round, the loads of
-        // four rounds under way together (10M pages, d = 128, KT = 4 .. 8: a round at a time 3.71, 2.63, 1.89, 1.65, 1.00 ms; so, and with all tiles resident
-        // from KT = 7 on, where a wavefront has its SIMD to itself anyway, 3.59, 2.50, 1.73, 1.39, 0.94)
+        // four rounds under way together (10M pages, d = 128, KT = 4 .. 8: a round at a time 3.71, 2.63, 1.89, 1.65, 1.00 ms; so 3.63,
+        // 2.52, 1.75, 1.30, 0.80, the last two with more tiles resident too, see wide_tiles)
         using GC = GatherCols<D>;
         constexpr int ROUND = 4 * GC::EPI, AHEAD = K / ROUND < 4 ? K / ROUND : 4;
         const int mine = 4 * (lane / GC::LPR);
