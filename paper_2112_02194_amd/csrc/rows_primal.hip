@@ -687,21 +687,29 @@ __device__ __forceinline__ bool reduce_solve_step(const LongRow lr, const float 
     return true;
 }
 
-// Long rows in strides of the grid (the walk costs eight registers here; a launch of its own for the rows that no hint announced
-// was one more that mostly found nothing).
-template <int D, bool BF16>
+// The two launch forms (see StepGrid): LOOP = false, long row first + blockIdx.x if there is one; LOOP = true, from `first` on in strides of
+// the grid.  The direct solver takes the walk for all rows (it costs eight registers there; a launch of its own for the rows that no hint
+// announced was one more that mostly found nothing), conjugate gradients both: their loop takes longer in the walk (15 000 rows of 700
+// entries, bf16, the kernel in one form / in two: d = 64 383 / 370 us, d = 128 2.79 / 2.72 ms).
+template <int D, bool BF16, bool LOOP>
 __global__ __launch_bounds__(Team<D>::THREADS) void reduce_solve_kernel(
     const LongRow *__restrict__ long_rows, const float *__restrict__ partials, const float *__restrict__ G,
-    float alpha, float lambda, void *__restrict__ X, int64_t ldx, const int32_t *__restrict__ n_long_ptr,
+    float alpha, float lambda, void *__restrict__ X, int64_t ldx, const int32_t *__restrict__ n_long_ptr, int first,
     int32_t *__restrict__ err_flag, int solver, int cg_iters, float cg_tol) {
     extern __shared__ float lds[];
     const int n_long = *n_long_ptr;
-    for (int row = blockIdx.x; row < n_long; row += gridDim.x) {
-        const bool last = row + (int)gridDim.x >= n_long;
-        if (!reduce_solve_step<D, BF16>(long_rows[row], opaque(partials), opaque(G), opaque(alpha), opaque(lambda),
-                                        opaque(X), opaque(ldx), opaque(err_flag), opaque(solver), opaque(cg_iters),
-                                        opaque(cg_tol), last, opaque(lds)))
-            return;
+    int row = first + (int)blockIdx.x;
+    if constexpr (!LOOP) {
+        if (row < n_long)
+            reduce_solve_step<D, BF16>(long_rows[row], partials, G, alpha, lambda, X, ldx, err_flag, solver, cg_iters, cg_tol, true, lds);
+    } else {
+        for (; row < n_long; row += gridDim.x) {
+            const bool last = row + (int)gridDim.x >= n_long;
+            if (!reduce_solve_step<D, BF16>(long_rows[row], opaque(partials), opaque(G), opaque(alpha), opaque(lambda),
+                                            opaque(X), opaque(ldx), opaque(err_flag), opaque(solver), opaque(cg_iters),
+                                            opaque(cg_tol), last, opaque(lds)))
+                return;
+        }
     }
 }
 
@@ -772,10 +780,20 @@ static als_status primal_typed(als_ctx *ctx, const als_csr *Y, const als_table *
         const unsigned red_blocks = std::max(1u, g_long.known + g_long.rest);  // grid-stride over the long rows
         if constexpr (!sums_segments<D>())
             hipLaunchKernelGGL(reduce_partials_kernel<D>, dim3(red_blocks, (D * D + D + 255) / 256), dim3(256), 0, s, long_rows, partials, counters);
-        auto kred = reduce_solve_kernel<D, BF16>;
+        auto kred = reduce_solve_kernel<D, BF16, false>, kred_loop = reduce_solve_kernel<D, BF16, true>;
         ALS_LDS(kred)
-        hipLaunchKernelGGL(kred, dim3(red_blocks), dim3(T), solve_lds, s, long_rows, (const float *)partials, G, prm->alpha, prm->lambda, X->data,
-                           X->ld, counters, err, prm->solver, cg_iters, cg_tol);
+        ALS_LDS(kred_loop)
+        auto reduce = [&](auto kern, unsigned blocks, unsigned first) {
+            if (blocks > 0)
+                hipLaunchKernelGGL(kern, dim3(blocks), dim3(T), solve_lds, s, long_rows, (const float *)partials, G, prm->alpha, prm->lambda, X->data,
+                                   X->ld, counters, (int)first, err, prm->solver, cg_iters, cg_tol);
+        };
+        if (prm->solver == ALS_SOLVER_DIRECT) {
+            reduce(kred_loop, red_blocks, 0);
+        } else {
+            reduce(kred, g_long.known, 0);
+            reduce(kred_loop, g_long.rest, g_long.known);
+        }
         timer_end(ctx, s);
     }
 #undef ALS_LDS

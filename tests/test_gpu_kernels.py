@@ -337,6 +337,19 @@ def test_primal_rows_beyond_a_launch_hint_that_is_too_small(gpu_device, d, dtype
         _stale_hint_case(d, dtype, first, second, 3000, als.make_params(0.1, 1e-2, path=als.PATH_PRIMAL, split_nnz=8), gpu_device)
 
 
+@pytest.mark.parametrize("d,dtype", [(16, torch.float32), (32, torch.bfloat16), (64, torch.float32), (128, torch.bfloat16)])
+def test_long_rows_under_conjugate_gradients_beyond_a_launch_hint_that_is_too_small(gpu_device, d, dtype):
+    """Long rows have two launches under this solver: 1024 workgroups walk the 5120 rows that a hint left out; without a hint each has a
+    workgroup.  Bit for bit the same."""
+    say(f"hint too small: long rows, conjugate gradients d={d} {dtype}")
+    rows = 6400
+    first = torch.full((rows,), 8)
+    second = torch.zeros(rows, dtype=torch.int64)
+    second[:5120] = 9 + torch.arange(5120) % 3
+    second[0] += 8 * rows - int(second.sum())
+    _stale_hint_case(d, dtype, first, second, 3000, als.make_params(0.1, 1e-2, path=als.PATH_PRIMAL, split_nnz=8, solver=als.SOLVER_CG), gpu_device)
+
+
 @pytest.mark.parametrize("d,dtype", [(16, torch.float32), (32, torch.float32), (32, torch.bfloat16), (64, torch.float32),
                                      (128, torch.float32), (128, torch.bfloat16)])
 def test_dual_rows_beyond_a_launch_hint_that_is_too_small(gpu_device, d, dtype):
