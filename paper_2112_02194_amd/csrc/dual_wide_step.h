@@ -219,9 +219,10 @@ __device__ __forceinline__ void dual_wide_step(const int64_t *__restrict__ indpt
     } else {
         // 16 bytes of an entry per lane, GatherCols<D>::EPI entries per instruction, four entries per lane and round, the loads of
         // four rounds under way together (10M pages, d = 128, KT = 4 .. 8: a round at a time 3.71, 2.63, 1.89, 1.65, 1.00 ms; so 3.63,
-        // 2.52, 1.75, 1.30, 0.80, the last two with more tiles resident too, see wide_tiles)
+        // 2.52, 1.75, 1.30, 0.80, the last two with more tiles resident too, see wide_tiles).  Not where conjugate gradients bring rows of up
+        // to 48 entries: 60 000 rows of 25 / of 33 to 48 281 / 402 us a round at a time, 296 / 417 with four.
         using GC = GatherCols<D>;
-        constexpr int ROUND = 4 * GC::EPI, AHEAD = K / ROUND < 4 ? K / ROUND : 4;
+        constexpr int ROUND = 4 * GC::EPI, AHEAD = CG && KT == 3 ? 1 : (K / ROUND < 4 ? K / ROUND : 4);
         const int mine = 4 * (lane / GC::LPR);
         const float *col = (const float *)Z + 4 * (lane % GC::LPR);
         floatx4 rv = floatx4{0.f, 0.f, 0.f, 0.f};
