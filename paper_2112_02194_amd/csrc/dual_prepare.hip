@@ -466,7 +466,7 @@ static als_status dual_rows_typed(als_ctx *ctx, const als_csr *Y, als_table *X, 
                            prm->cg_tol > 0.f ? prm->cg_tol : 1e-6f};
     FewLists few;
     int64_t steps = 0, listed = 0;  // all, and those in the common launch
-    const bool own_triple = D >= 64 && !ws.cg && (hints[2] < 0 ? caps[2] : hints[2]) >= few_triple_rows(D, zb16);
+    const bool own_triple = D >= 64 && !ws.cg && hints[2] >= few_triple_rows(D, zb16);
     for (int c = 0; c < 10; ++c) {
         few.list[c] = lists[c];
         few.count[c] = counts_dev[c];

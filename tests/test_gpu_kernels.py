@@ -776,8 +776,9 @@ def test_rows_that_leave_their_kernel_as_solutions(ctx, gpu_device, d, dtype, ro
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("alpha", [0.1, 1e-4])
 def test_rows_of_33_to_48_entries_one_and_four_per_wavefront(ctx, gpu_device, d, dtype, alpha):
-    """20 000 rows take the launch of four rows per wavefront, a few of them the launch that small calls share, where each has a wavefront:
-    the same bits for every length, entries that repeat and labels of both signs and zero.  Tolerance as for rows of 9 to 32 entries."""
+    """20 000 rows take the launch of four rows per wavefront once a call has seen them, and before that, like a few of them, the launch that
+    small calls share, where each has a wavefront: the same bits for every length, entries that repeat and labels of both signs and
+    zero.  Tolerance as for rows of 9 to 32 entries."""
     say(f"rows of 33 to 48 entries d={d} {dtype} alpha={alpha}")
     rows, n, lam = 20_000, 900, 1e-2
     gen = torch.Generator(device=gpu_device).manual_seed(d)
@@ -792,12 +793,18 @@ def test_rows_of_33_to_48_entries_one_and_four_per_wavefront(ctx, gpu_device, d,
     Y = als.Csr(rows, n, indptr, idx, val)
     H = (torch.randn((n, d), device=gpu_device, generator=gen) * 0.3 / np.sqrt(d)).to(dtype)
     G, prm = als.als_gramian(ctx, H), als.make_params(alpha, lam)
-    whole, parts = (torch.full((rows, d), 7.0, device=gpu_device, dtype=dtype) for _ in range(2))
+    first, whole, parts = (torch.full((rows, d), 7.0, device=gpu_device, dtype=dtype) for _ in range(3))
+    als.als_solve_rows(ctx, Y, H, G, prm, first)
+    als.als_status_sync(ctx)
+    als.als_set_timing(ctx, True)
     als.als_solve_rows(ctx, Y, H, G, prm, whole)
+    launches = als.als_get_timing(ctx)["launches"]
+    als.als_set_timing(ctx, False)
+    assert launches["dual_k48"] == 1 and launches["dual_k16"] == 1, launches  # the class, and the common launch for what else there is
     for r0, r1 in ((0, 1), (1, 4), (4, 40), (40, 1500)):
         als.als_solve_rows(ctx, Y, H, G, prm, parts, r0, r1)
     als.als_status_sync(ctx)
-    assert torch.equal(whole[:1500], parts[:1500]) and (parts[1500:] == 7).all()
+    assert torch.equal(first, whole) and torch.equal(whole[:1500], parts[:1500]) and (parts[1500:] == 7).all()
     bf16, h = dtype == torch.bfloat16, f64(H)
     L = np.linalg.cholesky(alpha * f64(G) + lam * np.eye(d))
     Z = np.linalg.solve(L, h.T).T
