@@ -16,6 +16,15 @@ def ctx(gpu_device):
     c.close()
 
 
+def _launches(ctx, call):
+    """`call`, and the timed launches of every kernel slot in it."""
+    als.als_set_timing(ctx, True)
+    call()
+    launches = als.als_get_timing(ctx)["launches"]
+    als.als_set_timing(ctx, False)
+    return launches
+
+
 @pytest.mark.parametrize("d", [16, 32, 64, 128])
 def test_shared_factor_against_the_closed_form_of_one_entry_rows(ctx, gpu_device, d):
     """1, 2, 4 and 8 blocks of 16 columns.  A row with the single entry v solves to B^-1 v / (1 + v^T B^-1 v)
@@ -560,17 +569,17 @@ def test_rows_are_sorted_alike_on_both_sides_of_a_line(ctx, gpu_device, d, dtype
 @pytest.mark.parametrize("walked", [False, True])
 def test_places_past_the_end_of_a_list_raise_no_flag(ctx, gpu_device, d, dtype, walked):
     """alpha = 0 and a tiny lambda: |z|^2 about 1e9, where a system of one entry repeated is singular in fp32.  Rows of 9 to 16 and
-    of 17 and 18 distinct entries are regular; lists of every length modulo four, by the launch that small calls share and (300 000
-    empty rows more) by the launches of their own.  fp32 rows are compared too: S is off by 2^-16 of its trace at most."""
+    of 17 and 18 distinct entries are regular; lists of every length modulo four, by the launch that small calls share and (24 000 rows
+    of 17 and 400 000 empty ones: the lists' capacities follow entries and rows) by the launches of their own.  fp32 rows are compared too: S is off by 2^-16 of its trace at most."""
     say(f"past the end of a list d={d} {dtype} walked={walked}")
     gen = torch.Generator().manual_seed(d)
     n, lam = 4000, 1e-10
     H = (torch.randn((n, d), generator=gen) * 0.3 / np.sqrt(d)).to(dtype)
     G = torch.zeros((d, d), device=gpu_device)
-    some = 17_000 if walked else 4
+    some = 24_000 if walked else 4
     for more in range(4):
         lens = torch.cat([torch.full((some + more,), 17), torch.tensor([18]), torch.full((1 + more,), 9 + 2 * more),
-                          torch.zeros(300_000 if walked else 0, dtype=torch.int64)])
+                          torch.zeros(400_000 if walked else 0, dtype=torch.int64)])
         ptr = torch.zeros(len(lens) + 1, dtype=torch.int64)
         ptr[1:] = torch.cumsum(lens, 0)
         nnz = int(ptr[-1])
@@ -578,10 +587,11 @@ def test_places_past_the_end_of_a_list_raise_no_flag(ctx, gpu_device, d, dtype, 
         idx = (start + torch.arange(nnz) - torch.repeat_interleave(ptr[:-1], lens)).to(torch.int32)  # distinct in a row
         X = torch.empty((len(lens), d), device=gpu_device, dtype=dtype)
         Y = als.Csr(len(lens), n, ptr.to(gpu_device), idx.to(gpu_device))
-        als.als_solve_rows(ctx, Y, H.to(gpu_device), G, als.make_params(0.0, lam), X)
+        ran = _launches(ctx, lambda: als.als_solve_rows(ctx, Y, H.to(gpu_device), G, als.make_params(0.0, lam), X))
+        assert ran["dual_k16"] == 1 and ran["dual_k32"] == walked, ran
         als.als_status_sync(ctx)
-        got = f64(X)
-        assert np.isfinite(got).all()
+        assert torch.isfinite(X).all()
+        got = f64(X[:some + 20])
         if dtype == torch.float32:
             for r in range(some, some + 2 * more + 2):
                 v = f64(H)[idx[ptr[r]:ptr[r + 1]].numpy()]
@@ -750,11 +760,13 @@ def test_rows_of_tables_with_a_stride(ctx, gpu_device, d, dtype):
 @pytest.mark.parametrize("rows", [1, 4, 5, 15, 16, 17, 35])
 def test_rows_that_leave_their_kernel_as_solutions(ctx, gpu_device, d, dtype, rows):
     """Launches of their own take X = R L^-1 along, sixteen rows at a time: `rows` rows of each class, which do not fill the last sixteen,
-    in a strided table, against the launch that small calls share and its pass over the lists, bit for bit."""
+    in a strided table, against the launch that small calls share and its pass over the lists, bit for bit.  320 000 rows too long for the
+    dual form, or empty, bring the lists' capacities, which follow rows and entries, beyond the 2^17 steps of the common launch."""
     say(f"solved in their kernel d={d} {dtype} rows={rows}")
     gen = torch.Generator(device=gpu_device).manual_seed(rows)
     n, few = 700, rows * 5
-    lens = torch.cat([torch.full((rows,), k) for k in (2, 7, 13, min(d, 25), min(d, 45))] + [torch.zeros(320_000, dtype=torch.int64)])
+    lens = torch.cat([torch.full((rows,), k) for k in (2, 7, 13, min(d, 25), min(d, 45))]
+                     + [torch.full((4000,), 500), torch.zeros(316_000, dtype=torch.int64)])
     lens = lens.to(gpu_device)
     indptr = torch.zeros(len(lens) + 1, dtype=torch.int64, device=gpu_device)
     indptr[1:] = torch.cumsum(lens, 0)
@@ -765,11 +777,17 @@ def test_rows_that_leave_their_kernel_as_solutions(ctx, gpu_device, d, dtype, ro
     G, prm = als.als_gramian(ctx, H), als.make_params(0.1, 1e-2)
     own = torch.full((len(lens), d + 16), 7.0, device=gpu_device, dtype=dtype)
     common = torch.full((len(lens), d), 7.0, device=gpu_device, dtype=dtype)
-    als.als_solve_rows(ctx, Y, H, G, prm, own[:, :d])
-    als.als_solve_rows(ctx, Y, H, G, prm, common, 0, few)
+    for _ in range(2):  # without and with a hint
+        ran = _launches(ctx, lambda: als.als_solve_rows(ctx, Y, H, G, prm, own[:, :d]))
+        assert all(ran[name] == 1 for name in ["dual_k4", "dual_k8", "dual_k16", "dual_k32"] + ["dual_k48"] * (d >= 64)), ran
+        als.als_status_sync(ctx)
+    # (the rows in a matrix of their own: of the large one the entries would bring the capacities along)
+    small = als.Csr(few, n, indptr[:few + 1].clone(), Y.indices[:int(indptr[few])].clone(), Y.values[:int(indptr[few])].clone())
+    ran = _launches(ctx, lambda: als.als_solve_rows(ctx, small, H, G, prm, common[:few]))
+    assert ran["dual_k16"] == 1 and ran["dual_k4"] == ran["dual_k8"] == ran["dual_k32"] == ran["dual_k48"] == 0, ran
     als.als_status_sync(ctx)
     assert torch.equal(own[:few, :d], common[:few]) and (own[:, d:] == 7).all()
-    assert not own[few:, :d].any() and (common[few:] == 7).all() and torch.isfinite(common[:few]).all()
+    assert not own[few + 4000:, :d].any() and torch.isfinite(own.float()).all() and not (own[:few + 4000, :d] == 7).all(dim=1).any()
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -796,11 +814,8 @@ def test_rows_of_33_to_48_entries_one_and_four_per_wavefront(ctx, gpu_device, d,
     first, whole, parts = (torch.full((rows, d), 7.0, device=gpu_device, dtype=dtype) for _ in range(3))
     als.als_solve_rows(ctx, Y, H, G, prm, first)
     als.als_status_sync(ctx)
-    als.als_set_timing(ctx, True)
-    als.als_solve_rows(ctx, Y, H, G, prm, whole)
-    launches = als.als_get_timing(ctx)["launches"]
-    als.als_set_timing(ctx, False)
-    assert launches["dual_k48"] == 1 and launches["dual_k16"] == 1, launches  # the class, and the common launch for what else there is
+    ran = _launches(ctx, lambda: als.als_solve_rows(ctx, Y, H, G, prm, whole))
+    assert ran["dual_k48"] == 1 and ran["dual_k16"] == 1, ran  # the class, and the common launch for what else there is
     for r0, r1 in ((0, 1), (1, 4), (4, 40), (40, 1500)):
         als.als_solve_rows(ctx, Y, H, G, prm, parts, r0, r1)
     als.als_status_sync(ctx)

@@ -18,6 +18,7 @@ def step_grid(tmp_path_factory):
                    'extern "C" void beside(int cu, int threads, int64_t cap, int64_t hint, int per_cu, int64_t blind, int64_t other, unsigned *out) {\n'
                    '    const als::StepGrid g = als::step_grid(cu, threads, cap, hint, per_cu, blind, other); out[0] = g.known; out[1] = g.rest; }\n'
                    'extern "C" unsigned walk(int64_t resident, int64_t cap, int64_t hint) { return als::walk_grid(resident, cap, hint); }\n'
+                   'extern "C" unsigned walk_blocks(int64_t resident, int64_t cap, int64_t hint) { return als::walk_blocks(resident, cap, hint); }\n'
                    'extern "C" void tiles(int cu, int64_t tiles, int64_t rows, int lists, unsigned *out) {\n'
                    '    const als::TileGrid g = als::tile_grid(cu, tiles, rows, lists); out[0] = g.blocks; out[1] = g.threads; }\n'
                    'extern "C" int xcd(int b, int grid, int steps) { return als::xcd_step(b, grid, steps); }\n'
@@ -31,6 +32,8 @@ def step_grid(tmp_path_factory):
     tile_grid.f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_void_p]
     walk_grid.f = ctypes.CDLL(str(lib)).walk
     walk_grid.f.argtypes, walk_grid.f.restype = [ctypes.c_int64] * 3, ctypes.c_uint
+    walk_blocks.f = ctypes.CDLL(str(lib)).walk_blocks
+    walk_blocks.f.argtypes, walk_blocks.f.restype = [ctypes.c_int64] * 3, ctypes.c_uint
     xcd.f = ctypes.CDLL(str(lib)).xcd
     list_steps.f = ctypes.CDLL(str(lib)).list_steps
     walk_range.f = ctypes.CDLL(str(lib)).walk_range
@@ -72,6 +75,10 @@ def walk_range(b, grid, count):
 
 def walk_grid(resident, cap, hint):
     return walk_grid.f(resident, cap, hint)
+
+
+def walk_blocks(resident, cap, hint):
+    return walk_blocks.f(resident, cap, hint)
 
 
 SIZES = [0, 1, 4095, 4096, 4097, 100_000, (1 << 24) - 1, 1 << 24, 25_000_000, 50_000_000, (1 << 26) - 1, 1 << 26, (1 << 31) - 1]
@@ -134,6 +141,19 @@ def test_a_walked_list_gets_enough_workgroups_and_no_more_than_a_launch_holds(st
             steps = cap if hint < 0 else min(cap, hint)
             assert g >= min(cap, 3072) and (g >= steps / 4 or g * 64 >= (1 << 32) - 512)  # at most four steps each, if a launch can hold that
             assert g <= max(steps / 4, min(cap, 3072)) + 8
+
+
+@pytest.mark.parametrize("resident", [8, 1000, 2048, 3072])
+def test_a_short_walked_list_gets_whole_rounds_of_what_the_device_holds(step_grid, resident):
+    for cap in SIZES[1:] + [resident, resident + 1, 4 * resident, 4 * resident + 1, 32 * resident, 32 * resident + 1]:
+        for hint in [-1] + SIZES:
+            g, steps = walk_blocks(resident, cap, hint), cap if hint < 0 else min(cap, hint)
+            assert g % 8 == 0 and 0 < g and g * 64 < 1 << 32
+            if steps <= resident or steps > 32 * resident:
+                assert g == walk_grid(resident, cap, hint)
+            else:  # one to eight rounds of at most four steps a wavefront, and not a round more than that takes
+                rounds = -(-steps // (4 * resident))
+                assert rounds * resident <= g < rounds * resident + 8 and steps <= 4 * g and 1 <= rounds <= 8
 
 
 @pytest.mark.parametrize("rows", [1, 4, 8, 16])
