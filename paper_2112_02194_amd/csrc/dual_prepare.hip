@@ -358,9 +358,12 @@ template <int D> __global__ __launch_bounds__(64) void x_matrix_kernel(const flo
 }
 
 // ---------------------------------------------------------------------------------------------- launchers
-// Rows of 48 < k <= 128 that one launch takes for several classes where an earlier call saw so few (or that no hint announced): as many as
-// find a SIMD to themselves.
-inline int64_t wide_rest_limit(int num_cu) { return 8 * (int64_t)num_cu; }
+// Rows of 48 < k <= 128 that one launch takes for several classes where an earlier call saw so few (or that no hint announced).  That launch has
+// the registers and the LDS of its largest class, one wavefront per SIMD with fp32 at d = 128, so a row takes longer in it, but a
+// class by itself ends with the chain of its last rows.  Calls that fold rows in, 4 / 8 / 16 / 32 rows per compute unit, us: 300 000 rows,
+// 3M items, d = 128, bf16 829 / 808 / 809 / 817; 150 000 rows, 1M items, d = 128, fp32 763 / 762 / 749 / 749, 300 000 1010 / 988 / 987 / 989, 1M
+// 2213 / 2212 / 2202 / 2200; 600 000 bf16 812 / 812 / 795 / 797.
+inline int64_t wide_rest_limit(int num_cu) { return 16 * (int64_t)num_cu; }
 
 int dual_supported_max_k(int d) { return d < 128 ? (d < 64 ? d : 64) : 128; }
 
