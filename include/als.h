@@ -194,10 +194,13 @@ als_status als_copy_probe(als_ctx *ctx, const void *src, void *dst, int64_t byte
 
 /* Diagnostics, not part of the method.  GPU time in milliseconds (HIP events on the call's stream) of the
  * kernels launched by the most recent als_gramian / als_solve_rows / als_epoch / als_loss, per kernel:
- *   [0] Gramian (2 or 3 kernels)   [1] row classification (4 kernels, 1 up to 8192 rows)   [2] shared factorisation + Z = V L^-T
- *   [3] X = R L^-1   [4] primal fused row kernel   [5] long-row segment accumulation   [6] long-row reduce + solve
+ *   [0] Gramian (2 or 3 kernels)   [1] row classification (4 kernels; up to 8192 rows 1, with the shared factorisation)
+ *   [2] shared factorisation, where not in [1], + Z = V L^-T   [3] X = R L^-1, where the row kernels leave R
+ *   [4] primal rows (d < 64, or few of them: with the segments)   [5] long-row segments   [6] long-row reduce + solve
  *   [7] dual rows k <= 4   [8] dual rows 5 <= k <= 8   [9 + c] dual rows 16c < k <= 16(c+1), c = 0..7 (c = 0: 8 < k)
- * Small calls, whose dual classes share one launch, have the time of all of them in [9]; [7], [8] and [10] to [16] are 0 then.
+ * Classes of 48 < k <= 128 that are short, and their rows that no earlier call saw, are in the last of [12] to [16] that d has.
+ * Small calls, whose dual classes share one launch, have the time of all of them in [9], but for 32 < k <= 48 where a call saw many
+ * such rows ([11]); the other slots from [7] on are 0 then.
  * followed by the number of timed launches of each slot in [ALS_TIMING_SLOTS + slot].  Timing is recorded only
  * while enabled with als_set_timing(ctx, 1); reading waits for the recorded events. */
 #define ALS_TIMING_SLOTS 17

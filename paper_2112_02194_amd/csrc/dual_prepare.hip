@@ -8,7 +8,7 @@
 // This is the same minimiser of Eq. 3 as the d x d system (exact algebra, no approximation), but
 // costs O(k^2 d + k^3) per row instead of O(k d^2 + d^3), and the k x k matrix has eigenvalues in
 // [1, 1 + k/alpha], so fp32 is comfortable.  Steps:
-//   factor_kernel     B -> L^{-1} in fp64 (one workgroup), stored fp32
+//   factor_kernel     B -> L^{-1} in fp64 (one workgroup, up to 8192 rows beside the sort: solve_rows.hip), stored fp32
 //   transform_kernel  Z = V L^{-T}   (fp32 MFMA, table-sized workspace)
 //   row kernels       by class of k (fixed by measurement on MI355X): all gather Z_I into MFMA operand
 //                     registers, straight or by way of LDS, form S = I + Z_I Z_I^T on the matrix cores,
@@ -17,8 +17,11 @@
 //                          the last step along, and so do dual_rows_x_kernel and dual_multi_x_kernel for bf16 tables)
 //       dual_rows_kernel   8 < k <= 16: four rows per wavefront, one lane per row of S, gather through LDS
 //       dual_multi_kernel  16 < k <= 32: four rows per wavefront, S in two blocks of 16
-//       dual_wide_kernel   32 < k <= 128 (d >= 64; k <= 64 at d = 64): one row per wavefront, S as a
+//       dual_triple_kernel 32 < k <= 48 (d >= 64): four rows per wavefront, S in three blocks of 16
+//       dual_wide_kernel, dual_wide_rest_kernel  48 < k <= 128 (d = 128; k <= 64 at d = 64): one row per wavefront, S as a
 //                          lower triangle in LDS, blocked elimination with MFMA trailing updates
+//       dual_few_kernel    all of them, where the lists are short together
+//                          (conjugate gradients: dual_wide_kernel for every class)
 //   transform_lists_kernel, transform_kernel (d = 16, fp32 with d = 32)
 //                     X = R L^{-1}   (rows r -> L^{-T} r), rounding to the table's element type
 #include "dual_common.h"

@@ -1,5 +1,5 @@
-// Dual row update for 32 < k <= 128 (d = 128; k <= 64 also at d = 64), in classes KT = 3..8
-// (k <= 16*KT).  The algebra is in the header comment of dual_prepare.hip.
+// Dual row update for 48 < k <= 128 (d = 128; k <= 64 also at d = 64), in classes KT = 4..8 (k <= 16*KT); under conjugate
+// gradients for all rows, those of up to 48 entries with KT = 3.  The algebra is in the header comment of dual_prepare.hip.
 #pragma once
 
 #include "dual_common.h"
@@ -24,9 +24,9 @@ template <int D, int KT, bool ZB> constexpr bool wide_resident() { return ZB; }
 // needed last, is loaded then; among the first it left the compiler no registers, which then waited for its eight loads one by
 // one (200 000 rows of 100 / 120 entries 5.23 / 6.72 ms, as it is 4.86 / 5.91; another tile fewer 4.86 / 6.12; with four resident 6.00 / 7.36).
 template <int KT, bool ZB> constexpr int wide_tiles() { return ZB || KT < 6 ? KT : KT - 1; }
-// Long rows of Z only.  10M pages with host locality (d = 128, fp32), KT = 3 .. 8, ms per epoch, straight into the operand
-// layout / staged: 5.66 / 5.48, 4.25 / 4.07, 2.98 / 2.91, 2.35 / 2.12, 1.93 / 1.86, 1.24 / 1.16; shorter rows lose: 1M x 1M
-// (d = 64) 1.22 / 1.26, 300k bf16 rows (d = 128, KT = 3) 76 / 81 us.
+// Long rows of Z only.  10M pages with host locality (d = 128, fp32), KT = 4 .. 8, ms per epoch, straight into the operand
+// layout / staged: 4.25 / 4.07, 2.98 / 2.91, 2.35 / 2.12, 1.93 / 1.86, 1.24 / 1.16.  Shorter rows lose (measured with the direct
+// solver's KT = 3, which dual_triple_step.h has replaced): 1M x 1M (d = 64) 1.22 / 1.26 ms, 300k bf16 rows (d = 128) 76 / 81 us.
 template <int D, bool ZB> constexpr bool wide_staged() { return D == 128 && !ZB; }
 
 template <int D, int KT> struct WideCfg {

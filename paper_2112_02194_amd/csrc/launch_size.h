@@ -11,7 +11,8 @@ namespace als {
 // row kernels come in two forms: one step per workgroup (launched with `known` workgroups, the length the
 // previous call on the same matrix saw; steps beyond the true length return at once), and a grid-stride walk
 // over everything from step `known` on (launched with `rest` workgroups; finds nothing to do when the hint
-// was right).  Together they cover the list whatever the hint was.  (Rows of 9 to 32 entries have one form, which walks: walk_grid; those of 33 to 128 share one launch for the rest, dual_wide_rest.hip.)
+// was right).  Together they cover the list whatever the hint was.  (Rows of 9 to 48 entries have one form, which walks: walk_blocks;
+// those of 49 to 128 share one launch for the rest, dual_wide_rest.hip.)
 struct StepGrid {
     unsigned known, rest;
 };
