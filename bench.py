@@ -208,7 +208,8 @@ def main():
     sx, rx = "_x" if is_x >= 8 else "", "_x" if is_x >= 32 else ""
     kernel_names = {"dual_k4": f"dual_small{sx}_kernel<{d},4,{zbt if sx else 'false'}>", "dual_k8": f"dual_small{sx}_kernel<{d},8,{zbt if sx else 'false'}>",
                     "dual_k16": f"dual_rows{rx}_kernel<{d}>", "dual_k32": f"dual_multi{rx}_kernel<{d}>"}
-    for c in range(2, 8):
+    kernel_names["dual_k48"] = f"dual_triple_kernel<{d},{zbt}>"
+    for c in range(3, 8):
         kernel_names[f"dual_k{16 * (c + 1)}"] = f"dual_wide_kernel<{d},{c + 1},{zbt},false>"  # (short classes: dual_wide_rest_kernel, timed with the longest)
     if args.solver == "cg" and d >= 64:  # every class runs the one-row-per-wavefront kernel with the CG solver
         for name, _, hi in bounds:
@@ -260,8 +261,8 @@ def main():
             work["primal"][1] += work["segment"][1]
     work["transform_z"] = ["hbm", float(m + n) * d * (es + zs)]
     work["transform_x"] = ["hbm", float(m + n) * d * (4 + es)]
-    # lists that are short together share one launch, which the library times in the slot of 8 < k <= 16
-    dual_names = [name for name, _, _ in bounds]
+    # lists that are short together share one launch, which the library times in the slot of 8 < k <= 16; 32 < k <= 48 may have its own beside it
+    dual_names = [name for name, _, _ in bounds if not (name == "dual_k48" and stage_launches.get(name, 0.0) > 0)]
     common = args.solver == "direct" and [name for name in dual_names if stage_launches.get(name, 0.0) > 0] == ["dual_k16"]
     if (zbt == "true" or (es == 4 and d >= 64)) and args.solver != "cg_free":  # of the rows that are not X yet
         lo = 0 if common else is_x
